@@ -66,6 +66,12 @@ struct WsLayout {
 
 size_t up256(size_t x) { return (x + 255) & ~(size_t)255; }
 
+// partial attention results (of all heads) the workspace holds
+size_t part_capacity(const ess_config& c) {
+  const size_t n = (size_t)c.max_batch * c.max_q_tokens * ESS_ROW_SPLITS;
+  return n > ESS_MIN_PARTS ? n : ESS_MIN_PARTS;
+}
+
 WsLayout ws_layout(const ess_config& c) {
   const size_t B = c.max_batch, T = c.max_q_tokens, k = c.topk, H = c.attn_heads, L = c.max_ctx;
   WsLayout w;
@@ -80,8 +86,8 @@ WsLayout ws_layout(const ess_config& c) {
   w.fill_tok = take(B * T * k * 4);
   w.fill_slot = take(B * T * k * 4);
   w.miss_cnt = take(B * 4);
-  w.o_part = take(B * T * ESS_MAX_SPLITS * H * ESS_LATENT_DIM * 2);
-  w.lse_part = take(B * T * ESS_MAX_SPLITS * H * 8);
+  w.o_part = take(part_capacity(c) * H * ESS_LATENT_DIM * 2);
+  w.lse_part = take(part_capacity(c) * H * 8);
   w.stats = take(4 * 8);
   w.seq_stats = take(B * 4 * 8);
   w.zero_row = take(ESS_ZERO_ROW_BYTES);
@@ -116,15 +122,38 @@ int check_cache(const ess_ctx* ctx, const ess_cache* c) {
   return ESS_OK;
 }
 
-// number of attention splits for a list of up to k entries: a workgroup is sized to own a CU, so aim at
-// a small multiple of the CU count; never fewer than the kernel's tiles-per-split limit allows
-// `long_lists`: the lists are about topk entries long (Attn0, resident attention); then no workgroup
-// gets more than 32 tiles: with several rounds of workgroups per CU, shorter ones overlap one's end
-// (the write of its partial result) with another's work (measured: 9 % at batch 128 x 2 tokens)
-int pick_splits(const ess_config& c, int B, int T, int cap, int target_wgs = 256, bool long_lists = true) {
+// Number of attention splits for lists of up to k entries.  A workgroup owns a CU, so the launch takes rounds of 256
+// workgroups, each as long as the tiles of its range and about five and a half more for its start and end (2.1 us a
+// tile; measured 12 us for queries, first gathers and the write of a partial result); every partial result is then
+// written and read once more by the merge, 256 KiB per 128 heads at about 4.5 TB/s, and
+// a small batch's merge takes 0.12 us longer per split.  The split count with the least sum is taken.  (Before, one count was aimed at that puts a workgroup on every CU, rounded up: 96 rows got three splits
+// each, 288 workgroups, i.e. a second round for 32 of them.)
+int pick_splits(const ess_ctx* ctx, int B, int T, int cap) {
+  const ess_config& c = ctx->cfg;
+  const int tiles = (c.topk + ESS_ATTN_TILE - 1) / ESS_ATTN_TILE;
+  const long rows = (long)B * T * ((c.attn_heads + 127) / 128);
+  const int lo = ess_attn_min_splits(c) > 1 ? ess_attn_min_splits(c) : 1;
+  if (cap > tiles) cap = tiles;
+  if ((size_t)cap * B * T > ctx->part_cap) cap = (int)(ctx->part_cap / ((size_t)B * T));
+  int best = lo;
+  double best_us = 1e30;
+  for (int ns = lo; ns <= cap; ++ns) {
+    const long rounds = (rows * ns + 255) / 256;
+    const double us = rounds * ((tiles + ns - 1) / ns + 5.5) * 2.1 + (double)B * T * ns * c.attn_heads * 2048.0 / 4.5e6 + 0.12 * ns;
+    if (us < best_us) { best_us = us; best = ns; }
+  }
+#ifdef ESS_FORCE_NS
+  best = ESS_FORCE_NS;
+#endif
+  return best;
+}
+
+// The same for lists beside or behind a fetch: about `target_wgs` workgroups for the whole batch.
+// `long_lists`: the lists are about topk entries long (Attn0); then no workgroup gets more than 32 tiles
+int pick_splits_target(const ess_config& c, int B, int T, int cap, int target_wgs, bool long_lists) {
   const int tiles = (c.topk + ESS_ATTN_TILE - 1) / ESS_ATTN_TILE;
   const int hgroups = (c.attn_heads + 127) / 128;      // a workgroup covers 128 heads
-  int want = (target_wgs + B * T * hgroups - 1) / (B * T * hgroups);   // one workgroup per CU: fewer partial results to merge
+  int want = (target_wgs + B * T * hgroups - 1) / (B * T * hgroups);
   if (want > tiles) want = tiles;
   if (want > cap) want = cap;
   int lo = ess_attn_min_splits(c);
@@ -132,6 +161,15 @@ int pick_splits(const ess_config& c, int B, int T, int cap, int target_wgs = 256
   if (want < lo) want = lo;
   return want < 1 ? 1 : want;
 }
+
+// most splits of Attn0 (the rest of a row's partial results is Attn1's): 16, more where the rows are few
+int attn0_cap(const ess_ctx* ctx, int B, int T) {
+  const size_t n = ctx->part_cap / ((size_t)B * T);
+  return (int)(n > ESS_MAX_SPLITS ? ESS_MAX_SPLITS : n) - (ESS_ROW_SPLITS - 16);
+}
+
+// Merge with four waves per row?  Where one wave per row leaves most of the chip idle.
+bool wide_merge(const ess_config& c, int B, int T) { return (long)B * T * c.attn_heads <= 2048; }
 
 // A view of the caller's cache arrays starting at sequence b0.
 ess_cache shift_cache(const ess_config& c, const ess_cache& in, int b0) {
@@ -228,6 +266,7 @@ int ess_create(const ess_config* cfg, ess_ctx** out) {
   ctx->fill_tok = reinterpret_cast<int32_t*>(base + w.fill_tok);
   ctx->fill_slot = reinterpret_cast<int32_t*>(base + w.fill_slot);
   ctx->miss_cnt = reinterpret_cast<int32_t*>(base + w.miss_cnt);
+  ctx->part_cap = part_capacity(*cfg);
   ctx->o_part = reinterpret_cast<uint16_t*>(base + w.o_part);
   ctx->lse_part = reinterpret_cast<float*>(base + w.lse_part);
   ctx->stats = reinterpret_cast<unsigned long long*>(base + w.stats);
@@ -428,10 +467,10 @@ int ess_sparse_mla_decode(ess_ctx* ctx, const void* q_bf16, const uint8_t* slot_
   if (!aligned16(q_bf16) || !aligned16(slot_pool) || !aligned16(out_bf16))
     return ess_fail(ESS_ERR_INVALID_ARG, "q, slot_pool and out must be 16-byte aligned");
   hipStream_t st = static_cast<hipStream_t>(stream);
-  const int ns = pick_splits(ctx->cfg, B, T, 16);
-  rc = ess_launch_attn_partial(ctx, q_bf16, slot_pool, slot_idx, nullptr, B, T, 0, ns, st);
+  const int ns = pick_splits(ctx, B, T, ESS_MAX_SPLITS);
+  rc = ess_launch_attn_partial(ctx, q_bf16, slot_pool, slot_idx, nullptr, B, T, 0, ns, ns, st);
   if (rc != ESS_OK) return rc;
-  return ess_launch_attn_merge(ctx, B, T, ns, out_bf16, lse, st);
+  return ess_launch_attn_merge(ctx, B, T, ns, wide_merge(ctx->cfg, B, T), out_bf16, lse, st);
 }
 
 int ess_decode_step(ess_ctx* ctx, const ess_cache* cache, const ess_step_args* a, void* stream) {
@@ -522,7 +561,7 @@ int ess_decode_step(ess_ctx* ctx, const ess_cache* cache, const ess_step_args* a
     // Attn0 on the XCDs the fetch leaves free (one workgroup per CU): rounds x (tiles x time per tile + start and end)
     const int work_cus = 32 * (8 - __builtin_popcount(ESS_FETCH_XCD_MASK & 0xffu));
     const int hg = (c.attn_heads + 127) / 128;
-    const int ns0e = pick_splits(c, B, T, 16, ESS_ATTN0_WGS);
+    const int ns0e = pick_splits_target(c, B, T, attn0_cap(ctx, B, T), ESS_ATTN0_WGS, true);
     const double hits = c.topk - (mean_miss / T < c.topk ? mean_miss / T : c.topk);
     const double tiles_item = (hits / ESS_ATTN_TILE) / ns0e + 1.0;
     const double rounds = (double)((long)B * T * hg * ns0e + work_cus - 1) / work_cus;
@@ -549,11 +588,12 @@ int ess_decode_step(ess_ctx* ctx, const ess_cache* cache, const ess_step_args* a
 
   // attention splits: chosen from the whole batch and the same for both halves, so that every schedule
   // sums in the same order and gives the same bits
-  const int ns0 = pick_splits(c, B, T, 16, offloaded ? ESS_ATTN0_WGS : 256);
+  const int ns0 = offloaded ? pick_splits_target(c, B, T, attn0_cap(ctx, B, T), ESS_ATTN0_WGS, true) : pick_splits(ctx, B, T, ESS_MAX_SPLITS);
+  const bool wide = wide_merge(c, B, T);
   int ns1 = 0;
   if (offloaded) {
     // Attn1 works on the short miss lists: as many splits as give the whole batch one workgroup per CU
-    ns1 = pick_splits(c, B, T, ESS_MAX_SPLITS - 16, 256, false);
+    ns1 = pick_splits_target(c, B, T, ESS_ROW_SPLITS - 16, 256, false);
   }
 
   // Stages 1 and 2 come in two forms: through the score array (index score, then top-k), or fused (the score array
@@ -653,11 +693,11 @@ int ess_decode_step(ess_ctx* ctx, const ess_cache* cache, const ess_step_args* a
     // nothing offloaded: slot == position, attention straight over the selection
     const int32_t* used = a->topk_override ? a->topk_override : a->idx_out;
     ESS_BEGIN(3);
-    rc = ess_launch_attn_partial(ctx, a->q_bf16, cache->slot_pool, used, nullptr, B, T, 0, ns0, st);
+    rc = ess_launch_attn_partial(ctx, a->q_bf16, cache->slot_pool, used, nullptr, B, T, 0, ns0, ns0 + ns1, st);
     if (rc != ESS_OK) return rc;
     ESS_END(3);
     ESS_BEGIN(4);
-    rc = ess_launch_attn_merge(ctx, B, T, ns0, a->out_bf16, a->lse, st, a->miss_count, B);   // no misses: the counts are zero
+    rc = ess_launch_attn_merge(ctx, B, T, ns0, wide, a->out_bf16, a->lse, st, a->miss_count, B);   // no misses: the counts are zero
     if (rc != ESS_OK) return rc;
     ESS_END(4);
     return ESS_OK;
@@ -674,7 +714,7 @@ int ess_decode_step(ess_ctx* ctx, const ess_cache* cache, const ess_step_args* a
     ESS_HIP(hipStreamWaitEvent(ctx->side, ctx->ev_book[0], 0));
     hipEvent_t* aev = (pev && ((ctx->prof_mask >> 3) & 1u)) ? pev + ESS_PROF_MAIN : nullptr;
     if (aev) ESS_HIP(hipEventRecord(aev[0], ctx->side));
-    rc = ess_launch_attn_partial(ctx, q16, cache->slot_pool, ctx->hit_list, ctx->n_hit, B, T, 0, ns0, ctx->side, 0,
+    rc = ess_launch_attn_partial(ctx, q16, cache->slot_pool, ctx->hit_list, ctx->n_hit, B, T, 0, ns0, ns0 + ns1, ctx->side, 0,
                                  confine_da ? tk_xcd(ESS_TKT_ATTN0) : ess_xcd{nullptr, 0, nullptr, 0});
     if (rc != ESS_OK) return rc;
     if (aev) {
@@ -689,10 +729,10 @@ int ess_decode_step(ess_ctx* ctx, const ess_cache* cache, const ess_step_args* a
     ESS_END(5);
     ESS_BEGIN(4);
     ESS_HIP(hipStreamWaitEvent(st, ctx->ev_fill[0], 0));
-    rc = ess_launch_attn_partial(ctx, q16, cache->slot_pool, ctx->miss_list, ctx->n_miss, B, T, ns0, ns1, st, 0);
+    rc = ess_launch_attn_partial(ctx, q16, cache->slot_pool, ctx->miss_list, ctx->n_miss, B, T, ns0, ns1, ns0 + ns1, st, 0);
     if (rc != ESS_OK) return rc;
     chk.need[ESS_TKT_ATTN0] += check_extra;
-    rc = ess_launch_attn_merge(ctx, B, T, ns0 + ns1, a->out_bf16, a->lse, st, nullptr, 0, 0, confine_da ? &chk : nullptr);
+    rc = ess_launch_attn_merge(ctx, B, T, ns0 + ns1, wide, a->out_bf16, a->lse, st, nullptr, 0, 0, confine_da ? &chk : nullptr);
     if (rc != ESS_OK) return rc;
     ESS_END(4);
     return ESS_OK;
@@ -719,18 +759,18 @@ int ess_decode_step(ess_ctx* ctx, const ess_cache* cache, const ess_step_args* a
     if (aev) ESS_HIP(hipEventRecord(aev[0], ctx->side));
     // Attn0 of the whole batch in one launch (behind the first fetch it could not start much earlier
     // anyway): one workgroup per CU, the same splits as in the other schedules
-    rc = ess_launch_attn_partial(ctx, q16, cache->slot_pool, ctx->hit_list, ctx->n_hit, B, T, 0, ns0, ctx->side, 0,
+    rc = ess_launch_attn_partial(ctx, q16, cache->slot_pool, ctx->hit_list, ctx->n_hit, B, T, 0, ns0, ns0 + ns1, ctx->side, 0,
                                  confine2 ? tk_xcd(ESS_TKT_ATTN0) : ess_xcd{nullptr, 0, nullptr, 0});
     if (rc != ESS_OK) return rc;
     if (aev) {
       ESS_HIP(hipEventRecord(aev[1], ctx->side));
       ESS_HIP(hipEventRecord(aev[2], ctx->side));
     }
-    rc = ess_launch_attn_partial(ctx, q16, c0.slot_pool, ctx->miss_list, ctx->n_miss, hB[0], T, ns0, ns1, ctx->side, hb0[0],
+    rc = ess_launch_attn_partial(ctx, q16, c0.slot_pool, ctx->miss_list, ctx->n_miss, hB[0], T, ns0, ns1, ns0 + ns1, ctx->side, hb0[0],
                                  confine2 ? tk_xcd(ESS_TKT_ATTN1) : ess_xcd{nullptr, 0, nullptr, 0});
     if (rc != ESS_OK) return rc;
     // each half is merged on the stream its Attn1 ran on: only half a merge is left behind the last fetch
-    rc = ess_launch_attn_merge(ctx, hB[0], T, ns0 + ns1, a->out_bf16, a->lse, ctx->side, nullptr, 0, hb0[0]);
+    rc = ess_launch_attn_merge(ctx, hB[0], T, ns0 + ns1, wide, a->out_bf16, a->lse, ctx->side, nullptr, 0, hb0[0]);
     if (rc != ESS_OK) return rc;
     if (aev) {
       ESS_HIP(hipEventRecord(aev[3], ctx->side));
@@ -741,11 +781,11 @@ int ess_decode_step(ess_ctx* ctx, const ess_cache* cache, const ess_step_args* a
     ESS_HIP(hipEventRecord(ctx->ev_fill[1], ctx->side));           // here: everything on the side stream done
     ESS_BEGIN(4);
     rc = ess_launch_attn_partial(ctx, q16 + bt1 * c.attn_heads * ESS_ROW_DIM, c1.slot_pool, ctx->miss_list + bt1 * k,
-                                 ctx->n_miss + bt1, hB[1], T, ns0, ns1, st, hb0[1]);
+                                 ctx->n_miss + bt1, hB[1], T, ns0, ns1, ns0 + ns1, st, hb0[1]);
     if (rc != ESS_OK) return rc;
     ESS_HIP(hipStreamWaitEvent(st, ctx->ev_fill[1], 0));          // Attn0 of the second half ran on the side stream
     chk.need[ESS_TKT_INDEX] += check_extra;
-    rc = ess_launch_attn_merge(ctx, hB[1], T, ns0 + ns1, a->out_bf16, a->lse, st, nullptr, 0, hb0[1], confine ? &chk : nullptr);
+    rc = ess_launch_attn_merge(ctx, hB[1], T, ns0 + ns1, wide, a->out_bf16, a->lse, st, nullptr, 0, hb0[1], confine ? &chk : nullptr);
     if (rc != ESS_OK) return rc;
     ESS_END(4);
     return ESS_OK;
@@ -758,7 +798,7 @@ int ess_decode_step(ess_ctx* ctx, const ess_cache* cache, const ess_step_args* a
     const size_t bt0 = (size_t)b0 * T;
     const ess_cache ch = shift_cache(c, *cache, b0);
     rc = ess_launch_attn_partial(ctx, q16 + bt0 * c.attn_heads * ESS_ROW_DIM, ch.slot_pool, ctx->hit_list + bt0 * k,
-                                 ctx->n_hit + bt0, Bh, T, 0, ns0, st, b0);
+                                 ctx->n_hit + bt0, Bh, T, 0, ns0, ns0 + ns1, st, b0);
     if (rc != ESS_OK) return rc;
   }
   ESS_END(3);
@@ -769,10 +809,10 @@ int ess_decode_step(ess_ctx* ctx, const ess_cache* cache, const ess_step_args* a
     const ess_cache ch = shift_cache(c, *cache, b0);
     if (pending[h]) ESS_HIP(hipStreamWaitEvent(st, ctx->ev_fill[h], 0));
     rc = ess_launch_attn_partial(ctx, q16 + bt0 * c.attn_heads * ESS_ROW_DIM, ch.slot_pool, ctx->miss_list + bt0 * k,
-                                 ctx->n_miss + bt0, Bh, T, ns0, ns1, st, b0);
+                                 ctx->n_miss + bt0, Bh, T, ns0, ns1, ns0 + ns1, st, b0);
     if (rc != ESS_OK) return rc;
   }
-  rc = ess_launch_attn_merge(ctx, B, T, ns0 + ns1, a->out_bf16, a->lse, st);
+  rc = ess_launch_attn_merge(ctx, B, T, ns0 + ns1, wide, a->out_bf16, a->lse, st);
   if (rc != ESS_OK) return rc;
   ESS_END(4);
   return ESS_OK;

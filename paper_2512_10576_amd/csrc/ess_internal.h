@@ -8,7 +8,9 @@
 #define ESS_MAX_TOPK 4096
 #define ESS_MAX_SEL 8192        // T * k
 #define ESS_ATTN_TILE 32        // entries per attention tile
-#define ESS_MAX_SPLITS 20       // partial results per (b,t): Attn0 splits + Attn1 splits
+#define ESS_MAX_SPLITS 64       // partial results per (b,t) at most: Attn0 splits + Attn1 splits (the merge gives each a lane)
+#define ESS_ROW_SPLITS 20       // ... that there is room for at the context's full batch
+#define ESS_MIN_PARTS 320       // ... and for all rows together in a small context
 #define ESS_ROW_DIM 576
 #define ESS_ZERO_ROW_BYTES 2048  // >= the largest row_stride
 #define ESS_TOPK_SHARED_ROWS 128 // rows (b,t) up to which a top-k row is shared by several workgroups
@@ -66,8 +68,9 @@ struct ess_ctx {
   int32_t* fill_tok;            // [B,T*k] token to fetch
   int32_t* fill_slot;           // [B,T*k] slot to fetch into
   int32_t* miss_cnt;            // [B]
-  uint16_t* o_part;             // [B*T, ESS_MAX_SPLITS, H, 512] partial attention results, fp16 bits (times lse_part[..][1])
-  float* lse_part;              // [B*T, ESS_MAX_SPLITS, H, 2]: log-sum-exp of a partial result and the power of two its fp16 values were divided by
+  size_t part_cap;              // partial results (of all heads) that the two arrays hold
+  uint16_t* o_part;             // [rows (b,t), splits, H, 512] partial attention results, fp16 bits (times lse_part[..][1])
+  float* lse_part;              // [rows (b,t), splits, H, 2]: log-sum-exp of a partial result and the power of two its fp16 values were divided by
   unsigned long long* stats;    // [4]
   unsigned long long* seq_stats; // [max_batch][4] the same four counters per sequence
   uint8_t* zero_row;            // ESS_ZERO_ROW_BYTES of zeros, never written: source of masked attention rows
@@ -255,13 +258,14 @@ int ess_launch_fill(ess_ctx* ctx, const ess_cache& cache, int B, hipStream_t st,
 int ess_launch_gather_rows(const ess_config& c, const uint8_t* slot_pool, const int32_t* slot_idx, int B, int T,
                            uint8_t* rows_out, hipStream_t st);
 // attention over list[b,t,0..n) (n = n_list[b,t], or k when n_list is NULL), written as `nsplit`
-// partial results starting at partial index `split0`
+// partial results starting at partial index `split0` of the row's `pitch`
 int ess_launch_attn_partial(ess_ctx* ctx, const void* q, const uint8_t* slot_pool, const int32_t* list,
-                            const int32_t* n_list, int B, int T, int split0, int nsplit, hipStream_t st, int b0 = 0,
+                            const int32_t* n_list, int B, int T, int split0, int nsplit, int pitch, hipStream_t st, int b0 = 0,
                             ess_xcd xcd = ess_xcd{nullptr, 0, nullptr, 0});
 int ess_attn_min_splits(const ess_config& c);   // fewest splits a list of k entries may be cut into
+// wide: four waves per row (small batches; the same for every sub-batch of a call, it sets the order of the sums);
 // zero_cnt (may be NULL): n_zero int32 counters that the merge kernel also clears; b0 = first sequence of the
 // sub-batch of B sequences (out_bf16 and lse are the whole batch's arrays)
-int ess_launch_attn_merge(ess_ctx* ctx, int B, int T, int nsplit_total, void* out_bf16, float* lse,
+int ess_launch_attn_merge(ess_ctx* ctx, int B, int T, int nsplit_total, bool wide, void* out_bf16, float* lse,
                           hipStream_t st, int32_t* zero_cnt = nullptr, int n_zero = 0, int b0 = 0,
                           const ess_ticket_check* check = nullptr);
