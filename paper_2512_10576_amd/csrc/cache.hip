@@ -77,7 +77,7 @@ template <bool REG, bool DYN>
 __global__ __launch_bounds__(BT) void k_bookkeeping(
     const int32_t* __restrict__ idx, int T, int kk, int Lmax, int S, int32_t* __restrict__ slot_of,
     int32_t* __restrict__ token_of, uint32_t* __restrict__ stamp, uint32_t step, int32_t* __restrict__ slot_idx_out,
-    int32_t* __restrict__ hit_list, int32_t* __restrict__ miss_list, int32_t* __restrict__ n_hit,
+    int32_t* __restrict__ fresh_idx, int32_t* __restrict__ hit_list, int32_t* __restrict__ miss_list, int32_t* __restrict__ n_hit,
     int32_t* __restrict__ n_miss, int32_t* __restrict__ fill_tok, int32_t* __restrict__ fill_slot, int fill_cap,
     int32_t* __restrict__ miss_cnt, int32_t* __restrict__ miss_count_out, unsigned long long* __restrict__ stats,
     unsigned long long* __restrict__ seq_stats,
@@ -324,6 +324,7 @@ __global__ __launch_bounds__(BT) void k_bookkeeping(
           slot = fresh ? so[s] : s0;
         }
         if (slot_idx_out) slot_idx_out[rowoff + j] = slot;
+        if (fresh_idx) fresh_idx[rowoff + j] = fresh ? slot | ESS_FRESH_BIT : slot;
       } else if (j < kk) {
         const int s = idx[rowoff + j];
         if (s >= 0 && s < Lmax) {
@@ -331,6 +332,7 @@ __global__ __launch_bounds__(BT) void k_bookkeeping(
           fresh = (bm[s >> 5] >> (s & 31)) & 1u;
         }
         if (slot_idx_out) slot_idx_out[rowoff + j] = slot;
+        if (fresh_idx) fresh_idx[rowoff + j] = fresh ? slot | ESS_FRESH_BIT : slot;
       }
       if (hit_list) {
         const uint32_t is_hit = (slot >= 0 && !fresh) ? 1u : 0u;
@@ -433,7 +435,10 @@ __global__ __launch_bounds__(FILL_WPB * 64) void k_fill(const uint8_t* __restric
   }
 }
 
-// rows_out[b,t,j,:] = slot_pool[b, slot_idx[b,t,j], :] (zeros where the slot is -1); one wave per row
+// rows_out[b,t,j,:] = slot_pool[b, slot_idx[b,t,j], :] (zeros where the slot is -1); one wave per row.
+// WHICH 1, 2: slot_idx marks the entries that this step fetches (ESS_FRESH_BIT); the others are gathered while the fetch
+// runs, these after it.
+template <int WHICH>
 __global__ __launch_bounds__(256) void k_gather_rows(const uint8_t* __restrict__ slot_pool,
                                                      const int32_t* __restrict__ slot_idx, int per_seq, int S,
                                                      int row_stride, uint8_t* __restrict__ rows_out) {
@@ -442,7 +447,12 @@ __global__ __launch_bounds__(256) void k_gather_rows(const uint8_t* __restrict__
   const int nw = gridDim.x * 4;
   const int chunks = row_stride >> 4;
   for (int i = blockIdx.x * 4 + (threadIdx.x >> 6); i < per_seq; i += nw) {
-    const int v = slot_idx[(size_t)b * per_seq + i];
+    int v = slot_idx[(size_t)b * per_seq + i];
+    if (WHICH) {
+      const bool fresh = v >= 0 && (v & ESS_FRESH_BIT);
+      if (fresh != (WHICH == 2)) continue;
+      if (fresh) v &= ~ESS_FRESH_BIT;
+    }
     uint4* dst = reinterpret_cast<uint4*>(rows_out + ((size_t)b * per_seq + i) * row_stride);
     if (v >= 0 && v < S) {
       const uint4* src = reinterpret_cast<const uint4*>(slot_pool + ((size_t)b * S + v) * row_stride);
@@ -646,7 +656,7 @@ int ess_launch_cache_reset(const ess_config& c, const ess_cache& cache, int B, h
 
 int ess_launch_bookkeeping(ess_ctx* ctx, const ess_cache& cache, const int32_t* idx, int B, int T, int kk,
                            uint32_t step, int32_t* slot_idx, int32_t* miss_count_out, hipStream_t st, int b0,
-                           bool count_step, ess_xcd xcd, uint32_t* zero_tickets, int n_zero_tickets) {
+                           bool count_step, ess_xcd xcd, uint32_t* zero_tickets, int n_zero_tickets, hipEvent_t done, int32_t* fresh_idx) {
   const ess_config& c = ctx->cfg;
   if (!ctx->book_fits)
     return ess_fail(ESS_ERR_UNSUPPORTED, "the cache bookkeeping of max_ctx %d with T*k = %d does not fit the LDS (max_ctx / 8 + "
@@ -658,14 +668,13 @@ int ess_launch_bookkeeping(ess_ctx* ctx, const ess_cache& cache, const int32_t* 
   const bool reg = c.slots_per_seq <= BT * 16;
   auto kern = xcd.ticket ? (reg ? &k_bookkeeping<true, true> : &k_bookkeeping<false, true>)
                          : (reg ? &k_bookkeeping<true, false> : &k_bookkeeping<false, false>);
-  hipLaunchKernelGGL(kern, dim3(ess_xcd_grid(B, xcd)), dim3(BT), lds, st, idx, T, kk, c.max_ctx, c.slots_per_seq,
-                     cache.slot_of, cache.token_of, cache.stamp, step, slot_idx,
+  ESS_HIP(ess_launch_done(done, kern, dim3(ess_xcd_grid(B, xcd)), dim3(BT), lds, st, idx, T, kk, c.max_ctx, c.slots_per_seq,
+                     cache.slot_of, cache.token_of, cache.stamp, step, slot_idx, fresh_idx,
                      lists ? ctx->hit_list + lo : nullptr, lists ? ctx->miss_list + lo : nullptr,
                      ctx->n_hit + (size_t)b0 * T, ctx->n_miss + (size_t)b0 * T, ctx->fill_tok + (size_t)b0 * cap,
                      ctx->fill_slot + (size_t)b0 * cap, cap, ctx->miss_cnt + b0, miss_count_out, ctx->stats, ctx->seq_stats + 4 * (size_t)b0,
                      c.row_stride, count_step ? 1 : 0, (c.flags & ESS_FLAG_AUTO) ? ctx->host_miss_dev + b0 : nullptr, xcd, B,
-                     zero_tickets, n_zero_tickets, (int)book_words(c.max_ctx), (int)book_union_bytes(cap));
-  ESS_HIP(hipGetLastError());
+                     zero_tickets, n_zero_tickets, (int)book_words(c.max_ctx), (int)book_union_bytes(cap)));
   return ESS_OK;
 }
 
@@ -687,7 +696,7 @@ int ess_init_cache_kernels(const ess_config& c, bool* fits) {
 }
 
 int ess_launch_fill(ess_ctx* ctx, const ess_cache& cache, int B, hipStream_t st, int b0, int wgs, uint32_t only_xcds,
-                    uint32_t* ticket) {
+                    uint32_t* ticket, hipEvent_t done) {
   wgs = wgs < 1 ? 1 : (wgs > 256 ? 256 : wgs);
   if (only_xcds) {                             // `wgs` workgroups on the chosen XCDs, if any 8 consecutive ones cover all XCDs
     if (!ticket) return ess_fail(ESS_ERR_INVALID_ARG, "internal: confined fetch without a ticket");
@@ -697,17 +706,15 @@ int ess_launch_fill(ess_ctx* ctx, const ess_cache& cache, int B, hipStream_t st,
   }
   const ess_config& c = ctx->cfg;
   const int cap = c.max_q_tokens * c.topk;
-  hipLaunchKernelGGL(k_fill, dim3(wgs), dim3(FILL_WPB * 64), (size_t)(B + 1) * sizeof(int32_t), st, cache.host_pool_dev, cache.slot_pool,
+  ESS_HIP(ess_launch_done(done, &k_fill, dim3(wgs), dim3(FILL_WPB * 64), (size_t)(B + 1) * sizeof(int32_t), st, cache.host_pool_dev, cache.slot_pool,
                      ctx->fill_tok + (size_t)b0 * cap, ctx->fill_slot + (size_t)b0 * cap, cap, ctx->miss_cnt + b0, B,
-                     c.max_ctx, c.slots_per_seq, c.row_stride, only_xcds, ticket);
-  ESS_HIP(hipGetLastError());
+                     c.max_ctx, c.slots_per_seq, c.row_stride, only_xcds, ticket));
   return ESS_OK;
 }
 
 int ess_launch_gather_rows(const ess_config& c, const uint8_t* slot_pool, const int32_t* slot_idx, int B, int T,
-                           uint8_t* rows_out, hipStream_t st) {
-  hipLaunchKernelGGL(k_gather_rows, dim3(64, B), dim3(256), 0, st, slot_pool, slot_idx, T * c.topk,
-                     c.slots_per_seq, c.row_stride, rows_out);
-  ESS_HIP(hipGetLastError());
+                           uint8_t* rows_out, hipStream_t st, int which, hipEvent_t done) {
+  auto kern = which == 0 ? &k_gather_rows<0> : (which == 1 ? &k_gather_rows<1> : &k_gather_rows<2>);
+  ESS_HIP(ess_launch_done(done, kern, dim3(64, B), dim3(256), 0, st, slot_pool, slot_idx, T * c.topk, c.slots_per_seq, c.row_stride, rows_out));
   return ESS_OK;
 }

@@ -149,15 +149,13 @@ int pick_splits(const ess_ctx* ctx, int B, int T, int cap) {
 }
 
 // The same for lists beside or behind a fetch: about `target_wgs` workgroups for the whole batch.
-// `long_lists`: the lists are about topk entries long (Attn0); then no workgroup gets more than 32 tiles
-int pick_splits_target(const ess_config& c, int B, int T, int cap, int target_wgs, bool long_lists) {
+int pick_splits_target(const ess_config& c, int B, int T, int cap, int target_wgs) {
   const int tiles = (c.topk + ESS_ATTN_TILE - 1) / ESS_ATTN_TILE;
   const int hgroups = (c.attn_heads + 127) / 128;      // a workgroup covers 128 heads
   int want = (target_wgs + B * T * hgroups - 1) / (B * T * hgroups);
   if (want > tiles) want = tiles;
   if (want > cap) want = cap;
-  int lo = ess_attn_min_splits(c);
-  if (long_lists && lo < (tiles + 31) / 32) lo = (tiles + 31) / 32;
+  const int lo = ess_attn_min_splits(c);
   if (want < lo) want = lo;
   return want < 1 ? 1 : want;
 }
@@ -183,32 +181,33 @@ ess_cache shift_cache(const ess_config& c, const ess_cache& in, int b0) {
 }
 
 // Bookkeeping + fetch of the sub-batch [b0, b0+B) (`cache`, `idx`, `slot_idx`, `miss_count` already
-// point at sequence b0), the fetch on the side stream unless serial, tracked by event pair `half`.
-// After return, work enqueued on `st` is ordered after the bookkeeping; *fill_pending tells whether
-// ev_fill[half] must still be waited for before the fetched rows are read.
+// point at sequence b0).  `half` >= 0: the fetch on the side stream unless serial, tracked by event pair `half`; after
+// return, work enqueued on `st` is ordered after the bookkeeping, and *fill_pending tells whether ev_fill[half] must
+// still be waited for before the fetched rows are read.  half < 0 (calls with nothing to overlap): the fetch on `st`
+// itself -- on the side stream the two waits across streams cost about 20 us.
 int run_cache_step(ess_ctx* ctx, const ess_cache& cache, const int32_t* idx, int B, int T, int kk, uint32_t step,
-                   int32_t* slot_idx, int32_t* miss_count, hipStream_t st, bool* fill_pending, int b0 = 0,
-                   int half = 0, hipEvent_t* fill_ev = nullptr, int fill_wgs = 64, bool confine = false) {
+                   int32_t* slot_idx, int32_t* miss_count, hipStream_t st, bool* fill_pending, int b0,
+                   int half, hipEvent_t* fill_ev = nullptr, int fill_wgs = 64, bool confine = false) {
   *fill_pending = false;
+  const bool aside = half >= 0 && cache.host_pool_dev && !(ctx->cfg.flags & ESS_FLAG_SERIAL);
   // confine: the fetch runs on the XCDs of ESS_FETCH_XCD_MASK and the kernels beside it stay off them, taking their work
   // through counters that this bookkeeping clears (counter 0: the fetch itself)
-  int rc = ess_launch_bookkeeping(ctx, cache, idx, B, T, kk, step, slot_idx, miss_count, st, b0, half == 0,
-                                  ess_xcd{nullptr, 0, nullptr, 0}, confine ? ctx->tickets : nullptr, ESS_TKT_FETCH2);
+  int rc = ess_launch_bookkeeping(ctx, cache, idx, B, T, kk, step, slot_idx, miss_count, st, b0, half <= 0,
+                                  ess_xcd{nullptr, 0, nullptr, 0}, confine ? ctx->tickets : nullptr, ESS_TKT_FETCH2,
+                                  aside ? ctx->ev_book[half] : nullptr);
   if (rc != ESS_OK) return rc;
   if (!cache.host_pool_dev) return ESS_OK;      // nothing offloaded: no entry can be missing
-  if (ctx->cfg.flags & ESS_FLAG_SERIAL) {
+  if (!aside) {
     if (fill_ev) ESS_HIP(hipEventRecord(fill_ev[0], st));
     rc = ess_launch_fill(ctx, cache, B, st, b0, fill_wgs);
     if (rc == ESS_OK && fill_ev) ESS_HIP(hipEventRecord(fill_ev[1], st));
     return rc;
   }
-  ESS_HIP(hipEventRecord(ctx->ev_book[half], st));
   ESS_HIP(hipStreamWaitEvent(ctx->side, ctx->ev_book[half], 0));
   if (fill_ev) ESS_HIP(hipEventRecord(fill_ev[0], ctx->side));
-  rc = ess_launch_fill(ctx, cache, B, ctx->side, b0, fill_wgs, confine ? ESS_FETCH_XCD_MASK : 0u, ctx->tickets);
+  rc = ess_launch_fill(ctx, cache, B, ctx->side, b0, fill_wgs, confine ? ESS_FETCH_XCD_MASK : 0u, ctx->tickets, ctx->ev_fill[half]);
   if (rc != ESS_OK) return rc;
   if (fill_ev) ESS_HIP(hipEventRecord(fill_ev[1], ctx->side));
-  ESS_HIP(hipEventRecord(ctx->ev_fill[half], ctx->side));
   *fill_pending = true;
   return ESS_OK;
 }
@@ -362,10 +361,7 @@ int ess_cache_admit(ess_ctx* ctx, const ess_cache* cache, const int32_t* tok, in
   hipStream_t st = static_cast<hipStream_t>(stream);
   bool pending = false;
   // one list of n entries per sequence, no per-query outputs
-  rc = run_cache_step(ctx, *cache, tok, B, 1, n, step, nullptr, nullptr, st, &pending);
-  if (rc != ESS_OK) return rc;
-  if (pending) ESS_HIP(hipStreamWaitEvent(st, ctx->ev_fill[0], 0));
-  return ESS_OK;
+  return run_cache_step(ctx, *cache, tok, B, 1, n, step, nullptr, nullptr, st, &pending, 0, -1);
 }
 
 int ess_index_score(ess_ctx* ctx, const uint8_t* q, const float* w, const uint8_t* key, const int32_t* ctx_len,
@@ -451,11 +447,24 @@ int ess_gather_latent(ess_ctx* ctx, const ess_cache* cache, const int32_t* idx, 
   if (step < 1) return ess_fail(ESS_ERR_INVALID_ARG, "step must be >= 1");
   (void)ctx_len;                                // visibility was already applied by the selection
   hipStream_t st = static_cast<hipStream_t>(stream);
-  bool pending = false;
-  rc = run_cache_step(ctx, *cache, idx, B, T, ctx->cfg.topk, step, slot_idx, miss_count, st, &pending);
+  if (!rows_out || !cache->host_pool_dev || (ctx->cfg.flags & ESS_FLAG_SERIAL)) {
+    bool pending = false;
+    rc = run_cache_step(ctx, *cache, idx, B, T, ctx->cfg.topk, step, slot_idx, miss_count, st, &pending, 0, -1);
+    if (rc != ESS_OK || !rows_out) return rc;
+    return ess_launch_gather_rows(ctx->cfg, cache->slot_pool, slot_idx, B, T, rows_out, st);
+  }
+  // The rows that were resident are gathered on the side stream while the fetch runs; behind it only the fetched ones are
+  // left (batch 32 x 64K, 340 misses of 2048 per sequence: 5 us instead of 30).
+  rc = ess_launch_bookkeeping(ctx, *cache, idx, B, T, ctx->cfg.topk, step, slot_idx, miss_count, st, 0, true,
+                              ess_xcd{nullptr, 0, nullptr, 0}, nullptr, 0, ctx->ev_book[0], ctx->slot_idx_ws);
   if (rc != ESS_OK) return rc;
-  if (pending) ESS_HIP(hipStreamWaitEvent(st, ctx->ev_fill[0], 0));
-  if (rows_out) return ess_launch_gather_rows(ctx->cfg, cache->slot_pool, slot_idx, B, T, rows_out, st);
+  ESS_HIP(hipStreamWaitEvent(ctx->side, ctx->ev_book[0], 0));
+  rc = ess_launch_gather_rows(ctx->cfg, cache->slot_pool, ctx->slot_idx_ws, B, T, rows_out, ctx->side, 1, ctx->ev_fill[0]);
+  if (rc != ESS_OK) return rc;
+  if ((rc = ess_launch_fill(ctx, *cache, B, st)) != ESS_OK) return rc;
+  rc = ess_launch_gather_rows(ctx->cfg, cache->slot_pool, ctx->slot_idx_ws, B, T, rows_out, st, 2);
+  if (rc != ESS_OK) return rc;
+  ESS_HIP(hipStreamWaitEvent(st, ctx->ev_fill[0], 0));
   return ESS_OK;
 }
 
@@ -551,6 +560,11 @@ int ess_decode_step(ess_ctx* ctx, const ess_cache* cache, const ess_step_args* a
   // The rules below compare rough times (microseconds) of the fetch and of what runs beside it; the miss
   // count of the previous step is only known under ESS_FLAG_AUTO, without it nothing is confined.
   bool confine = false, confine2 = false, confine_da = false;
+  // A fetch of little (under 35 us, as far as the last step tells) is not worth the two waits across streams that running
+  // Attn0 beside it costs (12 us until Attn0 starts, 11 us from its end to Attn1): then everything follows on the
+  // caller's stream, Attn0 and Attn1 in one launch (the same ranges and sums).  Batch 23 x 48K, two tokens, a fetch of 20 us beside
+  // an Attn0 of 60.
+  bool da_short = false;
   ess_ticket_check chk{};                       // filled in by the launches that take their work by ticket
   chk.tickets = ctx->tickets;
   chk.flag = ctx->host_miss_dev + c.max_batch;
@@ -561,7 +575,7 @@ int ess_decode_step(ess_ctx* ctx, const ess_cache* cache, const ess_step_args* a
     // Attn0 on the XCDs the fetch leaves free (one workgroup per CU): rounds x (tiles x time per tile + start and end)
     const int work_cus = 32 * (8 - __builtin_popcount(ESS_FETCH_XCD_MASK & 0xffu));
     const int hg = (c.attn_heads + 127) / 128;
-    const int ns0e = pick_splits_target(c, B, T, attn0_cap(ctx, B, T), ESS_ATTN0_WGS, true);
+    const int ns0e = pick_splits_target(c, B, T, attn0_cap(ctx, B, T), ESS_ATTN0_WGS);
     const double hits = c.topk - (mean_miss / T < c.topk ? mean_miss / T : c.topk);
     const double tiles_item = (hits / ESS_ATTN_TILE) / ns0e + 1.0;
     const double rounds = (double)((long)B * T * hg * ns0e + work_cus - 1) / work_cus;
@@ -571,6 +585,9 @@ int ess_decode_step(ess_ctx* ctx, const ess_cache* cache, const ess_step_args* a
     confine = dba && T <= 2 && fetch_half >= 1.5 * idx_half;
     confine2 = confine && attn5 + 40.0 <= 1.15 * fetch_half;        // + Attn1 and merge of the first half
     confine_da = da_swap && attn5 <= 1.6 * fetch_all;
+  }
+  if (mean_miss >= 0 && da_swap && !confine_da && (double)B * mean_miss * c.row_stride / 50e3 < 35.0) {
+    da_short = true;
   }
   ctx->last_confined = confine_da ? 1 : (confine2 ? 2 : (confine ? 1 : 0));
   const uint32_t check_extra = ctx->last_confined ? ctx->check_extra : 0u;   // test hook, one confined step
@@ -588,12 +605,12 @@ int ess_decode_step(ess_ctx* ctx, const ess_cache* cache, const ess_step_args* a
 
   // attention splits: chosen from the whole batch and the same for both halves, so that every schedule
   // sums in the same order and gives the same bits
-  const int ns0 = offloaded ? pick_splits_target(c, B, T, attn0_cap(ctx, B, T), ESS_ATTN0_WGS, true) : pick_splits(ctx, B, T, ESS_MAX_SPLITS);
+  const int ns0 = offloaded ? pick_splits_target(c, B, T, attn0_cap(ctx, B, T), ESS_ATTN0_WGS) : pick_splits(ctx, B, T, ESS_MAX_SPLITS);
   const bool wide = wide_merge(c, B, T);
   int ns1 = 0;
   if (offloaded) {
     // Attn1 works on the short miss lists: as many splits as give the whole batch one workgroup per CU
-    ns1 = pick_splits_target(c, B, T, ESS_ROW_SPLITS - 16, 256, false);
+    ns1 = pick_splits_target(c, B, T, ESS_ROW_SPLITS - 16, 256);
   }
 
   // Stages 1 and 2 come in two forms: through the score array (index score, then top-k), or fused (the score array
@@ -678,7 +695,8 @@ int ess_decode_step(ess_ctx* ctx, const ess_cache* cache, const ess_step_args* a
       rc = ess_launch_bookkeeping(ctx, ch, used, Bh, T, c.topk, a->step, ctx->slot_idx_ws + bt0 * k,
                                   a->miss_count ? a->miss_count + b0 : nullptr, st, b0, h == 0, xcd_of(ESS_TKT_BOOK),
                                   (confine2 || (da_swap && confine_da)) ? ctx->tickets + (da_swap ? 0 : ESS_TKT_FETCH2) * ESS_TICKET_WORDS : nullptr,
-                                  da_swap ? ESS_N_TICKETS : ESS_N_TICKETS - ESS_TKT_FETCH2);
+                                  da_swap ? ESS_N_TICKETS : ESS_N_TICKETS - ESS_TKT_FETCH2,
+                                  da_short ? nullptr : ctx->ev_book[h]);
       if (rc != ESS_OK) return rc;
     } else {
       rc = run_cache_step(ctx, ch, used, Bh, T, c.topk, a->step, ctx->slot_idx_ws + bt0 * k,
@@ -710,19 +728,33 @@ int ess_decode_step(ess_ctx* ctx, const ess_cache* cache, const ess_step_args* a
     // wait on another stream's event costs several microseconds when the event fires late and almost
     // nothing when it has fired long before: this way both waits of the step are of the second kind
     // (the side stream's wait for the bookkeeping delays only Attn0).
-    ESS_HIP(hipEventRecord(ctx->ev_book[0], st));
+    if (da_short) {
+      ESS_BEGIN(5);
+      rc = ess_launch_fill(ctx, *cache, B, st, 0, 64);
+      if (rc != ESS_OK) return rc;
+      ESS_END(5);
+      ESS_BEGIN(3);
+      rc = ess_launch_attn_partial(ctx, q16, cache->slot_pool, ctx->hit_list, ctx->n_hit, B, T, 0, ns0, ns0 + ns1, st, 0,
+                                   ess_xcd{nullptr, 0, nullptr, 0}, nullptr, ctx->miss_list, ctx->n_miss, ns1);
+      if (rc != ESS_OK) return rc;
+      ESS_END(3);
+      ESS_BEGIN(4);
+      rc = ess_launch_attn_merge(ctx, B, T, ns0 + ns1, wide, a->out_bf16, a->lse, st);
+      if (rc != ESS_OK) return rc;
+      ESS_END(4);
+      return ESS_OK;
+    }
     ESS_HIP(hipStreamWaitEvent(ctx->side, ctx->ev_book[0], 0));
     hipEvent_t* aev = (pev && ((ctx->prof_mask >> 3) & 1u)) ? pev + ESS_PROF_MAIN : nullptr;
     if (aev) ESS_HIP(hipEventRecord(aev[0], ctx->side));
     rc = ess_launch_attn_partial(ctx, q16, cache->slot_pool, ctx->hit_list, ctx->n_hit, B, T, 0, ns0, ns0 + ns1, ctx->side, 0,
-                                 confine_da ? tk_xcd(ESS_TKT_ATTN0) : ess_xcd{nullptr, 0, nullptr, 0});
+                                 confine_da ? tk_xcd(ESS_TKT_ATTN0) : ess_xcd{nullptr, 0, nullptr, 0}, ctx->ev_fill[0]);      // ev_fill[0] here: Attn0 done
     if (rc != ESS_OK) return rc;
     if (aev) {
       ESS_HIP(hipEventRecord(aev[1], ctx->side));
       ctx->prof_nfill[pslot] = 1;
       ctx->prof_pair_stage[(size_t)pslot * ESS_PROF_FILL] = 3;
     }
-    ESS_HIP(hipEventRecord(ctx->ev_fill[0], ctx->side));          // here: Attn0 done
     ESS_BEGIN(5);
     rc = confine_da ? ess_launch_fill(ctx, *cache, B, st, 0, wgs2, mask2, ctx->tickets) : ess_launch_fill(ctx, *cache, B, st, 0, 64);
     if (rc != ESS_OK) return rc;
@@ -747,7 +779,6 @@ int ess_decode_step(ess_ctx* ctx, const ess_cache* cache, const ess_step_args* a
     // of the first half.  The caller's stream ends with Attn1 of the second half and the merge.
     const ess_cache c0 = shift_cache(c, *cache, hb0[0]), c1 = shift_cache(c, *cache, hb0[1]);
     const size_t bt1 = (size_t)hb0[1] * T;
-    ESS_HIP(hipEventRecord(ctx->ev_book[1], st));                    // second half's bookkeeping done
     ESS_BEGIN(5);
     rc = confine2 ? ess_launch_fill(ctx, c1, hB[1], st, hb0[1], wgs2, mask2, ctx->tickets + ESS_TKT_FETCH2 * ESS_TICKET_WORDS)
                   : ess_launch_fill(ctx, c1, hB[1], st, hb0[1], 28);
@@ -770,7 +801,8 @@ int ess_decode_step(ess_ctx* ctx, const ess_cache* cache, const ess_step_args* a
                                  confine2 ? tk_xcd(ESS_TKT_ATTN1) : ess_xcd{nullptr, 0, nullptr, 0});
     if (rc != ESS_OK) return rc;
     // each half is merged on the stream its Attn1 ran on: only half a merge is left behind the last fetch
-    rc = ess_launch_attn_merge(ctx, hB[0], T, ns0 + ns1, wide, a->out_bf16, a->lse, ctx->side, nullptr, 0, hb0[0]);
+    rc = ess_launch_attn_merge(ctx, hB[0], T, ns0 + ns1, wide, a->out_bf16, a->lse, ctx->side, nullptr, 0, hb0[0], nullptr,
+                               ctx->ev_fill[1]);                     // ev_fill[1] here: everything on the side stream done
     if (rc != ESS_OK) return rc;
     if (aev) {
       ESS_HIP(hipEventRecord(aev[3], ctx->side));
@@ -778,7 +810,6 @@ int ess_decode_step(ess_ctx* ctx, const ess_cache* cache, const ess_step_args* a
       ctx->prof_pair_stage[(size_t)pslot * ESS_PROF_FILL + 1] = 3;
       ctx->prof_pair_stage[(size_t)pslot * ESS_PROF_FILL + 2] = 4;
     }
-    ESS_HIP(hipEventRecord(ctx->ev_fill[1], ctx->side));           // here: everything on the side stream done
     ESS_BEGIN(4);
     rc = ess_launch_attn_partial(ctx, q16 + bt1 * c.attn_heads * ESS_ROW_DIM, c1.slot_pool, ctx->miss_list + bt1 * k,
                                  ctx->n_miss + bt1, hB[1], T, ns0, ns1, ns0 + ns1, st, hb0[1]);

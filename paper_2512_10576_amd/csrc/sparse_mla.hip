@@ -229,7 +229,7 @@ __global__ __launch_bounds__(NTH, 1) void k_attn_partial_tr(
     const uint16_t* __restrict__ q, const uint8_t* __restrict__ pool, const int32_t* __restrict__ list,
     const int32_t* __restrict__ n_list, int T, int H, int kk, int S, int row_stride, float scale_log2e, int split0,
     int nsplit, int pitch, _Float16* __restrict__ o_part, float* __restrict__ lse_part, const uint8_t* __restrict__ zero_row,
-    ess_xcd xcd, int n_bt, int n_hg) {
+    ess_xcd xcd, int n_bt, int n_hg, const int32_t* __restrict__ list_b, const int32_t* __restrict__ n_list_b, int nsplit_b) {
   extern __shared__ __align__(16) uint8_t lds[];
   __shared__ int s_item;
   constexpr bool kDma = FMT == ESS_FMT_BF16;       // rows go to LDS as they are; else through registers, dequantised
@@ -243,7 +243,7 @@ __global__ __launch_bounds__(NTH, 1) void k_attn_partial_tr(
   // multiple of eight.  Drawn from counters (off the XCDs to be avoided): every XCD that takes work has a counter
   // of its own (class c of nw) that hands out the items of rows c, c + nw, c + 2 nw .. one after the other; a
   // workgroup whose class has run out goes on with the next class, so any one workgroup could finish the launch.
-  const int per_row = nsplit * n_hg;
+  const int per_row = (nsplit + nsplit_b) * n_hg;
   int cls = 0, nw = 1, tried = 1;
   if constexpr (DYN) {
     if (!ess_ticket_join(xcd, &s_item)) return;
@@ -264,10 +264,15 @@ __global__ __launch_bounds__(NTH, 1) void k_attn_partial_tr(
   const int head0 = hg * HPG + wave * HPW;
   const bool wave_active = head0 < H;
 
-  const int n = n_list ? min(n_list[bt], kk) : kk;
+  // (a launch may carry two lists: ranges 0 .. nsplit - 1 are the first's, the rest the second's)
+  const bool second = split >= nsplit;
+  const int32_t* const my_list = second ? list_b : list;
+  const int32_t* const my_n = second ? n_list_b : n_list;
+  const int ns = second ? nsplit_b : nsplit;
+  const int n = my_n ? min(my_n[bt], kk) : kk;
   const int tiles_total = (n + TILE - 1) / TILE;
-  const int tps = min((tiles_total + nsplit - 1) / nsplit, MAX_TPS);
-  const int tile_begin = split * tps;
+  const int tps = min((tiles_total + ns - 1) / ns, MAX_TPS);
+  const int tile_begin = (second ? split - nsplit : split) * tps;
   const int tile_end = min(tile_begin + tps, tiles_total);
   const int my_tiles = max(tile_end - tile_begin, 0);
   if (my_tiles == 0) {                             // an empty range (a short miss list): its rows are never read
@@ -278,7 +283,7 @@ __global__ __launch_bounds__(NTH, 1) void k_attn_partial_tr(
   __builtin_amdgcn_sched_barrier(0);
 
   // this thread's share of the split's entry list: asked for first, so that it arrives while the queries are staged
-  const int32_t* lrow = list + (size_t)bt * kk;
+  const int32_t* lrow = my_list + (size_t)bt * kk;
   const uint8_t* pbase = pool + (size_t)b * S * row_stride;
   constexpr int SLOTS_PT = MAX_TPS * TILE / NTH;   // 8 list entries per thread at most
   int my_slot[SLOTS_PT];
@@ -837,22 +842,23 @@ int ess_init_attn_kernels() {
 }
 
 int ess_launch_attn_partial(ess_ctx* ctx, const void* q, const uint8_t* slot_pool, const int32_t* list,
-                            const int32_t* n_list, int B, int T, int split0, int nsplit, int pitch, hipStream_t st, int b0, ess_xcd xcd) {
+                            const int32_t* n_list, int B, int T, int split0, int nsplit, int pitch, hipStream_t st, int b0, ess_xcd xcd,
+                            hipEvent_t done, const int32_t* list_b, const int32_t* n_list_b, int nsplit_b) {
   const ess_config& c = ctx->cfg;
-  if (split0 + nsplit > pitch || (size_t)(b0 + B) * T * pitch > ctx->part_cap) return ess_fail(ESS_ERR_INVALID_ARG, "internal: partial results");
+  if (split0 + nsplit + nsplit_b > pitch || (size_t)(b0 + B) * T * pitch > ctx->part_cap) return ess_fail(ESS_ERR_INVALID_ARG, "internal: partial results");
   if (nsplit < ess_attn_min_splits(c)) return ess_fail(ESS_ERR_INVALID_ARG, "internal: too few attention splits");
   const int n_hg = (c.attn_heads + HPG - 1) / HPG;      // 128 heads per workgroup
-  dim3 grid(B * T, nsplit, n_hg);
-  if (xcd.ticket) grid = dim3(ess_xcd_grid(nsplit * B * T * n_hg, xcd));     // one workgroup per CU
+  dim3 grid(B * T, nsplit + nsplit_b, n_hg);
+  if (xcd.ticket) grid = dim3(ess_xcd_grid((nsplit + nsplit_b) * B * T * n_hg, xcd));     // one workgroup per CU
   const float sc = c.sm_scale * kLog2e;
   const uint16_t* qq = static_cast<const uint16_t*>(q);
   // partial results of sequence b0 onward
   _Float16* op = reinterpret_cast<_Float16*>(ctx->o_part) + (size_t)b0 * T * pitch * c.attn_heads * ESS_LATENT_DIM;
   float* lp = ctx->lse_part + (size_t)b0 * T * pitch * c.attn_heads * 2;
 #define ESS_ATTN_LAUNCH(FMT, DYN)                                                                                      \
-  hipLaunchKernelGGL((k_attn_partial_tr<FMT, DYN>), grid, dim3(NTH), tr_lds_bytes(FMT), st, qq, slot_pool, list, n_list, T, \
+  ESS_HIP(ess_launch_done(done, &k_attn_partial_tr<FMT, DYN>, grid, dim3(NTH), (size_t)tr_lds_bytes(FMT), st, qq, slot_pool, list, n_list, T, \
                      c.attn_heads, c.topk, c.slots_per_seq, c.row_stride, sc, split0, nsplit, pitch, op, lp, ctx->zero_row, xcd,  \
-                     B * T, n_hg)
+                     B * T, n_hg, list_b, n_list_b, nsplit_b))
   if (c.latent_fmt == ESS_FMT_BF16) {
     if (xcd.ticket) ESS_ATTN_LAUNCH(ESS_FMT_BF16, true); else ESS_ATTN_LAUNCH(ESS_FMT_BF16, false);
   } else {
@@ -864,7 +870,7 @@ int ess_launch_attn_partial(ess_ctx* ctx, const void* q, const uint8_t* slot_poo
 }
 
 int ess_launch_attn_merge(ess_ctx* ctx, int B, int T, int nsplit_total, bool wide, void* out_bf16, float* lse, hipStream_t st,
-                          int32_t* zero_cnt, int n_zero, int b0, const ess_ticket_check* check) {
+                          int32_t* zero_cnt, int n_zero, int b0, const ess_ticket_check* check, hipEvent_t done) {
   const int H = ctx->cfg.attn_heads;
   ess_ticket_check chk{};
   if (check) chk = *check;
@@ -875,9 +881,8 @@ int ess_launch_attn_merge(ess_ctx* ctx, int B, int T, int nsplit_total, bool wid
   uint16_t* o = static_cast<uint16_t*>(out_bf16) + r0 * ESS_LATENT_DIM;
   float* ls = lse ? lse + r0 : nullptr;
   if (wide)
-    hipLaunchKernelGGL((k_attn_merge<4>), dim3(rows), dim3(256), 0, st, op, lp, H, nsplit_total, rows, o, ls, zero_cnt, n_zero, chk);
+    ESS_HIP(ess_launch_done(done, &k_attn_merge<4>, dim3(rows), dim3(256), 0, st, op, lp, H, nsplit_total, rows, o, ls, zero_cnt, n_zero, chk));
   else
-    hipLaunchKernelGGL((k_attn_merge<1>), dim3((rows + 3) / 4), dim3(256), 0, st, op, lp, H, nsplit_total, rows, o, ls, zero_cnt, n_zero, chk);
-  ESS_HIP(hipGetLastError());
+    ESS_HIP(ess_launch_done(done, &k_attn_merge<1>, dim3((rows + 3) / 4), dim3(256), 0, st, op, lp, H, nsplit_total, rows, o, ls, zero_cnt, n_zero, chk));
   return ESS_OK;
 }
