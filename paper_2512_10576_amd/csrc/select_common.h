@@ -93,4 +93,29 @@ __device__ __forceinline__ void sample_bins(const uint32_t* shist, uint32_t* wav
   __syncthreads();
 }
 
+// The bin of a complete histogram (laid out by sample_slot<NTH>) that holds the need-th largest of its entries
+// (1 <= need <= their number) -> *sel (LDS).  Ends with a barrier.
+template <int NTH>
+__device__ __forceinline__ void crossing_bin(const uint32_t* shist, uint32_t* wave_tot, uint32_t* sel, uint32_t need) {
+  constexpr int BPT = SBINS / NTH;
+  const int top_bin = SBINS - 1 - (int)threadIdx.x * BPT;
+  const int top_slot = sample_slot<NTH>(top_bin);
+  uint32_t mine = 0, bin[BPT];
+#pragma unroll
+  for (int r = 0; r < BPT; ++r) { bin[r] = shist[top_slot - r]; mine += bin[r]; }
+  uint32_t total;
+  const uint32_t inc = block_incl_scan<NTH>(mine, wave_tot, &total);
+  uint32_t above = inc - mine;
+  if (above < need && inc >= need) {
+    int at = -1;
+#pragma unroll
+    for (int r = 0; r < BPT; ++r) {
+      above += bin[r];
+      if (at < 0 && above >= need) at = r;
+    }
+    *sel = (uint32_t)(top_bin - at);
+  }
+  __syncthreads();
+}
+
 }  // namespace ess_sel

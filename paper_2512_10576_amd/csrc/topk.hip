@@ -38,7 +38,7 @@ using ess_sel::SBITS;
 using ess_sel::SBINS;
 constexpr int SAMPLE_TARGET = 4096;         // at most this many samples per row (four per thread), about every 16th score or fewer
 static_assert(SAMPLE_TARGET <= 4 * NT, "the sample is loaded in one round of four per thread");
-constexpr int FAST_MIN_VIS = 16384;
+constexpr int FAST_MIN_VIS = CAND_CAP + 1;   // rows above the candidate list's size are sampled (path A)
 
 struct __align__(16) TopkShared {
   union {
@@ -210,19 +210,13 @@ __device__ __forceinline__ void crossing_digit(TopkShared& sm, uint32_t need) {
 // that holds the k-th largest key is found, and inside it -- a handful of keys -- the key is found by counting.
 // Returns false, with the keys copied to sm.cand, when that digit holds more keys than the counting step takes
 // (massive ties, or a k-th largest score outside the range): the caller goes on with the general selection.
-template <bool SRC_LDS>
-__device__ __forceinline__ bool finish_fast(TopkShared& sm, const unsigned long long* grow, uint32_t listed,
+constexpr int PER = CAND_CAP / NT;           // keys per thread
+__device__ __forceinline__ bool finish_keys(TopkShared& sm, const unsigned long long (&c)[PER], uint32_t listed,
                                             uint32_t lo, uint32_t hi, int vis, int k, int IB, int32_t* __restrict__ orow) {
-  constexpr int PER = CAND_CAP / NT;
   constexpr uint32_t SMALL = 1024;           // keys the counting step takes: one per thread
   const int tid = threadIdx.x;
   const unsigned long long imask = (1ull << IB) - 1ull;
-  unsigned long long c[PER];
-#pragma unroll
-  for (int u = 0; u < PER; ++u)
-    c[u] = (uint32_t)(u * NT + tid) < listed ? (SRC_LDS ? sm.cand[u * NT + tid] : grow[u * NT + tid]) : 0ull;
-  if (SRC_LDS) __syncthreads();              // the bitmap shares its memory with the list: every thread holds its keys first
-  // while the keys are on their way: clear the histogram and the row's bitmap
+  // (keys of a list may still be on their way:) clear the histogram and the row's bitmap
   uint32_t* bmp = sm.hist;
   const int W = (vis + 31) >> 5;
   for (int j = tid; j < W; j += NT) bmp[j] = 0;
@@ -278,6 +272,18 @@ __device__ __forceinline__ bool finish_fast(TopkShared& sm, const unsigned long 
   __syncthreads();
   emit_bitmap(sm, bmp, W, k, orow);
   return true;
+}
+
+template <bool SRC_LDS>
+__device__ __forceinline__ bool finish_fast(TopkShared& sm, const unsigned long long* grow, uint32_t listed,
+                                            uint32_t lo, uint32_t hi, int vis, int k, int IB, int32_t* __restrict__ orow) {
+  const int tid = threadIdx.x;
+  unsigned long long c[PER];
+#pragma unroll
+  for (int u = 0; u < PER; ++u)
+    c[u] = (uint32_t)(u * NT + tid) < listed ? (SRC_LDS ? sm.cand[u * NT + tid] : grow[u * NT + tid]) : 0ull;
+  if (SRC_LDS) __syncthreads();              // the bitmap shares its memory with the list: every thread holds its keys first
+  return finish_keys(sm, c, listed, lo, hi, vis, k, IB, orow);
 }
 
 // MODE 0: one workgroup does the whole row (grid: rows).
@@ -339,6 +345,36 @@ __device__ __forceinline__ void topk_item(TopkShared& sm, int item, int parts, f
   bool all_in_cand = false;                 // ... and every key above it as well (path A)
   int nc = 0;
 
+  // ---- S: rows that fit the candidate list whole need no sample and no list: eight keys per thread in registers, a
+  // histogram of their top 14 bits tells exactly in which bin the k-th largest lies, and that bin's range is resolved
+  // like the range between two sampled bounds.  (They went through path B and a radix select of five 11-bit passes
+  // over 64-bit keys in LDS: 15 us for a row of 8192, now 8.5.)
+  if ((MODE == 0 || MODE == 2) && vis <= CAND_CAP) {
+    float sv[PER];
+#pragma unroll
+    for (int u = 0; u < PER; ++u) sv[u] = u * NT + tid < vis ? srow[u * NT + tid] : 0.f;
+    for (int j = tid; j < ess_sel::sample_words<NT>(); j += NT) sm.shist[j] = 0;
+    if (tid == 0) sm.sbin[0] = 0u;
+    __syncthreads();
+    unsigned long long c[PER];
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      const int i = u * NT + tid;
+      c[u] = i < vis ? comp_of(i, sv[u]) : 0ull;
+      if (i < vis) atomicAdd(&sm.shist[ess_sel::sample_slot<NT>((uint32_t)(c[u] >> IB) >> (32 - SBITS))], 1u);
+    }
+    __syncthreads();
+    ess_sel::crossing_bin<NT>(sm.shist, sm.wave_tot, sm.sbin, (uint32_t)k);     // (ends with a barrier: shist is dead from here)
+    const uint32_t bin = sm.sbin[0];
+    const uint32_t lo = bin << (32 - SBITS), hi = bin == SBINS - 1 ? 0xffffffffu : (bin + 1) << (32 - SBITS);
+    __syncthreads();
+    if (finish_keys(sm, c, (uint32_t)vis, lo, hi, vis, k, IB, orow)) return;
+    // (more than 1024 keys share a 2047th of the bin: the keys are in sm.cand now, the general selection takes them)
+    nc = vis;
+    have_cand = true;
+    all_in_cand = true;
+  }
+
   // ---- A: sampled one-pass collection for long rows
   const bool use_list = MODE >= 2 && listed >= (uint32_t)k && listed <= (uint32_t)CAND_CAP;
   if (MODE == 3 && !use_list) {
@@ -367,7 +403,7 @@ __device__ __forceinline__ void topk_item(TopkShared& sm, int item, int parts, f
       __syncthreads();
     }
   }
-  if (vis >= FAST_MIN_VIS || use_list) {
+  if ((vis >= FAST_MIN_VIS || use_list) && !have_cand) {
    uint32_t lo_bin = 0, hi_bin = 0xffffffffu;
    if (!use_list) {
     // samples: blocks of 16 consecutive scores (one 64-byte piece of a cache line), every bstride-th block,
@@ -662,7 +698,7 @@ int launch_topk(int max_ctx, int k, const float* score_in, const int32_t* ctx_le
   // workgroups on every row (as many as fill the chip, at most 8)
   const int rows = B * T;
   int parts = 1;
-  if (max_ctx >= 4 * FAST_MIN_VIS && rows <= ESS_TOPK_SHARED_ROWS) {
+  if (max_ctx >= 65536 && rows <= ESS_TOPK_SHARED_ROWS) {
     parts = 256 / rows;
     if (parts > 8) parts = 8;
   }

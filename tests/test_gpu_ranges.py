@@ -1,0 +1,144 @@
+"""GPU parity at the edges of the ranges that attention, top-k and the schedules divide their work by: list lengths
+around whole tiles and splits, head counts around a wave's 32, rows around the candidate list's size, gathered rows
+beside a fetch, and a fetch in line with attention against one beside it."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import ess_oracle as O
+from paper_2512_10576_amd import synth
+from tests.test_gpu_stages import _check_attn, _ctx, _qbits, _run_topk, _topk_sets_equal
+
+pytestmark = pytest.mark.gpu
+
+
+# lengths: nothing, one entry, a tile of 32 less and more, tiles that do not divide by the split count
+@pytest.mark.parametrize("fmt", [O.FMT_BF16, O.FMT_FP8])
+@pytest.mark.parametrize("B,T,H,k,lens", [
+    (1, 1, 128, 2048, [2048]),                            # many splits of one row, merged by four waves
+    (1, 1, 5, 65, [65]),
+    (3, 2, 40, 160, [0, 1, 31, 32, 33, 160]),             # a second wave with eight heads
+    (2, 2, 33, 97, [96, 97, 64, 63]),
+    (5, 1, 128, 300, [300, 0, 129, 128, 299]),
+    (65, 4, 16, 96, [96, 95, 0, 32]),                     # 260 rows: one split, no empty workgroup left over
+])
+def test_attention_list_lengths_and_heads(ess_lib, fmt, B, T, H, k, lens):
+    print("attention ranges", fmt, B, T, H, k, flush=True)
+    S = max(512, k)
+    rng = np.random.default_rng(B * 1000 + H)
+    rows = synth.latent_rows_bf16(B, B * S) if fmt == O.FMT_BF16 else synth.latent_rows_fp8(B, B * S)
+    pool = rows.reshape(B, S, -1)
+    q = synth.attn_query(H, B, T, H)
+    idx = np.full((B, T, k), -1, np.int32)
+    for i in range(B * T):
+        n = lens[i % len(lens)]
+        idx[i // T, i % T, :n] = rng.choice(S, n, replace=False)
+    if k > 2:
+        idx[0, 0, 1] = -1                                 # a hole
+    scale = 1 / 24
+    some = slice(0, min(B, 3))                            # the oracle on a few sequences
+    ref_out, ref_lse = O.sparse_mla(_qbits(q[some]), pool[some].numpy(), idx[some], fmt, scale)
+    ctx = _ctx(ess_lib, max_batch=B, max_q_tokens=T, max_ctx=S, idx_heads=4, idx_dim=32, topk=k, attn_heads=H, latent_fmt=fmt,
+               sm_scale=scale)
+    out = torch.full((B, T, H, 512), 9.0, dtype=torch.bfloat16, device="cuda")
+    lse = torch.full((B, T, H), 9.0, dtype=torch.float32, device="cuda")
+    ctx.sparse_mla_decode(q.cuda(), pool.cuda(), torch.from_numpy(idx).cuda(), out, lse)
+    torch.cuda.synchronize()
+    ctx.close()
+    # lists of a handful of quantised entries: few bf16-rounded weights, which do not average out (2^-8 of the values)
+    err = np.abs(out[some].float().cpu().numpy() - ref_out)
+    assert np.all(err <= 2e-2 + 2e-2 * np.abs(ref_out)), err.max()
+    short = (idx[some] >= 0).sum(-1) < 64
+    if not short.all():
+        long_rows = ~short
+        _check_attn(out[some][torch.from_numpy(long_rows)], lse[some][torch.from_numpy(long_rows)], ref_out[long_rows], ref_lse[long_rows])
+    assert np.array_equal(np.isneginf(lse[some].cpu().numpy()), np.isneginf(ref_lse))
+
+
+# rows around k, a thread's eight keys, the candidate list (8192) and the sampled path above it
+@pytest.mark.parametrize("kind", ["distinct", "ties", "one value", "low and high"])
+@pytest.mark.parametrize("vis,k", [(9, 8), (1025, 1024), (4097, 2048), (8191, 2048), (8192, 4096), (8193, 2048), (16384, 513)])
+def test_topk_short_rows(ess_lib, kind, vis, k):
+    print("topk", kind, vis, k, flush=True)
+    rng = np.random.default_rng(vis)
+    sc = rng.standard_normal((1, 1, vis)).astype(np.float32) * 100
+    if kind == "ties":
+        sc = np.round(sc / 64).astype(np.float32)         # a dozen values: thousands of equal scores
+    elif kind == "one value":
+        sc[:] = np.float32(-3.5)
+    elif kind == "low and high":                          # the k-th largest among the lowest value, infinities and NaN
+        sc[:] = np.float32(-np.inf)
+        sc[0, 0, rng.choice(vis, k - 3, replace=False)] = rng.standard_normal(k - 3).astype(np.float32)
+        sc[0, 0, 1] = np.float32(np.inf)
+        sc[0, 0, 2] = np.float32(np.nan)
+    lens = np.array([vis])
+    _topk_sets_equal(_run_topk(ess_lib, sc, [vis], k, 1), O.topk(sc, lens, k))
+
+
+@pytest.mark.parametrize("B,T,L,S,k", [(1, 1, 300, 40, 17), (3, 2, 1000, 257, 100), (2, 4, 3000, 1500, 333)])
+def test_gathered_rows_beside_a_fetch(ess_lib, B, T, L, S, k):
+    """the rows of resident and of fetched entries, entry counts that are no multiple of a wave's sixteen"""
+    from paper_2512_10576_amd import binding as bnd
+    print("gather ranges", B, T, L, S, k, flush=True)
+    rng = np.random.default_rng(L)
+    host = torch.empty((B, L, 1152), dtype=torch.uint8, pin_memory=True)
+    host.copy_(synth.latent_rows_bf16(L, B * L).reshape(B, L, 1152))
+    ctx = _ctx(ess_lib, max_batch=B, max_q_tokens=T, max_ctx=L, idx_heads=4, idx_dim=32, topk=k, attn_heads=8, slots_per_seq=max(S, T * k))
+    cache = bnd.Cache.allocate(ctx.cfg, B, host_pool=host)
+    ctx.cache_reset(cache, B)
+    lens = torch.full((B,), L, dtype=torch.int32, device="cuda")
+    slot = torch.empty((B, T, k), dtype=torch.int32, device="cuda")
+    rows = torch.empty((B, T, k, 1152), dtype=torch.uint8, device="cuda")
+    for step in range(1, 5):
+        idx = np.stack([np.stack([rng.choice(L, k, replace=False) for _ in range(T)]) for _ in range(B)]).astype(np.int32)
+        idx[:, :, step::7] = -1
+        rows.fill_(0xEE)
+        ctx.gather_latent(cache, torch.from_numpy(idx).cuda(), lens, step, slot, rows)
+        torch.cuda.synchronize()
+        want = np.zeros((B, T, k, 1152), np.uint8)
+        for b in range(B):
+            v = idx[b] >= 0
+            want[b][v] = host[b].numpy()[idx[b][v]]
+        assert np.array_equal(rows.cpu().numpy(), want), step
+    ctx.close()
+
+
+@pytest.mark.parametrize("B,T,fmt", [(3, 2, O.FMT_FP8), (2, 1, O.FMT_BF16)])
+def test_short_fetch_in_line_gives_the_bits_of_the_overlapped_schedule(ess_lib, B, T, fmt):
+    """With few misses the switch runs fetch and attention in line, Attn0 and Attn1 in one launch; the plain schedule runs
+    Attn0 beside the fetch: same outputs and cache state, bit for bit."""
+    from paper_2512_10576_amd import binding as bnd
+    print("short fetch", B, T, fmt, flush=True)
+    L, k, H, S = 9000, 512, 128, 4 * 512 * T
+    rows = synth.latent_rows_bf16 if fmt == O.FMT_BF16 else synth.latent_rows_fp8
+    host = rows(5, B * L)
+    hp = torch.empty((B, L, host.shape[-1]), dtype=torch.uint8, pin_memory=True)
+    hp.copy_(host.reshape(B, L, -1))
+    qi, w, key = (x.cuda() for x in synth.indexer_inputs(5, B, T, 64, 128, L, 8, 8, 16))
+    lens = torch.full((B,), L, dtype=torch.int32)
+    sets = synth.TopkTrace(3, lens, T, k, 0.97)
+    trace = [sets.next().cuda() for _ in range(4)]
+    lens = lens.cuda()
+    results = {}
+    for flags in (bnd.ESS_FLAG_AUTO, 0):
+        ctx = _ctx(ess_lib, max_batch=B, max_q_tokens=T, max_ctx=L, idx_heads=64, idx_dim=128, topk=k, attn_heads=H, latent_fmt=fmt,
+                   slots_per_seq=S, flags=flags)
+        cache = bnd.Cache.allocate(ctx.cfg, B, host_pool=hp)
+        ctx.cache_reset(cache, B)
+        idx = torch.empty((B, T, k), dtype=torch.int32, device="cuda")
+        out = torch.empty((B, T, H, 512), dtype=torch.bfloat16, device="cuda")
+        lse = torch.empty((B, T, H), dtype=torch.float32, device="cuda")
+        miss = torch.empty((B,), dtype=torch.int32, device="cuda")
+        got = []
+        for step in range(4):
+            q = synth.attn_query(50 + step, B, T, H).cuda()
+            ctx.decode_step(cache, qi, w, key, lens, q, step + 1, idx, out, lse, miss, topk_override=trace[step])
+            torch.cuda.synchronize()
+            assert ctx.last_overlap() == 0
+            got.append([x.clone() for x in (out, lse, miss, cache.slot_of, cache.token_of, cache.stamp, cache.slot_pool)])
+        assert int(miss.sum()) > 0
+        ctx.close()
+        results[flags] = got
+    for a, b in zip(results[bnd.ESS_FLAG_AUTO], results[0]):
+        for x, y in zip(a, b):
+            assert torch.equal(x, y)
