@@ -435,30 +435,52 @@ __global__ __launch_bounds__(FILL_WPB * 64) void k_fill(const uint8_t* __restric
   }
 }
 
-// rows_out[b,t,j,:] = slot_pool[b, slot_idx[b,t,j], :] (zeros where the slot is -1); one wave per row.
+// rows_out[b,t,j,:] = slot_pool[b, slot_idx[b,t,j], :] (zeros where the slot is -1).  A wave takes sixteen entries, their
+// slots in one load, and copies four rows at a time.
 // WHICH 1, 2: slot_idx marks the entries that this step fetches (ESS_FRESH_BIT); the others are gathered while the fetch
 // runs, these after it.
+constexpr int GATHER_ROWS = 16;
 template <int WHICH>
 __global__ __launch_bounds__(256) void k_gather_rows(const uint8_t* __restrict__ slot_pool,
                                                      const int32_t* __restrict__ slot_idx, int per_seq, int S,
                                                      int row_stride, uint8_t* __restrict__ rows_out) {
-  const int b = blockIdx.y;
-  const int lane = threadIdx.x & 63;
-  const int nw = gridDim.x * 4;
-  const int chunks = row_stride >> 4;
-  for (int i = blockIdx.x * 4 + (threadIdx.x >> 6); i < per_seq; i += nw) {
-    int v = slot_idx[(size_t)b * per_seq + i];
-    if (WHICH) {
-      const bool fresh = v >= 0 && (v & ESS_FRESH_BIT);
-      if (fresh != (WHICH == 2)) continue;
-      if (fresh) v &= ~ESS_FRESH_BIT;
+  const int b = blockIdx.y, lane = threadIdx.x & 63;
+  const int i0 = (blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6)) * GATHER_ROWS;
+  if (i0 >= per_seq) return;
+  const int chunks = row_stride >> 4;                        // <= 128
+  const bool in = lane < GATHER_ROWS && i0 + lane < per_seq;
+  int v = in ? slot_idx[(size_t)b * per_seq + i0 + lane] : -1;
+  bool mine = in;
+  if (WHICH) {
+    const bool fresh = v >= 0 && (v & ESS_FRESH_BIT);
+    mine = in && fresh == (WHICH == 2);
+    if (fresh) v &= ~ESS_FRESH_BIT;
+  }
+  uint32_t todo = (uint32_t)__ballot(mine);
+  const uint8_t* pool = slot_pool + (size_t)b * S * row_stride;
+  uint8_t* out = rows_out + ((size_t)b * per_seq + i0) * row_stride;
+  while (todo) {
+    uint4 x[4], y[4];
+    int row[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      row[u] = todo ? __ffs(todo) - 1 : -1;
+      if (row[u] < 0) continue;
+      todo &= todo - 1;
+      const int s = __builtin_amdgcn_readlane(v, row[u]);
+      x[u] = y[u] = make_uint4(0, 0, 0, 0);
+      if (s >= 0 && s < S) {
+        const uint4* src = reinterpret_cast<const uint4*>(pool + (size_t)s * row_stride);
+        if (lane < chunks) x[u] = src[lane];
+        if (lane + 64 < chunks) y[u] = src[lane + 64];
+      }
     }
-    uint4* dst = reinterpret_cast<uint4*>(rows_out + ((size_t)b * per_seq + i) * row_stride);
-    if (v >= 0 && v < S) {
-      const uint4* src = reinterpret_cast<const uint4*>(slot_pool + ((size_t)b * S + v) * row_stride);
-      for (int c = lane; c < chunks; c += 64) dst[c] = src[c];
-    } else {
-      for (int c = lane; c < chunks; c += 64) dst[c] = make_uint4(0, 0, 0, 0);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      if (row[u] < 0) continue;
+      uint4* dst = reinterpret_cast<uint4*>(out + (size_t)row[u] * row_stride);
+      if (lane < chunks) dst[lane] = x[u];
+      if (lane + 64 < chunks) dst[lane + 64] = y[u];
     }
   }
 }
@@ -715,6 +737,7 @@ int ess_launch_fill(ess_ctx* ctx, const ess_cache& cache, int B, hipStream_t st,
 int ess_launch_gather_rows(const ess_config& c, const uint8_t* slot_pool, const int32_t* slot_idx, int B, int T,
                            uint8_t* rows_out, hipStream_t st, int which, hipEvent_t done) {
   auto kern = which == 0 ? &k_gather_rows<0> : (which == 1 ? &k_gather_rows<1> : &k_gather_rows<2>);
-  ESS_HIP(ess_launch_done(done, kern, dim3(64, B), dim3(256), 0, st, slot_pool, slot_idx, T * c.topk, c.slots_per_seq, c.row_stride, rows_out));
+  const int wgs = (T * c.topk + 4 * GATHER_ROWS - 1) / (4 * GATHER_ROWS);
+  ESS_HIP(ess_launch_done(done, kern, dim3(wgs, B), dim3(256), 0, st, slot_pool, slot_idx, T * c.topk, c.slots_per_seq, c.row_stride, rows_out));
   return ESS_OK;
 }

@@ -605,12 +605,25 @@ int ess_decode_step(ess_ctx* ctx, const ess_cache* cache, const ess_step_args* a
 
   // attention splits: chosen from the whole batch and the same for both halves, so that every schedule
   // sums in the same order and gives the same bits
-  const int ns0 = offloaded ? pick_splits_target(c, B, T, attn0_cap(ctx, B, T), ESS_ATTN0_WGS) : pick_splits(ctx, B, T, ESS_MAX_SPLITS);
+  int ns0 = offloaded ? pick_splits_target(c, B, T, attn0_cap(ctx, B, T), ESS_ATTN0_WGS) : pick_splits(ctx, B, T, ESS_MAX_SPLITS);
   const bool wide = wide_merge(c, B, T);
   int ns1 = 0;
   if (offloaded) {
     // Attn1 works on the short miss lists: as many splits as give the whole batch one workgroup per CU
     ns1 = pick_splits_target(c, B, T, ESS_ROW_SPLITS - 16, 256);
+    // Attn0 has time to spare only beside a long fetch.  With few sequences the fetch is short (120 misses a sequence are
+    // assumed here: the choice must not depend on the misses, or results would), and Attn0 should fill the chip, together with
+    // Attn1, which then mostly shares its launch.  (Batch 23 x two tokens: 4 + 1 ranges a row instead of 3 + 4.)
+    const long rows = (long)B * T * ((c.attn_heads + 127) / 128);
+    const int tiles = (c.topk + ESS_ATTN_TILE - 1) / ESS_ATTN_TILE, cap = attn0_cap(ctx, B, T);
+    const double fetch_us = B * 120.0 * c.row_stride / 50e3;
+    bool raised = false;
+    while (ns0 < cap && ns0 < tiles && ((tiles + ns0 - 1) / ns0 + 5.5) * 2.2 > fetch_us && rows * (ns0 + 2) <= 256) {
+      ++ns0;
+      raised = true;
+    }
+    if (raised && rows * (ns0 + ns1) > 256) ns1 = (int)(256 / rows - ns0) > 1 ? (int)(256 / rows - ns0) : 1;
+    if (ns1 < ess_attn_min_splits(c)) ns1 = ess_attn_min_splits(c);
   }
 
   // Stages 1 and 2 come in two forms: through the score array (index score, then top-k), or fused (the score array
