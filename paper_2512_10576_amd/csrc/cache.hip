@@ -161,6 +161,22 @@ __global__ __launch_bounds__(BT) void k_bookkeeping(
   }
   __syncthreads();                               // also: the stamps of the hits are visible
 
+  // the counts leave here, so that their way to memory (and to the host) passes beside the work below
+  if (tid == 0) {
+    miss_cnt[b] = (int32_t)m;
+    if (miss_count_out) miss_count_out[b] = (int32_t)m;
+    if (host_miss) host_miss[b] = (int32_t)m;       // pinned host memory: the host's view for the overlap switch
+    if (b == 0 && count_step) atomicAdd(&stats[0], 1ull);
+    atomicAdd(&stats[1], (unsigned long long)nvalid);
+    atomicAdd(&stats[2], (unsigned long long)m);
+    atomicAdd(&stats[3], (unsigned long long)m * (unsigned long long)row_stride);
+    // the same per sequence (adds that return nothing: a read of the counters would be waited for)
+    atomicAdd(&seq_stats[4 * b + 0], 1ull);
+    atomicAdd(&seq_stats[4 * b + 1], (unsigned long long)nvalid);
+    atomicAdd(&seq_stats[4 * b + 2], (unsigned long long)m);
+    atomicAdd(&seq_stats[4 * b + 3], (unsigned long long)m * (unsigned long long)row_stride);
+  }
+
   if (m > 0) {
     // this thread's slots: [v0, v1), contiguous so that slot order is thread order
     const int spt = (S + BT - 1) / BT;
@@ -355,24 +371,62 @@ __global__ __launch_bounds__(BT) void k_bookkeeping(
       fill_slot[(size_t)b * fill_cap + i] = v;
     }
   }
-  if (tid == 0) {
-    miss_cnt[b] = (int32_t)m;
-    if (miss_count_out) miss_count_out[b] = (int32_t)m;
-    if (host_miss) host_miss[b] = (int32_t)m;       // pinned host memory: the host's view for the overlap switch
-    if (b == 0 && count_step) atomicAdd(&stats[0], 1ull);
-    atomicAdd(&stats[1], (unsigned long long)nvalid);
-    atomicAdd(&stats[2], (unsigned long long)m);
-    atomicAdd(&stats[3], (unsigned long long)m * (unsigned long long)row_stride);
-    // the same per sequence (this workgroup is the only writer of its sequence's four counters)
-    seq_stats[4 * b + 0] += 1ull;
-    seq_stats[4 * b + 1] += (unsigned long long)nvalid;
-    seq_stats[4 * b + 2] += (unsigned long long)m;
-    seq_stats[4 * b + 3] += (unsigned long long)m * (unsigned long long)row_stride;
-  }
   __syncthreads();                               // table updates visible to the whole workgroup
 
   // ---- per (b,t): slot of every selected entry, and the compacted hit / fetched lists
   if (slot_idx_out == nullptr && hit_list == nullptr) continue;
+  if (keep) {
+    // Entry u * BT + tid of the sequence was looked up by this thread in round u: a hit keeps the slot it had, a miss got
+    // its slot in the pairing above (all reads of a thread in flight together).  A query token's list is whole rounds,
+    // so one exchange of the waves' counts serves all of them.
+    const int rounds = nsel / BT, per_t = kk / BT;
+    uint32_t* const lists_tot = s_hist;            // [4][waves]: the victims' list is done with
+    uint32_t ex[4];
+    int sl[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) sl[u] = (u < rounds && sv[u] >= 0) ? (slv[u] < 0 ? so[sv[u]] : slv[u]) : -1;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      if (u >= rounds) break;
+      const size_t at = (size_t)b * nsel + u * BT + tid;
+      const bool fresh = sv[u] >= 0 && slv[u] < 0;
+      if (slot_idx_out) slot_idx_out[at] = sl[u];
+      if (fresh_idx) fresh_idx[at] = fresh ? sl[u] | ESS_FRESH_BIT : sl[u];
+      const uint32_t one = sl[u] < 0 ? 0u : (fresh ? 1u << 16 : 1u);
+      const uint32_t inc = wave_incl_scan(one, lane);
+      ex[u] = inc - one;
+      if (lane == 63) lists_tot[u * (BT / 64) + (tid >> 6)] = inc;
+    }
+    __syncthreads();
+    if (!hit_list) continue;
+    uint32_t run = 0;                              // hits | misses << 16 of the query token's rounds so far
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      if (u >= rounds) break;
+      const int t = u / per_t;
+      if (u % per_t == 0) run = 0;
+      uint32_t off = run, tot = 0;
+#pragma unroll
+      for (int x = 0; x < BT / 64; ++x) {
+        const uint32_t n = lists_tot[u * (BT / 64) + x];
+        if (x < (tid >> 6)) off += n;
+        tot += n;
+      }
+      off += ex[u];
+      const size_t rowoff = ((size_t)b * T + t) * kk;
+      if (sl[u] >= 0) {
+        if (slv[u] < 0) miss_list[rowoff + (off >> 16)] = sl[u];
+        else hit_list[rowoff + (off & 0xffffu)] = sl[u];
+      }
+      run += tot;
+      if (u % per_t == per_t - 1 && tid == 0) {
+        n_hit[b * T + t] = (int32_t)(run & 0xffffu);
+        n_miss[b * T + t] = (int32_t)(run >> 16);
+      }
+    }
+    if constexpr (DYN) __syncthreads();            // lists_tot is free for the next sequence
+    continue;
+  }
   for (int t = 0; t < T; ++t) {
     const size_t rowoff = ((size_t)b * T + t) * kk;
     uint32_t base_hit = 0, base_miss = 0;
@@ -380,19 +434,7 @@ __global__ __launch_bounds__(BT) void k_bookkeeping(
       const int j = j0 + tid;
       int slot = -1;
       bool fresh = false;
-      if (keep) {
-        // entry t * kk + j0 + tid was looked up by this thread in round u: a hit keeps the slot it had, a miss
-        // got its slot in the pairing above
-        const int u = (t * kk + j0) / BT;
-        const int s = u == 0 ? sv[0] : (u == 1 ? sv[1] : (u == 2 ? sv[2] : sv[3]));
-        const int s0 = u == 0 ? slv[0] : (u == 1 ? slv[1] : (u == 2 ? slv[2] : slv[3]));
-        if (s >= 0) {
-          fresh = s0 < 0;
-          slot = fresh ? so[s] : s0;
-        }
-        if (slot_idx_out) slot_idx_out[rowoff + j] = slot;
-        if (fresh_idx) fresh_idx[rowoff + j] = fresh ? slot | ESS_FRESH_BIT : slot;
-      } else if (j < kk) {
+      if (j < kk) {
         const int s = idx[rowoff + j];
         if (s >= 0 && s < Lmax) {
           slot = so[s];
