@@ -770,8 +770,17 @@ __global__ __launch_bounds__(256) void k_attn_merge(const _Float16* __restrict__
   if (rowi >= total_rows) return;                                          // (whole workgroups with WPR 4: their grid is exact)
   const int bt = rowi / H, h = rowi % H;
   const size_t base = ((size_t)bt * nsplit) * H + h;
-  // the split weights first: one load per lane
+  constexpr int U = 16 / (WPR == 1 ? 2 : 1);        // splits of a wave requested at a time
+  // one load per lane for the split weights ...
   const float2 lu = lane < nsplit ? *reinterpret_cast<const float2*>(lse_part + 2 * (base + (size_t)lane * H)) : make_float2(-__builtin_inff(), 1.f);
+  // ... and, with four waves per row (at most 16 splits each), all partial results beside it: waiting for the weights
+  // first would be most of such a kernel.  What the place of an empty split holds is not used.
+  halfx8 xy[U];
+  if constexpr (WPR > 1) {
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      xy[u] = *reinterpret_cast<const halfx8*>(o_part + (base + (size_t)min(sub + u * WPR, nsplit - 1) * H) * ESS_LATENT_DIM + lane * 8);
+  }
   float mx = lu.x;
 #pragma unroll
   for (int d = 1; d < 64; d <<= 1) mx = fmaxf(mx, __shfl_xor(mx, d, 64));
@@ -784,15 +793,15 @@ __global__ __launch_bounds__(256) void k_attn_merge(const _Float16* __restrict__
   // (every split that is not empty: a weight that underflows to 0 still meets the split's values)
   const unsigned long long full = any ? __ballot(lu.x != -__builtin_inff()) : 0ull;
   float a[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  constexpr int U = 8;
   for (int s0 = sub; s0 < nsplit; s0 += U * WPR) {
-    halfx8 xy[U];
+    if constexpr (WPR == 1) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int s = s0 + u * WPR;
-      xy[u] = halfx8{0, 0, 0, 0, 0, 0, 0, 0};
-      if (s < nsplit && ((full >> s) & 1ull))       // the same for the whole wave
-        xy[u] = *reinterpret_cast<const halfx8*>(o_part + (base + (size_t)s * H) * ESS_LATENT_DIM + lane * 8);
+      for (int u = 0; u < U; ++u) {
+        const int s = s0 + u;
+        xy[u] = halfx8{0, 0, 0, 0, 0, 0, 0, 0};
+        if (s < nsplit && ((full >> s) & 1ull))       // the same for the whole wave
+          xy[u] = *reinterpret_cast<const halfx8*>(o_part + (base + (size_t)s * H) * ESS_LATENT_DIM + lane * 8);
+      }
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
