@@ -609,6 +609,15 @@ __global__ __launch_bounds__(APPEND_NT) void k_append(
     const float* __restrict__ new_scale, const int32_t* __restrict__ block_table, int n_pages) {
   __shared__ unsigned long long red[APPEND_NT / 64];
   const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+  uint32_t* stp = stamp + (size_t)b * S;
+  // the stamps of a thread's slots (tid, tid + 1024, ..), asked for before anything that waits; held for all T tokens
+  constexpr int AS = 16;
+  const bool held = host_pool && S <= APPEND_NT * AS;
+  uint32_t sr[AS];
+  if (held) {
+#pragma unroll
+    for (int j = 0; j < AS; ++j) sr[j] = tid + j * APPEND_NT < S ? stp[tid + j * APPEND_NT] : 0xffffffffu;
+  }
   const int L0 = max(0, min(ctx_len[b], Lmax));
   int n = min(T, Lmax - L0);
   // paged Indexer-Cache: a token needs a mapped page; the first one without stops the append
@@ -621,7 +630,6 @@ __global__ __launch_bounds__(APPEND_NT) void k_append(
   const int kchunks = Di >> 4, rchunks = row_stride >> 4;
   int32_t* so = slot_of + (size_t)b * Lmax;
   int32_t* to = token_of + (size_t)b * S;
-  uint32_t* stp = stamp + (size_t)b * S;
   for (int t = 0; t < T; ++t) {
     if (t >= n) {                                  // no room left in the buffers: dropped
       if (tid == 0 && placed) placed[(size_t)b * T + t] = -1;
@@ -643,11 +651,19 @@ __global__ __launch_bounds__(APPEND_NT) void k_append(
     int v = p;
     if (host_pool) {
       unsigned long long best = ~0ull;
-      for (int s = tid; s < S; s += APPEND_NT) {
-        const uint32_t x = stp[s];
-        if (x < step) {
-          const unsigned long long cand = ((unsigned long long)x << 32) | (uint32_t)s;
-          best = cand < best ? cand : best;
+      if (held) {
+#pragma unroll
+        for (int j = 0; j < AS; ++j) {             // (a slot past the pool holds the largest stamp: never below step)
+          const unsigned long long cand = ((unsigned long long)sr[j] << 32) | (uint32_t)(tid + j * APPEND_NT);
+          if (sr[j] < step && tid + j * APPEND_NT < S) best = cand < best ? cand : best;
+        }
+      } else {
+        for (int s = tid; s < S; s += APPEND_NT) {
+          const uint32_t x = stp[s];
+          if (x < step) {
+            const unsigned long long cand = ((unsigned long long)x << 32) | (uint32_t)s;
+            best = cand < best ? cand : best;
+          }
         }
       }
 #pragma unroll
@@ -661,6 +677,10 @@ __global__ __launch_bounds__(APPEND_NT) void k_append(
 #pragma unroll
       for (int i = 1; i < APPEND_NT / 64; ++i) best = red[i] < best ? red[i] : best;
       v = best == ~0ull ? -1 : (int)(uint32_t)best;
+      if (held && v >= 0 && v % APPEND_NT == tid) {
+#pragma unroll
+        for (int j = 0; j < AS; ++j) sr[j] = v / APPEND_NT == j ? step : sr[j];
+      }
     }
     if (v >= 0) {
       if (tid >= 256 && tid - 256 < rchunks)
