@@ -11,10 +11,13 @@
 // One workgroup per sequence does the whole update without any serial list:
 //   - the selection is turned into a bitmap in LDS (dedups the T query
 //     tokens and yields misses in ascending position by a prefix sum);
-//   - victims come from a 4-pass radix select on the 32-bit stamps
-//     (conflict-free histogram: 32 interleaved copies, copy = lane & 31),
-//     ties on the threshold stamp broken by slot order with one block scan,
-//     then a bitonic sort of the (stamp, slot) pairs in LDS;
+//   - the threshold stamp of the victims comes from one histogram pass over
+//     the stamps' ages (conflict-free: 32 interleaved copies, copy =
+//     lane & 31); only where it is older than 254 steps does a radix select
+//     on the 32-bit stamps follow.  Ties on the threshold stamp are broken by
+//     slot order with one block scan.  Up to 1024 victims are ordered by a
+//     stable counting sort over their ages (by comparing all pairs where
+//     some are older than that), more by a bitonic sort in LDS;
 //   - the i-th miss is paired with the i-th victim and a fetch list is
 //     written for the fill kernel;
 //   - per (b,t), slots of hits and of fetched entries are compacted into two
@@ -35,7 +38,7 @@ struct BookShared {
 };
 // The large arrays of the bookkeeping kernel live in dynamic LDS, sized by the configuration:
 //   bm [W]  bitmap of the missed positions (W = max_ctx / 32 words, rounded up to an even number)
-//   un      histogram of the radix passes (256 x 32 counters, 32 KiB), later the victims' (stamp, slot) keys
+//   un      histogram of the stamps (256 x 32 counters, 32 KiB), later the victims' (stamp, slot) keys
 //           (vict_cap = sel_cap rounded up to a power of two, 8 bytes each)
 //   mt [sel_cap]  missed positions in ascending order (sel_cap = max_q_tokens * topk)
 constexpr int BOOK_HIST_BYTES = 256 * 32 * 4;
@@ -234,6 +237,9 @@ __global__ __launch_bounds__(BT) void k_bookkeeping(
     }
     find_digit(s_below);
     const bool by_age = sm.sel_digit > 0 || base == 0;
+    // whether a digit is one stamp for every victim: not if some are older than the digits tell apart (read here, as
+    // a long list of victims takes this place)
+    const bool one_stamp = base == 0 || s_below[1] == 0;
     if (by_age) {
       prefix = base + sm.sel_digit;
       __syncthreads();
@@ -295,8 +301,8 @@ __global__ __launch_bounds__(BT) void k_bookkeeping(
     }
     // ---- order the victims by (stamp, slot)
     const bool by_rank = m <= (uint32_t)BT;
-    if (by_rank && by_age) {
-      // The list is in slot order, so a stable counting sort by age is the order: a victim's place is the number of
+    if (by_rank && by_age && one_stamp) {
+      // A digit is one stamp here.  The list is in slot order, so a stable counting sort by age is the order: a victim's place is the number of
       // slots of smaller digits (all of them victims) plus the number of victims with its digit in front of it -- inside its
       // wave by matching the eight digit bits, and the counts of the waves before.  (Was: every key compared with
       // every other, 4.5 us for 280 victims; this takes 1.5.)

@@ -142,9 +142,6 @@ int pick_splits(const ess_ctx* ctx, int B, int T, int cap) {
     const double us = rounds * ((tiles + ns - 1) / ns + 5.5) * 2.1 + (double)B * T * ns * c.attn_heads * 2048.0 / 4.5e6 + 0.12 * ns;
     if (us < best_us) { best_us = us; best = ns; }
   }
-#ifdef ESS_FORCE_NS
-  best = ESS_FORCE_NS;
-#endif
   return best;
 }
 

@@ -142,3 +142,43 @@ def test_short_fetch_in_line_gives_the_bits_of_the_overlapped_schedule(ess_lib, 
     for a, b in zip(results[bnd.ESS_FLAG_AUTO], results[0]):
         for x, y in zip(a, b):
             assert torch.equal(x, y)
+
+
+# Steps with gaps between them, few and many entries in turn: victims of one stamp or of many, some or all of them older
+# than the 254 steps that the one-pass threshold search tells apart; more victims than a workgroup has threads; lists of
+# whole rounds of the workgroup and others; a pool too large for the registers
+@pytest.mark.parametrize("T,k,S,L", [(1, 100, 257, 1500), (1, 1024, 1500, 6000), (2, 1024, 4096, 9000), (2, 1000, 2500, 9000),
+                                     (1, 1500, 17000, 30000)])
+def test_bookkeeping_of_old_stamps(ess_lib, T, k, S, L):
+    from paper_2512_10576_amd import binding as bnd
+    print("old stamps", T, k, S, L, flush=True)
+    B = 2
+    host = torch.empty((B, L, 1152), dtype=torch.uint8, pin_memory=True)
+    host.zero_()
+    ctx = _ctx(ess_lib, max_batch=B, max_q_tokens=T, max_ctx=L, idx_heads=4, idx_dim=32, topk=k, attn_heads=8, slots_per_seq=S)
+    cache = bnd.Cache.allocate(ctx.cfg, B, host_pool=host)
+    ctx.cache_reset(cache, B)
+    oc = O.SlotCache(B, L, S)
+    rng = np.random.default_rng(S)
+    lens = torch.full((B,), L, dtype=torch.int32, device="cuda")
+    slot = torch.empty((B, T, k), dtype=torch.int32, device="cuda")
+    rows = torch.empty((B, T, k, 1152), dtype=torch.uint8, device="cuda")
+    steps = [1, 2, 3, 5, 90, 250, 254, 255, 256, 257, 258, 300, 301, 302, 303, 304, 560, 561, 562, 65530, 65535, 65536, 65537,
+             65700, 65701, 65950, (1 << 24) + 3, (1 << 24) + 4]
+    for i, step in enumerate(steps):
+        n = k if i % 3 == 2 else max(1, k // 5)
+        idx = np.full((B, T, k), -1, np.int32)
+        for b in range(B):
+            held = np.nonzero(oc.slot_of[b] >= 0)[0]
+            for t in range(T):
+                old = rng.choice(held, min(n // 3, held.size), replace=False) if held.size else held
+                rest = rng.choice(np.setdiff1d(np.arange(L), old), n - old.size, replace=False)
+                idx[b, t, :n] = rng.permutation(np.concatenate([old, rest]))
+        r = oc.step(idx, step)
+        ctx.gather_latent(cache, torch.from_numpy(idx).cuda(), lens, step, slot, rows)
+        torch.cuda.synchronize()
+        assert np.array_equal(slot.cpu().numpy(), r["slot_idx"]), step
+        assert np.array_equal(cache.slot_of.cpu().numpy(), oc.slot_of), step
+        assert np.array_equal(cache.token_of.cpu().numpy(), oc.token_of), step
+        assert np.array_equal(cache.stamp.cpu().numpy().view(np.uint32), oc.stamp), step
+    ctx.close()
