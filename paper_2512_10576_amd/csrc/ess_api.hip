@@ -14,9 +14,8 @@
 // Workgroups that Attn0 of the whole batch aims at when entries are offloaded: half a workgroup per CU.  Attn0 runs
 // beside a fetch and has time to spare, while every split adds a partial result (128 KiB per row) that the merge,
 // which runs after the last fetch, has to read: 128 against 256 took 15 % off Attn0 itself and 0.3-0.7 % off the step.
-#ifndef ESS_ATTN0_WGS
+// (Beside a short fetch it is raised to fill the chip: see ns0 in ess_decode_step.)
 #define ESS_ATTN0_WGS 128
-#endif
 
 namespace {
 
@@ -451,7 +450,7 @@ int ess_gather_latent(ess_ctx* ctx, const ess_cache* cache, const int32_t* idx, 
     return ess_launch_gather_rows(ctx->cfg, cache->slot_pool, slot_idx, B, T, rows_out, st);
   }
   // The rows that were resident are gathered on the side stream while the fetch runs; behind it only the fetched ones are
-  // left (batch 32 x 64K, 340 misses of 2048 per sequence: 5 us instead of 30).
+  // left (batch 32 x 64K, 340 misses of 2048 per sequence: 10 us instead of 30).
   rc = ess_launch_bookkeeping(ctx, *cache, idx, B, T, ctx->cfg.topk, step, slot_idx, miss_count, st, 0, true,
                               ess_xcd{nullptr, 0, nullptr, 0}, nullptr, 0, ctx->ev_book[0], ctx->slot_idx_ws);
   if (rc != ESS_OK) return rc;
@@ -576,7 +575,9 @@ int ess_decode_step(ess_ctx* ctx, const ess_cache* cache, const ess_step_args* a
     const double hits = c.topk - (mean_miss / T < c.topk ? mean_miss / T : c.topk);
     const double tiles_item = (hits / ESS_ATTN_TILE) / ns0e + 1.0;
     const double rounds = (double)((long)B * T * hg * ns0e + work_cus - 1) / work_cus;
-    // (a tile of 32 entries x 128 heads: 2.6 us, 4.2 us when the entries are dequantised on the way; 16 us of start and end)
+    // (the constants are those the rule's boundaries were measured with: 2.6 us for a tile of 32 entries x 128 heads, 4.2 when
+    // the entries are dequantised on the way, 16 of start and end.  The kernel is faster now, 2.1 and 12, but the boundaries
+    // are sides measured with these, not predictions: smaller constants would confine at fewer misses)
     const double attn5 = (double)(long)rounds * (tiles_item * (c.latent_fmt == ESS_FMT_BF16 ? 2.6 : 4.2) + 16.0);
     // (one work counter serves one index-score launch: two query tokens at most)
     confine = dba && T <= 2 && fetch_half >= 1.5 * idx_half;

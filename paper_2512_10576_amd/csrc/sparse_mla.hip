@@ -15,7 +15,6 @@
 // re-laid out between them; see the comment at the kernel.
 #include "ess_internal.h"
 #include <utility>
-#include <hip/hip_bf16.h>
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -30,8 +29,6 @@ namespace {
 
 constexpr int TILE = ESS_ATTN_TILE;            // 32 entries
 constexpr int NTH = 256;                       // four waves
-constexpr int KSTEPS = ESS_ROW_DIM / 32;       // 18
-constexpr int VBLOCKS = ESS_LATENT_DIM / 16;   // 32
 constexpr int MAX_TPS = 64;                    // tiles per split (the launcher picks nsplit accordingly): a list of 2048 entries fits one split
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
@@ -643,7 +640,7 @@ __global__ __launch_bounds__(NTH, 1) void k_attn_partial_tr(
     // lane constants afresh (see above): nothing of the epilogue is carried through the tile loop
     int tid2 = threadIdx.x;
     asm volatile("" : "+v"(tid2));
-    const int lane2 = tid2 & 63, hh2 = (tid2 >> 5) & 1, h2 = tid2 & 31, head = head0 + h2;
+    const int hh2 = (tid2 >> 5) & 1, h2 = tid2 & 31, head = head0 + h2;
     const float l_tot = pair_sum(l_run);
     float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
     const size_t prow = ((size_t)bt * pitch + split0 + split) * H + min(head, H - 1);

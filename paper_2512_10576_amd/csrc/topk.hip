@@ -348,7 +348,7 @@ __device__ __forceinline__ void topk_item(TopkShared& sm, int item, int parts, f
   // ---- S: rows that fit the candidate list whole need no sample and no list: eight keys per thread in registers, a
   // histogram of their top 14 bits tells exactly in which bin the k-th largest lies, and that bin's range is resolved
   // like the range between two sampled bounds.  (They went through path B and a radix select of five 11-bit passes
-  // over 64-bit keys in LDS: 15 us for a row of 8192, now 8.5.)
+  // over 64-bit keys in LDS: one row of 8192 15.2 us by kernel trace, now 14.0; the step of one sequence 42.9 us, now 40.6.)
   if ((MODE == 0 || MODE == 2) && vis <= CAND_CAP) {
     float sv[PER];
 #pragma unroll
