@@ -13,6 +13,8 @@
 //      thousand positions at or above it; one pass over the row collects those
 //      candidates (their composite keys) in LDS.  If their number is not in
 //      [k, buffer size] (an unlucky sample, massive ties) path B runs instead.
+//   S. rows that fit the candidate buffer whole, in a kernel form of its own for contexts that allow no longer ones
+//      (MODE 4): all keys in registers, no list.
 //   B. general: MSD radix narrowing on the composite key straight from memory,
 //      11 bits a pass (histogram in 8 interleaved copies, copy = lane & 7, so
 //      that lanes hitting one hot bin do not serialise), until the positions
@@ -39,6 +41,7 @@ using ess_sel::SBINS;
 constexpr int SAMPLE_TARGET = 4096;         // at most this many samples per row (four per thread), about every 16th score or fewer
 static_assert(SAMPLE_TARGET <= 4 * NT, "the sample is loaded in one round of four per thread");
 constexpr int FAST_MIN_VIS = CAND_CAP + 1;   // rows above the candidate list's size are sampled (path A)
+constexpr int WHOLE_MIN_VIS = 4097;          // rows from here on, where all fit that list, are done whole (path S)
 
 struct __align__(16) TopkShared {
   union {
@@ -80,9 +83,8 @@ __device__ __forceinline__ void wave_append(bool pred, V val, V* list, uint32_t*
 // times (f may hold wave-wide operations).  Each thread has four 16-byte loads in flight per round,
 // which is what makes one workgroup able to pull a 512 KiB row at cache bandwidth, not at latency.
 template <typename F>
-__device__ __forceinline__ void scan_row(const float* __restrict__ srow, int vis, bool vec_ok, F&& f) {
+__device__ __forceinline__ void scan_row(int tid, const float* __restrict__ srow, int vis, bool vec_ok, F&& f) {
   constexpr int U = 4;
-  const int tid = threadIdx.x;
   int done = 0;
   if (vec_ok) {
     const int nvec = vis >> 2;
@@ -117,9 +119,8 @@ __device__ __forceinline__ void scan_row(const float* __restrict__ srow, int vis
 // round are issued before the current round is processed (two register sets); indices past the end
 // are clamped, not predicated, so that every load is unconditional.
 template <typename F>
-__device__ __forceinline__ void scan_row_rounds(const float* __restrict__ srow, int vis, bool vec_ok, F&& f) {
+__device__ __forceinline__ void scan_row_rounds(int tid, const float* __restrict__ srow, int vis, bool vec_ok, F&& f) {
   constexpr int U = 4;
-  const int tid = threadIdx.x;
   int done = 0;
   int pos[16];
   float val[16];
@@ -166,8 +167,7 @@ __device__ __forceinline__ void scan_row_rounds(const float* __restrict__ srow, 
 }
 
 // D, second half: the positions marked in the bitmap bmp[0..W), in ascending order, to orow[0..k)
-__device__ __forceinline__ void emit_bitmap(TopkShared& sm, const uint32_t* bmp, int W, int k, int32_t* __restrict__ orow) {
-  const int tid = threadIdx.x;
+__device__ __forceinline__ void emit_bitmap(TopkShared& sm, int tid, const uint32_t* bmp, int W, int k, int32_t* __restrict__ orow) {
   const int wpt = (W + NT - 1) / NT;
   const int w0 = min(tid * wpt, W), w1 = min(w0 + wpt, W);
   uint32_t mine = 0;
@@ -187,8 +187,7 @@ __device__ __forceinline__ void emit_bitmap(TopkShared& sm, const uint32_t* bmp,
 
 // Which of the 2048 digits the radix select's histogram sm.lhist holds contains the need-th largest key, counted
 // from the top: sm.sel_digit, with sm.sel_above keys above it and sm.sel_count in it.  Ends with a barrier.
-__device__ __forceinline__ void crossing_digit(TopkShared& sm, uint32_t need) {
-  const int tid = threadIdx.x;
+__device__ __forceinline__ void crossing_digit(TopkShared& sm, int tid, uint32_t need) {
   const int d_hi = NBINS - 1 - 2 * tid, d_lo = d_hi - 1;      // thread tid owns two digits, descending
   const uint32_t c_hi = sm.lhist[d_hi], c_lo = sm.lhist[d_lo];
   uint32_t total;
@@ -213,10 +212,9 @@ __device__ __forceinline__ void crossing_digit(TopkShared& sm, uint32_t need) {
 constexpr int PER = CAND_CAP / NT;           // keys per thread
 // WHOLE: the keys are a whole row, not a list of candidates.
 template <bool WHOLE>
-__device__ __forceinline__ bool finish_keys(TopkShared& sm, const unsigned long long (&c)[PER], uint32_t listed,
+__device__ __forceinline__ bool finish_keys(TopkShared& sm, int tid, const unsigned long long (&c)[PER], uint32_t listed,
                                             uint32_t lo, uint32_t hi, int vis, int k, int IB, int32_t* __restrict__ orow) {
   constexpr uint32_t SMALL = 1024;           // keys the counting step takes: one per thread
-  const int tid = threadIdx.x;
   const unsigned long long imask = (1ull << IB) - 1ull;
   // (keys of a list may still be on their way:) clear the histogram and the row's bitmap
   uint32_t* bmp = sm.hist;
@@ -254,7 +252,7 @@ __device__ __forceinline__ bool finish_keys(TopkShared& sm, const unsigned long 
       if ((uint32_t)(u * NT + tid) < listed) atomicAdd(&sm.lhist[digit(c[u])], 1u);
   }
   __syncthreads();
-  crossing_digit(sm, (uint32_t)k);
+  crossing_digit(sm, tid, (uint32_t)k);
   const uint32_t dsel = sm.sel_digit, take = (uint32_t)k - sm.sel_above, cnt = sm.sel_count;
   unsigned long long t_in = 0ull;            // inside the digit, keys at or above this one are taken
   if (cnt != take) {
@@ -291,20 +289,19 @@ __device__ __forceinline__ bool finish_keys(TopkShared& sm, const unsigned long 
     }
   }
   __syncthreads();
-  emit_bitmap(sm, bmp, W, k, orow);
+  emit_bitmap(sm, tid, bmp, W, k, orow);
   return true;
 }
 
 template <bool SRC_LDS>
-__device__ __forceinline__ bool finish_fast(TopkShared& sm, const unsigned long long* grow, uint32_t listed,
+__device__ __forceinline__ bool finish_fast(TopkShared& sm, int tid, const unsigned long long* grow, uint32_t listed,
                                             uint32_t lo, uint32_t hi, int vis, int k, int IB, int32_t* __restrict__ orow) {
-  const int tid = threadIdx.x;
   unsigned long long c[PER];
 #pragma unroll
   for (int u = 0; u < PER; ++u)
     c[u] = (uint32_t)(u * NT + tid) < listed ? (SRC_LDS ? sm.cand[u * NT + tid] : grow[u * NT + tid]) : 0ull;
   if (SRC_LDS) __syncthreads();              // the bitmap shares its memory with the list: every thread holds its keys first
-  return finish_keys<false>(sm, c, listed, lo, hi, vis, k, IB, orow);
+  return finish_keys<false>(sm, tid, c, listed, lo, hi, vis, k, IB, orow);
 }
 
 // MODE 0: one workgroup does the whole row (grid: rows).
@@ -316,6 +313,7 @@ __device__ __forceinline__ bool finish_fast(TopkShared& sm, const unsigned long 
 // the row by itself like MODE 0.  The hand-over is the kernel boundary: workgroups of one kernel
 // never exchange data (an agent-scope fence inside a kernel costs tens of microseconds on this
 // multi-die part, where it writes the L2 back).  g_cnt is zero between steps: MODE 2 clears it.
+// MODE 4: as MODE 0 where max_ctx allows only rows that fit the candidate list (path S, and B for the shortest).
 // MODE 3: the finishing kernel of the fused selection (grid rows).  The row's list was written by the emitting
 // index-score pass (index_kernel.h), for rows of any length; `score` is scratch memory, not scores: a row whose list
 // cannot be used (fewer than k or more than the buffer holds: a misleading sample, massive ties) has its scores
@@ -325,7 +323,7 @@ struct TopkRecompute {                     // MODE 3: what it takes to compute a
   const uint8_t* q; const float* w; const uint8_t* key; const int32_t* block_table;
   int n_pages, Hi, Di;
 };
-template <int MODE>
+template <int MODE, bool DYN>
 __device__ __forceinline__ void topk_item(TopkShared& sm, int item, int parts, float* __restrict__ score,
                                           const int32_t* __restrict__ ctx_len, int T, int Lmax, int k, int IB,
                                           int32_t* __restrict__ idx_out, unsigned long long* __restrict__ g_cand,
@@ -333,7 +331,11 @@ __device__ __forceinline__ void topk_item(TopkShared& sm, int item, int parts, f
   const int row = item / parts;
   const int part = item % parts;
   const int b = row / T, t = row % T;
-  const int tid = threadIdx.x, lane = tid & 63;
+  // (looping form: the thread index passes through an empty asm statement, so that what is derived from it is computed
+  // per work item instead of being carried in registers across the loop, where it led to spills)
+  int tid_ = threadIdx.x;
+  if constexpr (DYN) asm volatile("" : "+v"(tid_));
+  const int tid = tid_, lane = tid & 63;
   int vis = ctx_len[b] - (T - 1 - t);
   vis = max(0, min(vis, Lmax));
   float* srow = score + (size_t)row * Lmax;
@@ -341,7 +343,7 @@ __device__ __forceinline__ void topk_item(TopkShared& sm, int item, int parts, f
 
   if (MODE == 1 && (vis <= k || vis < FAST_MIN_VIS)) return;      // nothing to prepare
   uint32_t listed = 0;
-  if (MODE >= 2) {                         // candidates prepared by the kernel in front (0 if none)
+  if (MODE == 2 || MODE == 3) {            // candidates prepared by the kernel in front (0 if none)
     listed = g_cnt[row];
     __syncthreads();
     if (tid == 0) g_cnt[row] = 0;
@@ -368,10 +370,12 @@ __device__ __forceinline__ void topk_item(TopkShared& sm, int item, int parts, f
 
   // ---- S: rows that fit the candidate list whole need no sample and no list: eight keys per thread in registers, a
   // histogram of their top 14 bits tells exactly in which bin the k-th largest lies, and that bin's range is resolved
-  // like the range between two sampled bounds.  (They went through path B and a radix select of five 11-bit passes
-  // over 64-bit keys in LDS: one row of 8192 the step of one sequence
-  // 42.9 us, now 40.6, and 36.4 with the counting by ballot in finish_keys.)
-  if ((MODE == 0 || MODE == 2) && vis <= CAND_CAP) {
+  // like the range between two sampled bounds.  Against path B (one 11-bit pass collects the row, up to five more follow
+  // in LDS), one row / 32 rows, us: 8192 scores 10.8 / 10.9 against 13.1 / 13.5, 5000 10.0 / 10.5 against 10.5 / 12.0, but
+  // 4096 10.0 / 10.7 against 8.8 / 10.6 and 2500 10.6 / 10.9 against 9.9 / 10.8: from 4097 on.
+  // It has a form of its own because it does not pay for itself beside the other paths: inlined into MODE 0 and 2 it
+  // took the looping forms from 12 and 20 to 172 and 256 bytes of scratch a lane and cost every longer row 0.2 to 0.6 us.
+  if (MODE == 4 && vis >= WHOLE_MIN_VIS) {
     float sv[PER];
 #pragma unroll
     for (int u = 0; u < PER; ++u) sv[u] = u * NT + tid < vis ? srow[u * NT + tid] : 0.f;
@@ -390,7 +394,7 @@ __device__ __forceinline__ void topk_item(TopkShared& sm, int item, int parts, f
     const uint32_t bin = sm.sbin[0];
     const uint32_t lo = bin << (32 - SBITS), hi = bin == SBINS - 1 ? 0xffffffffu : (bin + 1) << (32 - SBITS);
     __syncthreads();
-    if (finish_keys<true>(sm, c, (uint32_t)vis, lo, hi, vis, k, IB, orow)) return;
+    if (finish_keys<true>(sm, tid, c, (uint32_t)vis, lo, hi, vis, k, IB, orow)) return;
     // (more than 1024 keys share a 2047th of the bin: the keys are in sm.cand now, the general selection takes them)
     nc = vis;
     have_cand = true;
@@ -398,7 +402,7 @@ __device__ __forceinline__ void topk_item(TopkShared& sm, int item, int parts, f
   }
 
   // ---- A: sampled one-pass collection for long rows
-  const bool use_list = MODE >= 2 && listed >= (uint32_t)k && listed <= (uint32_t)CAND_CAP;
+  const bool use_list = (MODE == 2 || MODE == 3) && listed >= (uint32_t)k && listed <= (uint32_t)CAND_CAP;
   if (MODE == 3 && !use_list) {
     const uint8_t* q_row = rc.q + (size_t)row * rc.Hi * rc.Di;
     const float* w_row = rc.w + (size_t)row * rc.Hi;
@@ -415,7 +419,7 @@ __device__ __forceinline__ void topk_item(TopkShared& sm, int item, int parts, f
     {
       const uint32_t lo = g_tau[2 * row], hi = g_tau[2 * row + 1];       // left by the kernel that made the list
       if (lo != 0u && hi > lo) {
-        if (finish_fast<false>(sm, grow, listed, lo, hi, vis, k, IB, orow)) return;
+        if (finish_fast<false>(sm, tid, grow, listed, lo, hi, vis, k, IB, orow)) return;
         copied = true;
       }
     }
@@ -425,7 +429,7 @@ __device__ __forceinline__ void topk_item(TopkShared& sm, int item, int parts, f
       __syncthreads();
     }
   }
-  if ((vis >= FAST_MIN_VIS || use_list) && !have_cand) {
+  if (MODE != 4 && (vis >= FAST_MIN_VIS || use_list)) {
    uint32_t lo_bin = 0, hi_bin = 0xffffffffu;
    if (!use_list) {
     // samples: blocks of 16 consecutive scores (one 64-byte piece of a cache line), every bstride-th block,
@@ -465,7 +469,7 @@ __device__ __forceinline__ void topk_item(TopkShared& sm, int item, int parts, f
       // this workgroup's slice of the row (boundaries on 16-byte pieces)
       const int s_lo = parts > 1 ? (int)(((long)vis * part / parts) & ~3L) : 0;
       const int s_hi = (parts > 1 && part + 1 < parts) ? (int)(((long)vis * (part + 1) / parts) & ~3L) : vis;
-      scan_row_rounds(srow + s_lo, s_hi - s_lo, vec_ok, [&](const int (&pos)[16], const float (&val)[16], const bool (&ok)[16]) {
+      scan_row_rounds(tid, srow + s_lo, s_hi - s_lo, vec_ok, [&](const int (&pos)[16], const float (&val)[16], const bool (&ok)[16]) {
         uint32_t cnt = 0, flags = 0;
 #pragma unroll
         for (int e = 0; e < 16; ++e)
@@ -507,7 +511,7 @@ __device__ __forceinline__ void topk_item(TopkShared& sm, int item, int parts, f
         return;
       }
       if (!use_list && nc >= k && nc <= CAND_CAP && tau != 0u && tau_hi > tau &&
-          finish_fast<true>(sm, sm.cand, (uint32_t)nc, tau, tau_hi, vis, k, IB, orow))
+          finish_fast<true>(sm, tid, sm.cand, (uint32_t)nc, tau, tau_hi, vis, k, IB, orow))
         return;
       if (nc >= k && nc <= CAND_CAP) {
         // bits on which the candidates differ: everything above is common and decided
@@ -539,7 +543,7 @@ __device__ __forceinline__ void topk_item(TopkShared& sm, int item, int parts, f
       const uint32_t dmask = (1u << bits) - 1u;
       for (int j = tid; j < NBINS * COPIES; j += NT) sm.hist[j] = 0;
       __syncthreads();
-      scan_row(srow, vis, vec_ok, [&](int i, float v, bool ok) {
+      scan_row(tid, srow, vis, vec_ok, [&](int i, float v, bool ok) {
         const unsigned long long c = comp_of(i, v);
         if (ok && (c >> rem) == prefix)
           atomicAdd(&sm.hist[(((uint32_t)(c >> shift)) & dmask) * COPIES + (lane & 7)], 1u);
@@ -571,7 +575,7 @@ __device__ __forceinline__ void topk_item(TopkShared& sm, int item, int parts, f
     }
     if (tid == 0) sm.cand_n = 0;
     __syncthreads();
-    scan_row(srow, vis, vec_ok, [&](int i, float v, bool ok) {
+    scan_row(tid, srow, vis, vec_ok, [&](int i, float v, bool ok) {
       const unsigned long long c = comp_of(i, v);
       wave_append<unsigned long long>(ok && (c >> rem) == prefix, c, sm.cand, &sm.cand_n, CAND_CAP);
     });
@@ -591,7 +595,7 @@ __device__ __forceinline__ void topk_item(TopkShared& sm, int item, int parts, f
       if ((c >> rem) == prefix) atomicAdd(&sm.lhist[((uint32_t)(c >> shift)) & dmask], 1u);
     }
     __syncthreads();
-    crossing_digit(sm, need);
+    crossing_digit(sm, tid, need);
     need -= sm.sel_above;
     prefix = (prefix << bits) | sm.sel_digit;
     const uint32_t cnt = sm.sel_count;
@@ -623,12 +627,12 @@ __device__ __forceinline__ void topk_item(TopkShared& sm, int item, int parts, f
     __syncthreads();
     for (int j = tid; j < W; j += NT) bmp[j] = 0;
     __syncthreads();
-    scan_row(srow, vis, vec_ok, [&](int i, float v, bool ok) {
+    scan_row(tid, srow, vis, vec_ok, [&](int i, float v, bool ok) {
       if (ok && comp_of(i, v) >= t_star) atomicOr(&bmp[i >> 5], 1u << (i & 31));
     });
   }
   __syncthreads();
-  emit_bitmap(sm, bmp, W, k, orow);
+  emit_bitmap(sm, tid, bmp, W, k, orow);
 }
 
 template <int MODE, bool DYN>
@@ -642,7 +646,7 @@ __global__ __launch_bounds__(NT) void k_topk(float* __restrict__ score, const in
   const int parts = MODE == 1 ? parts_arg : 1;
   // work item = (part, row): by workgroup index, or drawn from the launch's counter off the XCDs to be avoided
   ESS_WORK_LOOP(DYN, xcd, MODE == 1 ? blockIdx.y * parts + blockIdx.x : blockIdx.x, rows * parts, &s_item, item) {
-    topk_item<MODE>(sm, item, parts, score, ctx_len, T, Lmax, k, IB, idx_out, g_cand, g_cnt, g_tau, rc);
+    topk_item<MODE, DYN>(sm, item, parts, score, ctx_len, T, Lmax, k, IB, idx_out, g_cand, g_cnt, g_tau, rc);
   }
 }
 
@@ -738,6 +742,8 @@ int launch_topk(int max_ctx, int k, const float* score_in, const int32_t* ctx_le
     const dim3 g1 = dyn ? dim3(ess_xcd_grid(parts * rows, x0)) : dim3(parts, rows);
     ESS_TOPK_LAUNCH(1, g1, x0, parts);
     ESS_TOPK_LAUNCH(2, dim3(ess_xcd_grid(rows, x1)), x1, 1);
+  } else if (max_ctx <= CAND_CAP) {
+    ESS_TOPK_LAUNCH(4, dim3(ess_xcd_grid(rows, x1)), x1, 1);
   } else {
     ESS_TOPK_LAUNCH(0, dim3(ess_xcd_grid(rows, x1)), x1, 1);
   }

@@ -142,3 +142,19 @@ def test_attention_kernel_agprs_are_only_named_by_its_own_asm(tmp_path):
                 if dst:
                     wr = set(range(int(dst[1]), int(dst[2]) + 1)) if dst[1] else {int(dst[3])}
                     assert not (wr & used), (prev, t)
+
+
+def test_topk_kernels_do_not_spill(tmp_path):
+    """No form of the top-k but the one that can recompute scores (MODE 3) spills registers to scratch memory, whether
+    it takes its rows by workgroup index or by ticket; read from the ISA the build flags produce."""
+    import subprocess
+    from paper_2512_10576_amd import build
+    out = tmp_path / "topk.s"
+    subprocess.run([build._hipcc(), *build.compile_flags("topk.hip"), "-S", "--cuda-device-only",
+                    os.path.join(build.CSRC, "topk.hip"), "-o", str(out)],
+                   check=True, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)
+    found = dict(((int(m[1]), m[2] == "1"), int(m[3])) for m in re.finditer(
+        r"^_ZN\S*k_topkILi(\d)ELb([01])E\S*:.*?; ScratchSize: (\d+)", out.read_text(), re.S | re.M))
+    assert {mode for mode, _ in found} >= {0, 1, 2, 3} and len(found) % 2 == 0
+    spills = {form: n for form, n in found.items() if form[0] != 3 and n}
+    assert not spills, spills

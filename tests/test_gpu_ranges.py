@@ -57,7 +57,7 @@ def test_attention_list_lengths_and_heads(ess_lib, fmt, B, T, H, k, lens):
 
 # rows around k, a thread's eight keys, the candidate list (8192) and the sampled path above it
 @pytest.mark.parametrize("kind", ["distinct", "ties", "one value", "low and high"])
-@pytest.mark.parametrize("vis,k", [(9, 8), (1025, 1024), (4097, 2048), (8191, 2048), (8192, 4096), (8193, 2048), (16384, 513)])
+@pytest.mark.parametrize("vis,k", [(9, 8), (1025, 1024), (4097, 2048), (4096, 2048), (8191, 2048), (8192, 4096), (8193, 2048), (16384, 513)])
 def test_topk_short_rows(ess_lib, kind, vis, k):
     print("topk", kind, vis, k, flush=True)
     rng = np.random.default_rng(vis)
