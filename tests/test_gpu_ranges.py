@@ -56,7 +56,7 @@ def test_attention_list_lengths_and_heads(ess_lib, fmt, B, T, H, k, lens):
 
 
 # rows around k, a thread's eight keys, the candidate list (8192) and the sampled path above it
-@pytest.mark.parametrize("kind", ["distinct", "ties", "one value", "low and high"])
+@pytest.mark.parametrize("kind", ["distinct", "ties", "one value", "low and high", "power of two"])
 @pytest.mark.parametrize("vis,k", [(9, 8), (1025, 1024), (4097, 2048), (4096, 2048), (8191, 2048), (8192, 4096), (8193, 2048), (16384, 513)])
 def test_topk_short_rows(ess_lib, kind, vis, k):
     print("topk", kind, vis, k, flush=True)
@@ -71,6 +71,10 @@ def test_topk_short_rows(ess_lib, kind, vis, k):
         sc[0, 0, rng.choice(vis, k - 3, replace=False)] = rng.standard_normal(k - 3).astype(np.float32)
         sc[0, 0, 1] = np.float32(np.inf)
         sc[0, 0, 2] = np.float32(np.nan)
+    elif kind == "power of two":                          # the k-th largest is the lower end of a histogram bin
+        order = np.argsort(-sc[0, 0], kind="stable")
+        sc[0, 0, order] = np.round(np.linspace(512 + k / 8, 512 - (vis - k) / 8, vis)).astype(np.float32)
+        assert np.sort(sc[0, 0])[-k] == 512
     lens = np.array([vis])
     _topk_sets_equal(_run_topk(ess_lib, sc, [vis], k, 1), O.topk(sc, lens, k))
 
