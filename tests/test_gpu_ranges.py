@@ -79,30 +79,50 @@ def test_topk_short_rows(ess_lib, kind, vis, k):
     _topk_sets_equal(_run_topk(ess_lib, sc, [vis], k, 1), O.topk(sc, lens, k))
 
 
-@pytest.mark.parametrize("B,T,L,S,k", [(1, 1, 300, 40, 17), (3, 2, 1000, 257, 100), (2, 4, 3000, 1500, 333)])
-def test_gathered_rows_beside_a_fetch(ess_lib, B, T, L, S, k):
+# (the last two: 32 MiB of rows and more, gathered on two streams beside the fetch; with quantised entries the rows of
+# concurrent kernels share cache lines)
+@pytest.mark.parametrize("fmt,B,T,L,S,k", [
+    (O.FMT_BF16, 1, 1, 300, 40, 17), (O.FMT_BF16, 3, 2, 1000, 257, 100), (O.FMT_BF16, 2, 4, 3000, 1500, 333),
+    (O.FMT_FP8, 1, 1, 300, 40, 17), (O.FMT_FP8, 3, 2, 1000, 257, 100),
+    (O.FMT_BF16, 8, 2, 9000, 5000, 2047), (O.FMT_FP8, 13, 2, 9000, 5000, 2047)])
+def test_gathered_rows_beside_a_fetch(ess_lib, fmt, B, T, L, S, k):
     """the rows of resident and of fetched entries, entry counts that are no multiple of a wave's sixteen"""
     from paper_2512_10576_amd import binding as bnd
-    print("gather ranges", B, T, L, S, k, flush=True)
+    print("gather ranges", fmt, B, T, L, S, k, flush=True)
     rng = np.random.default_rng(L)
-    host = torch.empty((B, L, 1152), dtype=torch.uint8, pin_memory=True)
-    host.copy_(synth.latent_rows_bf16(L, B * L).reshape(B, L, 1152))
-    ctx = _ctx(ess_lib, max_batch=B, max_q_tokens=T, max_ctx=L, idx_heads=4, idx_dim=32, topk=k, attn_heads=8, slots_per_seq=max(S, T * k))
+    src = (synth.latent_rows_bf16 if fmt == O.FMT_BF16 else synth.latent_rows_fp8)(L, B * L)
+    stride = src.shape[-1]
+    host = torch.empty((B, L, stride), dtype=torch.uint8, pin_memory=True)
+    host.copy_(src.reshape(B, L, stride))
+    ctx = _ctx(ess_lib, max_batch=B, max_q_tokens=T, max_ctx=L, idx_heads=4, idx_dim=32, topk=k, attn_heads=8, latent_fmt=fmt,
+               slots_per_seq=max(S, T * k))
     cache = bnd.Cache.allocate(ctx.cfg, B, host_pool=host)
     ctx.cache_reset(cache, B)
     lens = torch.full((B,), L, dtype=torch.int32, device="cuda")
     slot = torch.empty((B, T, k), dtype=torch.int32, device="cuda")
-    rows = torch.empty((B, T, k, 1152), dtype=torch.uint8, device="cuda")
+    rows = torch.empty((B, T, k, stride), dtype=torch.uint8, device="cuda")
+    miss = torch.empty((B,), dtype=torch.int32, device="cuda")
+    idx = None
     for step in range(1, 5):
-        idx = np.stack([np.stack([rng.choice(L, k, replace=False) for _ in range(T)]) for _ in range(B)]).astype(np.int32)
+        # after the first step about half of every list was selected by the step before: both gathers have rows to copy
+        new = np.stack([np.stack([rng.permutation(L)[:k] for _ in range(T)]) for _ in range(B)]).astype(np.int32)
+        if idx is not None:
+            for b in range(B):
+                for t in range(T):
+                    old = idx[b, t][idx[b, t] >= 0][:k // 2]
+                    fresh = new[b, t][~np.isin(new[b, t], old)]
+                    new[b, t] = rng.permutation(np.concatenate([old, fresh])[:k])
+        idx = new
         idx[:, :, step::7] = -1
         rows.fill_(0xEE)
-        ctx.gather_latent(cache, torch.from_numpy(idx).cuda(), lens, step, slot, rows)
+        ctx.gather_latent(cache, torch.from_numpy(idx).cuda(), lens, step, slot, rows, miss)
         torch.cuda.synchronize()
-        want = np.zeros((B, T, k, 1152), np.uint8)
+        want = np.zeros((B, T, k, stride), np.uint8)
         for b in range(B):
             v = idx[b] >= 0
             want[b][v] = host[b].numpy()[idx[b][v]]
+            if step > 1:
+                assert 0 < int(miss[b]) < np.unique(idx[b][v]).size
         assert np.array_equal(rows.cpu().numpy(), want), step
     ctx.close()
 
