@@ -194,7 +194,9 @@ __global__ __launch_bounds__(BT) void k_bookkeeping(
     // ---- m-th smallest stamp among evictable slots (stamp < step).  One pass by age: the stamps of the last 254 steps
     // have a digit each, everything older shares digit 0.  In a pool in its steady state the victims are some 50 steps
     // old, so the threshold stamp is known after this pass whatever the step number; only when it falls among the older
-    // ones (and their stamps differ: base > 0) do the 4 x 8-bit MSD radix passes follow.
+    // ones (base > 0) do 8-bit MSD radix passes over these follow.  32 sequences, 16384 slots, 280 misses each, with this
+    // pass against radix passes alone: steady state 21.6 us against 25.8; a new pool first used at step 300 26.4 against
+    // 27.3, at step 70000 29.4 against 28.5; victims 6000 steps old 28.1 against 27.2: there it is one pass too many.
     uint32_t prefix = 0, need = m;
     const uint32_t base = step > 255u ? step - 255u : 0u;
     auto age_digit = [&](uint32_t st) -> uint32_t { return st > base ? st - base : 0u; };     // <= 254 for st < step
@@ -244,9 +246,9 @@ __global__ __launch_bounds__(BT) void k_bookkeeping(
       prefix = base + sm.sel_digit;
       __syncthreads();
     } else {
-      // evictable stamps are < step, so digits above step's top byte are zero for all of them: skip those passes
+      // among the older ones (stamp <= base): digits above base's top byte are zero for all of them, skip those passes
       need = m;
-      const int first_pass = step < (1u << 16) ? 2 : (step < (1u << 24) ? 1 : 0);
+      const int first_pass = base < (1u << 8) ? 3 : (base < (1u << 16) ? 2 : (base < (1u << 24) ? 1 : 0));
       for (int pass = first_pass; pass < 4; ++pass) {
         const int shift = 24 - 8 * pass;
         __syncthreads();
@@ -255,7 +257,7 @@ __global__ __launch_bounds__(BT) void k_bookkeeping(
         for (int j = 0; j < nj; ++j) {
           if (v0 + j >= v1) continue;
           const uint32_t st = stamp_at(j);
-          if (st < step && (pass == first_pass || (st >> (shift + 8)) == prefix))
+          if (st <= base && (pass == first_pass || (st >> (shift + 8)) == prefix))
             atomicAdd(&s_hist[((st >> shift) & 255u) * 32 + (lane & 31)], 1u);
         }
         find_digit(nullptr);
@@ -348,7 +350,15 @@ __global__ __launch_bounds__(BT) void k_bookkeeping(
         my_key = s_vict[i];
         const int j0 = (int)((long)m * p / shares), j1 = (int)((long)m * (p + 1) / shares);
         int rk = 0;
-        for (int j = j0; j < j1; ++j) rk += s_vict[j] < my_key ? 1 : 0;
+        int j = j0;
+        for (; j + 8 <= j1; j += 8) {            // eight independent LDS reads in flight (the plain loop waits for each: 280 victims 2.2 us longer)
+          unsigned long long x[8];
+#pragma unroll
+          for (int u = 0; u < 8; ++u) x[u] = s_vict[j + u];
+#pragma unroll
+          for (int u = 0; u < 8; ++u) rk += x[u] < my_key ? 1 : 0;
+        }
+        for (; j < j1; ++j) rk += s_vict[j] < my_key ? 1 : 0;
         atomicAdd(&s_rank[i], (uint32_t)rk);
       }
       __syncthreads();

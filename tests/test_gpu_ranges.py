@@ -168,14 +168,22 @@ def test_short_fetch_in_line_gives_the_bits_of_the_overlapped_schedule(ess_lib, 
             assert torch.equal(x, y)
 
 
-# Steps with gaps between them, few and many entries in turn: victims of one stamp or of many, some or all of them older
-# than the 254 steps that the one-pass threshold search tells apart; more victims than a workgroup has threads; lists of
-# whole rounds of the workgroup and others; a pool too large for the registers
+# Steps with gaps between them, few and many entries in turn: victims never used, of one stamp or of many, some or all of
+# them older than the 254 steps that the one-pass threshold search tells apart, so that one or more passes over the older
+# ones follow; more victims than a workgroup has threads; lists of whole rounds of the workgroup and others; a pool too
+# large for the registers.  "late": a pool whose first step is past 255.
+FROM_ONE = [1, 2, 3, 5, 90, 250, 254, 255, 256, 257, 258, 300, 301, 302, 303, 304, 560, 561, 562, 65530, 65535, 65536, 65537,
+            65700, 65701, 65950, (1 << 24) + 3, (1 << 24) + 4]
+LATE = [300, 301, 302, 303, 428, 429, 430, 509, 510, 511, 512, 556, 813, 814, 40000, 40001, 40127, 40128, 40129, 40400, (1 << 20) + 5,
+        (1 << 20) + 6, (1 << 20) + 132, (1 << 20) + 133, (1 << 20) + 134, (1 << 32) - 300, (1 << 32) - 173, (1 << 32) - 1]
+
+
+@pytest.mark.parametrize("steps", [FROM_ONE, LATE], ids=["from one", "late"])
 @pytest.mark.parametrize("T,k,S,L", [(1, 100, 257, 1500), (1, 1024, 1500, 6000), (2, 1024, 4096, 9000), (2, 1000, 2500, 9000),
                                      (1, 1500, 17000, 30000)])
-def test_bookkeeping_of_old_stamps(ess_lib, T, k, S, L):
+def test_bookkeeping_of_old_stamps(ess_lib, T, k, S, L, steps):
     from paper_2512_10576_amd import binding as bnd
-    print("old stamps", T, k, S, L, flush=True)
+    print("old stamps", T, k, S, L, steps[0], flush=True)
     B = 2
     host = torch.empty((B, L, 1152), dtype=torch.uint8, pin_memory=True)
     host.zero_()
@@ -187,8 +195,6 @@ def test_bookkeeping_of_old_stamps(ess_lib, T, k, S, L):
     lens = torch.full((B,), L, dtype=torch.int32, device="cuda")
     slot = torch.empty((B, T, k), dtype=torch.int32, device="cuda")
     rows = torch.empty((B, T, k, 1152), dtype=torch.uint8, device="cuda")
-    steps = [1, 2, 3, 5, 90, 250, 254, 255, 256, 257, 258, 300, 301, 302, 303, 304, 560, 561, 562, 65530, 65535, 65536, 65537,
-             65700, 65701, 65950, (1 << 24) + 3, (1 << 24) + 4]
     for i, step in enumerate(steps):
         n = k if i % 3 == 2 else max(1, k // 5)
         idx = np.full((B, T, k), -1, np.int32)
