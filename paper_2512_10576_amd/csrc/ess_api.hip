@@ -311,7 +311,8 @@ int ess_create(const ess_config* cfg, ess_ctx** out) {
   if (ess_probe_xcds(ctx->tickets, &ctx->xcds_even) != ESS_OK) return bail("XCD probe", hipGetLastError());
   if ((e = hipHostMalloc(reinterpret_cast<void**>(&ctx->host_miss), ((size_t)cfg->max_batch + 1) * sizeof(int32_t),
                          hipHostMallocMapped)) != hipSuccess) return bail("hipHostMalloc", e);
-  memset(ctx->host_miss, 0, ((size_t)cfg->max_batch + 1) * sizeof(int32_t));
+  memset(ctx->host_miss, 0xff, (size_t)cfg->max_batch * sizeof(int32_t));      // -1: no bookkeeping of this sequence yet
+  ctx->host_miss[cfg->max_batch] = 0;
   if ((e = hipHostGetDevicePointer(reinterpret_cast<void**>(&ctx->host_miss_dev), ctx->host_miss, 0)) != hipSuccess)
     return bail("hipHostGetDevicePointer", e);
   ctx->auto_threshold = 150;
@@ -539,12 +540,17 @@ int ess_decode_step(ess_ctx* ctx, const ess_cache* cache, const ess_step_args* a
     // miss counts of the latest bookkeeping as the host sees them now (no wait: possibly a step old)
     const volatile int32_t* hm = ctx->host_miss;
     long sum = 0;
-    for (int b = 0; b < B; ++b) sum += hm[b];
-    mean_miss = sum / B;
+    bool known = true;
+    for (int b = 0; b < B; ++b) {
+      const int32_t m = hm[b];
+      known = known && m >= 0;
+      sum += m;
+    }
+    if (known) mean_miss = sum / B;
     // the split pays by hiding half the batch's index score behind a fetch: it must be long enough to be
     // worth two rounds of top-k and bookkeeping (at 32K context and batch 64 it is not, whatever the misses)
     const double idx_half_us = 0.5 * B * (double)c.max_ctx * (c.idx_dim + 4.0 * T) / 5.3e6;   // at 5.3 TB/s
-    want_dba = sum > (long)ctx->auto_threshold * B && (ctx->auto_calibrated || idx_half_us >= 50.0);
+    want_dba = known && sum > (long)ctx->auto_threshold * B && (ctx->auto_calibrated || idx_half_us >= 50.0);
   }
   const bool dba = offloaded && want_dba && !(c.flags & ESS_FLAG_SERIAL) && B >= 2;
   ctx->last_overlap = (c.flags & ESS_FLAG_SERIAL) ? 2 : (dba ? 1 : 0);
@@ -590,7 +596,9 @@ int ess_decode_step(ess_ctx* ctx, const ess_cache* cache, const ess_step_args* a
     confine_da = da_swap && attn5 <= 1.6 * fetch_all;
   }
   if (mean_miss >= 0 && da_swap && !confine_da && (double)B * mean_miss * c.row_stride / 50e3 < 35.0) {
-    da_short = true;
+    // (not into a graph: its replays would keep a choice that only this step's misses speak for)
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    da_short = hipStreamIsCapturing(st, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
   }
   ctx->last_confined = confine_da ? 1 : (confine2 ? 2 : (confine ? 1 : 0));
   const uint32_t check_extra = ctx->last_confined ? ctx->check_extra : 0u;   // test hook, one confined step
