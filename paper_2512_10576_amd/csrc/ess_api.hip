@@ -556,14 +556,32 @@ int ess_decode_step(ess_ctx* ctx, const ess_cache* cache, const ess_step_args* a
   ctx->last_overlap = (c.flags & ESS_FLAG_SERIAL) ? 2 : (dba ? 1 : 0);
   const bool da_swap = offloaded && !dba && !(c.flags & ESS_FLAG_SERIAL);
   const int nh = dba ? 2 : 1;
+  // attention splits: chosen from the whole batch and the same for both halves, so that every schedule
+  // sums in the same order and gives the same bits
+  int ns0 = offloaded ? pick_splits_target(c, B, T, attn0_cap(ctx, B, T), ESS_ATTN0_WGS) : pick_splits(ctx, B, T, ESS_MAX_SPLITS);
+  const bool wide = wide_merge(c, B, T);
+  int ns1 = 0;
+  if (offloaded) {
+    // Attn1 works on the short miss lists: as many splits as give the whole batch one workgroup per CU
+    ns1 = pick_splits_target(c, B, T, ESS_ROW_SPLITS - 16, 256);
+    // Attn0 has time to spare only beside a long fetch.  With few sequences the fetch is short (120 misses a sequence are
+    // assumed here: the choice must not depend on the misses, or results would), and Attn0 should fill the chip, together with
+    // Attn1, which then mostly shares its launch.  (Batch 23 x two tokens: 4 + 1 ranges a row instead of 3 + 4.)
+    const long rows = (long)B * T * ((c.attn_heads + 127) / 128);
+    const int tiles = (c.topk + ESS_ATTN_TILE - 1) / ESS_ATTN_TILE, cap = attn0_cap(ctx, B, T);
+    const double fetch_us = B * 120.0 * c.row_stride / 50e3;
+    bool raised = false;
+    while (ns0 < cap && ns0 < tiles && ((tiles + ns0 - 1) / ns0 + 5.5) * 2.2 > fetch_us && rows * (ns0 + 2) <= 256) {
+      ++ns0;
+      raised = true;
+    }
+    if (raised && rows * (ns0 + ns1) > 256) ns1 = (int)(256 / rows - ns0) > 1 ? (int)(256 / rows - ns0) : 1;
+    if (ns1 < ess_attn_min_splits(c)) ns1 = ess_attn_min_splits(c);
+  }
+
   // A fetch confined to a few XCDs (ESS_FETCH_XCD_MASK), with the kernels beside it kept off them (see ess_xcd),
   // pays when the fetch is long: the kernels beside it then run as if alone, but on the other XCDs only.  With few misses the lost
-  // CUs cost more (Attn0, in more rounds of workgroups, becomes the longer side).  Measured (with three XCDs) at batch 64,
-  // 128K context, 1152-byte entries (step time, confined vs not): single-fetch schedule 0.436 vs 0.398 ms
-  // at 31 misses per sequence, 0.447 vs 0.482 at 114, 0.557 vs 0.570 at 195; split-batch, first fetch:
-  // 0.497 vs 0.476 at 114, 0.529 vs 0.529 at 195, 0.607 vs 0.631 at 289; second fetch as well: 0.546 vs
-  // 0.529 at 195, 0.605 vs 0.607 at 289, 0.891 vs 0.933 at 494; at batch 128 with two query tokens and
-  // quantised entries, where attention is as long as the fetches, the second confinement costs 5 %.
+  // CUs cost more (Attn0, in more rounds of workgroups, becomes the longer side).
   // The rules below compare rough times (microseconds) of the fetch and of what runs beside it; the miss
   // count of the previous step is only known under ESS_FLAG_AUTO, without it nothing is confined.
   bool confine = false, confine2 = false, confine_da = false;
@@ -582,14 +600,21 @@ int ess_decode_step(ess_ctx* ctx, const ess_cache* cache, const ess_step_args* a
     // Attn0 on the XCDs the fetch leaves free (one workgroup per CU): rounds x (tiles x time per tile + start and end)
     const int work_cus = 32 * (8 - __builtin_popcount(ESS_FETCH_XCD_MASK & 0xffu));
     const int hg = (c.attn_heads + 127) / 128;
-    const int ns0e = pick_splits_target(c, B, T, attn0_cap(ctx, B, T), ESS_ATTN0_WGS);
     const double hits = c.topk - (mean_miss / T < c.topk ? mean_miss / T : c.topk);
-    const double tiles_item = (hits / ESS_ATTN_TILE) / ns0e + 1.0;
-    const double rounds = (double)((long)B * T * hg * ns0e + work_cus - 1) / work_cus;
-    // (the constants are those the rule's boundaries were measured with: 2.6 us for a tile of 32 entries x 128 heads, 4.2 when
-    // the entries are dequantised on the way, 16 of start and end.  The kernel is faster now, 2.1 and 12, but the boundaries
-    // are sides measured with these, not predictions: smaller constants would confine at fewer misses)
-    const double attn5 = (double)(long)rounds * (tiles_item * (c.latent_fmt == ESS_FMT_BF16 ? 2.6 : 4.2) + 16.0);
+    const double tiles_item = (hits / ESS_ATTN_TILE) / ns0 + 1.0;
+    const double rounds = (double)((long)B * T * hg * ns0 + work_cus - 1) / work_cus;
+    // (a tile of 32 entries x 128 heads: 2.4 us on a full chip, 2.6 when the entries are dequantised on the way, and 12 of
+    // start and end; 2.6 and 14 put the boundary best among these measurements.  Not confined against confined, us, single
+    // fetch: 8 x 128K 120 misses 113 against 125, 240 153 against 143; 16 x 128K 60 misses 152 against 163, 120 187 against
+    // 173, 400 266 against 271; 23 x 48K, two tokens, quantised, 60 misses 152 against 167, 120 187 against 171, 240 201
+    // against 206; 32 x 32K 60 misses 163 against 142, 240 258 against 260; 64 x 128K 31 misses 370 against 355, 114 433
+    // against 438, 494 950 against 943; 128 x 128K, two tokens, quantised, 60 misses 772 against 825, 150 824 against 823,
+    // 388 1251 against 1233.  What it costs for long fetches is within 3 %, what it brings where the fetch is a little
+    // longer than Attn0 up to 15 %; at 8 x 128K with 120 misses the rule confines and loses 10 %.  Split batch, the first
+    // fetch confined against both: 128 x 32K quantised 240 misses 656 against 638, bf16 120 misses 511 against 531, 240 867
+    // against 839; 128 x 128K, two tokens, quantised, 289 misses 962 against 980, 388 1025 against 1024, 600 1442 against
+    // 1404.)
+    const double attn5 = (double)(long)rounds * (tiles_item * 2.6 + 14.0);
     // (one work counter serves one index-score launch: two query tokens at most)
     confine = dba && T <= 2 && fetch_half >= 1.5 * idx_half;
     confine2 = confine && attn5 + 40.0 <= 1.15 * fetch_half;        // + Attn1 and merge of the first half
@@ -613,29 +638,6 @@ int ess_decode_step(ess_ctx* ctx, const ess_cache* cache, const ess_step_args* a
   const int hB[2] = {dba ? B / 2 : B, B - B / 2};
   const size_t k = (size_t)c.topk;
   bool pending[2] = {false, false};
-
-  // attention splits: chosen from the whole batch and the same for both halves, so that every schedule
-  // sums in the same order and gives the same bits
-  int ns0 = offloaded ? pick_splits_target(c, B, T, attn0_cap(ctx, B, T), ESS_ATTN0_WGS) : pick_splits(ctx, B, T, ESS_MAX_SPLITS);
-  const bool wide = wide_merge(c, B, T);
-  int ns1 = 0;
-  if (offloaded) {
-    // Attn1 works on the short miss lists: as many splits as give the whole batch one workgroup per CU
-    ns1 = pick_splits_target(c, B, T, ESS_ROW_SPLITS - 16, 256);
-    // Attn0 has time to spare only beside a long fetch.  With few sequences the fetch is short (120 misses a sequence are
-    // assumed here: the choice must not depend on the misses, or results would), and Attn0 should fill the chip, together with
-    // Attn1, which then mostly shares its launch.  (Batch 23 x two tokens: 4 + 1 ranges a row instead of 3 + 4.)
-    const long rows = (long)B * T * ((c.attn_heads + 127) / 128);
-    const int tiles = (c.topk + ESS_ATTN_TILE - 1) / ESS_ATTN_TILE, cap = attn0_cap(ctx, B, T);
-    const double fetch_us = B * 120.0 * c.row_stride / 50e3;
-    bool raised = false;
-    while (ns0 < cap && ns0 < tiles && ((tiles + ns0 - 1) / ns0 + 5.5) * 2.2 > fetch_us && rows * (ns0 + 2) <= 256) {
-      ++ns0;
-      raised = true;
-    }
-    if (raised && rows * (ns0 + ns1) > 256) ns1 = (int)(256 / rows - ns0) > 1 ? (int)(256 / rows - ns0) : 1;
-    if (ns1 < ess_attn_min_splits(c)) ns1 = ess_attn_min_splits(c);
-  }
 
   // Stages 1 and 2 come in two forms: through the score array (index score, then top-k), or fused (the score array
   // never exists: a sample pass gives each row a lower bound, the index pass emits only candidates, the top-k is
