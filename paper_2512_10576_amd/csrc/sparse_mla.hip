@@ -649,9 +649,9 @@ __global__ __launch_bounds__(NTH, 1) void k_attn_partial_tr(
     // neighbour's.  A wave stages and writes its own 32 rows; rows at a pitch of 264 bytes: the 32 heads of a
     // half-wave write 8 bytes each to 64 different banks.
     // fp16 holds magnitudes below 65504.  The rows are written as they are, the largest magnitude noted on the way;
-    // should a head's reach 2^15 (entry values of that size: rare) or be no number, the wave writes once more, such
-    // heads divided by the power of two that brings their largest value below 2^15 -- exact, and undone by the merge
-    // -- and what fp16 still cannot hold clamped.
+    // should a head's reach 2^15 (entry values of that size: rare) the wave writes once more, such heads divided by the
+    // power of two that brings their largest value below 2^15 -- exact, and undone by the merge -- and what fp16 still
+    // cannot hold clamped.  A value that is no number is written as one in either pass.
     __syncthreads();                                 // every wave is done with the last tile
     float amax = 0.f, down = 1.f;
     const int rows_here = min(HPW, H - head0);
@@ -673,10 +673,13 @@ __global__ __launch_bounds__(NTH, 1) void k_attn_partial_tr(
             floatx4 ov = floatx4{o[4 * qd] * inv, o[4 * qd + 1] * inv, o[4 * qd + 2] * inv, o[4 * qd + 3] * inv};
             if constexpr (CLAMP) {
 #pragma unroll
-              for (int i = 0; i < 4; ++i) ov[i] = __builtin_amdgcn_fmed3f(ov[i], -65504.f, 65504.f);   // never inf in the fp16 image
+              for (int i = 0; i < 4; ++i) {          // never inf in the fp16 image; what is no number stays so (fmed3 would make it -65504)
+                const float in_range = __builtin_amdgcn_fmed3f(ov[i], -65504.f, 65504.f);
+                ov[i] = ov[i] != ov[i] ? ov[i] : in_range;
+              }
             } else {
-              amax = __builtin_elementwise_maximum(amax, __builtin_elementwise_maximum(fabsf(ov[0]), fabsf(ov[1])));   // a NaN stays
-              amax = __builtin_elementwise_maximum(amax, __builtin_elementwise_maximum(fabsf(ov[2]), fabsf(ov[3])));
+              amax = fmaxf(amax, fmaxf(fabsf(ov[0]), fabsf(ov[1])));       // (of the numbers: a NaN is skipped)
+              amax = fmaxf(amax, fmaxf(fabsf(ov[2]), fabsf(ov[3])));
             }
             *reinterpret_cast<halfx4*>(orow + (v4 * 32 + 8 * qd) * 2) = __builtin_convertvector(ov, halfx4);   // round to nearest even
           }
@@ -696,11 +699,8 @@ __global__ __launch_bounds__(NTH, 1) void k_attn_partial_tr(
     };
     if (wave_active) {
     write_rows(std::false_type{});
-    {
-      const uint2v a2 = __builtin_amdgcn_permlane32_swap(__float_as_uint(amax), __float_as_uint(amax), false, false);
-      amax = __builtin_elementwise_maximum(__uint_as_float(a2.x), __uint_as_float(a2.y));
-    }
-    if (__any(!(amax < 32768.f))) {
+    amax = pair_max(amax);
+    if (__any(amax >= 32768.f)) {
       int ex = 0;
       (void)frexpf(amax, &ex);                       // amax < 2^ex
       down = (amax >= 32768.f && amax <= 3.0e38f) ? ldexpf(1.f, ex - 15) : 1.f;

@@ -55,6 +55,31 @@ def test_attention_list_lengths_and_heads(ess_lib, fmt, B, T, H, k, lens):
     assert np.array_equal(np.isneginf(lse[some].cpu().numpy()), np.isneginf(ref_lse))
 
 
+@pytest.mark.parametrize("k", [64, 2048])
+def test_attention_of_an_infinite_value_with_weight_zero(ess_lib, k):
+    """An entry that is infinite in one column, where every query is negative: its logit is -inf, its weight zero, and
+    zero times infinity is no number -- in that column alone.  The others, values beyond the fp16 range among them, are
+    what they are without it (the plain average of identical entries, exact)."""
+    print("attention, infinite value", k, flush=True)
+    B, T, H, L = 1, 2, 128, 2048
+    rows = torch.zeros((B, L, 576), dtype=torch.bfloat16)
+    rows[..., 0], rows[..., 1] = 3.0e5, -0.5
+    rows[0, 3, 7] = float("inf")
+    q = torch.zeros((B, T, H, 576), dtype=torch.bfloat16)
+    q[..., 7] = -1.0
+    idx = torch.arange(k, dtype=torch.int32).expand(B, T, k).contiguous()
+    ctx = _ctx(ess_lib, max_batch=B, max_q_tokens=T, max_ctx=L, idx_heads=4, idx_dim=32, topk=k, attn_heads=H)
+    out = torch.full((B, T, H, 512), 9.0, dtype=torch.bfloat16, device="cuda")
+    lse = torch.full((B, T, H), 9.0, dtype=torch.float32, device="cuda")
+    ctx.sparse_mla_decode(q.cuda(), rows.view(torch.uint8).reshape(B, L, 1152).cuda(), idx.cuda(), out, lse)
+    torch.cuda.synchronize()
+    ctx.close()
+    want = torch.zeros((B, T, H, 512))
+    want[..., 0], want[..., 1], want[..., 7] = rows[0, 0, 0].float(), -0.5, float("nan")
+    assert torch.equal(out.float().cpu().nan_to_num(nan=-12345.0), want.nan_to_num(nan=-12345.0)), out[0, 0, 0, :9]
+    assert np.allclose(lse.cpu().numpy(), np.log(k - 1), atol=1e-4)
+
+
 # rows around k, a thread's eight keys, the candidate list (8192) and the sampled path above it
 @pytest.mark.parametrize("kind", ["distinct", "ties", "one value", "low and high", "power of two"])
 @pytest.mark.parametrize("vis,k", [(9, 8), (1025, 1024), (4097, 2048), (4096, 2048), (8191, 2048), (8192, 4096), (8193, 2048), (16384, 513)])
