@@ -686,6 +686,10 @@ __global__ __launch_bounds__(NTH, 1) void k_attn_partial_tr(
         };
         block(std::integral_constant<int, 0>{}); block(std::integral_constant<int, 1>{});
         block(std::integral_constant<int, 2>{}); block(std::integral_constant<int, 3>{});
+        // lanes read what other lanes of their wave wrote: a wave's LDS accesses are in order, and nothing may be moved across
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 #pragma unroll
         for (int r4 = 0; r4 < HPW / 4; ++r4) {
           const int r = min(4 * r4 + ((t3 & 63) >> 4), rows_here - 1);      // past the last head: its row once more
