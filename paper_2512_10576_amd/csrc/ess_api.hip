@@ -65,10 +65,12 @@ struct WsLayout {
 
 size_t up256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-// partial attention results (of all heads) the workspace holds
+// partial attention results (of all heads) the workspace holds; a row never has more than ESS_MAX_SPLITS (128 heads:
+// 128 KiB each, 8 MiB for a context of one row, 40 MiB for five to sixteen)
 size_t part_capacity(const ess_config& c) {
-  const size_t n = (size_t)c.max_batch * c.max_q_tokens * ESS_ROW_SPLITS;
-  return n > ESS_MIN_PARTS ? n : ESS_MIN_PARTS;
+  const size_t rows = (size_t)c.max_batch * c.max_q_tokens;
+  const size_t few = rows * ESS_MAX_SPLITS < ESS_MIN_PARTS ? rows * ESS_MAX_SPLITS : ESS_MIN_PARTS;
+  return rows * ESS_ROW_SPLITS > few ? rows * ESS_ROW_SPLITS : few;
 }
 
 WsLayout ws_layout(const ess_config& c) {

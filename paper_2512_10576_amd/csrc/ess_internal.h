@@ -10,7 +10,7 @@
 #define ESS_ATTN_TILE 32        // entries per attention tile
 #define ESS_MAX_SPLITS 64       // partial results per (b,t) at most: Attn0 splits + Attn1 splits (the merge gives each a lane)
 #define ESS_ROW_SPLITS 20       // ... that there is room for at the context's full batch
-#define ESS_MIN_PARTS 320       // ... and for all rows together in a small context
+#define ESS_MIN_PARTS 320       // ... and for all rows together in a small context (as far as they can use it)
 #define ESS_ROW_DIM 576
 #define ESS_ZERO_ROW_BYTES 2048  // >= the largest row_stride
 #define ESS_TOPK_SHARED_ROWS 128 // rows (b,t) up to which a top-k row is shared by several workgroups

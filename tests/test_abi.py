@@ -68,6 +68,15 @@ def test_config_validation_reports_errors(lib):
         b.workspace_bytes(bad)
 
 
+@pytest.mark.parametrize("rows,parts", [((1, 1), 64), ((1, 2), 128), ((4, 1), 256), ((5, 1), 320), ((16, 1), 320), ((32, 2), 1280)])
+def test_workspace_holds_no_more_partial_results_than_rows_can_use(rows, parts):
+    """The room for partial attention results (512 fp16 values, a log-sum-exp and a scale per head): at most 64 splits a
+    row, 320 in all for few rows, 20 a row for many.  What 64 more heads add to the workspace is 64 times that."""
+    from paper_2512_10576_amd import binding as b
+    size = [b.workspace_bytes(b.make_config(*rows, 4096, 64, 128, 512, heads)) for heads in (64, 128)]
+    assert size[1] - size[0] == parts * 64 * (512 * 2 + 8)
+
+
 def test_attention_kernel_agprs_are_only_named_by_its_own_asm(tmp_path):
     """k_attn_partial_tr keeps its 256 output accumulators in AGPRs a0..a255 that its own asm statements name, and
     tells the compiler that the whole AGPR file is taken from a claim statement to a release statement.  Checked in
