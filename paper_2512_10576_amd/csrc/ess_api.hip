@@ -14,7 +14,7 @@
 // Workgroups that Attn0 of the whole batch aims at when entries are offloaded: half a workgroup per CU.  Attn0 runs
 // beside a fetch and has time to spare, while every split adds a partial result (128 KiB per row) that the merge,
 // which runs after the last fetch, has to read: 128 against 256 took 15 % off Attn0 itself and 0.3-0.7 % off the step.
-// (Beside a short fetch it is raised to fill the chip: see ns0 in ess_decode_step.)
+// (With few sequences, whose fetches are short, it is raised: see ns0 in ess_decode_step.)
 #define ESS_ATTN0_WGS 128
 
 namespace {
@@ -567,18 +567,20 @@ int ess_decode_step(ess_ctx* ctx, const ess_cache* cache, const ess_step_args* a
     // Attn1 works on the short miss lists: as many splits as give the whole batch one workgroup per CU
     ns1 = pick_splits_target(c, B, T, ESS_ROW_SPLITS - 16, 256);
     // Attn0 has time to spare only beside a long fetch.  With few sequences the fetch is short (120 misses a sequence are
-    // assumed here: the choice must not depend on the misses, or results would), and Attn0 should fill the chip, together with
-    // Attn1, which then mostly shares its launch.  (Batch 23 x two tokens: 4 + 1 ranges a row instead of 3 + 4.)
+    // assumed here: the choice must not depend on the misses, or results would), and Attn0 gets more ranges, as many as the
+    // CUs a confined fetch leaves (192) hold in one round, and none that do not shorten the longest range.  Attn1 keeps its
+    // ranges: with many misses it is what follows the fetch.  Ranges of Attn0 + Attn1 a row, us a step: 23 x 48K, two tokens,
+    // quantised, 30 / 480 misses: 3 + 4 152 / 278, 4 + 4 144 / 278, 4 + 1 144 / 296; 13 x 32K quantised, 30 / 200 / 900:
+    // 10 + 4 93 / 126 / 264, 13 + 4 90 / 127 / 265, 15 + 4 90 / 133 / 265, 17 + 2 90 / 137 / 278; 5 x 64K, 30 / 1500:
+    // 26 + 4 78 / 280, 32 + 4 77 / 280, 49 + 2 78 / 299.
     const long rows = (long)B * T * ((c.attn_heads + 127) / 128);
-    const int tiles = (c.topk + ESS_ATTN_TILE - 1) / ESS_ATTN_TILE, cap = attn0_cap(ctx, B, T);
+    const int tiles = (c.topk + ESS_ATTN_TILE - 1) / ESS_ATTN_TILE, cap = attn0_cap(ctx, B, T), base = ns0;
     const double fetch_us = B * 120.0 * c.row_stride / 50e3;
-    bool raised = false;
-    while (ns0 < cap && ns0 < tiles && ((tiles + ns0 - 1) / ns0 + 5.5) * 2.2 > fetch_us && rows * (ns0 + 2) <= 256) {
-      ++ns0;
-      raised = true;
+    while (ns0 < cap && ns0 < tiles && ((tiles + ns0 - 1) / ns0 + 5.5) * 2.2 > fetch_us && rows * (ns0 + 1) <= 192) ++ns0;
+    if (ns0 > base) {
+      const int longest = (tiles + ns0 - 1) / ns0, fewest = (tiles + longest - 1) / longest;
+      ns0 = fewest > base ? fewest : base;
     }
-    if (raised && rows * (ns0 + ns1) > 256) ns1 = (int)(256 / rows - ns0) > 1 ? (int)(256 / rows - ns0) : 1;
-    if (ns1 < ess_attn_min_splits(c)) ns1 = ess_attn_min_splits(c);
   }
 
   // A fetch confined to a few XCDs (ESS_FETCH_XCD_MASK), with the kernels beside it kept off them (see ess_xcd),
