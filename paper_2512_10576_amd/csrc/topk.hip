@@ -13,8 +13,7 @@
 //      thousand positions at or above it; one pass over the row collects those
 //      candidates (their composite keys) in LDS.  If their number is not in
 //      [k, buffer size] (an unlucky sample, massive ties) path B runs instead.
-//   S. rows that fit the candidate buffer whole, in a kernel form of its own for contexts that allow no longer ones
-//      (MODE 4): all keys in registers, no list.
+//   S. rows that fit the candidate buffer whole: all keys in registers, no list.
 //   B. general: MSD radix narrowing on the composite key straight from memory,
 //      11 bits a pass (histogram in 8 interleaved copies, copy = lane & 7, so
 //      that lanes hitting one hot bin do not serialise), until the positions
@@ -41,7 +40,8 @@ using ess_sel::SBINS;
 constexpr int SAMPLE_TARGET = 4096;         // at most this many samples per row (four per thread), about every 16th score or fewer
 static_assert(SAMPLE_TARGET <= 4 * NT, "the sample is loaded in one round of four per thread");
 constexpr int FAST_MIN_VIS = CAND_CAP + 1;   // rows above the candidate list's size are sampled (path A)
-constexpr int WHOLE_MIN_VIS = 4097;          // rows from here on, where all fit that list, are done whole (path S)
+constexpr int WHOLE_MIN_VIS = 4097;          // rows from here on that fit that list are done whole (path S)
+constexpr uint32_t ROW_DONE = 0xffffffffu;   // in place of a candidate count: the candidate pass did the row itself
 
 struct __align__(16) TopkShared {
   union {
@@ -308,6 +308,39 @@ __device__ __forceinline__ bool finish_fast(TopkShared& sm, int tid, const unsig
   return finish_keys<false>(sm, tid, c, listed, lo, hi, vis, k, IB, orow);
 }
 
+// Path S: a row that fits the candidate list whole needs no sample and no list: eight keys per thread in registers, a
+// histogram of their top 14 bits tells exactly in which bin the k-th largest lies, and that bin's range is resolved like
+// the range between two sampled bounds.  Against path B (one 11-bit pass collects the row, up to five more follow in
+// LDS), one row / 32 rows, us: 8192 scores 10.8 / 10.9 against 13.1 / 13.5, 5000 10.0 / 10.5 against 10.5 / 12.0, but
+// 4096 10.0 / 10.7 against 8.8 / 10.6 and 2500 10.6 / 10.9 against 9.9 / 10.8: from 4097 on (WHOLE_MIN_VIS).
+// Where rows are shared it is part 0 of the candidate pass (MODE 1) that takes such a row, not the finishing kernel:
+// inlined there beside its other paths it cost every longer row 0.4 to 0.6 us (and 256 bytes of scratch a lane where
+// work is drawn by ticket).
+// Returns false, with the keys in sm.cand, when more than 1024 keys share a digit of the bin.
+__device__ __forceinline__ bool whole_row(TopkShared& sm, int tid, const float* __restrict__ srow, int vis, int k, int IB,
+                                          int32_t* __restrict__ orow) {
+  const unsigned long long imask = (1ull << IB) - 1ull;
+  float sv[PER];
+#pragma unroll
+  for (int u = 0; u < PER; ++u) sv[u] = u * NT + tid < vis ? srow[u * NT + tid] : 0.f;
+  for (int j = tid; j < ess_sel::sample_words<NT>(); j += NT) sm.shist[j] = 0;
+  if (tid == 0) sm.sbin[0] = 0u;
+  __syncthreads();
+  unsigned long long c[PER];
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    const int i = u * NT + tid;
+    c[u] = i < vis ? ((unsigned long long)orderable(sv[u]) << IB) | (imask - (unsigned long long)i) : 0ull;
+    if (i < vis) atomicAdd(&sm.shist[ess_sel::sample_slot<NT>((uint32_t)(c[u] >> IB) >> (32 - SBITS))], 1u);
+  }
+  __syncthreads();
+  ess_sel::crossing_bin<NT>(sm.shist, sm.wave_tot, sm.sbin, (uint32_t)k);     // (ends with a barrier: shist is dead from here)
+  const uint32_t bin = sm.sbin[0];
+  const uint32_t lo = bin << (32 - SBITS), hi = bin == SBINS - 1 ? 0xffffffffu : (bin + 1) << (32 - SBITS);
+  __syncthreads();
+  return finish_keys<true>(sm, tid, c, (uint32_t)vis, lo, hi, vis, k, IB, orow);
+}
+
 // MODE 0: one workgroup does the whole row (grid: rows).
 // MODE 1 + MODE 2, for small batches of long rows: the candidate pass of path A, the only part that
 // scales with the row, is spread over `parts` workgroups per row in a kernel of its own (MODE 1, grid
@@ -317,7 +350,8 @@ __device__ __forceinline__ bool finish_fast(TopkShared& sm, int tid, const unsig
 // the row by itself like MODE 0.  The hand-over is the kernel boundary: workgroups of one kernel
 // never exchange data (an agent-scope fence inside a kernel costs tens of microseconds on this
 // multi-die part, where it writes the L2 back).  g_cnt is zero between steps: MODE 2 clears it.
-// MODE 4: as MODE 0 where max_ctx allows only rows that fit the candidate list (path S, and B for the shortest).
+// MODE 4: as MODE 0 where max_ctx allows only rows that fit the candidate list (path S, and B for the shortest): without
+// path A's code one row of 8000 takes 9.9 us instead of 10.2.
 // MODE 3: the finishing kernel of the fused selection (grid rows).  The row's list was written by the emitting
 // index-score pass (index_kernel.h), for rows of any length; `score` is scratch memory, not scores: a row whose list
 // cannot be used (fewer than k or more than the buffer holds: a misleading sample, massive ties) has its scores
@@ -345,12 +379,16 @@ __device__ __forceinline__ void topk_item(TopkShared& sm, int item, int parts, f
   float* srow = score + (size_t)row * Lmax;
   int32_t* orow = idx_out + (size_t)row * k;
 
-  if (MODE == 1 && (vis <= k || vis < FAST_MIN_VIS)) return;      // nothing to prepare
+  if (MODE == 1 && (vis <= k || vis < FAST_MIN_VIS)) {            // nothing to prepare: a short row is done here, or later
+    if (part == 0 && vis > k && vis >= WHOLE_MIN_VIS && whole_row(sm, tid, srow, vis, k, IB, orow) && tid == 0) g_cnt[row] = ROW_DONE;
+    return;
+  }
   uint32_t listed = 0;
   if (MODE == 2 || MODE == 3) {            // candidates prepared by the kernel in front (0 if none)
     listed = g_cnt[row];
     __syncthreads();
     if (tid == 0) g_cnt[row] = 0;
+    if (MODE == 2 && listed == ROW_DONE) return;
   }
   if (vis <= k) {                          // everything visible is selected
     for (int j = tid; j < k; j += NT) orow[j] = j < vis ? j : -1;
@@ -372,35 +410,10 @@ __device__ __forceinline__ void topk_item(TopkShared& sm, int item, int parts, f
   bool all_in_cand = false;                 // ... and every key above it as well (path A)
   int nc = 0;
 
-  // ---- S: rows that fit the candidate list whole need no sample and no list: eight keys per thread in registers, a
-  // histogram of their top 14 bits tells exactly in which bin the k-th largest lies, and that bin's range is resolved
-  // like the range between two sampled bounds.  Against path B (one 11-bit pass collects the row, up to five more follow
-  // in LDS), one row / 32 rows, us: 8192 scores 10.8 / 10.9 against 13.1 / 13.5, 5000 10.0 / 10.5 against 10.5 / 12.0, but
-  // 4096 10.0 / 10.7 against 8.8 / 10.6 and 2500 10.6 / 10.9 against 9.9 / 10.8: from 4097 on.
-  // It has a form of its own because it does not pay for itself beside the other paths: inlined into MODE 0 and 2 it
-  // took the looping forms from 12 and 20 to 172 and 256 bytes of scratch a lane and cost every longer row 0.2 to 0.6 us.
-  if (MODE == 4 && vis >= WHOLE_MIN_VIS) {
-    float sv[PER];
-#pragma unroll
-    for (int u = 0; u < PER; ++u) sv[u] = u * NT + tid < vis ? srow[u * NT + tid] : 0.f;
-    for (int j = tid; j < ess_sel::sample_words<NT>(); j += NT) sm.shist[j] = 0;
-    if (tid == 0) sm.sbin[0] = 0u;
-    __syncthreads();
-    unsigned long long c[PER];
-#pragma unroll
-    for (int u = 0; u < PER; ++u) {
-      const int i = u * NT + tid;
-      c[u] = i < vis ? comp_of(i, sv[u]) : 0ull;
-      if (i < vis) atomicAdd(&sm.shist[ess_sel::sample_slot<NT>((uint32_t)(c[u] >> IB) >> (32 - SBITS))], 1u);
-    }
-    __syncthreads();
-    ess_sel::crossing_bin<NT>(sm.shist, sm.wave_tot, sm.sbin, (uint32_t)k);     // (ends with a barrier: shist is dead from here)
-    const uint32_t bin = sm.sbin[0];
-    const uint32_t lo = bin << (32 - SBITS), hi = bin == SBINS - 1 ? 0xffffffffu : (bin + 1) << (32 - SBITS);
-    __syncthreads();
-    if (finish_keys<true>(sm, tid, c, (uint32_t)vis, lo, hi, vis, k, IB, orow)) return;
-    // (more than 1024 keys share a digit of the bin: the keys are in sm.cand now, the general selection takes them)
-    nc = vis;
+  // ---- S: rows that fit the candidate list whole
+  if ((MODE == 0 || MODE == 4) && vis >= WHOLE_MIN_VIS && vis <= CAND_CAP) {
+    if (whole_row(sm, tid, srow, vis, k, IB, orow)) return;
+    nc = vis;                              // the keys are in sm.cand now, the general selection takes them
     have_cand = true;
     all_in_cand = true;
   }

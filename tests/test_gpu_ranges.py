@@ -104,6 +104,63 @@ def test_topk_short_rows(ess_lib, kind, vis, k):
     _topk_sets_equal(_run_topk(ess_lib, sc, [vis], k, 1), O.topk(sc, lens, k))
 
 
+def test_topk_short_rows_of_a_long_context(ess_lib):
+    """Contexts from 65536 share their rows: those that fit the candidate list are done by the candidate pass, the
+    shortest, and those with too many ties, by the finishing kernel; and nothing of a call is left for the next."""
+    print("topk, short rows of a long context", flush=True)
+    rng = np.random.default_rng(3)
+    L, k = 65536, 2048
+    lens = [4096, 65536, 4097, 8192, 8193, 2048, 100, 0, 8000, 6000, 30000, 5000]
+    B = len(lens)
+    ctx = _ctx(ess_lib, max_batch=B, max_q_tokens=1, max_ctx=L, idx_heads=4, idx_dim=32, topk=k, attn_heads=8)
+    for turn in range(4):
+        sc = (rng.standard_normal((B, 1, L)) * 100).astype(np.float32)
+        if turn % 2:
+            sc = np.round(sc)
+        sc[8] = np.round(sc[8] / 64)                         # a dozen values: thousands of equal scores
+        idx = torch.full((B, 1, k), -5, dtype=torch.int32, device="cuda")
+        ctx.topk(torch.from_numpy(sc).cuda(), torch.tensor(lens, dtype=torch.int32).cuda(), idx)
+        torch.cuda.synchronize()
+        _topk_sets_equal(idx.cpu().numpy(), O.topk(sc, np.array(lens), k))
+        lens = lens[1:] + lens[:1]                           # another length for every row of the next call
+    ctx.close()
+
+
+@pytest.mark.parametrize("L", [9000, 65536])                 # one kernel, two kernels
+def test_topk_of_short_rows_by_ticket(ess_lib, L):
+    """Short rows of a longer context in the split-batch schedule with confined fetches, where the top-k of the second
+    half takes its rows by ticket: the selections of the plain schedule."""
+    from paper_2512_10576_amd import binding as bnd
+    print("topk by ticket", L, flush=True)
+    B, T, k, H, S = 8, 1, 512, 16, 2048
+    host = torch.zeros((B, L, 656), dtype=torch.uint8, pin_memory=True)
+    lens = torch.tensor([4097, L, 8192, 4096, 8192, 5000, L, 600], dtype=torch.int32).cuda()
+    key = synth.indexer_inputs(1, B, T, 64, 128, L, 8, 8, 16)[2].cuda()
+    qws = [tuple(x.cuda() for x in synth.indexer_inputs(30 + s, B, T, 64, 128, 64, 8, 8, 16)[:2]) for s in range(3)]
+    q = synth.attn_query(9, B, T, H).cuda()
+    results, confined = {}, []
+    for flags in (0, bnd.ESS_FLAG_AUTO):
+        ctx = _ctx(ess_lib, max_batch=B, max_q_tokens=T, max_ctx=L, idx_heads=64, idx_dim=128, topk=k, attn_heads=H,
+                   latent_fmt=O.FMT_FP8, slots_per_seq=S, flags=flags)
+        if flags:
+            ctx.set_overlap_threshold(0)
+        cache = bnd.Cache.allocate(ctx.cfg, B, host_pool=host)
+        ctx.cache_reset(cache, B)
+        got = []
+        for step in range(3):
+            idx = torch.empty((B, T, k), dtype=torch.int32, device="cuda")
+            out = torch.empty((B, T, H, 512), dtype=torch.bfloat16, device="cuda")
+            ctx.decode_step(cache, *qws[step], key, lens, q, step + 1, idx, out)
+            torch.cuda.synchronize()
+            if flags:
+                confined.append((ctx.last_overlap(), ctx.last_confined()))
+            got.append(idx)
+        results[flags] = got
+        ctx.close()
+    assert all(mode == 1 and n >= 1 for mode, n in confined[1:]), confined
+    assert all(torch.equal(a, b) for a, b in zip(results[0], results[bnd.ESS_FLAG_AUTO]))
+
+
 # (the last two: 32 MiB of rows and more, gathered on two streams beside the fetch; with quantised entries the rows of
 # concurrent kernels share cache lines)
 @pytest.mark.parametrize("fmt,B,T,L,S,k", [
