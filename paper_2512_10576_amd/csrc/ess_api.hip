@@ -126,9 +126,12 @@ int check_cache(const ess_ctx* ctx, const ess_cache* c) {
 // Number of attention splits for lists of up to k entries.  A workgroup owns a CU, so the launch takes rounds of 256
 // workgroups, each as long as the tiles of its range and about five and a half more for its start and end (2.1 us a
 // tile; measured 12 us for queries, first gathers and the write of a partial result); every partial result is then
-// written and read once more by the merge, 256 KiB per 128 heads at about 4.5 TB/s, and
-// a small batch's merge takes 0.12 us longer per split.  The split count with the least sum is taken.  (Before, one count was aimed at that puts a workgroup on every CU, rounded up: 96 rows got three splits
-// each, 288 workgroups, i.e. a second round for 32 of them.)
+// written and read once more by the merge, 256 KiB per 128 heads at about 4.5 TB/s, and a small batch's merge takes
+// 0.12 us longer per split.  The split count with the least sum is taken.  (Before, one count was aimed at that puts a
+// workgroup on every CU, rounded up: 96 rows got three splits each, 288 workgroups, i.e. a second round for 32 of them.)
+// One time per tile serves both formats: 256 rows of 2048 N(0,1) entries take 179 us, quantised ones 195 (2.4 and 2.6 us a
+// tile with every CU at work, 1.6 and 2.0 where the power limit leaves the clock alone), 64 rows 53 and 58: the ratio of a
+// tile to start and end, which decides, is nearly the same.
 int pick_splits(const ess_ctx* ctx, int B, int T, int cap) {
   const ess_config& c = ctx->cfg;
   const int tiles = (c.topk + ESS_ATTN_TILE - 1) / ESS_ATTN_TILE;
@@ -146,7 +149,12 @@ int pick_splits(const ess_ctx* ctx, int B, int T, int cap) {
   return best;
 }
 
-// The same for lists beside or behind a fetch: about `target_wgs` workgroups for the whole batch.
+// The same for lists beside or behind a fetch: about `target_wgs` workgroups for the whole batch.  From 128 rows on that is
+// one range of the whole list; at most 32 tiles a workgroup, as it was, is the better bound only where nothing is confined.
+// Whole lists against two ranges, us a step: 128 x 32K, 60 / 120 / 240 misses (confined) 346 / 506 / 823 against 349 / 508 /
+// 826, split batch 373 / 515 / 847 against 391 / 529 / 864, 30 misses (not confined) 338 against 327; quantised, 120 misses
+// 403 against 407, split batch 415 against 432; 128 x 128K, two tokens, quantised, split batch, 388 misses 1025 against
+// 1026, 195 (not confined) 889 against 853.
 int pick_splits_target(const ess_config& c, int B, int T, int cap, int target_wgs) {
   const int tiles = (c.topk + ESS_ATTN_TILE - 1) / ESS_ATTN_TILE;
   const int hgroups = (c.attn_heads + 127) / 128;      // a workgroup covers 128 heads

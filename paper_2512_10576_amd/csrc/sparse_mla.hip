@@ -82,8 +82,8 @@ __device__ __forceinline__ void wait_vmcnt() {     // vmcnt <= N, other counters
 // ---------------------------------------------------------------- the partial-attention kernel
 // Four waves, one per SIMD, 32 heads each: a workgroup covers all (up to 128) heads of one range of the entry
 // list, so an entry is brought from memory once per range.  Tiles of 32 entries sit in LDS as bf16 rows: bf16
-// entries gathered by global_load_lds, quantised entries (512 fp8 + 4 scales + rope) loaded into registers a tile
-// ahead, dequantised and written in the same layout.  Matrix-core mapping (v_mfma_f32_32x32x16_bf16), both
+// entries gathered there by global_load_lds, quantised entries (512 fp8 + 4 scales + rope) brought whole into a raw ring
+// in the same way, a tile ahead, and dequantised from it into the same layout.  Matrix-core mapping (v_mfma_f32_32x32x16_bf16), both
 // products transposed so that nothing is re-laid out between them:
 //   S^T[r,h] = sum_d K[r,d] Q[h,d]      A = entry rows from LDS (lane: row l%32, 8 dims), B = Q^T (registers)
 //   O^T[v,h] = sum_r V^T[v,r] P^T[r,h]  A = V^T, read transposed from the same rows, B = P^T (registers)
@@ -93,8 +93,9 @@ __device__ __forceinline__ void wait_vmcnt() {     // vmcnt <= N, other counters
 // (head, half); the two halves of a head meet in one v_permlane32_swap.
 // What bounds it.  Per tile a SIMD's matrix pipe is busy for 2176 cycles (68 MFMAs of 32), and one wave issues its
 // instructions one at a time, four cycles each or more, so what a tile costs is decided by what the wave waits for and
-// by how many instructions it needs, not by the LDS (278 KiB of fragments per tile; it delivers above 200 bytes per
-// clock).  Measured with phase timers, cycles per tile: before, 5500-5900 (bf16; 760 instructions) and 6900
+// by how many instructions it needs.  The LDS is close behind: to one wave per SIMD it delivers 127 bytes per clock of K
+// fragments and 78 of transposed ones (215 and 168 to four waves per SIMD), so the 144 + 128 KiB of a tile alone are
+// about 2800 cycles of reads beside the 2176 of MFMAs.  Measured with phase timers, cycles per tile: before, 5500-5900 (bf16; 760 instructions) and 6900
 // (quantised); now 2250 + 1400 (first + second product, bf16; 530 instructions) and 2350 + 2240 (quantised).  What did it:
 //  * the accumulation of S^T in two chains (a dependent MFMA of this shape waits for twice its 32 cycles);
 //  * fragments read six and eight steps ahead, in a program order pinned by scheduling barriers, with the softmax, the
@@ -113,7 +114,7 @@ __device__ __forceinline__ void wait_vmcnt() {     // vmcnt <= N, other counters
 //    16s+8+4hh+i) make one A fragment whose k order is the order in which S^T leaves the first product.
 //  * Rows have no padding (pitch 1024 bytes); the 16-byte granules of a row are XOR-swizzled with
 //    f(row) = (row&3)<<2 | (row>>2)&3, applied on the way in by letting lane l of the gather fetch granule
-//    l ^ f(row).  The LDS has 64 banks (256 bytes per clock): K fragments (16 rows of one granule per clock) are
+//    l ^ f(row).  The LDS has 64 banks: K fragments (16 rows of one granule per clock) are
 //    conflict-free because f is a bijection of the row's low four bits, transposing reads (4 rows x 64 bytes per
 //    clock) because f puts the row's low two bits above the granule pair.
 //  * The running maximum is only moved when a tile exceeds it by more than 2^8, so the 256 accumulator registers
@@ -229,7 +230,7 @@ __global__ __launch_bounds__(NTH, 1) void k_attn_partial_tr(
     ess_xcd xcd, int n_bt, int n_hg, const int32_t* __restrict__ list_b, const int32_t* __restrict__ n_list_b, int nsplit_b) {
   extern __shared__ __align__(16) uint8_t lds[];
   __shared__ int s_item;
-  constexpr bool kDma = FMT == ESS_FMT_BF16;       // rows go to LDS as they are; else through registers, dequantised
+  constexpr bool kDma = FMT == ESS_FMT_BF16;       // rows go to their tile as they are; else to the raw ring, and from there dequantised
   constexpr int NBUF = tr_nbuf(FMT), NRAW = tr_nraw(FMT), RAW_OFF = NBUF * TR_RAW_BYTES;
   constexpr int PER_TILE = kDma ? DMA_PER_TILE : 8;    // memory instructions of a wave per tile
   int32_t* slot_cache = reinterpret_cast<int32_t*>(lds + tr_slot_off(FMT));   // [MAX_TPS][32], masked entries -inf
@@ -490,7 +491,7 @@ __global__ __launch_bounds__(NTH, 1) void k_attn_partial_tr(
     float psum = 0.f;
     auto exp_row = [&](auto ic) {              // one row of tile it-1: exponential, row sum, and every second row a bf16 pair
       constexpr int i = decltype(ic)::value;
-      sprev[i] = __builtin_amdgcn_exp2f(fmaf(sprev[i], scale_log2e, -m_use));     // the argument is <= 2^kLazyMax: no range reduction needed
+      sprev[i] = __builtin_amdgcn_exp2f(fmaf(sprev[i], scale_log2e, -m_use));     // the argument is <= kLazyMax: no range reduction needed
       psum += sprev[i];
       if constexpr (i & 1) {
         pq[i >> 1] = pack_bf16(sprev[i - 1], sprev[i]);
