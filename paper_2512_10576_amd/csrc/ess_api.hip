@@ -172,8 +172,11 @@ int attn0_cap(const ess_ctx* ctx, int B, int T) {
   return (int)(n > ESS_MAX_SPLITS ? ESS_MAX_SPLITS : n) - (ESS_ROW_SPLITS - 16);
 }
 
-// Merge with four waves per row?  Where one wave per row leaves most of the chip idle.
-bool wide_merge(const ess_config& c, int B, int T) { return (long)B * T * c.attn_heads <= 2048; }
+// Merge with four waves per row (b,t,h)?  Where one wave per row leaves most of the chip idle and has many splits to read.
+// One wave against four, attention and merge of lists of 2048, us (32, 32, 21, 16 splits): 128 rows 28.4 / 19.1, 1024 29.2 /
+// 27.8 (quantised 32.3 / 31.2), 1536 28.9 / 29.1 (32.3 / 33.3), 2048 29.9 / 32.6 (33.1 / 36.3); with 16 heads 512 rows of 8
+// splits 29.3 / 27.9, 1024 of 4 splits 40.1 / 42.2.
+bool wide_merge(const ess_config& c, int B, int T, int nsplit) { return (long)B * T * c.attn_heads <= 1024 && nsplit >= 8; }
 
 // A view of the caller's cache arrays starting at sequence b0.
 ess_cache shift_cache(const ess_config& c, const ess_cache& in, int b0) {
@@ -491,7 +494,7 @@ int ess_sparse_mla_decode(ess_ctx* ctx, const void* q_bf16, const uint8_t* slot_
   const int ns = pick_splits(ctx, B, T, ESS_MAX_SPLITS);
   rc = ess_launch_attn_partial(ctx, q_bf16, slot_pool, slot_idx, nullptr, B, T, 0, ns, ns, st);
   if (rc != ESS_OK) return rc;
-  return ess_launch_attn_merge(ctx, B, T, ns, wide_merge(ctx->cfg, B, T), out_bf16, lse, st);
+  return ess_launch_attn_merge(ctx, B, T, ns, wide_merge(ctx->cfg, B, T, ns), out_bf16, lse, st);
 }
 
 int ess_decode_step(ess_ctx* ctx, const ess_cache* cache, const ess_step_args* a, void* stream) {
@@ -569,7 +572,6 @@ int ess_decode_step(ess_ctx* ctx, const ess_cache* cache, const ess_step_args* a
   // attention splits: chosen from the whole batch and the same for both halves, so that every schedule
   // sums in the same order and gives the same bits
   int ns0 = offloaded ? pick_splits_target(c, B, T, attn0_cap(ctx, B, T), ESS_ATTN0_WGS) : pick_splits(ctx, B, T, ESS_MAX_SPLITS);
-  const bool wide = wide_merge(c, B, T);
   int ns1 = 0;
   if (offloaded) {
     // Attn1 works on the short miss lists: as many splits as give the whole batch one workgroup per CU
@@ -590,6 +592,7 @@ int ess_decode_step(ess_ctx* ctx, const ess_cache* cache, const ess_step_args* a
       ns0 = fewest > base ? fewest : base;
     }
   }
+  const bool wide = wide_merge(c, B, T, ns0 + ns1);
 
   // A fetch confined to a few XCDs (ESS_FETCH_XCD_MASK), with the kernels beside it kept off them (see ess_xcd),
   // pays when the fetch is long: the kernels beside it then run as if alone, but on the other XCDs only.  With few misses the lost
