@@ -91,7 +91,7 @@ struct ess_ctx {
   size_t ws_bytes;
   // overlap switch (ESS_FLAG_AUTO): per-sequence miss counts of the latest bookkeeping, written by the
   // kernel into pinned host memory and read by the host, without a synchronisation, at the next step
-  int32_t* host_miss;           // [max_batch] host address
+  int32_t* host_miss;           // [max_batch] host address; -1: not known yet
   int32_t* host_miss_dev;       // device alias of the same memory
   int32_t auto_threshold;       // mean misses per sequence above which the split-batch schedule is used
   bool auto_calibrated;         // threshold set by the caller: no further condition on the index-score time
