@@ -602,10 +602,12 @@ __global__ __launch_bounds__(NTH, 1) void k_attn_partial_tr(
       const bool move = tmax > m_ref + kLazyMax;
       if (__any(move)) {
         const float m_new = move ? tmax : m_ref;
-        alpha_pending = m_new == -__builtin_inff() ? 1.f : exp2f(m_ref - m_new);   // m_ref = -inf: 0, acc is 0 anyway
+        alpha_pending = m_ref == -__builtin_inff() ? 1.f : exp2f(m_ref - m_new);   // m_ref = -inf: nothing has been added up yet
         l_run *= alpha_pending;
+        // The accumulators are rescaled once the MFMAs of tile it-1 are through -- 1280 instructions, 2.5 us -- but not where
+        // every head that moves comes from -inf, as in the first tile of nearly every range.
+        scale_pending = __any(move && m_ref != -__builtin_inff());
         m_ref = m_new;
-        scale_pending = true;                  // the accumulators are rescaled once the MFMAs of tile it-1 are through
       }
       m_use = (m_ref == -__builtin_inff()) ? 0.f : m_ref;
       sprev = sacc;
