@@ -16,14 +16,15 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libess.so")
-SOURCES = ["ess_api.hip", "index_score.hip", "index_select.hip", "index_sample.hip", "topk.hip", "cache.hip", "sparse_mla.hip"]
+SOURCES = ["ess_api.hip", "index_score.hip", "index_select.hip", "index_sample.hip", "topk.hip", "cache.hip", "sparse_mla.hip", "sparse_mla_h32.hip"]
 FLAGS = ["-O3", "--offload-arch=gfx950", "-fPIC", "-std=c++17", "-I" + os.path.join(ROOT, "include"),
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wno-unused-command-line-argument"]
 
 
 # per-source additions: sparse_mla.hip keeps the results of compiler-generated MFMAs in VGPRs, because its
 # kernel holds the output accumulators in AGPRs that it names itself (see the comment there)
-EXTRA_FLAGS = {"sparse_mla.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form", "-std=c++20"]}
+EXTRA_FLAGS = {"sparse_mla.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form", "-std=c++20"],
+               "sparse_mla_h32.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form", "-std=c++20"]}
 
 
 def compile_flags(src: str) -> list:

@@ -166,6 +166,31 @@ int pick_splits_target(const ess_config& c, int B, int T, int cap, int target_wg
   return want < 1 ? 1 : want;
 }
 
+// Which kernel, and how many ranges a row, for lists of up to k entries with nothing beside them.  A workgroup of
+// k_attn_h32 has 32 heads: it costs little to start and end (7 us against 9.5), but brings an entry through LDS once per 32
+// heads (1.5 us per 64 entries, against 2.1 per 32 entries of 128 heads, 1.1 where half the workgroup's waves have no
+// heads), and with one range a row it needs no merge.  Times of both from the same terms: rounds of 256 workgroups, start
+// and end, tiles, and the merge.  Attention and merge of lists of 2048, 128 heads, us, k_attn_partial_tr / k_attn_h32: 1 row
+// 16.0 / 12.4, 4 rows 20.8 / 16.0, 8 rows 25.2 / 20.1, 16 rows 28.0 / 23.9, 32 rows 37.0 / 37.5, 46 quantised rows 50.4 /
+// 60.8; 64 heads: 13 rows 22.5 / 19.1, 40 rows 32.0 / 28.7, 128 quantised rows 79.0 / 66.0; 16 heads, 32 rows 25.8 / 20.8.
+struct attn_form { bool h32; int ns; };
+attn_form pick_form(const ess_ctx* ctx, int B, int T) {
+  const ess_config& c = ctx->cfg;
+  attn_form f{false, pick_splits(ctx, B, T, ESS_MAX_SPLITS)};
+  // (lists of one tile keep their fp16 partial result: of values that far apart, what lies 2^29 below a head's largest one
+  // comes out as zero there, which callers may have seen; 2 rows of 64 entries, 16 heads, 12.4 us, k_attn_h32 9.2)
+  if (c.topk > ESS_H32_LIST || c.topk <= 64) return f;
+  const int rows = B * T, waves = (c.attn_heads + 31) / 32;
+  auto merge_us = [&](int ns) { return ns * (0.05 + (double)rows * c.attn_heads * 2048.0 / 9e6) + 2.5; };
+  const int t32 = (c.topk + 31) / 32, t64 = (c.topk + 63) / 64;
+  double best = 0.95 * (((long)rows * f.ns + 255) / 256 * ((t32 + f.ns - 1) / f.ns * (waves > 2 ? 2.1 : 1.1) + 9.5) + merge_us(f.ns));
+  for (int ns = 1; ns <= t64 && ns <= ESS_MAX_SPLITS && (size_t)ns * rows <= ctx->part_cap; ++ns) {
+    const double us = ((long)rows * ns * waves + 255) / 256 * ((t64 + ns - 1) / ns * 1.5 + 7.0) + (ns > 1 ? merge_us(ns) : 0.0);
+    if (us < best) { best = us; f = attn_form{true, ns}; }
+  }
+  return f;
+}
+
 // most splits of Attn0 (the rest of a row's partial results is Attn1's): 16, more where the rows are few
 int attn0_cap(const ess_ctx* ctx, int B, int T) {
   const size_t n = ctx->part_cap / ((size_t)B * T);
@@ -219,6 +244,69 @@ int run_cache_step(ess_ctx* ctx, const ess_cache& cache, const int32_t* idx, int
   if (fill_ev) ESS_HIP(hipEventRecord(fill_ev[1], ctx->side));
   *fill_pending = true;
   return ESS_OK;
+}
+
+// Attention over whole lists, nothing beside it: partial results, or (one range a row) the rows themselves.
+int run_attn(ess_ctx* ctx, attn_form f, const void* q, const uint8_t* slot_pool, const int32_t* list, int B, int T, void* out, float* lse,
+             int32_t* zero_cnt, int n_zero, hipStream_t st) {
+  if (!f.h32) return ess_launch_attn_partial(ctx, q, slot_pool, list, nullptr, B, T, 0, f.ns, f.ns, st);
+  ess_attn_final fin{};
+  fin.out = static_cast<uint16_t*>(out);
+  fin.lse = lse;
+  fin.zero_cnt = zero_cnt;
+  fin.n_zero = zero_cnt ? n_zero : 0;
+  return ess_launch_attn_h32(ctx, q, slot_pool, list, nullptr, B, T, 0, f.ns, f.ns, st, 0, ess_xcd{nullptr, 0, nullptr, 0}, nullptr,
+                             f.ns == 1 ? &fin : nullptr);
+}
+int run_merge(ess_ctx* ctx, attn_form f, int B, int T, void* out, float* lse, int32_t* zero_cnt, int n_zero, hipStream_t st) {
+  if (f.h32 && f.ns == 1) return ESS_OK;
+  return ess_launch_attn_merge(ctx, B, T, f.ns, wide_merge(ctx->cfg, B, T, f.ns), out, lse, st, zero_cnt, n_zero);
+}
+
+// Attn0 and Attn1 of an offloaded step: ranges a row of each and their kernels.  Chosen from shapes alone, the same for
+// every schedule, so that every schedule sums in the same order and gives the same bits.
+//  * From 12 rows on Attn1, which follows the last fetch, is one range of k_attn_h32 that merges the row in its epilogue:
+//    no merge behind it, a quarter of the partial results.  Behind the fetch of 64 x 32K, about 200 misses a sequence,
+//    Attn1 and merge took 20 + 13 us, k_attn_h32 takes 19 (step 381 -> 365); half of 64 x 128K 20 + 6 + 10 against 20 (547 ->
+//    537).  A single range of 1500 misses takes what four ranges of k_attn_partial_tr and the merge took.
+//  * Fewer rows: ranges of both lists fill the chip in one round of k_attn_h32, then the merge (Attn0 in few enough ranges
+//    for an epilogue would be twice as long).
+//  * Lists longer than k_attn_h32 takes: k_attn_partial_tr and the merge throughout.
+struct attn_plan { bool h32, finish; int ns0, ns1; };
+attn_plan plan_offloaded(const ess_ctx* ctx, int B, int T) {
+  const ess_config& c = ctx->cfg;
+  const long rows = (long)B * T;
+  const int hg = (c.attn_heads + 127) / 128, n_hg = (c.attn_heads + 31) / 32;
+  attn_plan p{false, false, 1, 1};
+  if (c.topk <= ESS_H32_LIST && rows < 12) {
+    const int t64 = (c.topk + 63) / 64;
+    p.h32 = true;
+    p.ns1 = (int)(64 / (rows * n_hg) > 4 ? 4 : (64 / (rows * n_hg) < 1 ? 1 : 64 / (rows * n_hg)));
+    p.ns0 = (int)(192 / (rows * n_hg) < 1 ? 1 : 192 / (rows * n_hg));
+    if (p.ns0 > t64) p.ns0 = t64;
+    if (p.ns0 > ESS_MAX_SPLITS - p.ns1) p.ns0 = ESS_MAX_SPLITS - p.ns1;
+    const int longest = (t64 + p.ns0 - 1) / p.ns0;       // no ranges that do not shorten the longest one
+    p.ns0 = (t64 + longest - 1) / longest;
+    return p;
+  }
+  p.finish = c.topk <= ESS_H32_LIST;
+  const int room = attn0_cap(ctx, B, T), cap = p.finish && room > ESS_FINAL_PREV ? ESS_FINAL_PREV : room;
+  p.ns0 = pick_splits_target(c, B, T, cap, ESS_ATTN0_WGS);
+  // Attn1 works on the short miss lists: without a kernel that finishes rows, as many splits as give the whole batch one
+  // workgroup per CU
+  p.ns1 = p.finish ? 1 : pick_splits_target(c, B, T, ESS_ROW_SPLITS - 16, 256);
+  // Attn0 has time to spare only beside a long fetch.  With few sequences the fetch is short (120 misses a sequence are
+  // assumed here: the choice must not depend on the misses, or results would), and Attn0 gets more ranges, as many as the
+  // CUs a confined fetch leaves (192) hold in one round, and none that do not shorten the longest range.  Attn1 keeps its
+  // ranges: with many misses it is what follows the fetch.
+  const int tiles = (c.topk + ESS_ATTN_TILE - 1) / ESS_ATTN_TILE, base = p.ns0;
+  const double fetch_us = B * 120.0 * c.row_stride / 50e3;
+  while (p.ns0 < cap && p.ns0 < tiles && ((tiles + p.ns0 - 1) / p.ns0 + 5.5) * 2.2 > fetch_us && rows * hg * (p.ns0 + 1) <= 192) ++p.ns0;
+  if (p.ns0 > base) {
+    const int longest = (tiles + p.ns0 - 1) / p.ns0, fewest = (tiles + longest - 1) / longest;
+    p.ns0 = fewest > base ? fewest : base;
+  }
+  return p;
 }
 
 }  // namespace
@@ -491,10 +579,9 @@ int ess_sparse_mla_decode(ess_ctx* ctx, const void* q_bf16, const uint8_t* slot_
   if (!aligned16(q_bf16) || !aligned16(slot_pool) || !aligned16(out_bf16))
     return ess_fail(ESS_ERR_INVALID_ARG, "q, slot_pool and out must be 16-byte aligned");
   hipStream_t st = static_cast<hipStream_t>(stream);
-  const int ns = pick_splits(ctx, B, T, ESS_MAX_SPLITS);
-  rc = ess_launch_attn_partial(ctx, q_bf16, slot_pool, slot_idx, nullptr, B, T, 0, ns, ns, st);
-  if (rc != ESS_OK) return rc;
-  return ess_launch_attn_merge(ctx, B, T, ns, wide_merge(ctx->cfg, B, T, ns), out_bf16, lse, st);
+  const attn_form form = pick_form(ctx, B, T);
+  rc = run_attn(ctx, form, q_bf16, slot_pool, slot_idx, B, T, out_bf16, lse, nullptr, 0, st);
+  return rc != ESS_OK ? rc : run_merge(ctx, form, B, T, out_bf16, lse, nullptr, 0, st);
 }
 
 int ess_decode_step(ess_ctx* ctx, const ess_cache* cache, const ess_step_args* a, void* stream) {
@@ -569,29 +656,9 @@ int ess_decode_step(ess_ctx* ctx, const ess_cache* cache, const ess_step_args* a
   ctx->last_overlap = (c.flags & ESS_FLAG_SERIAL) ? 2 : (dba ? 1 : 0);
   const bool da_swap = offloaded && !dba && !(c.flags & ESS_FLAG_SERIAL);
   const int nh = dba ? 2 : 1;
-  // attention splits: chosen from the whole batch and the same for both halves, so that every schedule
-  // sums in the same order and gives the same bits
-  int ns0 = offloaded ? pick_splits_target(c, B, T, attn0_cap(ctx, B, T), ESS_ATTN0_WGS) : pick_splits(ctx, B, T, ESS_MAX_SPLITS);
-  int ns1 = 0;
-  if (offloaded) {
-    // Attn1 works on the short miss lists: as many splits as give the whole batch one workgroup per CU
-    ns1 = pick_splits_target(c, B, T, ESS_ROW_SPLITS - 16, 256);
-    // Attn0 has time to spare only beside a long fetch.  With few sequences the fetch is short (120 misses a sequence are
-    // assumed here: the choice must not depend on the misses, or results would), and Attn0 gets more ranges, as many as the
-    // CUs a confined fetch leaves (192) hold in one round, and none that do not shorten the longest range.  Attn1 keeps its
-    // ranges: with many misses it is what follows the fetch.  Ranges of Attn0 + Attn1 a row, us a step: 23 x 48K, two tokens,
-    // quantised, 30 / 480 misses: 3 + 4 152 / 278, 4 + 4 144 / 278, 4 + 1 144 / 296; 13 x 32K quantised, 30 / 200 / 900:
-    // 10 + 4 93 / 126 / 264, 13 + 4 90 / 127 / 265, 15 + 4 90 / 133 / 265, 17 + 2 90 / 137 / 278; 5 x 64K, 30 / 1500:
-    // 26 + 4 78 / 280, 32 + 4 77 / 280, 49 + 2 78 / 299.
-    const long rows = (long)B * T * ((c.attn_heads + 127) / 128);
-    const int tiles = (c.topk + ESS_ATTN_TILE - 1) / ESS_ATTN_TILE, cap = attn0_cap(ctx, B, T), base = ns0;
-    const double fetch_us = B * 120.0 * c.row_stride / 50e3;
-    while (ns0 < cap && ns0 < tiles && ((tiles + ns0 - 1) / ns0 + 5.5) * 2.2 > fetch_us && rows * (ns0 + 1) <= 192) ++ns0;
-    if (ns0 > base) {
-      const int longest = (tiles + ns0 - 1) / ns0, fewest = (tiles + longest - 1) / longest;
-      ns0 = fewest > base ? fewest : base;
-    }
-  }
+  // attention of an offloaded step: chosen from the whole batch and the same for both halves
+  const attn_plan plan = offloaded ? plan_offloaded(ctx, B, T) : attn_plan{false, false, 1, 0};
+  const int ns0 = plan.ns0, ns1 = plan.ns1, pitch = ns0 + ns1;
   const bool wide = wide_merge(c, B, T, ns0 + ns1);
 
   // A fetch confined to a few XCDs (ESS_FETCH_XCD_MASK), with the kernels beside it kept off them (see ess_xcd),
@@ -614,7 +681,7 @@ int ess_decode_step(ess_ctx* ctx, const ess_cache* cache, const ess_step_args* a
     const double idx_half = 0.5 * B * (double)c.max_ctx * (c.idx_dim + 4.0 * T) / 5.3e6;
     // Attn0 on the XCDs the fetch leaves free (one workgroup per CU): rounds x (tiles x time per tile + start and end)
     const int work_cus = 32 * (8 - __builtin_popcount(ESS_FETCH_XCD_MASK & 0xffu));
-    const int hg = (c.attn_heads + 127) / 128;
+    const int hg = plan.h32 ? (c.attn_heads + 31) / 32 : (c.attn_heads + 127) / 128;
     const double hits = c.topk - (mean_miss / T < c.topk ? mean_miss / T : c.topk);
     const double tiles_item = (hits / ESS_ATTN_TILE) / ns0 + 1.0;
     const double rounds = (double)((long)B * T * hg * ns0 + work_cus - 1) / work_cus;
@@ -629,7 +696,8 @@ int ess_decode_step(ess_ctx* ctx, const ess_cache* cache, const ess_step_args* a
     // fetch confined against both: 128 x 32K quantised 240 misses 656 against 638, bf16 120 misses 511 against 531, 240 867
     // against 839; 128 x 128K, two tokens, quantised, 289 misses 962 against 980, 388 1025 against 1024, 600 1442 against
     // 1404.)
-    const double attn5 = (double)(long)rounds * (tiles_item * 2.6 + 14.0);
+    // (k_attn_h32, fewer than 12 rows: 1.5 us per 64 entries of 32 heads; 16 puts the boundary where it was measured)
+    const double attn5 = (double)(long)rounds * (plan.h32 ? hits / 64 / ns0 * 1.5 + 16.0 : tiles_item * 2.6 + 14.0);
     // (one work counter serves one index-score launch: two query tokens at most)
     confine = dba && T <= 2 && fetch_half >= 1.5 * idx_half;
     confine2 = confine && attn5 + 40.0 <= 1.15 * fetch_half;        // + Attn1 and merge of the first half
@@ -752,17 +820,43 @@ int ess_decode_step(ess_ctx* ctx, const ess_cache* cache, const ess_step_args* a
     // nothing offloaded: slot == position, attention straight over the selection
     const int32_t* used = a->topk_override ? a->topk_override : a->idx_out;
     ESS_BEGIN(3);
-    rc = ess_launch_attn_partial(ctx, a->q_bf16, cache->slot_pool, used, nullptr, B, T, 0, ns0, ns0 + ns1, st);
+    const attn_form form = pick_form(ctx, B, T);
+    rc = run_attn(ctx, form, a->q_bf16, cache->slot_pool, used, B, T, a->out_bf16, a->lse, a->miss_count, B, st);   // no misses: the counts are zero
     if (rc != ESS_OK) return rc;
     ESS_END(3);
     ESS_BEGIN(4);
-    rc = ess_launch_attn_merge(ctx, B, T, ns0, wide, a->out_bf16, a->lse, st, a->miss_count, B);   // no misses: the counts are zero
+    rc = run_merge(ctx, form, B, T, a->out_bf16, a->lse, a->miss_count, B, st);
     if (rc != ESS_OK) return rc;
     ESS_END(4);
     return ESS_OK;
   }
 
   const uint16_t* q16 = static_cast<const uint16_t*>(a->q_bf16);
+  // Attn0 (over entries resident before the step) and Attn1 (over fetched ones, which may finish the rows) of the
+  // sub-batch [b0, b0 + Bh); check: the launch is the step's last
+  const ess_xcd anywhere{nullptr, 0, nullptr, 0};
+  auto attn0 = [&](int b0, int Bh, hipStream_t on, ess_xcd x, hipEvent_t done) {
+    const size_t bt0 = (size_t)b0 * T;
+    const uint16_t* qh = q16 + bt0 * c.attn_heads * ESS_ROW_DIM;
+    const uint8_t* pool = cache->slot_pool + (size_t)b0 * c.slots_per_seq * c.row_stride;
+    return plan.h32 ? ess_launch_attn_h32(ctx, qh, pool, ctx->hit_list + bt0 * k, ctx->n_hit + bt0, Bh, T, 0, ns0, pitch, on, b0, x, done)
+                    : ess_launch_attn_partial(ctx, qh, pool, ctx->hit_list + bt0 * k, ctx->n_hit + bt0, Bh, T, 0, ns0, pitch, on, b0, x, done);
+  };
+  auto attn1 = [&](int b0, int Bh, hipStream_t on, ess_xcd x, hipEvent_t done, const ess_ticket_check* check) {
+    const size_t bt0 = (size_t)b0 * T;
+    const uint16_t* qh = q16 + bt0 * c.attn_heads * ESS_ROW_DIM;
+    const uint8_t* pool = cache->slot_pool + (size_t)b0 * c.slots_per_seq * c.row_stride;
+    if (!plan.h32 && !plan.finish)
+      return ess_launch_attn_partial(ctx, qh, pool, ctx->miss_list + bt0 * k, ctx->n_miss + bt0, Bh, T, ns0, ns1, pitch, on, b0, x, done);
+    ess_attn_final fin{};
+    if (plan.finish) {
+      fin.out = static_cast<uint16_t*>(a->out_bf16);
+      fin.lse = a->lse;
+      fin.n_prev = ns0;
+      if (check) fin.chk = *check;
+    }
+    return ess_launch_attn_h32(ctx, qh, pool, ctx->miss_list + bt0 * k, ctx->n_miss + bt0, Bh, T, ns0, ns1, pitch, on, b0, x, done, &fin);
+  };
   if (da_swap) {
     // DA schedule.  The fetch is the critical path, so it stays on the caller's stream, right behind the
     // bookkeeping and right before Attn1; Attn0, which has time to spare, goes to the side stream.  A
@@ -775,12 +869,18 @@ int ess_decode_step(ess_ctx* ctx, const ess_cache* cache, const ess_step_args* a
       if (rc != ESS_OK) return rc;
       ESS_END(5);
       ESS_BEGIN(3);
-      rc = ess_launch_attn_partial(ctx, q16, cache->slot_pool, ctx->hit_list, ctx->n_hit, B, T, 0, ns0, ns0 + ns1, st, 0,
-                                   ess_xcd{nullptr, 0, nullptr, 0}, nullptr, ctx->miss_list, ctx->n_miss, ns1);
+      if (plan.finish)
+        rc = attn0(0, B, st, anywhere, nullptr);
+      else if (plan.h32)
+        rc = ess_launch_attn_h32(ctx, q16, cache->slot_pool, ctx->hit_list, ctx->n_hit, B, T, 0, ns0, pitch, st, 0, anywhere, nullptr, nullptr,
+                                 ctx->miss_list, ctx->n_miss, ns1);
+      else
+        rc = ess_launch_attn_partial(ctx, q16, cache->slot_pool, ctx->hit_list, ctx->n_hit, B, T, 0, ns0, pitch, st, 0, anywhere, nullptr,
+                                     ctx->miss_list, ctx->n_miss, ns1);
       if (rc != ESS_OK) return rc;
       ESS_END(3);
       ESS_BEGIN(4);
-      rc = ess_launch_attn_merge(ctx, B, T, ns0 + ns1, wide, a->out_bf16, a->lse, st);
+      rc = plan.finish ? attn1(0, B, st, anywhere, nullptr, nullptr) : ess_launch_attn_merge(ctx, B, T, pitch, wide, a->out_bf16, a->lse, st);
       if (rc != ESS_OK) return rc;
       ESS_END(4);
       return ESS_OK;
@@ -788,8 +888,7 @@ int ess_decode_step(ess_ctx* ctx, const ess_cache* cache, const ess_step_args* a
     ESS_HIP(hipStreamWaitEvent(ctx->side, ctx->ev_book[0], 0));
     hipEvent_t* aev = (pev && ((ctx->prof_mask >> 3) & 1u)) ? pev + ESS_PROF_MAIN : nullptr;
     if (aev) ESS_HIP(hipEventRecord(aev[0], ctx->side));
-    rc = ess_launch_attn_partial(ctx, q16, cache->slot_pool, ctx->hit_list, ctx->n_hit, B, T, 0, ns0, ns0 + ns1, ctx->side, 0,
-                                 confine_da ? tk_xcd(ESS_TKT_ATTN0) : ess_xcd{nullptr, 0, nullptr, 0}, ctx->ev_fill[0]);      // ev_fill[0] here: Attn0 done
+    rc = attn0(0, B, ctx->side, confine_da ? tk_xcd(ESS_TKT_ATTN0) : anywhere, ctx->ev_fill[0]);      // ev_fill[0] here: Attn0 done
     if (rc != ESS_OK) return rc;
     if (aev) {
       ESS_HIP(hipEventRecord(aev[1], ctx->side));
@@ -802,11 +901,13 @@ int ess_decode_step(ess_ctx* ctx, const ess_cache* cache, const ess_step_args* a
     ESS_END(5);
     ESS_BEGIN(4);
     ESS_HIP(hipStreamWaitEvent(st, ctx->ev_fill[0], 0));
-    rc = ess_launch_attn_partial(ctx, q16, cache->slot_pool, ctx->miss_list, ctx->n_miss, B, T, ns0, ns1, ns0 + ns1, st, 0);
-    if (rc != ESS_OK) return rc;
     chk.need[ESS_TKT_ATTN0] += check_extra;
-    rc = ess_launch_attn_merge(ctx, B, T, ns0 + ns1, wide, a->out_bf16, a->lse, st, nullptr, 0, 0, confine_da ? &chk : nullptr);
+    rc = attn1(0, B, st, anywhere, nullptr, confine_da ? &chk : nullptr);
     if (rc != ESS_OK) return rc;
+    if (!plan.finish) {
+      rc = ess_launch_attn_merge(ctx, B, T, pitch, wide, a->out_bf16, a->lse, st, nullptr, 0, 0, confine_da ? &chk : nullptr);
+      if (rc != ESS_OK) return rc;
+    }
     ESS_END(4);
     return ESS_OK;
   }
@@ -831,20 +932,20 @@ int ess_decode_step(ess_ctx* ctx, const ess_cache* cache, const ess_step_args* a
     if (aev) ESS_HIP(hipEventRecord(aev[0], ctx->side));
     // Attn0 of the whole batch in one launch (behind the first fetch it could not start much earlier
     // anyway): one workgroup per CU, the same splits as in the other schedules
-    rc = ess_launch_attn_partial(ctx, q16, cache->slot_pool, ctx->hit_list, ctx->n_hit, B, T, 0, ns0, ns0 + ns1, ctx->side, 0,
-                                 confine2 ? tk_xcd(ESS_TKT_ATTN0) : ess_xcd{nullptr, 0, nullptr, 0});
+    rc = attn0(0, B, ctx->side, confine2 ? tk_xcd(ESS_TKT_ATTN0) : anywhere, nullptr);
     if (rc != ESS_OK) return rc;
     if (aev) {
       ESS_HIP(hipEventRecord(aev[1], ctx->side));
       ESS_HIP(hipEventRecord(aev[2], ctx->side));
     }
-    rc = ess_launch_attn_partial(ctx, q16, c0.slot_pool, ctx->miss_list, ctx->n_miss, hB[0], T, ns0, ns1, ns0 + ns1, ctx->side, hb0[0],
-                                 confine2 ? tk_xcd(ESS_TKT_ATTN1) : ess_xcd{nullptr, 0, nullptr, 0});
+    // ev_fill[1] here: everything on the side stream done.  Each half is merged on the stream its Attn1 ran on: only half
+    // a merge, if any, is left behind the last fetch.
+    rc = attn1(hb0[0], hB[0], ctx->side, confine2 ? tk_xcd(ESS_TKT_ATTN1) : anywhere, plan.finish ? ctx->ev_fill[1] : nullptr, nullptr);
     if (rc != ESS_OK) return rc;
-    // each half is merged on the stream its Attn1 ran on: only half a merge is left behind the last fetch
-    rc = ess_launch_attn_merge(ctx, hB[0], T, ns0 + ns1, wide, a->out_bf16, a->lse, ctx->side, nullptr, 0, hb0[0], nullptr,
-                               ctx->ev_fill[1]);                     // ev_fill[1] here: everything on the side stream done
-    if (rc != ESS_OK) return rc;
+    if (!plan.finish) {
+      rc = ess_launch_attn_merge(ctx, hB[0], T, pitch, wide, a->out_bf16, a->lse, ctx->side, nullptr, 0, hb0[0], nullptr, ctx->ev_fill[1]);
+      if (rc != ESS_OK) return rc;
+    }
     if (aev) {
       ESS_HIP(hipEventRecord(aev[3], ctx->side));
       ctx->prof_nfill[pslot] = 3;
@@ -852,40 +953,31 @@ int ess_decode_step(ess_ctx* ctx, const ess_cache* cache, const ess_step_args* a
       ctx->prof_pair_stage[(size_t)pslot * ESS_PROF_FILL + 2] = 4;
     }
     ESS_BEGIN(4);
-    rc = ess_launch_attn_partial(ctx, q16 + bt1 * c.attn_heads * ESS_ROW_DIM, c1.slot_pool, ctx->miss_list + bt1 * k,
-                                 ctx->n_miss + bt1, hB[1], T, ns0, ns1, ns0 + ns1, st, hb0[1]);
-    if (rc != ESS_OK) return rc;
-    ESS_HIP(hipStreamWaitEvent(st, ctx->ev_fill[1], 0));          // Attn0 of the second half ran on the side stream
+    // Attn0 of the second half ran on the side stream: waited for where its results are read
     chk.need[ESS_TKT_INDEX] += check_extra;
-    rc = ess_launch_attn_merge(ctx, hB[1], T, ns0 + ns1, wide, a->out_bf16, a->lse, st, nullptr, 0, hb0[1], confine ? &chk : nullptr);
+    if (plan.finish) ESS_HIP(hipStreamWaitEvent(st, ctx->ev_fill[1], 0));
+    rc = attn1(hb0[1], hB[1], st, anywhere, nullptr, confine ? &chk : nullptr);
     if (rc != ESS_OK) return rc;
+    if (!plan.finish) {
+      ESS_HIP(hipStreamWaitEvent(st, ctx->ev_fill[1], 0));
+      rc = ess_launch_attn_merge(ctx, hB[1], T, pitch, wide, a->out_bf16, a->lse, st, nullptr, 0, hb0[1], confine ? &chk : nullptr);
+      if (rc != ESS_OK) return rc;
+    }
     ESS_END(4);
     return ESS_OK;
   }
 
   // stage 4: Attn0 over resident entries while the fetches run, Attn1 over fetched ones, merge
   ESS_BEGIN(3);
-  for (int h = 0; h < nh; ++h) {
-    const int b0 = hb0[h], Bh = hB[h];
-    const size_t bt0 = (size_t)b0 * T;
-    const ess_cache ch = shift_cache(c, *cache, b0);
-    rc = ess_launch_attn_partial(ctx, q16 + bt0 * c.attn_heads * ESS_ROW_DIM, ch.slot_pool, ctx->hit_list + bt0 * k,
-                                 ctx->n_hit + bt0, Bh, T, 0, ns0, ns0 + ns1, st, b0);
-    if (rc != ESS_OK) return rc;
-  }
+  for (int h = 0; h < nh; ++h)
+    if ((rc = attn0(hb0[h], hB[h], st, anywhere, nullptr)) != ESS_OK) return rc;
   ESS_END(3);
   ESS_BEGIN(4);
   for (int h = 0; h < nh; ++h) {
-    const int b0 = hb0[h], Bh = hB[h];
-    const size_t bt0 = (size_t)b0 * T;
-    const ess_cache ch = shift_cache(c, *cache, b0);
     if (pending[h]) ESS_HIP(hipStreamWaitEvent(st, ctx->ev_fill[h], 0));
-    rc = ess_launch_attn_partial(ctx, q16 + bt0 * c.attn_heads * ESS_ROW_DIM, ch.slot_pool, ctx->miss_list + bt0 * k,
-                                 ctx->n_miss + bt0, Bh, T, ns0, ns1, ns0 + ns1, st, b0);
-    if (rc != ESS_OK) return rc;
+    if ((rc = attn1(hb0[h], hB[h], st, anywhere, nullptr, nullptr)) != ESS_OK) return rc;
   }
-  rc = ess_launch_attn_merge(ctx, B, T, ns0 + ns1, wide, a->out_bf16, a->lse, st);
-  if (rc != ESS_OK) return rc;
+  if (!plan.finish && (rc = ess_launch_attn_merge(ctx, B, T, pitch, wide, a->out_bf16, a->lse, st)) != ESS_OK) return rc;
   ESS_END(4);
   return ESS_OK;
 #undef ESS_RECORD

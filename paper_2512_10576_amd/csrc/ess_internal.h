@@ -129,7 +129,29 @@ struct ess_ticket_check {
   int32_t* flag;
   uint32_t need[ESS_N_TICKETS];
 };
+// An attention launch that finishes its rows: it merges its own result with the first n_prev partial results of each row
+// and writes output and log-sum-exp.  out null: it writes a partial result.
+#define ESS_FINAL_PREV 8
+#define ESS_H32_LIST 2048        // longest list k_attn_h32 takes
+struct ess_attn_final {
+  uint16_t* out;                // bf16 [B,T,H,512] of the whole batch
+  float* lse;                   // [B,T,H], may be null
+  int n_prev;                   // at most ESS_FINAL_PREV
+  int32_t* zero_cnt;            // n_zero counters that the launch clears (for steps that have no other kernel to do it in)
+  int n_zero;
+  ess_ticket_check chk;         // the step's last launch
+};
 #ifdef __HIPCC__
+__device__ __forceinline__ void ess_check_tickets(const ess_ticket_check& chk) {
+  bool short_of = false;
+#pragma unroll
+  for (int i = 0; i < ESS_N_TICKETS; ++i) {
+    uint32_t handed = chk.tickets[i * ESS_TICKET_WORDS + ESS_TK_WORK];   // the launch's counter, or its per-XCD counters
+    for (int c = 0; c < 8; ++c) handed += chk.tickets[i * ESS_TICKET_WORDS + ESS_TK_CLASS + ESS_TK_STRIDE * c];
+    short_of |= chk.need[i] != 0 && handed < chk.need[i];
+  }
+  if (short_of) *chk.flag = 1;
+}
 // Non-temporal 16-byte store.  The large outputs of a step (scores, fetched rows, partial attention results, the
 // attention output) are written this way: lines written with ordinary stores stay in the memory-side cache as
 // modified lines until something displaces them, and that something is the next index-score launch, whose key
@@ -288,6 +310,12 @@ int ess_launch_attn_partial(ess_ctx* ctx, const void* q, const uint8_t* slot_poo
                             ess_xcd xcd = ess_xcd{nullptr, 0, nullptr, 0}, hipEvent_t done = nullptr,
                             // a second list in the same launch, its partial results behind those of the first
                             const int32_t* list_b = nullptr, const int32_t* n_list_b = nullptr, int nsplit_b = 0);
+// the same with 32 heads per workgroup (sparse_mla_h32.hip); final (one range per row only): the rows are finished
+int ess_launch_attn_h32(ess_ctx* ctx, const void* q, const uint8_t* slot_pool, const int32_t* list, const int32_t* n_list, int B, int T,
+                        int split0, int nsplit, int pitch, hipStream_t st, int b0 = 0, ess_xcd xcd = ess_xcd{nullptr, 0, nullptr, 0},
+                        hipEvent_t done = nullptr, const ess_attn_final* final = nullptr,
+                        const int32_t* list_b = nullptr, const int32_t* n_list_b = nullptr, int nsplit_b = 0);
+int ess_init_attn_h32();
 int ess_attn_min_splits(const ess_config& c);   // fewest splits a list of k entries may be cut into
 // wide: four waves per row (small batches; the same for every sub-batch of a call, it sets the order of the sums);
 // zero_cnt (may be NULL): n_zero int32 counters that the merge kernel also clears; b0 = first sequence of the
