@@ -27,6 +27,7 @@
 // one wave per 1152- or 656-byte entry, many entries in flight.
 #include "ess_internal.h"
 #include "select_common.h"
+#include "fetch.h"
 
 namespace {
 
@@ -494,11 +495,7 @@ __global__ __launch_bounds__(BT) void k_bookkeeping(
 constexpr int FILL_WPB = 8;                                 // waves per workgroup
 constexpr int FILL_MAX_B = 4096;
 
-__global__ __launch_bounds__(FILL_WPB * 64) void k_fill(const uint8_t* __restrict__ host_pool, uint8_t* __restrict__ slot_pool,
-                                               const int32_t* __restrict__ fill_tok,
-                                               const int32_t* __restrict__ fill_slot, int fill_cap,
-                                               const int32_t* __restrict__ miss_cnt, int B, int Lmax, int S,
-                                               int row_stride, uint32_t only_xcds, uint32_t* __restrict__ ticket) {
+__global__ __launch_bounds__(FILL_WPB * 64) void k_fill(const ess_fetch f, uint32_t only_xcds, uint32_t* __restrict__ ticket) {
   // confined fetch: only workgroups on the XCDs in `only_xcds` work (or, should none sit there, the last one to
   // arrive), entries are handed out through `ticket`
   __shared__ int s_join;
@@ -506,50 +503,25 @@ __global__ __launch_bounds__(FILL_WPB * 64) void k_fill(const uint8_t* __restric
   extern __shared__ int32_t pref[];                          // [B + 1] pref[b] = entries of sequences < b (kept small:
                                                              // the kernel must fit beside workgroups that fill the LDS)
   const int tid = threadIdx.x, lane = tid & 63;
-  // exclusive prefix sum of the per-sequence miss counts, by the first wave
-  if (tid < 64) {
-    int run = 0;
-    for (int b0 = 0; b0 <= B; b0 += 64) {
-      const int b = b0 + lane;
-      const int cnt = b < B ? min(miss_cnt[b], fill_cap) : 0;
-      const int inc = (int)wave_incl_scan((uint32_t)cnt, lane);
-      if (b <= B) pref[b] = run + inc - cnt;
-      run += __shfl(inc, 63, 64);
-    }
-  }
-  __syncthreads();
-  const int M = pref[B];
   const int gw = blockIdx.x * FILL_WPB + (tid >> 6);         // wave index in the grid
   const int FILL_WAVES = gridDim.x * FILL_WPB;
-  const int chunks = row_stride >> 4;                        // <= 128 for the supported entry sizes
+  if (!only_xcds) {
+    ess_fill::entries<2>(f, pref, gw, FILL_WAVES);
+    return;
+  }
+  const int M = ess_fill::prefix(f.miss_cnt, f.fill_cap, f.B, pref);
+  const int chunks = f.row_stride >> 4;                      // <= 128 for the supported entry sizes
   const int c0 = lane, c1 = lane + 64;
-  auto locate = [&](int r, const uint4*& src, uint4*& dst) { // r-th entry of the flattened list
-    int lo = 0, hi = B;                                      // largest b with pref[b] <= r
-    while (hi - lo > 1) {
-      const int mid = (lo + hi) >> 1;
-      if (pref[mid] <= r) lo = mid; else hi = mid;
-    }
-    const int i = r - pref[lo];
-    const int tok = fill_tok[(size_t)lo * fill_cap + i], slot = fill_slot[(size_t)lo * fill_cap + i];
-    src = reinterpret_cast<const uint4*>(host_pool + ((size_t)lo * Lmax + tok) * row_stride);
-    dst = reinterpret_cast<uint4*>(slot_pool + ((size_t)lo * S + slot) * row_stride);
-  };
-  for (int r = gw;; r += 2 * FILL_WAVES) {                   // two entries of this wave in flight
-    int rB;
-    if (only_xcds) {                                         // entries r, r + 1 by ticket
-      uint32_t tk = 0;
-      if (lane == 0) tk = atomicAdd(ticket, 2u);
-      r = (int)__shfl(tk, 0, 64);
-      rB = r + 1;
-    } else {
-      rB = r + FILL_WAVES;
-    }
+  for (;;) {                                                 // entries r, r + 1 by ticket: two of this wave in flight
+    uint32_t tk = 0;
+    if (lane == 0) tk = atomicAdd(ticket, 2u);
+    const int r = (int)__shfl(tk, 0, 64);
     if (r >= M) break;
-    const bool two = rB < M;
+    const bool two = r + 1 < M;
     const uint4 *srcA, *srcB;
     uint4 *dstA, *dstB;
-    locate(r, srcA, dstA);
-    locate(two ? rB : r, srcB, dstB);
+    ess_fill::locate(f, pref, r, srcA, dstA);
+    ess_fill::locate(f, pref, two ? r + 1 : r, srcB, dstB);
     uint4 a0 = make_uint4(0, 0, 0, 0), a1 = a0, b0 = a0, b1 = a0;
     if (c0 < chunks) a0 = srcA[c0];
     if (c1 < chunks) a1 = srcA[c1];
@@ -868,6 +840,13 @@ int ess_init_cache_kernels(const ess_config& c, bool* fits) {
   return ESS_OK;
 }
 
+ess_fetch ess_fetch_of(ess_ctx* ctx, const ess_cache& cache, int B, int b0, int wgs) {
+  const ess_config& c = ctx->cfg;
+  const int cap = c.max_q_tokens * c.topk;
+  return ess_fetch{cache.host_pool_dev, cache.slot_pool, ctx->fill_tok + (size_t)b0 * cap, ctx->fill_slot + (size_t)b0 * cap, ctx->miss_cnt + b0,
+                   cap, B, c.max_ctx, c.slots_per_seq, c.row_stride, wgs};
+}
+
 int ess_launch_fill(ess_ctx* ctx, const ess_cache& cache, int B, hipStream_t st, int b0, int wgs, uint32_t only_xcds,
                     uint32_t* ticket, hipEvent_t done) {
   wgs = wgs < 1 ? 1 : (wgs > 256 ? 256 : wgs);
@@ -877,11 +856,8 @@ int ess_launch_fill(ess_ctx* ctx, const ess_cache& cache, int B, hipStream_t st,
     wgs = (wgs + on - 1) / on * 8;
     if (ctx->ticket_grid > 0) wgs = ctx->ticket_grid;
   }
-  const ess_config& c = ctx->cfg;
-  const int cap = c.max_q_tokens * c.topk;
-  ESS_HIP(ess_launch_done(done, &k_fill, dim3(wgs), dim3(FILL_WPB * 64), (size_t)(B + 1) * sizeof(int32_t), st, cache.host_pool_dev, cache.slot_pool,
-                     ctx->fill_tok + (size_t)b0 * cap, ctx->fill_slot + (size_t)b0 * cap, cap, ctx->miss_cnt + b0, B,
-                     c.max_ctx, c.slots_per_seq, c.row_stride, only_xcds, ticket));
+  ESS_HIP(ess_launch_done(done, &k_fill, dim3(wgs), dim3(FILL_WPB * 64), (size_t)(B + 1) * sizeof(int32_t), st,
+                          ess_fetch_of(ctx, cache, B, b0, wgs), only_xcds, ticket));
   return ESS_OK;
 }
 

@@ -708,7 +708,12 @@ int ess_decode_step(ess_ctx* ctx, const ess_cache* cache, const ess_step_args* a
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     da_short = hipStreamIsCapturing(st, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
   }
-  ctx->last_confined = confine_da ? 1 : (confine2 ? 2 : (confine ? 1 : 0));
+  // Attn0 and the fetch in one launch (see ess_fetch), nothing on the side stream: no event behind the bookkeeping (4 us until
+  // what follows it starts), no wait for the other stream in front of Attn1 (6 us, 11 where Attn0 ends last), and a short
+  // fetch runs beside Attn0 instead of in front of it.  Not for launches of a given size (test hook) or with the two timed apart.
+  const bool carried = mean_miss >= 0 && da_swap && ctx->xcds_even && (confine_da || da_short) && ctx->ticket_grid == 0 &&
+                       !(pev && (ctx->prof_mask & 0x28u));
+  ctx->last_confined = carried || confine_da ? 1 : (confine2 ? 2 : (confine ? 1 : 0));
   const uint32_t check_extra = ctx->last_confined ? ctx->check_extra : 0u;   // test hook, one confined step
   if (ctx->last_confined) ctx->check_extra = 0;
   const uint32_t mask2 = ESS_FETCH_XCD_MASK;
@@ -803,9 +808,9 @@ int ess_decode_step(ess_ctx* ctx, const ess_cache* cache, const ess_step_args* a
     if (da_swap || (dba && h == 1)) {      // bookkeeping only; the fetch follows on this stream further down
       rc = ess_launch_bookkeeping(ctx, ch, used, Bh, T, c.topk, a->step, ctx->slot_idx_ws + bt0 * k,
                                   a->miss_count ? a->miss_count + b0 : nullptr, st, b0, h == 0, xcd_of(ESS_TKT_BOOK),
-                                  (confine2 || (da_swap && confine_da)) ? ctx->tickets + (da_swap ? 0 : ESS_TKT_FETCH2) * ESS_TICKET_WORDS : nullptr,
+                                  (confine2 || (da_swap && confine_da && !carried)) ? ctx->tickets + (da_swap ? 0 : ESS_TKT_FETCH2) * ESS_TICKET_WORDS : nullptr,
                                   da_swap ? ESS_N_TICKETS : ESS_N_TICKETS - ESS_TKT_FETCH2,
-                                  da_short ? nullptr : ctx->ev_book[h]);
+                                  da_short || carried ? nullptr : ctx->ev_book[h]);
       if (rc != ESS_OK) return rc;
     } else {
       rc = run_cache_step(ctx, ch, used, Bh, T, c.topk, a->step, ctx->slot_idx_ws + bt0 * k,
@@ -835,12 +840,12 @@ int ess_decode_step(ess_ctx* ctx, const ess_cache* cache, const ess_step_args* a
   // Attn0 (over entries resident before the step) and Attn1 (over fetched ones, which may finish the rows) of the
   // sub-batch [b0, b0 + Bh); check: the launch is the step's last
   const ess_xcd anywhere{nullptr, 0, nullptr, 0};
-  auto attn0 = [&](int b0, int Bh, hipStream_t on, ess_xcd x, hipEvent_t done) {
+  auto attn0 = [&](int b0, int Bh, hipStream_t on, ess_xcd x, hipEvent_t done, const ess_fetch* fetch = nullptr) {
     const size_t bt0 = (size_t)b0 * T;
     const uint16_t* qh = q16 + bt0 * c.attn_heads * ESS_ROW_DIM;
     const uint8_t* pool = cache->slot_pool + (size_t)b0 * c.slots_per_seq * c.row_stride;
-    return plan.h32 ? ess_launch_attn_h32(ctx, qh, pool, ctx->hit_list + bt0 * k, ctx->n_hit + bt0, Bh, T, 0, ns0, pitch, on, b0, x, done)
-                    : ess_launch_attn_partial(ctx, qh, pool, ctx->hit_list + bt0 * k, ctx->n_hit + bt0, Bh, T, 0, ns0, pitch, on, b0, x, done);
+    return plan.h32 ? ess_launch_attn_h32(ctx, qh, pool, ctx->hit_list + bt0 * k, ctx->n_hit + bt0, Bh, T, 0, ns0, pitch, on, b0, x, done, nullptr, nullptr, nullptr, 0, fetch)
+                    : ess_launch_attn_partial(ctx, qh, pool, ctx->hit_list + bt0 * k, ctx->n_hit + bt0, Bh, T, 0, ns0, pitch, on, b0, x, done, nullptr, nullptr, 0, fetch);
   };
   auto attn1 = [&](int b0, int Bh, hipStream_t on, ess_xcd x, hipEvent_t done, const ess_ticket_check* check) {
     const size_t bt0 = (size_t)b0 * T;
@@ -863,6 +868,18 @@ int ess_decode_step(ess_ctx* ctx, const ess_cache* cache, const ess_step_args* a
     // wait on another stream's event costs several microseconds when the event fires late and almost
     // nothing when it has fired long before: this way both waits of the step are of the second kind
     // (the side stream's wait for the bookkeeping delays only Attn0).
+    if (carried) {
+      const ess_fetch fetch = ess_fetch_of(ctx, *cache, B, 0, ESS_CARRIED_WGS);
+      ESS_BEGIN(3);
+      if ((rc = attn0(0, B, st, anywhere, nullptr, &fetch)) != ESS_OK) return rc;
+      ESS_END(3);
+      ESS_BEGIN(4);
+      chk.need[ESS_TKT_ATTN0] += check_extra;
+      if ((rc = attn1(0, B, st, anywhere, nullptr, &chk)) != ESS_OK) return rc;
+      if (!plan.finish && (rc = ess_launch_attn_merge(ctx, B, T, pitch, wide, a->out_bf16, a->lse, st, nullptr, 0, 0, &chk)) != ESS_OK) return rc;
+      ESS_END(4);
+      return ESS_OK;
+    }
     if (da_short) {
       ESS_BEGIN(5);
       rc = ess_launch_fill(ctx, *cache, B, st, 0, 64);

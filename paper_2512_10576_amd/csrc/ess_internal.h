@@ -141,6 +141,16 @@ struct ess_attn_final {
   int n_zero;
   ess_ticket_check chk;         // the step's last launch
 };
+// A fetch that an attention launch carries: of every eight consecutive workgroups the first two, which the hardware places
+// on XCDs 0 and 1, fetch (the first `wgs` of them), the other six take attention items by their number.  Who does what
+// follows from the workgroup number alone: the launch is complete under any placement.
+#define ESS_CARRIED_WGS 64
+struct ess_fetch {
+  const uint8_t* host_pool; uint8_t* slot_pool;
+  const int32_t *fill_tok, *fill_slot, *miss_cnt;
+  int fill_cap, B, Lmax, S, row_stride;
+  int wgs;                      // 0: no fetch
+};
 #ifdef __HIPCC__
 __device__ __forceinline__ void ess_check_tickets(const ess_ticket_check& chk) {
   bool short_of = false;
@@ -297,6 +307,7 @@ int ess_launch_bookkeeping(ess_ctx* ctx, const ess_cache& cache, const int32_t* 
                            bool count_step = true, ess_xcd xcd = ess_xcd{nullptr, 0, nullptr, 0}, uint32_t* zero_tickets = nullptr,
                            int n_zero_tickets = 0, hipEvent_t done = nullptr, int32_t* fresh_idx = nullptr);
 // only_xcds != 0: the fetch runs on these XCDs alone (`wgs` workgroups there, rows handed out through `ticket`)
+ess_fetch ess_fetch_of(ess_ctx* ctx, const ess_cache& cache, int B, int b0, int wgs);
 int ess_launch_fill(ess_ctx* ctx, const ess_cache& cache, int B, hipStream_t st, int b0 = 0, int wgs = 64,
                     uint32_t only_xcds = 0, uint32_t* ticket = nullptr, hipEvent_t done = nullptr);
 // which: 0 all entries of slot_idx; of a list with fetched entries marked (ESS_FRESH_BIT), 1 the others, 2 the marked ones
@@ -309,12 +320,14 @@ int ess_launch_attn_partial(ess_ctx* ctx, const void* q, const uint8_t* slot_poo
                             const int32_t* n_list, int B, int T, int split0, int nsplit, int pitch, hipStream_t st, int b0 = 0,
                             ess_xcd xcd = ess_xcd{nullptr, 0, nullptr, 0}, hipEvent_t done = nullptr,
                             // a second list in the same launch, its partial results behind those of the first
-                            const int32_t* list_b = nullptr, const int32_t* n_list_b = nullptr, int nsplit_b = 0);
+                            const int32_t* list_b = nullptr, const int32_t* n_list_b = nullptr, int nsplit_b = 0,
+                            const ess_fetch* fetch = nullptr);
 // the same with 32 heads per workgroup (sparse_mla_h32.hip); final (one range per row only): the rows are finished
 int ess_launch_attn_h32(ess_ctx* ctx, const void* q, const uint8_t* slot_pool, const int32_t* list, const int32_t* n_list, int B, int T,
                         int split0, int nsplit, int pitch, hipStream_t st, int b0 = 0, ess_xcd xcd = ess_xcd{nullptr, 0, nullptr, 0},
                         hipEvent_t done = nullptr, const ess_attn_final* final = nullptr,
-                        const int32_t* list_b = nullptr, const int32_t* n_list_b = nullptr, int nsplit_b = 0);
+                        const int32_t* list_b = nullptr, const int32_t* n_list_b = nullptr, int nsplit_b = 0,
+                        const ess_fetch* fetch = nullptr);
 int ess_init_attn_h32();
 int ess_attn_min_splits(const ess_config& c);   // fewest splits a list of k entries may be cut into
 // wide: four waves per row (small batches; the same for every sub-batch of a call, it sets the order of the sums);

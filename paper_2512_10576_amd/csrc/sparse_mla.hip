@@ -14,6 +14,7 @@
 // comes with it.  Both products are computed transposed so that nothing is
 // re-laid out between them; see the comment at the kernel.
 #include "attn_common.h"
+#include "fetch.h"
 #include <utility>
 
 namespace {
@@ -95,7 +96,8 @@ __global__ __launch_bounds__(NTH, 1) void k_attn_partial_tr(
     const uint16_t* __restrict__ q, const uint8_t* __restrict__ pool, const int32_t* __restrict__ list,
     const int32_t* __restrict__ n_list, int T, int H, int kk, int S, int row_stride, float scale_log2e, int split0,
     int nsplit, int pitch, _Float16* __restrict__ o_part, float* __restrict__ lse_part, const uint8_t* __restrict__ zero_row,
-    ess_xcd xcd, int n_bt, int n_hg, const int32_t* __restrict__ list_b, const int32_t* __restrict__ n_list_b, int nsplit_b) {
+    ess_xcd xcd, int n_bt, int n_hg, const int32_t* __restrict__ list_b, const int32_t* __restrict__ n_list_b, int nsplit_b, const ess_fetch fetch,
+    uint32_t bt_inv) {
   extern __shared__ __align__(16) uint8_t lds[];
   __shared__ int s_item;
   constexpr bool kDma = FMT == ESS_FMT_BF16;       // rows go to their tile as they are; else to the raw ring, and from there dequantised
@@ -609,7 +611,19 @@ __global__ __launch_bounds__(NTH, 1) void k_attn_partial_tr(
       run_item((item % per_row) / n_hg, item / per_row, item % n_hg);
     }
   } else {
-    run_item(blockIdx.y, blockIdx.x, blockIdx.z);
+    int split = blockIdx.y, bt = blockIdx.x;
+    if (fetch.wgs) {                               // (see ess_fetch; one head group)
+      const int x = blockIdx.x & 7, j = blockIdx.x >> 3;
+      if (x < 2) {
+        if (2 * j + x < fetch.wgs) ess_fill::entries<4>(fetch, reinterpret_cast<int32_t*>(lds), (2 * j + x) * 4 + (int)(threadIdx.x >> 6), fetch.wgs * 4);
+        return;
+      }
+      const uint32_t item = (uint32_t)(6 * j + x - 2);
+      split = (int)(n_bt == 1 ? item : __umulhi(item, bt_inv));
+      bt = (int)item - split * n_bt;
+      if (split >= nsplit) return;
+    }
+    run_item(split, bt, blockIdx.z);
   }
 }
 
@@ -715,13 +729,21 @@ int ess_init_attn_kernels() {
 
 int ess_launch_attn_partial(ess_ctx* ctx, const void* q, const uint8_t* slot_pool, const int32_t* list,
                             const int32_t* n_list, int B, int T, int split0, int nsplit, int pitch, hipStream_t st, int b0, ess_xcd xcd,
-                            hipEvent_t done, const int32_t* list_b, const int32_t* n_list_b, int nsplit_b) {
+                            hipEvent_t done, const int32_t* list_b, const int32_t* n_list_b, int nsplit_b, const ess_fetch* fetch) {
   const ess_config& c = ctx->cfg;
   if (split0 + nsplit + nsplit_b > pitch || (size_t)(b0 + B) * T * pitch > ctx->part_cap) return ess_fail(ESS_ERR_INVALID_ARG, "internal: partial results");
   if (nsplit < ess_attn_min_splits(c)) return ess_fail(ESS_ERR_INVALID_ARG, "internal: too few attention splits");
   const int n_hg = (c.attn_heads + HPG - 1) / HPG;      // 128 heads per workgroup
   dim3 grid(B * T, nsplit + nsplit_b, n_hg);
   if (xcd.ticket) grid = dim3(ess_xcd_grid((nsplit + nsplit_b) * B * T * n_hg, xcd));     // one workgroup per CU
+  ess_fetch fe{};
+  if (fetch) {
+    if (xcd.ticket || nsplit_b || n_hg != 1) return ess_fail(ESS_ERR_INVALID_ARG, "internal: attention launch with a fetch");
+    fe = *fetch;
+    const int groups = (nsplit * B * T + 5) / 6;
+    grid = dim3(8 * (groups > (fe.wgs + 1) / 2 ? groups : (fe.wgs + 1) / 2));
+  }
+  const uint32_t bt_inv = 0xffffffffu / (uint32_t)(B * T) + 1;      // division by B * T > 1 of numbers up to 2^18: exact
   const float sc = c.sm_scale * kLog2e;
   const uint16_t* qq = static_cast<const uint16_t*>(q);
   // partial results of sequence b0 onward
@@ -730,7 +752,7 @@ int ess_launch_attn_partial(ess_ctx* ctx, const void* q, const uint8_t* slot_poo
 #define ESS_ATTN_LAUNCH(FMT, DYN)                                                                                      \
   ESS_HIP(ess_launch_done(done, &k_attn_partial_tr<FMT, DYN>, grid, dim3(NTH), (size_t)tr_lds_bytes(FMT), st, qq, slot_pool, list, n_list, T, \
                      c.attn_heads, c.topk, c.slots_per_seq, c.row_stride, sc, split0, nsplit, pitch, op, lp, ctx->zero_row, xcd,  \
-                     B * T, n_hg, list_b, n_list_b, nsplit_b))
+                     B * T, n_hg, list_b, n_list_b, nsplit_b, fe, bt_inv))
   if (c.latent_fmt == ESS_FMT_BF16) {
     if (xcd.ticket) ESS_ATTN_LAUNCH(ESS_FMT_BF16, true); else ESS_ATTN_LAUNCH(ESS_FMT_BF16, false);
   } else {

@@ -4,6 +4,7 @@
 // workgroup owns 32 heads and its four waves share every tile: over the entries in the first product, over the value
 // columns in the second.  It can also finish a row: merge its result with partial results written before it.
 #include "attn_common.h"
+#include "fetch.h"
 #include <type_traits>
 
 namespace {
@@ -92,7 +93,7 @@ __global__ __launch_bounds__(NT, 2) void k_attn_h32(
     const int32_t* __restrict__ n_list, uint32_t t_inv, int H, int kk, int S, int row_stride, float scale_log2e, int split0,
     int nsplit, uint32_t ns_inv, int pitch, _Float16* __restrict__ o_part, float* __restrict__ lse_part, const uint8_t* __restrict__ zero_row,
     ess_xcd xcd, int n_bt, int n_hg, int quads, const int32_t* __restrict__ list_b, const int32_t* __restrict__ n_list_b, int nsplit_a,
-    uint32_t ns_inv_a, uint32_t ns_inv_b, ess_attn_final fin) {
+    uint32_t ns_inv_a, uint32_t ns_inv_b, ess_attn_final fin, const ess_fetch fetch, uint32_t hg_inv) {
   extern __shared__ __align__(16) uint8_t lds[];
   __shared__ int s_item;
   __shared__ __align__(16) int s_last[NW];
@@ -601,8 +602,18 @@ __global__ __launch_bounds__(NT, 2) void k_attn_h32(
       for (int i = threadIdx.x; i < fin.n_zero; i += NT) fin.zero_cnt[i] = 0;
       if (fin.chk.tickets && threadIdx.x == 0) ess_check_tickets(fin.chk);
     }
-    const uint32_t u = 8 * blockIdx.y + (blockIdx.x & 7), bt = nsplit == 1 ? u : __umulhi(u, ns_inv);
-    if (bt < (uint32_t)n_bt) run_item((int)(u - bt * nsplit), (int)bt, blockIdx.x >> 3);
+    uint32_t u = 8 * blockIdx.y + (blockIdx.x & 7), hg = blockIdx.x >> 3;
+    if (fetch.wgs) {                               // (see ess_fetch)
+      const uint32_t x = blockIdx.x & 7, j = blockIdx.x >> 3, jg = j * hg_inv >> 16;
+      if (x < 2) {
+        if (2 * j + x < (uint32_t)fetch.wgs) ess_fill::entries<2>(fetch, reinterpret_cast<int32_t*>(lds), (int)((2 * j + x) * NW + (threadIdx.x >> 6)), fetch.wgs * NW);
+        return;
+      }
+      u = 6 * jg + x - 2;
+      hg = j - jg * n_hg;
+    }
+    const uint32_t bt = nsplit == 1 ? u : __umulhi(u, ns_inv);
+    if (bt < (uint32_t)n_bt) run_item((int)(u - bt * nsplit), (int)bt, (int)hg);
   }
 }
 
@@ -622,7 +633,7 @@ int ess_init_attn_h32() {
 
 int ess_launch_attn_h32(ess_ctx* ctx, const void* q, const uint8_t* slot_pool, const int32_t* list, const int32_t* n_list, int B, int T,
                         int split0, int nsplit, int pitch, hipStream_t st, int b0, ess_xcd xcd, hipEvent_t done, const ess_attn_final* final,
-                        const int32_t* list_b, const int32_t* n_list_b, int nsplit_b) {
+                        const int32_t* list_b, const int32_t* n_list_b, int nsplit_b, const ess_fetch* fetch) {
   const ess_config& c = ctx->cfg;
   if (split0 + nsplit + nsplit_b > pitch || (size_t)(b0 + B) * T * pitch > ctx->part_cap) return ess_fail(ESS_ERR_INVALID_ARG, "internal: partial results");
   if (c.topk > MAX_LIST) return ess_fail(ESS_ERR_INVALID_ARG, "internal: attention form");
@@ -632,6 +643,13 @@ int ess_launch_attn_h32(ess_ctx* ctx, const void* q, const uint8_t* slot_pool, c
   const int ns = nsplit + nsplit_b, n_hg = (c.attn_heads + HT - 1) / HT;
   dim3 grid(8 * n_hg, (B * T * ns + 7) / 8);
   if (xcd.ticket) grid = dim3(ess_xcd_grid(ns * B * T * n_hg, xcd));
+  ess_fetch fe{};
+  if (fetch) {
+    if (xcd.ticket || fin.out) return ess_fail(ESS_ERR_INVALID_ARG, "internal: attention launch with a fetch");
+    fe = *fetch;
+    const int groups = (ns * B * T + 5) / 6 * n_hg;
+    grid = dim3(8 * (groups > (fe.wgs + 1) / 2 ? groups : (fe.wgs + 1) / 2));
+  }
   const float sc = c.sm_scale * kLog2e;
   const uint16_t* qq = static_cast<const uint16_t*>(q);
   _Float16* op = reinterpret_cast<_Float16*>(ctx->o_part) + (size_t)b0 * T * pitch * c.attn_heads * ESS_LATENT_DIM;
@@ -641,12 +659,13 @@ int ess_launch_attn_h32(ess_ctx* ctx, const void* q, const uint8_t* slot_pool, c
     if (fin.lse) fin.lse += (size_t)b0 * T * c.attn_heads;
   }
   const int quads = (c.topk & 3) == 0 && ((reinterpret_cast<uintptr_t>(list) | reinterpret_cast<uintptr_t>(list_b)) & 15) == 0;
+  const uint32_t hg_inv = 65535u / n_hg + 1;
   const uint32_t t_inv = 65535u / T + 1, ns_inv = 0xffffffffu / ns + 1, ns_inv_a = 0xffffffffu / nsplit + 1,
                  ns_inv_b = 0xffffffffu / (nsplit_b > 0 ? nsplit_b : 1) + 1;      // divisions by T of numbers up to 16384, by nsplit > 1 up to 2^20: exact
 #define ESS_H32_LAUNCH(FMT, DYN)                                                                                                       \
   ESS_HIP(ess_launch_done(done, &k_attn_h32<FMT, DYN>, grid, dim3(NT), (size_t)Lay<FMT>::BYTES, st, qq, slot_pool, list, n_list, t_inv, \
                           c.attn_heads, c.topk, c.slots_per_seq, c.row_stride, sc, split0, ns, ns_inv, pitch, op, lp, ctx->zero_row, xcd, \
-                          B * T, n_hg, quads, list_b, n_list_b, nsplit, ns_inv_a, ns_inv_b, fin))
+                          B * T, n_hg, quads, list_b, n_list_b, nsplit, ns_inv_a, ns_inv_b, fin, fe, hg_inv))
   if (c.latent_fmt == ESS_FMT_BF16) { if (xcd.ticket) ESS_H32_LAUNCH(ESS_FMT_BF16, true); else ESS_H32_LAUNCH(ESS_FMT_BF16, false); }
   else { if (xcd.ticket) ESS_H32_LAUNCH(ESS_FMT_FP8, true); else ESS_H32_LAUNCH(ESS_FMT_FP8, false); }
 #undef ESS_H32_LAUNCH
