@@ -34,8 +34,8 @@ namespace {
 constexpr int BT = 1024;
 
 struct BookShared {
-  uint32_t wave_tot[BT / 64];
-  uint32_t sel_digit, sel_below;
+  uint32_t wave_tot[BT / 64], wave_tot2[BT / 64];
+  uint32_t sel_digit, sel_below, sel_upto;
 };
 // The large arrays of the bookkeeping kernel live in dynamic LDS, sized by the configuration:
 //   bm [W]  bitmap of the missed positions (W = max_ctx / 32 words, rounded up to an even number)
@@ -43,6 +43,13 @@ struct BookShared {
 //           (vict_cap = sel_cap rounded up to a power of two, 8 bytes each)
 //   mt [sel_cap]  missed positions in ascending order (sel_cap = max_q_tokens * topk)
 constexpr int BOOK_HIST_BYTES = 256 * 32 * 4;
+// Inside `un`, in words, while the victims' list takes no more than its first 2048 (up to 1024 victims):
+constexpr int BOOK_CNT = 2048;       // [256 digits][16 waves] bytes: the list's slots of a digit in a wave's part of it
+constexpr int BOOK_LISTS = 6144;     // [4][16] totals of the hit / miss lists (a longer list of victims is done with by then)
+constexpr int BOOK_BELOW = 7168;     // [256] victims of smaller digits
+constexpr int BOOK_PRE = 7424;       // [1024] 16 bits each: misses in front of a thread's bitmap words
+constexpr int BOOK_HITS = 7680;      // [512] bitmap of the slots that were hit, before the histogram (pools up to 16384 slots)
+static_assert(BOOK_PRE + BT / 2 <= BOOK_HIST_BYTES / 4 && BOOK_HITS + 16 * BT / 32 <= BOOK_HIST_BYTES / 4, "book layout");
 inline int book_pow2(int n) { int p = 1; while (p < n) p <<= 1; return p; }
 inline size_t book_words(int max_ctx) { return (size_t)(((max_ctx + 31) / 32 + 1) & ~1); }
 inline size_t book_union_bytes(int sel_cap) {
@@ -74,9 +81,21 @@ __device__ void bitonic_sort_u64(unsigned long long* a, int n) {
   __syncthreads();
 }
 
+// set bits of the wave's mask in front of this lane's
+__device__ __forceinline__ uint32_t lanes_below(uint64_t mask) {
+  return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+}
+
 // idx: [B, T, kk] selected positions (-1 = none).  Dynamic LDS: bitmap of Lmax bits.
-// REG: the slots a thread owns (S / 1024, rounded up, at most 16) are held in registers, so the
-// stamps are read from memory once, all loads of a thread in flight together.
+// REG: pools up to 16384 slots.  A wave owns a contiguous range of slots, 64 of them (one a lane) at a time, at most
+// 16 times: the stamps are read once, whole lines at a time and at the kernel's start, while the selection is looked
+// up, and held in registers; hits are marked in an LDS bitmap, from which the owners of the slots stamp them.  A thread that owns up
+// to 16 consecutive slots instead makes a load of a wave touch some 30 lines, and stamping the hits by a scattered store
+// each puts those stores in front of the stamps' loads.  What bounds the kernel then: two dependent trips to memory (5 us) and
+// the instructions of 16 waves on one CU (four to a SIMD: each costs all of them 16 cycles), hence the counts by ballot and the
+// sums over waves by one row of lanes.  One sequence, cycles at 2.4 GHz, threads owning consecutive slots / this: 8192 slots,
+// 190 misses 40500 / 32500; 6554 slots, 360 misses 34300 / 31800; 9001 slots, two tokens, 110 misses 39600 / 35000; 13108
+// slots, two tokens, 420 misses 66300 / 56000.
 template <bool REG, bool DYN>
 __global__ __launch_bounds__(BT) void k_bookkeeping(
     const int32_t* __restrict__ idx, int T, int kk, int Lmax, int S, int32_t* __restrict__ slot_of,
@@ -114,45 +133,98 @@ __global__ __launch_bounds__(BT) void k_bookkeeping(
   int32_t* to = token_of + (size_t)b * S;
   uint32_t* stp = stamp + (size_t)b * S;
 
+  // this wave's slots in the register form: [ws, ws + 64 * nj), nj <= 16
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int nj_reg = (S + BT - 1) / BT;
+  const int ws = wave * nj_reg * 64;
+  uint32_t sr[RS];
   for (int j = tid; j < W; j += BT) bm[j] = 0;
-  __syncthreads();
+  {
+    uint2* const h2 = reinterpret_cast<uint2*>(s_hist);          // the counters of the age pass, and the bitmap of hit slots among them
+    for (int j = tid; j < BOOK_HIST_BYTES / 8; j += BT) h2[j] = make_uint2(0, 0);
+  }
   // look-up straight from the selection list (all gathers of a thread in flight together): hits get
   // their stamp, misses set their bit; duplicates across the T query tokens do the same thing twice
   // (kept: when one round covers the selection and a query token's list is whole rounds of the workgroup, the
   // lists at the end are built from these registers instead of a second look-up)
   const bool keep = nsel <= 4 * BT && kk % BT == 0;
+  if (tid == 0) sm.sel_upto = 0xffffffffu;       // (stays so where a step has too few slots that it may evict)
   uint32_t my_valid = 0;
   int sv[4] = {-1, -1, -1, -1}, slv[4] = {-1, -1, -1, -1};
-  for (int e0 = 0; e0 < nsel; e0 += 4 * BT) {
+  uint32_t* const s_hits = s_hist + BOOK_HITS;
+  auto select = [&](int e0) {
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const int e = e0 + u * BT + tid;
       sv[u] = e < nsel ? sel[e] : -1;
-      if (sv[u] >= Lmax) sv[u] = -1;
     }
+  };
+  auto look_up = [&]() {
 #pragma unroll
-    for (int u = 0; u < 4; ++u) slv[u] = sv[u] >= 0 ? so[sv[u]] : -1;
+    for (int u = 0; u < 4; ++u) {
+      if (sv[u] >= Lmax) sv[u] = -1;
+      slv[u] = sv[u] >= 0 ? so[sv[u]] : -1;
+    }
+  };
+  auto mark = [&]() {
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       if (sv[u] < 0) continue;
       ++my_valid;
-      if (slv[u] >= 0) stp[slv[u]] = step;
-      else atomicOr(&bm[sv[u] >> 5], 1u << (sv[u] & 31));
+      if (slv[u] < 0) atomicOr(&bm[sv[u] >> 5], 1u << (sv[u] & 31));
+      else if constexpr (REG) atomicOr(&s_hits[slv[u] >> 5], 1u << (slv[u] & 31));
+      else stp[slv[u]] = step;
+    }
+  };
+  select(0);
+  look_up();
+  if constexpr (REG) {
+    const int left = min(S - ws, 64 * nj_reg);
+#pragma unroll
+    for (int j = 0; j < RS; ++j) {
+      sr[j] = 0xffffffffu;                       // never evictable
+      if (64 * j + 64 <= left) sr[j] = stp[ws + 64 * j + lane];
+      else if (64 * j < left && 64 * j + lane < left) sr[j] = stp[ws + 64 * j + lane];
     }
   }
+  __syncthreads();                               // bitmaps are clear
+  mark();
+  for (int e0 = 4 * BT; e0 < nsel; e0 += 4 * BT) {
+    select(e0);
+    look_up();
+    mark();
+  }
   __syncthreads();
+  if constexpr (REG) {
+    // hits get their stamp; the bitmap's words of a wave are read and cleared by that wave alone
+    uint32_t* const mine = s_hits + wave * 2 * nj_reg;
+    const uint32_t word = lane < 2 * nj_reg ? mine[lane] : 0u;
+    if (lane < 2 * nj_reg) mine[lane] = 0;
+#pragma unroll
+    for (int j = 0; j < RS; ++j) {
+      if (j >= nj_reg) continue;
+      const uint64_t hit = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)word, 2 * j) |
+                           ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)word, 2 * j + 1) << 32);
+      if (__builtin_amdgcn_inverse_ballot_w64(hit)) {
+        sr[j] = step;
+        stp[ws + 64 * j + lane] = step;
+      }
+    }
+  }
 
-  // misses in ascending position: prefix sum over the bitmap words
-  const int wpt = (W + BT - 1) / BT;
-  const int w0 = min(tid * wpt, W), w1 = min(w0 + wpt, W);
+  // misses in ascending position: prefix sum over the bitmap words (a thread's words: a power of two of them)
+  int wsh = 0;
+  while ((BT << wsh) < W) ++wsh;
+  const int w0 = min(tid << wsh, W), w1 = min(w0 + (1 << wsh), W);
   uint32_t my_miss = 0;
   for (int wd = w0; wd < w1; ++wd) my_miss += __popc(bm[wd]);
   // one scan for both counts (each at most T * k <= 8192: 16 bits apiece)
   uint32_t both;
   const uint32_t miss_inc = block_incl_scan(my_miss | (my_valid << 16), sm.wave_tot, &both) & 0xffffu;
   const uint32_t m = both & 0xffffu, nvalid = both >> 16;
+  const uint32_t miss_before = miss_inc - my_miss;
   {
-    uint32_t pos = miss_inc - my_miss;
+    uint32_t pos = miss_before;
     for (int wd = w0; wd < w1; ++wd) {
       uint32_t bits = bm[wd];
       while (bits) {
@@ -163,35 +235,51 @@ __global__ __launch_bounds__(BT) void k_bookkeeping(
       }
     }
   }
-  __syncthreads();                               // also: the stamps of the hits are visible
+  if constexpr (!REG) __syncthreads();           // the stamps of the hits are visible
 
   // the counts leave here, so that their way to memory (and to the host) passes beside the work below
   if (tid == 0) {
     miss_cnt[b] = (int32_t)m;
     if (miss_count_out) miss_count_out[b] = (int32_t)m;
     if (host_miss) host_miss[b] = (int32_t)m;       // pinned host memory: the host's view for the overlap switch
-    if (b == 0 && count_step) atomicAdd(&stats[0], 1ull);
-    atomicAdd(&stats[1], (unsigned long long)nvalid);
-    atomicAdd(&stats[2], (unsigned long long)m);
-    atomicAdd(&stats[3], (unsigned long long)m * (unsigned long long)row_stride);
-    // the same per sequence (adds that return nothing: a read of the counters would be waited for)
-    atomicAdd(&seq_stats[4 * b + 0], 1ull);
-    atomicAdd(&seq_stats[4 * b + 1], (unsigned long long)nvalid);
-    atomicAdd(&seq_stats[4 * b + 2], (unsigned long long)m);
-    atomicAdd(&seq_stats[4 * b + 3], (unsigned long long)m * (unsigned long long)row_stride);
+  }
+  if (tid < 8) {
+    // counters of the context (steps, valid entries, misses, bytes) and the same of the sequence, a lane each (adds that
+    // return nothing: a read of the counters would be waited for)
+    const int which = tid & 3;
+    const bool whole = tid < 4;
+    const unsigned long long add = which == 0 ? (whole && !(b == 0 && count_step) ? 0ull : 1ull)
+                                 : which == 1 ? nvalid
+                                 : which == 2 ? m : (unsigned long long)m * (unsigned long long)row_stride;
+    atomicAdd(whole ? &stats[which] : &seq_stats[4 * (size_t)b + which], add);
   }
 
+  // pair the i-th miss with victim v, whose former token is `old`
+  auto pair = [&](uint32_t i, int v, int old) {
+    const int s = s_miss_tok[i];
+    if (old >= 0) so[old] = -1;
+    to[v] = s;
+    so[s] = v;
+    stp[v] = step;
+    fill_tok[(size_t)b * fill_cap + i] = s;
+    fill_slot[(size_t)b * fill_cap + i] = v;
+  };
+  const bool by_rank = m <= (uint32_t)BT;
+  uint16_t* const s_pre = reinterpret_cast<uint16_t*>(s_hist + BOOK_PRE);
   if (m > 0) {
-    // this thread's slots: [v0, v1), contiguous so that slot order is thread order
-    const int spt = (S + BT - 1) / BT;
-    const int v0 = min(tid * spt, S), v1 = min(v0 + spt, S);
-    uint32_t sr[RS];
-    if (REG) {
+    // (larger pools) this thread's slots: [v0, v1), contiguous so that slot order is thread order
+    const int v0 = min(tid * nj_reg, S), v1 = min(v0 + nj_reg, S);
+    // f(stamp) of every slot this thread owns
+    auto each_stamp = [&](auto&& f) {
+      if constexpr (REG) {
 #pragma unroll
-      for (int j = 0; j < RS; ++j) sr[j] = (v0 + j < v1) ? stp[v0 + j] : 0xffffffffu;   // never evictable
-    }
-    auto stamp_at = [&](int j) -> uint32_t { return REG ? sr[j] : stp[v0 + j]; };
-    const int nj = REG ? RS : spt;
+        for (int j = 0; j < RS; ++j) {
+          if (j < nj_reg) f(sr[j]);
+        }
+      } else {
+        for (int j = v0; j < v1; ++j) f(stp[j]);
+      }
+    };
     // ---- m-th smallest stamp among evictable slots (stamp < step).  One pass by age: the stamps of the last 254 steps
     // have a digit each, everything older shares digit 0.  In a pool in its steady state the victims are some 50 steps
     // old, so the threshold stamp is known after this pass whatever the step number; only when it falls among the older
@@ -200,7 +288,7 @@ __global__ __launch_bounds__(BT) void k_bookkeeping(
     // 27.3, at step 70000 29.4 against 28.5; victims 6000 steps old 28.1 against 27.2: there it is one pass too many.
     uint32_t prefix = 0, need = m;
     const uint32_t base = step > 255u ? step - 255u : 0u;
-    auto age_digit = [&](uint32_t st) -> uint32_t { return st > base ? st - base : 0u; };     // <= 254 for st < step
+    auto age_digit = [&](uint32_t st) -> uint32_t { return __builtin_elementwise_sub_sat(st, base); };     // <= 254 for st < step
     // counters (cleared here) and the prefix sum over the 256 digits; the digit that holds the need-th smallest
     auto clear_hist = [&]() {
       uint2* h2 = reinterpret_cast<uint2*>(s_hist);
@@ -209,8 +297,8 @@ __global__ __launch_bounds__(BT) void k_bookkeeping(
     };
     auto find_digit = [&](uint32_t* below_out) {
       __syncthreads();
-      uint32_t c = 0;
-      if (tid < 256) {
+      uint32_t c = 0, inc = 0;
+      if (wave < 4) {                                  // (the other waves only meet the barriers)
         // a thread's 32 copies are consecutive words, so consecutive threads start 32 words apart: the 16-byte
         // pieces are taken in an order rotated by the thread index, which spreads a read over the banks
         const uint4* h4 = reinterpret_cast<const uint4*>(s_hist + tid * 32);
@@ -219,25 +307,24 @@ __global__ __launch_bounds__(BT) void k_bookkeeping(
           const uint4 x = h4[(g + tid) & 7];
           c += x.x + x.y + x.z + x.w;
         }
+        inc = wave_incl_scan(c, lane);
+        if (lane == 63) sm.wave_tot[wave] = inc;
       }
-      uint32_t total;
-      const uint32_t inc = block_incl_scan(c, sm.wave_tot, &total);
-      const uint32_t below = inc - c;
-      if (tid < 256) {
-        if (below < need && below + c >= need) { sm.sel_digit = tid; sm.sel_below = below; }
+      __syncthreads();
+      if (wave < 4) {
+        inc += ess_sel::waves_before<4>(sm.wave_tot, wave, lane);
+        const uint32_t below = inc - c;
+        if (below < need && inc >= need) { sm.sel_digit = tid; sm.sel_below = below; sm.sel_upto = inc; }
         if (below_out) below_out[tid] = below;
       }
       __syncthreads();
       need -= sm.sel_below;
     };
-    uint32_t* const s_below = s_hist + 7168;         // [256], past what the victims' list and the counters below use
-    clear_hist();
-#pragma unroll
-    for (int j = 0; j < nj; ++j) {
-      if (v0 + j >= v1) continue;
-      const uint32_t st = stamp_at(j);
+    uint32_t* const s_below = s_hist + BOOK_BELOW;
+    // (the counters were cleared with the bitmap; the barriers of the scan above lie between)
+    each_stamp([&](uint32_t st) {
       if (st < step) atomicAdd(&s_hist[age_digit(st) * 32 + (lane & 31)], 1u);
-    }
+    });
     find_digit(s_below);
     const bool by_age = sm.sel_digit > 0 || base == 0;
     // whether a digit is one stamp for every victim: not if some are older than the digits tell apart (read here, as
@@ -256,88 +343,131 @@ __global__ __launch_bounds__(BT) void k_bookkeeping(
         const int shift = 24 - 8 * pass;
         __syncthreads();
         clear_hist();
-#pragma unroll
-        for (int j = 0; j < nj; ++j) {
-          if (v0 + j >= v1) continue;
-          const uint32_t st = stamp_at(j);
+        each_stamp([&](uint32_t st) {
           if (st < step && (pass == first_pass || (st >> (shift + 8)) == prefix))
             atomicAdd(&s_hist[((st >> shift) & 255u) * 32 + (lane & 31)], 1u);
-        }
+        });
         find_digit(nullptr);
         prefix = (prefix << 8) | sm.sel_digit;
         __syncthreads();
       }
     }
     const uint32_t tau = prefix;               // threshold stamp; `need` slots with stamp == tau are taken, lowest slots first
-    // ---- collect victims: stamp < tau, plus the first `need` slots (in slot order) with stamp == tau
-    uint32_t my_eq = 0, my_lt = 0;
+    // ---- collect victims: stamp < tau, plus the first `need` slots (in slot order) with stamp == tau.  The list is in
+    // slot order.  Where it is ordered by counting below (one stamp a digit) and there is room, every slot up to tau goes in: the
+    // order alone then tells the victims, its first m.  (A pool in its steady state has about as many slots at tau as it needs victims.)
+    const uint32_t upto = sm.sel_upto;
+    const bool counted = by_rank && by_age && one_stamp;
+    const bool all = REG && counted && upto <= (uint32_t)BT;
+    const int n_list = all ? (int)upto : (int)m;
+    uint32_t* const s_cnt = s_hist + BOOK_CNT;
+    s_cnt[tid] = 0;
+    if (all) {
+      uint32_t n = 0;
 #pragma unroll
-    for (int j = 0; j < nj; ++j)
-      if (v0 + j < v1) {
-        const uint32_t st = stamp_at(j);
+      for (int j = 0; j < RS; ++j)
+        if (j < nj_reg) n += (uint32_t)__popcll(__ballot(sr[j] <= tau));
+      if (lane == 0) sm.wave_tot2[wave] = n;
+      __syncthreads();
+      uint32_t at = ess_sel::waves_before<BT / 64>(sm.wave_tot2, wave, lane);
+#pragma unroll
+      for (int j = 0; j < RS; ++j) {
+        if (j >= nj_reg) continue;
+        const uint64_t take = __ballot(sr[j] <= tau);
+        if (sr[j] <= tau) s_vict[at + lanes_below(take)] = ((unsigned long long)sr[j] << 32) | (uint32_t)(ws + 64 * j + lane);
+        at += (uint32_t)__popcll(take);
+      }
+    } else
+    if constexpr (REG) {
+      // counts of the wave by ballot, 16 bits each (at most 16384 slots)
+      uint32_t n_both = 0;
+#pragma unroll
+      for (int j = 0; j < RS; ++j)                         // (never a victim: what lies past the pool)
+        n_both += (uint32_t)__popcll(__ballot(sr[j] == tau)) | ((uint32_t)__popcll(__ballot(sr[j] < tau)) << 16);
+      if (lane == 0) sm.wave_tot2[wave] = n_both;
+      __syncthreads();
+      const uint32_t before = ess_sel::waves_before<BT / 64>(sm.wave_tot2, wave, lane);
+      uint32_t rank = before & 0xffffu;                    // slots at the threshold stamp in front of the next 64
+      uint32_t at = (before >> 16) + min(rank, need);      // victims in front of them
+#pragma unroll
+      for (int j = 0; j < RS; ++j) {
+        asm volatile("" : "+v"(sr[j]));                    // (the masks of the counts are not worth keeping)
+        const uint64_t eq = __ballot(sr[j] == tau);
+        const uint64_t take = __ballot(sr[j] < tau || (sr[j] == tau && rank + lanes_below(eq) < need));
+        if (take) {
+          const uint32_t i = at + lanes_below(take);
+          if (((take >> lane) & 1u) && i < (uint32_t)vict_cap)
+            s_vict[i] = ((unsigned long long)sr[j] << 32) | (uint32_t)(ws + 64 * j + lane);
+        }
+        rank += (uint32_t)__popcll(eq);
+        at += (uint32_t)__popcll(take);
+      }
+    } else {
+      uint32_t my_eq = 0, my_lt = 0;
+      each_stamp([&](uint32_t st) {
         my_eq += (st == tau) ? 1u : 0u;
         my_lt += (st < tau) ? 1u : 0u;
-      }
-    // slots at the threshold stamp (their order decides which of them are taken) and slots below it (all taken: fewer
-    // than m <= 8192).  Where the pool is small enough both counts share one scan.
-    uint32_t rank, lt_before;
-    if (REG) {                                  // at most 16384 slots: 16 bits each
-      uint32_t tot;
-      const uint32_t ex = block_incl_scan(my_eq | (my_lt << 16), sm.wave_tot, &tot) - (my_eq | (my_lt << 16));
-      rank = ex & 0xffffu;
-      lt_before = ex >> 16;
-    } else {
+      });
       uint32_t tot_eq, tot_lt;
-      rank = block_incl_scan(my_eq, sm.wave_tot, &tot_eq) - my_eq;      // slots at the threshold stamp in front of this thread's
-      lt_before = block_incl_scan(my_lt, sm.wave_tot, &tot_lt) - my_lt;
-    }
-    // where this thread's victims go: those of the threads before it come first (the list is in slot order)
-    uint32_t at = lt_before + min(rank, need);
-#pragma unroll
-    for (int j = 0; j < nj; ++j) {
-      if (v0 + j >= v1) continue;
-      const uint32_t st = stamp_at(j);
-      bool take = st < tau;
-      if (st == tau) { take = rank < need; ++rank; }
-      if (take) {
-        if (at < (uint32_t)vict_cap) s_vict[at] = ((unsigned long long)st << 32) | (uint32_t)(v0 + j);
-        ++at;
+      uint32_t rank = block_incl_scan(my_eq, sm.wave_tot, &tot_eq) - my_eq;      // slots at the threshold stamp in front of this thread's
+      // where this thread's victims go: those of the threads before it come first
+      uint32_t at = block_incl_scan(my_lt, sm.wave_tot, &tot_lt) - my_lt + min(rank, need);
+      for (int j = v0; j < v1; ++j) {
+        const uint32_t st = stp[j];
+        bool take = st < tau;
+        if (st == tau) { take = rank < need; ++rank; }
+        if (take) {
+          if (at < (uint32_t)vict_cap) s_vict[at] = ((unsigned long long)st << 32) | (uint32_t)j;
+          ++at;
+        }
       }
     }
+    if (by_rank) s_pre[tid] = (uint16_t)miss_before;       // (read where the lists are built)
     // ---- order the victims by (stamp, slot)
-    const bool by_rank = m <= (uint32_t)BT;
-    if (by_rank && by_age && one_stamp) {
+    if (counted) {
       // A digit is one stamp here.  The list is in slot order, so a stable counting sort by age is the order: a victim's place is the number of
       // slots of smaller digits (all of them victims) plus the number of victims with its digit in front of it -- inside its
       // wave by matching the eight digit bits, and the counts of the waves before.  (Was: every key compared with
       // every other, 4.5 us for 280 victims; this takes 1.5.)
-      uint32_t* const s_cnt = s_hist + 2048;           // [16 waves][256], behind the list's 8 KiB
-      for (int j = tid; j < (BT / 64) * 256; j += BT) s_cnt[j] = 0;
+      // Its former token is asked for as soon as the victim is known, and the pairing follows from the registers.
+      // The former token is asked for as soon as the slot is known, and the pairing follows from the registers.
+      uint8_t* const cnt8 = reinterpret_cast<uint8_t*>(s_cnt);         // [256 digits][16 waves]: at most 64 each
       __syncthreads();
-      const int wv = tid >> 6;
-      const bool in = tid < (int)m;
+      const bool in = tid < n_list;
       unsigned long long my_key = 0;
       uint32_t dg = 0, ahead = 0;
-      if (wv * 64 < (int)m) {                          // whole waves
-        if (in) my_key = s_vict[tid];
-        dg = in ? age_digit((uint32_t)(my_key >> 32)) : 0u;
+      int my_old = -1;
+      if (wave * 64 < n_list) {                        // whole waves
+        if (in) {
+          my_key = s_vict[tid];
+          my_old = to[(uint32_t)my_key];
+          dg = age_digit((uint32_t)(my_key >> 32));
+        }
         unsigned long long same = __ballot(in);
 #pragma unroll
         for (int bit = 0; bit < 8; ++bit) {
           const unsigned long long bal = __ballot((dg >> bit) & 1u);
           same &= ((dg >> bit) & 1u) ? bal : ~bal;
         }
-        ahead = (uint32_t)__popcll(same & ((1ull << lane) - 1ull));
-        if (in && ahead == 0) s_cnt[wv * 256 + dg] = (uint32_t)__popcll(same);
+        ahead = lanes_below(same);
+        if (in && ahead == 0) cnt8[dg * 16 + wave] = (uint8_t)__popcll(same);
       }
       __syncthreads();
       if (in) {
         ahead += s_below[dg];
-        for (int x = 0; x < wv; ++x) ahead += s_cnt[x * 256 + dg];
+        const uint4 c = reinterpret_cast<const uint4*>(s_cnt)[dg];     // the waves in front: their bytes, summed
+        const uint32_t cw[4] = {c.x, c.y, c.z, c.w};
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {
+          const int n = wave - 4 * x;
+          const uint32_t mask = n >= 4 ? 0xffffffffu : (n > 0 ? (1u << (8 * n)) - 1u : 0u);
+          ahead = __builtin_amdgcn_sad_u8(cw[x] & mask, 0u, ahead);
+        }
+        if (ahead < m) {
+          s_vict[ahead] = my_key;                      // (every key of the list is in its thread's registers)
+          pair(ahead, (int)(uint32_t)my_key, my_old);
+        }
       }
-      __syncthreads();
-      if (in) s_vict[ahead] = my_key;
-      __syncthreads();
     } else if (by_rank) {
       __syncthreads();
       // every victim's rank = the number of smaller keys, counted by BT / m threads per victim, each over its share
@@ -378,18 +508,21 @@ __global__ __launch_bounds__(BT) void k_bookkeeping(
       bitonic_sort_u64(s_vict, np);
     }
     // ---- pair the i-th miss with the i-th victim
-    for (uint32_t i = tid; i < m; i += BT) {
-      const int s = s_miss_tok[i];
-      const int v = (int)(uint32_t)s_vict[i];
-      const int old = to[v];
-      if (old >= 0) so[old] = -1;
-      to[v] = s;
-      so[s] = v;
-      stp[v] = step;
-      fill_tok[(size_t)b * fill_cap + i] = s;
-      fill_slot[(size_t)b * fill_cap + i] = v;
-    }
+    if (!counted)
+      for (uint32_t i = tid; i < m; i += BT) {
+        const int v = (int)(uint32_t)s_vict[i];
+        pair(i, v, to[v]);
+      }
   }
+  // a miss's place among the misses: the bits before its own in the bitmap
+  auto miss_place = [&](int pos) -> uint32_t {
+    const int wd = pos >> 5;
+    uint32_t i = s_pre[wd >> wsh] + (uint32_t)__popc(bm[wd] & ((1u << (pos & 31)) - 1u));
+    for (int x = wd & (int)(~0u << wsh); x < wd; ++x) i += (uint32_t)__popc(bm[x]);
+    return i;
+  };
+  // A miss finds its slot in the victims' list; in a longer list, or where the selection is read again, the table itself tells, once it is written.
+  const bool by_list = keep && by_rank;
   __syncthreads();                               // table updates visible to the whole workgroup
 
   // ---- per (b,t): slot of every selected entry, and the compacted hit / fetched lists
@@ -399,11 +532,15 @@ __global__ __launch_bounds__(BT) void k_bookkeeping(
     // its slot in the pairing above (all reads of a thread in flight together).  A query token's list is whole rounds,
     // so one exchange of the waves' counts serves all of them.
     const int rounds = nsel / BT, per_t = kk / BT;
-    uint32_t* const lists_tot = s_hist;            // [4][waves]: the victims' list is done with
+    uint32_t* const lists_tot = s_hist + BOOK_LISTS;
     uint32_t ex[4];
     int sl[4];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) sl[u] = (u < rounds && sv[u] >= 0) ? (slv[u] < 0 ? so[sv[u]] : slv[u]) : -1;
+    for (int u = 0; u < 4; ++u) {
+      const bool fresh = u < rounds && sv[u] >= 0 && slv[u] < 0;
+      sl[u] = u < rounds && sv[u] >= 0 ? slv[u] : -1;
+      if (fresh) sl[u] = by_list ? (int)(uint32_t)s_vict[miss_place(sv[u])] : so[sv[u]];
+    }
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       if (u >= rounds) break;
@@ -411,33 +548,28 @@ __global__ __launch_bounds__(BT) void k_bookkeeping(
       const bool fresh = sv[u] >= 0 && slv[u] < 0;
       if (slot_idx_out) slot_idx_out[at] = sl[u];
       if (fresh_idx) fresh_idx[at] = fresh ? sl[u] | ESS_FRESH_BIT : sl[u];
-      const uint32_t one = sl[u] < 0 ? 0u : (fresh ? 1u << 16 : 1u);
-      const uint32_t inc = wave_incl_scan(one, lane);
-      ex[u] = inc - one;
-      if (lane == 63) lists_tot[u * (BT / 64) + (tid >> 6)] = inc;
+      const uint64_t hits = __ballot(sl[u] >= 0 && !fresh), misses = __ballot(sl[u] >= 0 && fresh);
+      ex[u] = lanes_below(fresh ? misses : hits);
+      if (lane == 0) lists_tot[u * (BT / 64) + wave] = (uint32_t)__popcll(hits) | ((uint32_t)__popcll(misses) << 16);
     }
     __syncthreads();
     if (!hit_list) continue;
-    uint32_t run = 0;                              // hits | misses << 16 of the query token's rounds so far
+    // one read for the totals of all rounds: a row of 16 lanes holds a round's waves (counts: hits | misses << 16)
+    const uint32_t upto_wave = ess_sel::row_incl_scan(lists_tot[lane]);
+    uint32_t run = 0;                              // the query token's rounds so far
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       if (u >= rounds) break;
       const int t = u / per_t;
       if (u % per_t == 0) run = 0;
-      uint32_t off = run, tot = 0;
-#pragma unroll
-      for (int x = 0; x < BT / 64; ++x) {
-        const uint32_t n = lists_tot[u * (BT / 64) + x];
-        if (x < (tid >> 6)) off += n;
-        tot += n;
-      }
-      off += ex[u];
+      uint32_t off = run;
+      if (wave > 0) off += (uint32_t)__builtin_amdgcn_readlane((int)upto_wave, u * 16 + wave - 1);
       const size_t rowoff = ((size_t)b * T + t) * kk;
       if (sl[u] >= 0) {
-        if (slv[u] < 0) miss_list[rowoff + (off >> 16)] = sl[u];
-        else hit_list[rowoff + (off & 0xffffu)] = sl[u];
+        if (slv[u] < 0) miss_list[rowoff + (off >> 16) + ex[u]] = sl[u];
+        else hit_list[rowoff + (off & 0xffffu) + ex[u]] = sl[u];
       }
-      run += tot;
+      run += (uint32_t)__builtin_amdgcn_readlane((int)upto_wave, u * 16 + 15);
       if (u % per_t == per_t - 1 && tid == 0) {
         n_hit[b * T + t] = (int32_t)(run & 0xffffu);
         n_miss[b * T + t] = (int32_t)(run >> 16);

@@ -32,22 +32,37 @@ __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v, int /*lane*/) {
   return (uint32_t)r;
 }
 
+// The same inside each row of 16 lanes.
+__device__ __forceinline__ uint32_t row_incl_scan(uint32_t v) {
+  const int x = (int)v;
+  int r = x + __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, true);
+  r += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, true);
+  r += __builtin_amdgcn_update_dpp(0, x, 0x113, 0xf, 0xf, true);
+  r += __builtin_amdgcn_update_dpp(0, r, 0x114, 0xf, 0xe, true);
+  r += __builtin_amdgcn_update_dpp(0, r, 0x118, 0xf, 0xc, true);
+  return (uint32_t)r;
+}
+
+// Sum of the first `wave` of NW (at most 16) words of LDS, the same in all lanes; *total the sum of all: each of the first
+// lanes reads one and a row scan adds them up (a dozen instructions; a sum of NW broadcast reads, each with its select, is three times that, and a wave
+// alone issues one in five cycles).
+template <int NW>
+__device__ __forceinline__ uint32_t waves_before(const uint32_t* wave_tot, int wave, int lane, uint32_t* total = nullptr) {
+  static_assert(NW <= 16, "one row of lanes");
+  const int upto = (int)row_incl_scan(lane < NW ? wave_tot[lane] : 0u);
+  if (total) *total = (uint32_t)__builtin_amdgcn_readlane(upto, 15);
+  return wave > 0 ? (uint32_t)__builtin_amdgcn_readlane(upto, wave - 1) : 0u;
+}
+
 // inclusive scan over the NTH threads of the workgroup in thread order; *total gets the sum
 template <int NTH>
 __device__ __forceinline__ uint32_t block_incl_scan(uint32_t v, uint32_t* wave_tot, uint32_t* total) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t inc = wave_incl_scan(v, lane);
   __syncthreads();                         // wave_tot may still be read from a previous call
   if (lane == 63) wave_tot[wave] = inc;
   __syncthreads();
-  uint32_t off = 0, tot = 0;
-#pragma unroll
-  for (int i = 0; i < NTH / 64; ++i) {
-    const uint32_t x = wave_tot[i];
-    if (i < wave) off += x;
-    tot += x;
-  }
-  *total = tot;
+  const uint32_t off = waves_before<NTH / 64>(wave_tot, wave, lane, total);
   return inc + off;
 }
 
