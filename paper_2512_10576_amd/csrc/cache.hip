@@ -672,11 +672,11 @@ __global__ __launch_bounds__(FILL_WPB * 64) void k_fill(const ess_fetch f, uint3
 // runs, these after it.
 constexpr int GATHER_ROWS = 16;
 template <int WHICH>
-__global__ __launch_bounds__(256) void k_gather_rows(const uint8_t* __restrict__ slot_pool,
-                                                     const int32_t* __restrict__ slot_idx, int per_seq, int S,
-                                                     int row_stride, uint8_t* __restrict__ rows_out) {
-  const int b = blockIdx.y, lane = threadIdx.x & 63;
-  const int i0 = (blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6)) * GATHER_ROWS;
+__device__ __forceinline__ void gather_rows(int part, int b, const uint8_t* __restrict__ slot_pool,
+                                            const int32_t* __restrict__ slot_idx, int per_seq, int S,
+                                            int row_stride, uint8_t* __restrict__ rows_out) {
+  const int lane = threadIdx.x & 63;
+  const int i0 = (part * 4 + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6)) * GATHER_ROWS;
   if (i0 >= per_seq) return;
   const int chunks = row_stride >> 4;                        // <= 128
   const bool in = lane < GATHER_ROWS && i0 + lane < per_seq;
@@ -714,6 +714,27 @@ __global__ __launch_bounds__(256) void k_gather_rows(const uint8_t* __restrict__
       if (lane + 64 < chunks) dst[lane + 64] = y[u];
     }
   }
+}
+
+template <int WHICH>
+__global__ __launch_bounds__(256) void k_gather_rows(const uint8_t* __restrict__ slot_pool, const int32_t* __restrict__ slot_idx,
+                                                     int per_seq, int S, int row_stride, uint8_t* __restrict__ rows_out) {
+  gather_rows<WHICH>(blockIdx.x, blockIdx.y, slot_pool, slot_idx, per_seq, S, row_stride, rows_out);
+}
+
+// The fetch and the gather of the rows that were resident in one launch (see ess_fetch for the roles): the two touch different
+// slots.  `parts` workgroups gather a sequence.
+__global__ __launch_bounds__(256) void k_fill_gather(const ess_fetch f, const int32_t* __restrict__ slot_idx, int per_seq, int parts,
+                                                     uint8_t* __restrict__ rows_out) {
+  extern __shared__ int32_t pref[];                          // [B + 1]
+  const int i = blockIdx.x, low = i & 7;
+  if (low < 2) {
+    const int wg = 2 * (i >> 3) + low;
+    if (wg < f.wgs) ess_fill::entries<2>(f, pref, wg * 4 + (int)(threadIdx.x >> 6), f.wgs * 4);
+    return;
+  }
+  const int item = 6 * (i >> 3) + low - 2, b = item / parts;
+  if (b < f.B) gather_rows<1>(item - b * parts, b, f.slot_pool, slot_idx, per_seq, f.S, f.row_stride, rows_out);
 }
 
 // Append (Sec. 3.3): the entries a step produced enter the caches.  One workgroup per sequence; for each
@@ -993,10 +1014,20 @@ int ess_launch_fill(ess_ctx* ctx, const ess_cache& cache, int B, hipStream_t st,
   return ESS_OK;
 }
 
-int ess_launch_gather_rows(const ess_config& c, const uint8_t* slot_pool, const int32_t* slot_idx, int B, int T,
-                           uint8_t* rows_out, hipStream_t st, int which, hipEvent_t done) {
-  auto kern = which == 0 ? &k_gather_rows<0> : (which == 1 ? &k_gather_rows<1> : &k_gather_rows<2>);
+// which: 0 every row, 1 the rows that were resident, with the fetch of the others in the same launch, 2 the fetched ones
+int ess_launch_gather_rows(ess_ctx* ctx, const ess_cache& cache, const int32_t* slot_idx, int B, int T, uint8_t* rows_out, hipStream_t st, int which) {
+  const ess_config& c = ctx->cfg;
   const int wgs = (T * c.topk + 4 * GATHER_ROWS - 1) / (4 * GATHER_ROWS);
-  ESS_HIP(ess_launch_done(done, kern, dim3(wgs, B), dim3(256), 0, st, slot_pool, slot_idx, T * c.topk, c.slots_per_seq, c.row_stride, rows_out));
+  if (which == 1) {
+    const int fetch_wgs = 2 * 64;                             // of 4 waves: the bytes in flight of the fetch kernel's 64
+    const long gather = ((long)wgs * B + 5) / 6;              // groups of eight workgroups
+    const long groups = gather > fetch_wgs / 2 ? gather : fetch_wgs / 2;
+    hipLaunchKernelGGL(k_fill_gather, dim3((unsigned)(groups * 8)), dim3(256), (size_t)(B + 1) * sizeof(int32_t), st,
+                       ess_fetch_of(ctx, cache, B, 0, fetch_wgs), slot_idx, T * c.topk, wgs, rows_out);
+  } else {
+    auto kern = which == 0 ? &k_gather_rows<0> : &k_gather_rows<2>;
+    hipLaunchKernelGGL(kern, dim3(wgs, B), dim3(256), 0, st, cache.slot_pool, slot_idx, T * c.topk, c.slots_per_seq, c.row_stride, rows_out);
+  }
+  ESS_HIP(hipGetLastError());
   return ESS_OK;
 }

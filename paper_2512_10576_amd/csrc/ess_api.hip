@@ -545,30 +545,21 @@ int ess_gather_latent(ess_ctx* ctx, const ess_cache* cache, const int32_t* idx, 
   if (step < 1) return ess_fail(ESS_ERR_INVALID_ARG, "step must be >= 1");
   (void)ctx_len;                                // visibility was already applied by the selection
   hipStream_t st = static_cast<hipStream_t>(stream);
-  // Rows of less than 32 MiB: the time their gather takes (2 bytes moved per byte, about 5 TB/s) is less than what the
-  // second stream costs, whatever the misses.  Overlapped against in line, us: one sequence, 2048 rows of 1152 bytes,
-  // 30 misses 50 against 28; 21 MB and 300 misses a sequence 100 against 99; 32 MB and 100 misses 68 against 68; 57 MB
-  // and 100 misses 88 against 91; 75 MB 171 against 180 at 200 misses (but 70 against 65 at 30).
-  const bool small = (size_t)B * T * ctx->cfg.topk * ctx->cfg.row_stride < ((size_t)32 << 20);
-  if (!rows_out || !cache->host_pool_dev || small || (ctx->cfg.flags & ESS_FLAG_SERIAL)) {
+  if (!rows_out || !cache->host_pool_dev || (ctx->cfg.flags & ESS_FLAG_SERIAL)) {
     bool pending = false;
     rc = run_cache_step(ctx, *cache, idx, B, T, ctx->cfg.topk, step, slot_idx, miss_count, st, &pending, 0, -1);
     if (rc != ESS_OK || !rows_out) return rc;
-    return ess_launch_gather_rows(ctx->cfg, cache->slot_pool, slot_idx, B, T, rows_out, st);
+    return ess_launch_gather_rows(ctx, *cache, slot_idx, B, T, rows_out, st, 0);
   }
-  // The rows that were resident are gathered on the side stream while the fetch runs; behind it only the fetched ones are
-  // left (batch 32 x 64K, 340 misses of 2048 per sequence: 10 us instead of 30).
+  // The rows that were resident are gathered beside the fetch, by the same launch; behind it only the fetched ones are left
+  // (batch 32 x 64K, 340 misses of 2048 per sequence: 10 us instead of 30).  Against the gather on a second stream (32 MiB of rows and
+  // more; less: fetch and gather in line), us: one sequence, 2048 rows, 30 misses 22.8 / 23.9; two tokens, 200 misses 23.8
+  // / 30.1; 21 MB of rows, 300 misses a sequence 81 / 86; 33 MB, 100 misses 53 / 61; 75 MB, 30 misses 45 / 66; 75 MB,
+  // 200 misses 161 / 168; batch 32 x 64K 277.5 / 281.2 (all but the last: 2 to 4 us of it the bookkeeping's).
   rc = ess_launch_bookkeeping(ctx, *cache, idx, B, T, ctx->cfg.topk, step, slot_idx, miss_count, st, 0, true,
-                              ess_xcd{nullptr, 0, nullptr, 0}, nullptr, 0, ctx->ev_book[0], ctx->slot_idx_ws);
-  if (rc != ESS_OK) return rc;
-  ESS_HIP(hipStreamWaitEvent(ctx->side, ctx->ev_book[0], 0));
-  rc = ess_launch_gather_rows(ctx->cfg, cache->slot_pool, ctx->slot_idx_ws, B, T, rows_out, ctx->side, 1, ctx->ev_fill[0]);
-  if (rc != ESS_OK) return rc;
-  if ((rc = ess_launch_fill(ctx, *cache, B, st)) != ESS_OK) return rc;
-  rc = ess_launch_gather_rows(ctx->cfg, cache->slot_pool, ctx->slot_idx_ws, B, T, rows_out, st, 2);
-  if (rc != ESS_OK) return rc;
-  ESS_HIP(hipStreamWaitEvent(st, ctx->ev_fill[0], 0));
-  return ESS_OK;
+                              ess_xcd{nullptr, 0, nullptr, 0}, nullptr, 0, nullptr, ctx->slot_idx_ws);
+  if (rc == ESS_OK) rc = ess_launch_gather_rows(ctx, *cache, ctx->slot_idx_ws, B, T, rows_out, st, 1);
+  return rc != ESS_OK ? rc : ess_launch_gather_rows(ctx, *cache, ctx->slot_idx_ws, B, T, rows_out, st, 2);
 }
 
 int ess_sparse_mla_decode(ess_ctx* ctx, const void* q_bf16, const uint8_t* slot_pool, const int32_t* slot_idx,

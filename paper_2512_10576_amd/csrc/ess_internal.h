@@ -312,8 +312,7 @@ int ess_launch_fill(ess_ctx* ctx, const ess_cache& cache, int B, hipStream_t st,
                     uint32_t only_xcds = 0, uint32_t* ticket = nullptr, hipEvent_t done = nullptr);
 // which: 0 all entries of slot_idx; of a list with fetched entries marked (ESS_FRESH_BIT), 1 the others, 2 the marked ones
 #define ESS_FRESH_BIT 0x40000000
-int ess_launch_gather_rows(const ess_config& c, const uint8_t* slot_pool, const int32_t* slot_idx, int B, int T,
-                           uint8_t* rows_out, hipStream_t st, int which = 0, hipEvent_t done = nullptr);
+int ess_launch_gather_rows(ess_ctx* ctx, const ess_cache& cache, const int32_t* slot_idx, int B, int T, uint8_t* rows_out, hipStream_t st, int which);
 // attention over list[b,t,0..n) (n = n_list[b,t], or k when n_list is NULL), written as `nsplit`
 // partial results starting at partial index `split0` of the row's `pitch`
 int ess_launch_attn_partial(ess_ctx* ctx, const void* q, const uint8_t* slot_pool, const int32_t* list,

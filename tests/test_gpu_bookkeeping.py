@@ -1,6 +1,7 @@
 """Look-up and LRU update where the kernel's work changes shape: pools that end inside a group of 64 slots or fill the last
 one, more slots at the victims' threshold stamp than fit one list (a new pool), more misses than one list holds, stamps
-older than 254 steps, selections that are not whole rounds of the workgroup, several bitmap words a thread."""
+older than 254 steps, selections that are not whole rounds of the workgroup, several bitmap words a thread.  And the selected
+rows, whose gather shares a launch with the fetch, from a few workgroups up, ragged."""
 import numpy as np
 import pytest
 import torch
@@ -29,7 +30,8 @@ def test_lookup_and_update_against_oracle(ess_lib, L, S, k, T, kept, first):
     print("bookkeeping:", L, S, k, T, kept, first, flush=True)
     B = 2
     hp = torch.empty((B, L, 656), dtype=torch.uint8, pin_memory=True)
-    hp.zero_()
+    hp.copy_(torch.randint(0, 256, (L, 656), generator=torch.Generator().manual_seed(4), dtype=torch.uint8))
+    hp[1].add_(1)                           # sequences differ
     ctx_len = torch.tensor([L, L - 7], dtype=torch.int32)
     ctx = bnd.Context(bnd.make_config(max_batch=B, max_q_tokens=T, max_ctx=L, idx_heads=4, idx_dim=32, topk=k, attn_heads=8,
                                       slots_per_seq=S, latent_fmt=1))
@@ -38,16 +40,22 @@ def test_lookup_and_update_against_oracle(ess_lib, L, S, k, T, kept, first):
     oc = O.SlotCache(B, L, S)
     trace = synth.TopkTrace(9, ctx_len, T, k, kept, zipf_s=0.2)
     slot_idx = torch.empty((B, T, k), dtype=torch.int32, device="cuda")
+    rows = torch.empty((B, T, k, 656), dtype=torch.uint8, device="cuda")
     mc = torch.empty((B,), dtype=torch.int32, device="cuda")
     for step in range(first, first + 14):
         idx = trace.next()
         if step == first + 5:
             idx[1] = -1                   # a sequence that selects nothing
         r = oc.step(idx.numpy(), step)
-        ctx.gather_latent(cache, idx.cuda(), ctx_len.cuda(), step, slot_idx, None, mc)
+        ctx.gather_latent(cache, idx.cuda(), ctx_len.cuda(), step, slot_idx, rows, mc)
         torch.cuda.synchronize()
         assert np.array_equal(mc.cpu().numpy(), r["miss_count"]), step
         assert np.array_equal(slot_idx.cpu().numpy(), r["slot_idx"]), step
         assert np.array_equal(cache.token_of.cpu().numpy(), oc.token_of), step
         assert np.array_equal(cache.stamp.cpu().numpy().astype(np.int64), oc.stamp.astype(np.int64)), step
+        # the rows of the selection, gathered beside the fetch and behind it: bytes of the host pool, zeros where nothing is selected
+        sel = idx.long()
+        want = torch.stack([hp[b][sel[b].clamp(min=0)] for b in range(B)])
+        want[sel < 0] = 0
+        assert torch.equal(rows.cpu(), want), step
     ctx.close()
