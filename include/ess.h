@@ -218,9 +218,9 @@ int ess_topk_static(const float* score, const int32_t* ctx_len, int32_t B, int32
  *   slot_idx [B,T,k]  slot of every selected entry after the step (-1 where idx is -1)
  *   rows_out [B,T,k,row_stride] or NULL: the selected rows, gathered (zero where idx is -1)
  *   miss_count [B] or NULL
- * Everything runs on `stream`.  With rows_out and a host pool, and without
- * ESS_FLAG_SERIAL, the rows of resident entries are gathered beside the fetch
- * (one launch) and those of fetched ones behind it. */
+ * Everything runs on `stream`.  With rows_out of 32 MiB or more and a host pool,
+ * and without ESS_FLAG_SERIAL, the rows of resident entries are gathered beside
+ * the fetch (one launch) and those of fetched ones behind it. */
 int ess_gather_latent(ess_ctx* ctx, const ess_cache* cache, const int32_t* idx, const int32_t* ctx_len,
                       int32_t B, int32_t T, uint32_t step, int32_t* slot_idx, uint8_t* rows_out,
                       int32_t* miss_count, void* stream);

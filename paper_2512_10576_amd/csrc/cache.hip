@@ -48,8 +48,7 @@ constexpr int BOOK_CNT = 2048;       // [256 digits][16 waves] bytes: the list's
 constexpr int BOOK_LISTS = 6144;     // [4][16] totals of the hit / miss lists (a longer list of victims is done with by then)
 constexpr int BOOK_BELOW = 7168;     // [256] victims of smaller digits
 constexpr int BOOK_PRE = 7424;       // [1024] 16 bits each: misses in front of a thread's bitmap words
-constexpr int BOOK_HITS = 7680;      // [512] bitmap of the slots that were hit, before the histogram (pools up to 16384 slots)
-static_assert(BOOK_PRE + BT / 2 <= BOOK_HIST_BYTES / 4 && BOOK_HITS + 16 * BT / 32 <= BOOK_HIST_BYTES / 4, "book layout");
+static_assert(BOOK_PRE + BT / 2 <= BOOK_HIST_BYTES / 4, "book layout");
 inline int book_pow2(int n) { int p = 1; while (p < n) p <<= 1; return p; }
 inline size_t book_words(int max_ctx) { return (size_t)(((max_ctx + 31) / 32 + 1) & ~1); }
 inline size_t book_union_bytes(int sel_cap) {
@@ -88,14 +87,13 @@ __device__ __forceinline__ uint32_t lanes_below(uint64_t mask) {
 
 // idx: [B, T, kk] selected positions (-1 = none).  Dynamic LDS: bitmap of Lmax bits.
 // REG: pools up to 16384 slots.  A wave owns a contiguous range of slots, 64 of them (one a lane) at a time, at most
-// 16 times: the stamps are read once, whole lines at a time and at the kernel's start, while the selection is looked
-// up, and held in registers; hits are marked in an LDS bitmap, from which the owners of the slots stamp them.  A thread that owns up
-// to 16 consecutive slots instead makes a load of a wave touch some 30 lines, and stamping the hits by a scattered store
-// each puts those stores in front of the stamps' loads.  What bounds the kernel then: two dependent trips to memory (5 us) and
-// the instructions of 16 waves on one CU (four to a SIMD: each costs all of them 16 cycles), hence the counts by ballot and the
-// sums over waves by one row of lanes.  One sequence, cycles at 2.4 GHz, threads owning consecutive slots / this: 8192 slots,
-// 190 misses 40500 / 32500; 6554 slots, 360 misses 34300 / 31800; 9001 slots, two tokens, 110 misses 39600 / 35000; 13108
-// slots, two tokens, 420 misses 66300 / 56000.
+// 16 times: the stamps are read once, whole lines at a time, and held in registers.  (Sixteen consecutive slots a thread make a
+// load of a wave touch some 30 lines.)  What bounds the kernel: two dependent trips to memory (5 us) and the instructions of
+// 16 waves on one CU (four to a SIMD: each costs all of them 16 cycles), hence the counts by ballot and the sums over waves by
+// one row of lanes.  One sequence, cycles at 2.4 GHz, threads owning consecutive slots / this: 8192 slots, 190 misses
+// 40500 / 32500; 6554 slots, 360 misses 34300 / 31800; 9001 slots, two tokens, 110 misses 39600 / 35000; 13108 slots,
+// two tokens, 420 misses 66300 / 56000.  (Reading the stamps at the start, beside the look-up, with an LDS bitmap of the
+// hit slots instead of a store each: the same with misses, 3 us longer where there are none.)
 template <bool REG, bool DYN>
 __global__ __launch_bounds__(BT) void k_bookkeeping(
     const int32_t* __restrict__ idx, int T, int kk, int Lmax, int S, int32_t* __restrict__ slot_of,
@@ -140,7 +138,7 @@ __global__ __launch_bounds__(BT) void k_bookkeeping(
   uint32_t sr[RS];
   for (int j = tid; j < W; j += BT) bm[j] = 0;
   {
-    uint2* const h2 = reinterpret_cast<uint2*>(s_hist);          // the counters of the age pass, and the bitmap of hit slots among them
+    uint2* const h2 = reinterpret_cast<uint2*>(s_hist);          // the counters of the age pass
     for (int j = tid; j < BOOK_HIST_BYTES / 8; j += BT) h2[j] = make_uint2(0, 0);
   }
   // look-up straight from the selection list (all gathers of a thread in flight together): hits get
@@ -151,7 +149,6 @@ __global__ __launch_bounds__(BT) void k_bookkeeping(
   if (tid == 0) sm.sel_upto = 0xffffffffu;       // (stays so where a step has too few slots that it may evict)
   uint32_t my_valid = 0;
   int sv[4] = {-1, -1, -1, -1}, slv[4] = {-1, -1, -1, -1};
-  uint32_t* const s_hits = s_hist + BOOK_HITS;
   auto select = [&](int e0) {
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
@@ -172,22 +169,12 @@ __global__ __launch_bounds__(BT) void k_bookkeeping(
       if (sv[u] < 0) continue;
       ++my_valid;
       if (slv[u] < 0) atomicOr(&bm[sv[u] >> 5], 1u << (sv[u] & 31));
-      else if constexpr (REG) atomicOr(&s_hits[slv[u] >> 5], 1u << (slv[u] & 31));
       else stp[slv[u]] = step;
     }
   };
   select(0);
   look_up();
-  if constexpr (REG) {
-    const int left = min(S - ws, 64 * nj_reg);
-#pragma unroll
-    for (int j = 0; j < RS; ++j) {
-      sr[j] = 0xffffffffu;                       // never evictable
-      if (64 * j + 64 <= left) sr[j] = stp[ws + 64 * j + lane];
-      else if (64 * j < left && 64 * j + lane < left) sr[j] = stp[ws + 64 * j + lane];
-    }
-  }
-  __syncthreads();                               // bitmaps are clear
+  __syncthreads();                               // the bitmap is clear
   mark();
   for (int e0 = 4 * BT; e0 < nsel; e0 += 4 * BT) {
     select(e0);
@@ -195,23 +182,6 @@ __global__ __launch_bounds__(BT) void k_bookkeeping(
     mark();
   }
   __syncthreads();
-  if constexpr (REG) {
-    // hits get their stamp; the bitmap's words of a wave are read and cleared by that wave alone
-    uint32_t* const mine = s_hits + wave * 2 * nj_reg;
-    const uint32_t word = lane < 2 * nj_reg ? mine[lane] : 0u;
-    if (lane < 2 * nj_reg) mine[lane] = 0;
-#pragma unroll
-    for (int j = 0; j < RS; ++j) {
-      if (j >= nj_reg) continue;
-      const uint64_t hit = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)word, 2 * j) |
-                           ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)word, 2 * j + 1) << 32);
-      if (__builtin_amdgcn_inverse_ballot_w64(hit)) {
-        sr[j] = step;
-        stp[ws + 64 * j + lane] = step;
-      }
-    }
-  }
-
   // misses in ascending position: prefix sum over the bitmap words (a thread's words: a power of two of them)
   int wsh = 0;
   while ((BT << wsh) < W) ++wsh;
@@ -235,7 +205,7 @@ __global__ __launch_bounds__(BT) void k_bookkeeping(
       }
     }
   }
-  if constexpr (!REG) __syncthreads();           // the stamps of the hits are visible
+  __syncthreads();                               // the stamps of the hits are visible
 
   // the counts leave here, so that their way to memory (and to the host) passes beside the work below
   if (tid == 0) {
@@ -267,6 +237,15 @@ __global__ __launch_bounds__(BT) void k_bookkeeping(
   const bool by_rank = m <= (uint32_t)BT;
   uint16_t* const s_pre = reinterpret_cast<uint16_t*>(s_hist + BOOK_PRE);
   if (m > 0) {
+    if constexpr (REG) {
+      const int left = min(S - ws, 64 * nj_reg);
+#pragma unroll
+      for (int j = 0; j < RS; ++j) {
+        sr[j] = 0xffffffffu;                       // never evictable
+        if (64 * j + 64 <= left) sr[j] = stp[ws + 64 * j + lane];
+        else if (64 * j < left && 64 * j + lane < left) sr[j] = stp[ws + 64 * j + lane];
+      }
+    }
     // (larger pools) this thread's slots: [v0, v1), contiguous so that slot order is thread order
     const int v0 = min(tid * nj_reg, S), v1 = min(v0 + nj_reg, S);
     // f(stamp) of every slot this thread owns
@@ -380,27 +359,35 @@ __global__ __launch_bounds__(BT) void k_bookkeeping(
     } else
     if constexpr (REG) {
       // counts of the wave by ballot, 16 bits each (at most 16384 slots)
-      uint32_t n_both = 0;
+      uint32_t n_eq = 0, n_lt = 0;
 #pragma unroll
-      for (int j = 0; j < RS; ++j)                         // (never a victim: what lies past the pool)
-        n_both += (uint32_t)__popcll(__ballot(sr[j] == tau)) | ((uint32_t)__popcll(__ballot(sr[j] < tau)) << 16);
-      if (lane == 0) sm.wave_tot2[wave] = n_both;
+      for (int j = 0; j < RS; ++j)
+        if (j < nj_reg) {
+          n_eq += (uint32_t)__popcll(__ballot(sr[j] == tau));
+          n_lt += (uint32_t)__popcll(__ballot(sr[j] < tau));
+        }
+      if (lane == 0) sm.wave_tot2[wave] = n_eq | (n_lt << 16);
       __syncthreads();
       const uint32_t before = ess_sel::waves_before<BT / 64>(sm.wave_tot2, wave, lane);
-      uint32_t rank = before & 0xffffu;                    // slots at the threshold stamp in front of the next 64
-      uint32_t at = (before >> 16) + min(rank, need);      // victims in front of them
+      uint32_t left = need - min(before & 0xffffu, need);            // slots at the threshold stamp still to be taken
+      uint32_t at = (before >> 16) + need - left;                    // victims in front of the next 64 slots
 #pragma unroll
       for (int j = 0; j < RS; ++j) {
-        asm volatile("" : "+v"(sr[j]));                    // (the masks of the counts are not worth keeping)
-        const uint64_t eq = __ballot(sr[j] == tau);
-        const uint64_t take = __ballot(sr[j] < tau || (sr[j] == tau && rank + lanes_below(eq) < need));
+        if (j >= nj_reg) continue;
+        asm volatile("" : "+v"(sr[j]));                              // (the masks of the counts are not worth keeping)
+        uint64_t take = __ballot(sr[j] < tau);
+        if (left > 0) {
+          uint64_t eq = __ballot(sr[j] == tau);
+          if ((uint32_t)__popcll(eq) > left) eq = __ballot(sr[j] == tau && lanes_below(eq) < left);
+          left -= (uint32_t)__popcll(eq);
+          take |= eq;
+        }
         if (take) {
           const uint32_t i = at + lanes_below(take);
-          if (((take >> lane) & 1u) && i < (uint32_t)vict_cap)
+          if (__builtin_amdgcn_inverse_ballot_w64(take) && i < (uint32_t)vict_cap)
             s_vict[i] = ((unsigned long long)sr[j] << 32) | (uint32_t)(ws + 64 * j + lane);
+          at += (uint32_t)__popcll(take);
         }
-        rank += (uint32_t)__popcll(eq);
-        at += (uint32_t)__popcll(take);
       }
     } else {
       uint32_t my_eq = 0, my_lt = 0;

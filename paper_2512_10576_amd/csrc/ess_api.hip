@@ -545,17 +545,20 @@ int ess_gather_latent(ess_ctx* ctx, const ess_cache* cache, const int32_t* idx, 
   if (step < 1) return ess_fail(ESS_ERR_INVALID_ARG, "step must be >= 1");
   (void)ctx_len;                                // visibility was already applied by the selection
   hipStream_t st = static_cast<hipStream_t>(stream);
-  if (!rows_out || !cache->host_pool_dev || (ctx->cfg.flags & ESS_FLAG_SERIAL)) {
+  // Rows of less than 32 MiB: fetch, then gather.  In two passes beside the fetch and behind it a small gather takes its latency
+  // twice, which a call that misses nothing has no fetch to hide (one sequence, two tokens, 4096 rows: 18 us against 21;
+  // with 200 misses 32 against 28.5).
+  const bool small = (size_t)B * T * ctx->cfg.topk * ctx->cfg.row_stride < ((size_t)32 << 20);
+  if (!rows_out || !cache->host_pool_dev || small || (ctx->cfg.flags & ESS_FLAG_SERIAL)) {
     bool pending = false;
     rc = run_cache_step(ctx, *cache, idx, B, T, ctx->cfg.topk, step, slot_idx, miss_count, st, &pending, 0, -1);
     if (rc != ESS_OK || !rows_out) return rc;
     return ess_launch_gather_rows(ctx, *cache, slot_idx, B, T, rows_out, st, 0);
   }
   // The rows that were resident are gathered beside the fetch, by the same launch; behind it only the fetched ones are left
-  // (batch 32 x 64K, 340 misses of 2048 per sequence: 10 us instead of 30).  Against the gather on a second stream (32 MiB of rows and
-  // more; less: fetch and gather in line), us: one sequence, 2048 rows, 30 misses 22.8 / 23.9; two tokens, 200 misses 23.8
-  // / 30.1; 21 MB of rows, 300 misses a sequence 81 / 86; 33 MB, 100 misses 53 / 61; 75 MB, 30 misses 45 / 66; 75 MB,
-  // 200 misses 161 / 168; batch 32 x 64K 277.5 / 281.2 (all but the last: 2 to 4 us of it the bookkeeping's).
+  // (batch 32 x 64K, 340 misses of 2048 per sequence: 10 us instead of 30).  Against the gather on a second stream, us: 33 MB of rows, 100
+  // misses a sequence 53 / 61; 38 MB, none 27 / 48; 75 MB, 30 misses 45 / 66; 75 MB, 200 misses 161 / 168; batch 32 x 64K
+  // 277.5 / 281.2 (in all but the last 2 to 4 us of it are the look-up's).
   rc = ess_launch_bookkeeping(ctx, *cache, idx, B, T, ctx->cfg.topk, step, slot_idx, miss_count, st, 0, true,
                               ess_xcd{nullptr, 0, nullptr, 0}, nullptr, 0, nullptr, ctx->slot_idx_ws);
   if (rc == ESS_OK) rc = ess_launch_gather_rows(ctx, *cache, ctx->slot_idx_ws, B, T, rows_out, st, 1);

@@ -1,7 +1,7 @@
 """Look-up and LRU update where the kernel's work changes shape: pools that end inside a group of 64 slots or fill the last
 one, more slots at the victims' threshold stamp than fit one list (a new pool), more misses than one list holds, stamps
 older than 254 steps, selections that are not whole rounds of the workgroup, several bitmap words a thread.  And the selected
-rows, whose gather shares a launch with the fetch, from a few workgroups up, ragged."""
+rows, whose gather shares a launch with the fetch from 32 MiB of them on (odd batch, ragged last workgroups)."""
 import numpy as np
 import pytest
 import torch
@@ -58,4 +58,35 @@ def test_lookup_and_update_against_oracle(ess_lib, L, S, k, T, kept, first):
         want = torch.stack([hp[b][sel[b].clamp(min=0)] for b in range(B)])
         want[sel < 0] = 0
         assert torch.equal(rows.cpu(), want), step
+    ctx.close()
+
+
+@pytest.mark.parametrize("B,k,missing", [(27, 2047, 2047), (13, 2600, 40), (13, 2600, 0)])
+def test_rows_gathered_beside_the_fetch(ess_lib, B, k, missing):
+    """every entry fetched, a few, none; rows that end inside a workgroup's share"""
+    from paper_2512_10576_amd import binding as bnd
+    print("rows beside the fetch:", B, k, missing, flush=True)
+    L, S = 6000, 2700
+    assert B * k * 1152 >= 32 << 20
+    hp = torch.empty((B, L, 1152), dtype=torch.uint8, pin_memory=True)
+    hp.copy_(torch.randint(0, 256, (B, L, 1152), generator=torch.Generator().manual_seed(4), dtype=torch.uint8))
+    ctx = bnd.Context(bnd.make_config(max_batch=B, max_q_tokens=1, max_ctx=L, idx_heads=4, idx_dim=32, topk=k, attn_heads=8,
+                                      slots_per_seq=S, latent_fmt=0))
+    cache = bnd.Cache.allocate(ctx.cfg, B, host_pool=hp)
+    ctx.cache_reset(cache, B)
+    ctx_len = torch.full((B,), L, dtype=torch.int32, device="cuda")
+    slot_idx = torch.empty((B, 1, k), dtype=torch.int32, device="cuda")
+    rows = torch.empty((B, 1, k, 1152), dtype=torch.uint8, device="cuda")
+    mc = torch.empty((B,), dtype=torch.int32, device="cuda")
+    for step in range(1, 4):
+        idx = (torch.arange(k, dtype=torch.int32) + (step - 1) * missing) % L
+        idx = idx.expand(B, 1, k).contiguous()
+        idx[B - 1, 0, k // 2] = -1
+        rows.fill_(7)
+        ctx.gather_latent(cache, idx.cuda(), ctx_len, step, slot_idx, rows, mc)
+        torch.cuda.synchronize()
+        assert int(mc[0]) == (k if step == 1 else missing), step
+        want = hp[:, idx[0, 0].long()].clone()
+        want[B - 1, k // 2] = 0
+        assert torch.equal(rows.cpu()[:, 0], want), step
     ctx.close()
