@@ -167,3 +167,69 @@ def test_topk_kernels_do_not_spill(tmp_path):
     assert {mode for mode, _ in found} >= {0, 1, 2, 3} and len(found) % 2 == 0
     spills = {form: n for form, n in found.items() if form[0] != 3 and n}
     assert not spills, spills
+
+
+def _isa(tmp_path, source):
+    import subprocess
+    from paper_2512_10576_amd import build
+    out = tmp_path / source.replace(".hip", ".s")
+    subprocess.run([build._hipcc(), *build.compile_flags(source), "-S", "--cuda-device-only", os.path.join(build.CSRC, source), "-o", str(out)],
+                   check=True, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)
+    return out.read_text().split("\n")
+
+
+def _sgprs(operand):
+    m = re.match(r"s\[(0x[0-9a-f]+|\d+):(0x[0-9a-f]+|\d+)\]$", operand)
+    if m:
+        return set(range(int(m[1], 0), int(m[2], 0) + 1))
+    m = re.match(r"s(\d+)$", operand)
+    return {int(m[1])} if m else set()
+
+
+def _wait_states_before_gathers(lines, start, end):
+    """For every memory instruction inside an asm statement that reads scalar registers: the wait states between the last
+    vector ALU instruction in front of it that wrote one of them and the instruction (None: none within 40)."""
+    body, in_asm, got = [], False, []
+    for l in lines[start:end]:
+        t = l.strip()
+        if t.startswith((";;#ASMSTART", ";;#ASMEND")):
+            in_asm = t.startswith(";;#ASMSTART")
+            continue
+        t = t.split(";")[0].strip()
+        if not t or t.startswith(".") or t.endswith(":"):
+            continue
+        if in_asm and re.match(r"(global|buffer)_", t):
+            used = set().union(*(_sgprs(o.split()[0]) for o in t.split(None, 1)[1].split(", ")))
+            states, found = 0, None
+            for prev in reversed(body[-40:]):
+                name, ops = (prev.split(None, 1) + [""])[:2]
+                ops = ops.split(", ")
+                if name == "s_nop":
+                    states += int(ops[0]) + 1
+                    continue
+                written = _sgprs(ops[0]) | (_sgprs(ops[1]) if re.search("_co_|_u64_u32|_i64_i32|div_scale", name) else set())
+                if name.startswith("v_") and written & used:
+                    found = states
+                    break
+                states += 1
+            if used:
+                got.append((found, body[-6:] + [t]))
+        body.append(t)
+    return got
+
+
+@pytest.mark.parametrize("source,kernel", [("sparse_mla.hip", "k_attn_partial_tr"), ("sparse_mla_h32.hip", "k_attn_h32")])
+def test_gathers_wait_for_their_scalar_addresses(tmp_path, source, kernel):
+    """A memory instruction may read a scalar register that a vector ALU instruction (v_readlane) wrote only five wait states
+    later.  The compiler sees to that, but not inside asm statements, which the gathers of the attention kernels are.  Checked
+    in the ISA of all instances; also: no instance spills registers to scratch memory."""
+    lines = _isa(tmp_path, source)
+    starts = [i for i, l in enumerate(lines) if re.match(r"^_ZN\S*%s\S*:" % kernel, l)]
+    assert len(starts) == 4                      # one instance per entry format and per way of taking work
+    for start in starts:
+        end = [i for i in range(start, len(lines)) if lines[i].startswith(".Lfunc_end")][0]
+        assert re.search(r"; ScratchSize: 0\b", "\n".join(lines[end:end + 80])), "the attention kernel spills registers to scratch memory"
+        gathers = _wait_states_before_gathers(lines, start, end)
+        assert len(gathers) >= 16
+        for states, text in gathers:
+            assert states is None or states >= 5, "\n".join(text)
