@@ -271,14 +271,21 @@ int ess_last_overlap(const ess_ctx* ctx, int32_t* mode);
  * ends with a device-side assertion that every launch handed out at least as many tickets as it had
  * work items; a failure is reported, as ESS_ERR_INTERNAL, by the next ess_decode_step or
  * ess_get_stats on the context, and the context confines nothing from then on.
- * ess_last_confined: fetches of the latest ess_decode_step that were confined (0, 1 or 2).
- * ess_selfcheck_inject: test hook.  The assertion of the next confined step expects `extra_items`
- * more work items than there are, so that it fails (for extra_items > the workgroups of the launch)
- * although the step itself is complete; every kernel runs and ends as usual.
+ * In the DA schedule a fetch that would be confined, and one so short that it would otherwise run in
+ * front of Attn0, may travel with Attn0 in one launch: of every eight consecutive workgroups two fetch
+ * and six take attention items by their number.  Such a step takes no tickets and asserts nothing.
+ * ess_last_confined: fetches of the latest ess_decode_step that were long enough to be confined (0, 1
+ * or 2; those that travelled with Attn0 among them).
+ * ess_last_carried: 1 if the fetch of the latest ess_decode_step travelled with Attn0, else 0.
+ * ess_selfcheck_inject: test hook.  The assertion of the next confined step (which then carries no
+ * fetch) expects `extra_items` more work items than there are, so that it fails (for extra_items > eight
+ * times the workgroups of the launch) although the step itself is complete; every kernel runs and ends
+ * as usual.
  * ess_debug_ticket_grid: test hook.  Ticket-fed launches (and confined fetches) of later steps use
  * exactly `workgroups` workgroups, whatever their number of work items (0 = the library's own
  * sizing); results are the same for every value >= 1. */
 int ess_last_confined(const ess_ctx* ctx, int32_t* fetches);
+int ess_last_carried(const ess_ctx* ctx, int32_t* carried);
 int ess_selfcheck_inject(ess_ctx* ctx, int32_t extra_items);
 int ess_debug_ticket_grid(ess_ctx* ctx, int32_t workgroups);
 

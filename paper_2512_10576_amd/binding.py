@@ -96,6 +96,7 @@ def load() -> C.CDLL:
         "ess_set_overlap_threshold": [vp, i32],
         "ess_last_overlap": [vp, C.POINTER(i32)],
         "ess_last_confined": [vp, C.POINTER(i32)],
+        "ess_last_carried": [vp, C.POINTER(i32)],
         "ess_selfcheck_inject": [vp, i32],
         "ess_debug_ticket_grid": [vp, i32],
         "ess_calib_memcpy_rows": [vp, vp, vp, C.c_int64, i32, i32, vp],
@@ -299,10 +300,16 @@ class Context:
         return m.value
 
     def last_confined(self) -> int:
-        """fetches of the latest decode_step that were confined to part of the XCDs (0, 1 or 2)"""
+        """fetches of the latest decode_step that were long enough to be confined to part of the XCDs (0, 1 or 2)"""
         m = C.c_int32(-1)
         _check(self.lib.ess_last_confined(self.h, C.byref(m)))
         return m.value
+
+    def last_carried(self) -> bool:
+        """the fetch of the latest decode_step travelled with Attn0 in one launch"""
+        m = C.c_int32(-1)
+        _check(self.lib.ess_last_carried(self.h, C.byref(m)))
+        return bool(m.value)
 
     def selfcheck_inject(self, extra_items: int) -> None:
         """test hook: the self-check of the next confined step expects extra_items more work items"""

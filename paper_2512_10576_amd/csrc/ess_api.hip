@@ -419,6 +419,7 @@ int ess_create(const ess_config* cfg, ess_ctx** out) {
   ctx->auto_threshold = 150;
   ctx->auto_calibrated = false;
   ctx->last_confined = 0;
+  ctx->last_carried = 0;
   ctx->check_extra = 0;
   *out = ctx;
   return ESS_OK;
@@ -704,10 +705,12 @@ int ess_decode_step(ess_ctx* ctx, const ess_cache* cache, const ess_step_args* a
   }
   // Attn0 and the fetch in one launch (see ess_fetch), nothing on the side stream: no event behind the bookkeeping (4 us until
   // what follows it starts), no wait for the other stream in front of Attn1 (6 us, 11 where Attn0 ends last), and a short
-  // fetch runs beside Attn0 instead of in front of it.  Not for launches of a given size (test hook) or with the two timed apart.
-  const bool carried = mean_miss >= 0 && da_swap && ctx->xcds_even && (confine_da || da_short) && ctx->ticket_grid == 0 &&
+  // fetch runs beside Attn0 instead of in front of it.  Nothing of such a step takes tickets.  With launches of a given size or a
+  // check that is to fail (test hooks) a confined DA step is ticket-fed on two streams instead; not with the two timed apart.
+  const bool carried = mean_miss >= 0 && da_swap && ctx->xcds_even && (confine_da || da_short) && ctx->ticket_grid == 0 && ctx->check_extra == 0 &&
                        !(pev && (ctx->prof_mask & 0x28u));
-  ctx->last_confined = carried || confine_da ? 1 : (confine2 ? 2 : (confine ? 1 : 0));
+  ctx->last_carried = carried ? 1 : 0;
+  ctx->last_confined = confine_da ? 1 : (confine2 ? 2 : (confine ? 1 : 0));
   const uint32_t check_extra = ctx->last_confined ? ctx->check_extra : 0u;   // test hook, one confined step
   if (ctx->last_confined) ctx->check_extra = 0;
   const uint32_t mask2 = ESS_FETCH_XCD_MASK;
@@ -868,9 +871,8 @@ int ess_decode_step(ess_ctx* ctx, const ess_cache* cache, const ess_step_args* a
       if ((rc = attn0(0, B, st, anywhere, nullptr, &fetch)) != ESS_OK) return rc;
       ESS_END(3);
       ESS_BEGIN(4);
-      chk.need[ESS_TKT_ATTN0] += check_extra;
-      if ((rc = attn1(0, B, st, anywhere, nullptr, &chk)) != ESS_OK) return rc;
-      if (!plan.finish && (rc = ess_launch_attn_merge(ctx, B, T, pitch, wide, a->out_bf16, a->lse, st, nullptr, 0, 0, &chk)) != ESS_OK) return rc;
+      if ((rc = attn1(0, B, st, anywhere, nullptr, nullptr)) != ESS_OK) return rc;
+      if (!plan.finish && (rc = ess_launch_attn_merge(ctx, B, T, pitch, wide, a->out_bf16, a->lse, st)) != ESS_OK) return rc;
       ESS_END(4);
       return ESS_OK;
     }
@@ -1037,6 +1039,12 @@ int ess_set_overlap_threshold(ess_ctx* ctx, int32_t misses_per_seq) {
 int ess_last_confined(const ess_ctx* ctx, int32_t* fetches) {
   if (!ctx || !fetches) return ess_fail(ESS_ERR_INVALID_ARG, "NULL argument");
   *fetches = ctx->last_confined;
+  return ESS_OK;
+}
+
+int ess_last_carried(const ess_ctx* ctx, int32_t* carried) {
+  if (!ctx || !carried) return ess_fail(ESS_ERR_INVALID_ARG, "NULL argument");
+  *carried = ctx->last_carried;
   return ESS_OK;
 }
 

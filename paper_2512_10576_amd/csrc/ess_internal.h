@@ -87,6 +87,7 @@ struct ess_ctx {
   bool book_fits;               // the bookkeeping kernel's LDS arrays fit this configuration (else the cache calls are refused)
   int ticket_grid;              // > 0: ticket-fed launches use exactly this many workgroups (ess_debug_ticket_grid)
   int last_confined;            // fetches of the latest decode step that were confined to ESS_FETCH_XCD_MASK
+  int last_carried;             // the latest decode step's fetch travelled with Attn0 in one launch (see ess_fetch)
   uint32_t check_extra;         // ess_selfcheck_inject: work items the next confined step's check expects on top
   size_t ws_bytes;
   // overlap switch (ESS_FLAG_AUTO): per-sequence miss counts of the latest bookkeeping, written by the
