@@ -333,7 +333,8 @@ int ess_reset_stats(ess_ctx* ctx, void* stream);
  * ess_profile_read WAITS for the recorded events and returns, per recorded step, the
  * milliseconds of: [0] index score, [1] top-k, [2] cache bookkeeping, [3] Attn0,
  * [4] Attn1 (including any wait for the fetch) + merge, [5] the miss fetch kernel on its own
- * stream (0 when nothing is offloaded).  host_ms holds n*6 floats. */
+ * stream (0 when nothing is offloaded).  Where the fetch travelled with Attn0 (ess_last_carried) [3] and
+ * [5] are both the time of the launch that holds the two.  host_ms holds n*6 floats. */
 #define ESS_PROFILE_STAGES 6
 int ess_profile_enable(ess_ctx* ctx, int32_t max_steps);
 int ess_profile_read(ess_ctx* ctx, float* host_ms, int32_t* n_steps);

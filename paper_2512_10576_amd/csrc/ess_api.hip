@@ -706,9 +706,8 @@ int ess_decode_step(ess_ctx* ctx, const ess_cache* cache, const ess_step_args* a
   // Attn0 and the fetch in one launch (see ess_fetch), nothing on the side stream: no event behind the bookkeeping (4 us until
   // what follows it starts), no wait for the other stream in front of Attn1 (6 us, 11 where Attn0 ends last), and a short
   // fetch runs beside Attn0 instead of in front of it.  Nothing of such a step takes tickets.  With launches of a given size or a
-  // check that is to fail (test hooks) a confined DA step is ticket-fed on two streams instead; not with the two timed apart.
-  const bool carried = mean_miss >= 0 && da_swap && ctx->xcds_even && (confine_da || da_short) && ctx->ticket_grid == 0 && ctx->check_extra == 0 &&
-                       !(pev && (ctx->prof_mask & 0x28u));
+  // check that is to fail (test hooks) a confined DA step is ticket-fed on two streams instead.
+  const bool carried = mean_miss >= 0 && da_swap && ctx->xcds_even && (confine_da || da_short) && ctx->ticket_grid == 0 && ctx->check_extra == 0;
   ctx->last_carried = carried ? 1 : 0;
   ctx->last_confined = confine_da ? 1 : (confine2 ? 2 : (confine ? 1 : 0));
   const uint32_t check_extra = ctx->last_confined ? ctx->check_extra : 0u;   // test hook, one confined step
@@ -866,9 +865,16 @@ int ess_decode_step(ess_ctx* ctx, const ess_cache* cache, const ess_step_args* a
     // nothing when it has fired long before: this way both waits of the step are of the second kind
     // (the side stream's wait for the bookkeeping delays only Attn0).
     if (carried) {
+      // (timed, the launch is booked as Attn0 by the marks and as the fetch by an event pair around it)
       const ess_fetch fetch = ess_fetch_of(ctx, *cache, B, 0, ESS_CARRIED_WGS);
+      hipEvent_t* fev = (pev && ((ctx->prof_mask >> 5) & 1u)) ? pev + ESS_PROF_MAIN : nullptr;
       ESS_BEGIN(3);
+      if (fev) ESS_HIP(hipEventRecord(fev[0], st));
       if ((rc = attn0(0, B, st, anywhere, nullptr, &fetch)) != ESS_OK) return rc;
+      if (fev) {
+        ESS_HIP(hipEventRecord(fev[1], st));
+        ctx->prof_nfill[pslot] = 1;
+      }
       ESS_END(3);
       ESS_BEGIN(4);
       if ((rc = attn1(0, B, st, anywhere, nullptr, nullptr)) != ESS_OK) return rc;

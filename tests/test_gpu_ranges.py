@@ -217,8 +217,8 @@ def test_gathered_rows_beside_a_fetch(ess_lib, fmt, B, T, L, S, k):
 
 @pytest.mark.parametrize("B,T,fmt", [(3, 2, O.FMT_FP8), (2, 1, O.FMT_BF16)])
 def test_short_fetch_in_line_gives_the_bits_of_the_overlapped_schedule(ess_lib, B, T, fmt):
-    """With few misses the switch runs fetch and attention in line, Attn0 and Attn1 in one launch; the plain schedule runs
-    Attn0 beside the fetch: same outputs and cache state, bit for bit."""
+    """With few misses the switch keeps everything on the caller's stream, the fetch in Attn0's launch; the plain schedule runs
+    Attn0 on the side stream: same outputs and cache state, bit for bit."""
     from paper_2512_10576_amd import binding as bnd
     print("short fetch", B, T, fmt, flush=True)
     L, k, H, S = 9000, 512, 128, 4 * 512 * T
@@ -248,7 +248,7 @@ def test_short_fetch_in_line_gives_the_bits_of_the_overlapped_schedule(ess_lib, 
             ctx.decode_step(cache, qi, w, key, lens, q, step + 1, idx, out, lse, miss, topk_override=trace[step])
             torch.cuda.synchronize()
             assert ctx.last_overlap() == 0
-            # in line, attention (stage 3) is timed on the caller's stream; beside the fetch it runs on the side stream.
+            # in line, Attn0 (stage 3) is timed on the caller's stream; beside the fetch's own launch it runs on the side stream.
             # The first step knows no miss counts yet: nothing tells that its fetch is short; the second follows a step
             # that fetched everything
             in_line = 3 in [stage for _, stage in ctx.profile_intervals(step)]

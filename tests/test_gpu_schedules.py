@@ -102,3 +102,24 @@ def test_selfcheck_of_a_step_in_the_da_schedule(ess_lib):
     run(sets[3])
     assert run.ctx.get_stats()["steps"] == 4 and run.ctx.last_confined() == 0
     run.ctx.close()
+
+
+@pytest.mark.parametrize("mask", [0x3F, 0x08, 0x20])
+def test_timed_steps_take_the_schedule_of_untimed_ones(ess_lib, mask):
+    """Timing the stages of a step whose fetch travels with Attn0 does not take it apart: the launch that holds both is
+    booked as Attn0 (stage 3) and as the fetch (stage 5)."""
+    from paper_2512_10576_amd import binding as b
+    B, T, H, k, L, S = 4, 1, 128, 512, 6000, 1100
+    sets, hp = _moving_sets(B, T, L, k, [0, k, k, 2]), _host(0, B, L)
+    run = _Run(0, B, T, H, k, L, S, b.ESS_FLAG_AUTO, hp)
+    run.ctx.set_overlap_threshold(1 << 20)
+    run(sets[0])
+    run.ctx.profile_enable(3, stage_mask=mask)
+    for sel in sets[1:]:
+        run(sel)
+        assert run.ctx.last_carried()
+    for ms in run.ctx.profile_read():
+        assert (ms[3] > 0) == bool(mask & 0x08) and (ms[5] > 0) == bool(mask & 0x20)
+        if mask == 0x3F:
+            assert ms[5] <= ms[3]                                 # the marks are outside the pair
+    run.ctx.close()
