@@ -268,7 +268,10 @@ int run_merge(ess_ctx* ctx, attn_form f, int B, int T, void* out, float* lse, in
 //  * From 12 rows on Attn1, which follows the last fetch, is one range of k_attn_h32 that merges the row in its epilogue:
 //    no merge behind it, a quarter of the partial results.  Behind the fetch of 64 x 32K, about 200 misses a sequence,
 //    Attn1 and merge took 20 + 13 us, k_attn_h32 takes 19 (step 381 -> 365); half of 64 x 128K 20 + 6 + 10 against 20 (547 ->
-//    537).  A single range of 1500 misses takes what four ranges of k_attn_partial_tr and the merge took.
+//    537).  A single range of 1500 misses takes what four ranges of k_attn_partial_tr and the merge took.  It loses where next to
+//    nothing is missed, many rows are there and nothing runs beside Attn0 (a workgroup takes 9 us for one entry; before, Attn0 and
+//    Attn1 were one launch, with the merge behind): bf16, one miss, before / now, us: 97 x 16K 165 / 172, 100 x 32K 210 / 214, 200 x
+//    16K 269 / 281; but 120 x 32K quantised 251 / 244, 256 quantised rows 291 / 286, and 100 x 32K with 30 misses 286 / 272.
 //  * Fewer rows: ranges of both lists fill the chip in one round of k_attn_h32, then the merge (Attn0 in few enough ranges
 //    for an epilogue would be twice as long).
 //  * Lists longer than k_attn_h32 takes: k_attn_partial_tr and the merge throughout.
@@ -663,10 +666,9 @@ int ess_decode_step(ess_ctx* ctx, const ess_cache* cache, const ess_step_args* a
   // count of the previous step is only known under ESS_FLAG_AUTO, without it nothing is confined.
   bool confine = false, confine2 = false, confine_da = false;
   // A fetch of little (under 35 us, as far as the last step tells) is not worth the two waits across streams that running
-  // Attn0 beside it costs (12 us until Attn0 starts, 11 us from its end to Attn1): then everything follows on the
-  // caller's stream, Attn0 and Attn1 in one launch (the same ranges and sums).  Batch 23 x 48K, two tokens, a fetch of 20 us beside
-  // an Attn0 of 60.
-  bool da_short = false;
+  // Attn0 beside it costs (12 us until Attn0 starts, 11 us from its end to Attn1): then everything stays on the caller's
+  // stream, the fetch in Attn0's launch or in front of it (see carried).
+  bool da_short = false, free_cus_do = false;
   ess_ticket_check chk{};                       // filled in by the launches that take their work by ticket
   chk.tickets = ctx->tickets;
   chk.flag = ctx->host_miss_dev + c.max_batch;
@@ -679,7 +681,7 @@ int ess_decode_step(ess_ctx* ctx, const ess_cache* cache, const ess_step_args* a
     const int hg = plan.h32 ? (c.attn_heads + 31) / 32 : (c.attn_heads + 127) / 128;
     const double hits = c.topk - (mean_miss / T < c.topk ? mean_miss / T : c.topk);
     const double tiles_item = (hits / ESS_ATTN_TILE) / ns0 + 1.0;
-    const double rounds = (double)((long)B * T * hg * ns0 + work_cus - 1) / work_cus;
+    const long items = (long)B * T * hg * ns0, rounds = (items + work_cus - 1) / work_cus;
     // (a tile of 32 entries x 128 heads: 2.4 us on a full chip, 2.6 when the entries are dequantised on the way, and 12 of
     // start and end; 2.6 and 14 put the boundary best among these measurements.  Not confined against confined, us, single
     // fetch: 8 x 128K 120 misses 113 against 125, 240 153 against 143; 16 x 128K 60 misses 152 against 163, 120 187 against
@@ -692,11 +694,13 @@ int ess_decode_step(ess_ctx* ctx, const ess_cache* cache, const ess_step_args* a
     // against 839; 128 x 128K, two tokens, quantised, 289 misses 962 against 980, 388 1025 against 1024, 600 1442 against
     // 1404.)
     // (k_attn_h32, fewer than 12 rows: 1.5 us per 64 entries of 32 heads; 16 puts the boundary where it was measured)
-    const double attn5 = (double)(long)rounds * (plan.h32 ? hits / 64 / ns0 * 1.5 + 16.0 : tiles_item * 2.6 + 14.0);
+    const double item = plan.h32 ? hits / 64 / ns0 * 1.5 + 16.0 : tiles_item * 2.6 + 14.0, attn5 = rounds * item;
     // (one work counter serves one index-score launch: two query tokens at most)
     confine = dba && T <= 2 && fetch_half >= 1.5 * idx_half;
     confine2 = confine && attn5 + 40.0 <= 1.15 * fetch_half;        // + Attn1 and merge of the first half
     confine_da = da_swap && attn5 <= 1.6 * fetch_all;
+    // (8: the launch saved)
+    free_cus_do = attn5 <= (items + 255) / 256 * item + fetch_all + 8.0;
   }
   if (mean_miss >= 0 && da_swap && !confine_da && (double)B * mean_miss * c.row_stride / 50e3 < 35.0) {
     // (not into a graph: its replays would keep a choice that only this step's misses speak for)
@@ -705,9 +709,13 @@ int ess_decode_step(ess_ctx* ctx, const ess_cache* cache, const ess_step_args* a
   }
   // Attn0 and the fetch in one launch (see ess_fetch), nothing on the side stream: no event behind the bookkeeping (4 us until
   // what follows it starts), no wait for the other stream in front of Attn1 (6 us, 11 where Attn0 ends last), and a short
-  // fetch runs beside Attn0 instead of in front of it.  Nothing of such a step takes tickets.  With launches of a given size or a
-  // check that is to fail (test hooks) a confined DA step is ticket-fed on two streams instead.
-  const bool carried = mean_miss >= 0 && da_swap && ctx->xcds_even && (confine_da || da_short) && ctx->ticket_grid == 0 && ctx->check_extra == 0;
+  // fetch runs beside Attn0 instead of in front of it.  A short one only where the CUs that the fetch leaves free do Attn0 in
+  // as many rounds as the whole chip, or what a round more takes is less than the fetch: with 193 to 256 workgroups of Attn0 the fetch goes
+  // in front.  In front / carried, us: 100 x 32K, 1 and 14 misses, 214 / 261 and 240 / 263; 200 x 16K, 1 miss, 281 / 378; 128 x 16K, two
+  // tokens, quantised, 8 misses 299 / 413; with 128 workgroups (64 x 32K, two tokens, 10 misses) 241 / 226.
+  // Nothing of a carried step takes tickets.  With launches of a given size or a check that is to fail (test hooks) a confined DA
+  // step is ticket-fed on two streams instead.
+  const bool carried = mean_miss >= 0 && da_swap && ctx->xcds_even && (confine_da || (da_short && free_cus_do)) && ctx->ticket_grid == 0 && ctx->check_extra == 0;
   ctx->last_carried = carried ? 1 : 0;
   ctx->last_confined = confine_da ? 1 : (confine2 ? 2 : (confine ? 1 : 0));
   const uint32_t check_extra = ctx->last_confined ? ctx->check_extra : 0u;   // test hook, one confined step

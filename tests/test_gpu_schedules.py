@@ -123,3 +123,24 @@ def test_timed_steps_take_the_schedule_of_untimed_ones(ess_lib, mask):
         if mask == 0x3F:
             assert ms[5] <= ms[3]                                 # the marks are outside the pair
     run.ctx.close()
+
+
+@pytest.mark.parametrize("fmt,B,T,k,with_attn0", [(0, 96, 1, 128, True), (0, 97, 1, 128, False), (1, 64, 4, 64, False), (1, 128, 1, 320, True),
+                                                  (0, 100, 1, 2100, False)])
+def test_short_fetch_goes_in_front_where_it_would_cost_attn0_a_round(ess_lib, fmt, B, T, k, with_attn0):
+    """A carried fetch takes two of eight XCDs: where Attn0 has 193 to 256 workgroups (96 x 2 ranges; 97 x 2; 256 rows; 128; 100 x
+    2 ranges) the 192 CUs left would do it in two rounds instead of one, and a short fetch runs in front of it.  Outputs and
+    cache state are those of the plain schedule, bit for bit, either way."""
+    from paper_2512_10576_amd import binding as b
+    print("short fetch", fmt, B, T, k, flush=True)
+    H, L, S = 128, 4 * T * k + 100, 2 * T * k
+    sets, hp = _moving_sets(B, T, L, k, [0, 2, 2, 0]), _host(fmt, B, L)
+    auto, plain = _Run(fmt, B, T, H, k, L, S, b.ESS_FLAG_AUTO, hp), _Run(fmt, B, T, H, k, L, S, 0, hp)
+    auto.ctx.set_overlap_threshold(1 << 20)
+    for i, sel in enumerate(sets):
+        x, y = auto(sel), plain(sel)
+        assert all(torch.equal(a, c) for a, c in zip(x, y)), i
+        if i > 1:                                                 # (follow a step of few misses)
+            assert (auto.ctx.last_carried(), auto.ctx.last_confined()) == (with_attn0, 0), i
+    auto.ctx.close()
+    plain.ctx.close()
