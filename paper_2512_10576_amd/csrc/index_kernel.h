@@ -288,12 +288,12 @@ int launch_series(const ess_config& c, int T, dim3 grid, hipStream_t st, IdxArgs
 }
 
 // tokens per workgroup: a multiple of the 256 tokens the four waves cover per round; 2048 when that still leaves several
-// workgroups per CU, else 1024, and 512 up to 131072 keys in all, where the launch is a chain of a wave's batches and no
-// more than 256 workgroups result (one sequence of 8192: 7.6 us, two batches a wave 5.7, one batch 5.7; 4 x 128K with 512
-// tokens 14.8 against 12.9)
+// workgroups per CU, else 1024, and 512 where no more than 256 workgroups result, i.e. the launch is a chain of a wave's
+// batches (one sequence of 8192: 7.6 us, two batches a wave 5.7, one batch 5.7; 4 x 128K, 1024 workgroups of 512 tokens, 14.8
+// against 12.9)
 inline int pick_chunk(int B, int Lmax) {
-  const long keys = (long)B * Lmax;
-  return keys >= 2048L * 1024 ? 2048 : (keys > 131072 ? 1024 : 512);
+  if ((long)B * ((Lmax + 511) / 512) <= 256) return 512;
+  return (long)B * Lmax >= 2048L * 1024 ? 2048 : 1024;
 }
 
 }  // namespace ess_idx

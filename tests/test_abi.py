@@ -233,3 +233,22 @@ def test_gathers_wait_for_their_scalar_addresses(tmp_path, source, kernel):
         assert len(gathers) >= 16
         for states, text in gathers:
             assert states is None or states >= 5, "\n".join(text)
+
+
+def test_short_index_chunks_only_where_they_fit_the_chip_at_once(tmp_path):
+    """The index score takes 512 tokens a workgroup only where that makes no more than one workgroup per CU (250 sequences of
+    520 tokens would be 500, half of them with 8 tokens); 1024 or, from 2M keys on, 2048 otherwise.  The rule itself,
+    compiled for the host."""
+    import subprocess
+    from paper_2512_10576_amd import build
+    shapes = [(1, 1), (1, 8192), (1, 131072), (1, 131073), (2, 65536), (4, 131072), (250, 520), (256, 512), (256, 513), (257, 512), (128, 520),
+              (4096, 20), (255, 1), (16, 131072), (13, 131072), (40, 102400), (3, 43691)]
+    src = tmp_path / "chunk.hip"
+    src.write_text('#include "index_kernel.h"\n#include <stdio.h>\nint main() {\n' + "".join(
+        '  printf("%%d\\n", ess_idx::pick_chunk(%d, %d));\n' % s for s in shapes) + "}\n")
+    exe = tmp_path / "chunk"
+    subprocess.run([build._hipcc(), *build.FLAGS, "-I" + build.CSRC, str(src), "-o", str(exe)], check=True, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)
+    got = [int(x) for x in subprocess.run([str(exe)], check=True, stdout=subprocess.PIPE, text=True).stdout.split()]
+    for (B, L), chunk in zip(shapes, got):
+        want = 512 if B * -(-L // 512) <= 256 else (2048 if B * L >= 2048 * 1024 else 1024)
+        assert chunk == want, (B, L, chunk)
