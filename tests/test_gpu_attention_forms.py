@@ -70,19 +70,27 @@ def test_lists_heads_and_ranges(ess_lib, fmt, B, T, H, k, kind):
 
 @pytest.mark.parametrize("fmt,scale", [(0, 0.5), (1, 0.5), (0, 8.0)])
 def test_reference_moves_from_tile_to_tile(ess_lib, fmt, scale):
-    """Logits that grow along the list by far more than 2^8 a tile (a peaky softmax): the accumulators are rescaled in
-    most tiles; heads move at different tiles."""
+    """Lists in the order of one head's logits, which grow by far more than 2^8 from tile to tile (a peaky softmax): the
+    accumulators are rescaled in half the tiles of that head or more, and the other heads of the row move at other tiles.  128 rows of two
+    workgroups: one range a row, all its tiles behind one another."""
     from paper_2512_10576_amd import binding as b
-    B, T, H, k = 1, 1, 48, 640
+    B, T, H, k = 32, 4, 48, 640
     stride = (1152, 656)[fmt]
-    pool = (synth.latent_rows_bf16, synth.latent_rows_fp8)[fmt](5, k).reshape(1, k, stride)
+    pool = (synth.latent_rows_bf16, synth.latent_rows_fp8)[fmt](5, B * k).reshape(B, k, stride)
     q = synth.attn_query(8, B, T, H)
+    z = np.matmul(O.decode_bf16(_qbits(q)), O.decode_rows(pool.numpy(), fmt).transpose(0, 2, 1)[:, None]) * (scale * np.log2(np.e))
+    idx = np.empty((B, T, k), np.int32)
+    for r in range(B * T):
+        row = z.reshape(B * T, H, k)[r]
+        order = np.argsort(row[r % H])
+        idx.reshape(B * T, k)[r] = order
+        tiles = row[:, order].reshape(H, k // 64, 64).max(-1)
+        ref, moved = tiles[:, 0].copy(), np.zeros((H, k // 64), bool)
+        for t in range(1, k // 64):                               # what the kernel does with the reference, 8 = kLazyMax
+            moved[:, t] = tiles[:, t] > ref + 8
+            ref = np.where(moved[:, t], tiles[:, t], ref)
+        assert moved[r % H].sum() >= 4 and len({m.tobytes() for m in moved}) > 3, r
     ctx = b.Context(b.make_config(B, T, k, 4, 32, k, H, latent_fmt=fmt, slots_per_seq=k, sm_scale=scale))
-    z = O.sparse_mla(_qbits(q), pool.numpy(), np.arange(k, dtype=np.int32).reshape(1, 1, k), fmt, 1.0)
-    assert np.isfinite(z[1]).all()
-    rows = O.decode_bf16(pool.view(torch.int16).numpy().view(np.uint16)) if fmt == 0 else None
-    order = np.arange(k) if rows is None else np.argsort(rows.reshape(k, 576) @ O.decode_bf16(_qbits(q))[0, 0, 0])
-    idx = order.astype(np.int32).reshape(1, 1, k)
     out = torch.empty((B, T, H, 512), dtype=torch.bfloat16, device="cuda")
     lse = torch.empty((B, T, H), dtype=torch.float32, device="cuda")
     ctx.sparse_mla_decode(q.cuda(), pool.cuda(), torch.from_numpy(idx).cuda(), out, lse)
