@@ -172,14 +172,13 @@ int pick_splits_target(const ess_config& c, int B, int T, int cap, int target_wg
 // heads), and with one range a row it needs no merge.  Times of both from the same terms: rounds of 256 workgroups, start
 // and end, tiles, and the merge.  Attention and merge of lists of 2048, 128 heads, us, k_attn_partial_tr / k_attn_h32: 1 row
 // 16.0 / 12.4, 4 rows 20.8 / 16.0, 8 rows 25.2 / 20.1, 16 rows 28.0 / 23.9, 32 rows 37.0 / 37.5, 46 quantised rows 50.4 /
-// 60.8; 64 heads: 13 rows 22.5 / 19.1, 40 rows 32.0 / 28.7, 128 quantised rows 79.0 / 66.0; 16 heads, 32 rows 25.8 / 20.8.
+// 60.8; 64 heads: 13 rows 22.5 / 19.1, 40 rows 32.0 / 28.7, 128 quantised rows 79.0 / 66.0; 16 heads, 32 rows 25.8 / 20.8.  Lists
+// of 64: 1 row 13.5 / 8.9, 16 rows 15.3 / 8.8, 64 rows 20.0 / 8.5, 128 rows of 16 heads 14.2 / 9.4.
 struct attn_form { bool h32; int ns; };
 attn_form pick_form(const ess_ctx* ctx, int B, int T) {
   const ess_config& c = ctx->cfg;
   attn_form f{false, pick_splits(ctx, B, T, ESS_MAX_SPLITS)};
-  // (lists of one tile keep their fp16 partial result: of values that far apart, what lies 2^29 below a head's largest one
-  // comes out as zero there, which callers may have seen; 2 rows of 64 entries, 16 heads, 12.4 us, k_attn_h32 9.2)
-  if (c.topk > ESS_H32_LIST || c.topk <= 64) return f;
+  if (c.topk > ESS_H32_LIST) return f;
   const int rows = B * T, waves = (c.attn_heads + 31) / 32;
   auto merge_us = [&](int ns) { return ns * (0.05 + (double)rows * c.attn_heads * 2048.0 / 9e6) + 2.5; };
   const int t32 = (c.topk + 31) / 32, t64 = (c.topk + 63) / 64;

@@ -29,7 +29,7 @@ def _check(out, lse, ref_out, ref_lse, lse_tol=1e-4):
 
 @pytest.mark.parametrize("fmt", [0, 1])
 @pytest.mark.parametrize("B,T,H,k,kind", [
-    (1, 1, 1, 65, "full"), (1, 2, 31, 128, "full"), (2, 1, 33, 129, "ragged"), (1, 1, 128, 2048, "full"),
+    (1, 1, 128, 64, "full"), (2, 2, 16, 33, "ragged"), (1, 1, 40, 1, "full"), (64, 1, 128, 48, "ragged"), (1, 1, 1, 65, "full"), (1, 2, 31, 128, "full"), (2, 1, 33, 129, "ragged"), (1, 1, 128, 2048, "full"),
     (3, 1, 40, 513, "holes"), (1, 4, 16, 1000, "ragged"), (9, 1, 64, 191, "ragged"), (64, 1, 16, 320, "ragged"),
     (130, 1, 20, 192, "ragged"), (2, 2, 128, 514, "unaligned")])
 def test_lists_heads_and_ranges(ess_lib, fmt, B, T, H, k, kind):
@@ -152,3 +152,28 @@ def test_offloaded_rows_finished_by_attn1(ess_lib, fmt, B, T, H, k):
     for flags, got in runs.items():
         for (o0, l0), (o1, l1) in zip(runs[0], got):
             assert torch.equal(o0, o1) and torch.equal(l0, l1), flags
+
+
+@pytest.mark.parametrize("H,k", [(128, 64), (40, 640), (128, 2048), (128, 2100)])
+def test_values_beyond_fp16_in_every_form(ess_lib, H, k):
+    """One row: finished by the kernel of 32 heads (64 entries), several ranges of it (640, 2048), and the kernel of 128 heads.
+    With all logits equal the output is the entry itself, exactly, for values within 2^29 of a head's largest one; a value
+    2^81 below it is exact or zero."""
+    from paper_2512_10576_amd import binding as b
+    print("values beyond fp16", H, k, flush=True)
+    vals = {0: 1.0e30, 1: -7.5e29, 2: 9.5e23, 3: 3.0e5, 200: 2.5e29, 511: -1.0e30}
+    rows = torch.zeros((1, k, 576), dtype=torch.bfloat16)
+    for col, v in vals.items():
+        rows[..., col] = v
+    ctx = b.Context(b.make_config(1, 1, k, 4, 32, k, H, slots_per_seq=k))
+    out = torch.full((1, 1, H, 512), 9.0, dtype=torch.bfloat16, device="cuda")
+    lse = torch.full((1, 1, H), 9.0, dtype=torch.float32, device="cuda")
+    idx = torch.arange(k, dtype=torch.int32, device="cuda").view(1, 1, k)
+    ctx.sparse_mla_decode(torch.zeros((1, 1, H, 576), dtype=torch.bfloat16, device="cuda"), rows.view(torch.uint8).reshape(1, k, 1152).cuda(), idx, out, lse)
+    torch.cuda.synchronize()
+    got, want = out.float().cpu()[0, 0], rows[0, 0, :512].float()
+    keep = [c for c in range(512) if c != 3]
+    assert torch.equal(got[:, keep], want[keep].expand(H, -1))
+    assert bool(((got[:, 3] == 0) | (got[:, 3] == want[3])).all())
+    assert np.allclose(lse.cpu().numpy(), np.log(k), atol=1e-4)
+    ctx.close()
