@@ -958,15 +958,20 @@ int ess_decode_step(ess_ctx* ctx, const ess_cache* cache, const ess_step_args* a
     if (aev) ESS_HIP(hipEventRecord(aev[0], ctx->side));
     // Attn0 of the whole batch in one launch (behind the first fetch it could not start much earlier
     // anyway): one workgroup per CU, the same splits as in the other schedules
-    rc = attn0(0, B, ctx->side, confine2 ? tk_xcd(ESS_TKT_ATTN0) : anywhere, nullptr);
+    // (ev_fill[0] from here: Attn0 done)
+    rc = attn0(0, B, ctx->side, confine2 ? tk_xcd(ESS_TKT_ATTN0) : anywhere, plan.finish ? ctx->ev_fill[0] : nullptr);
     if (rc != ESS_OK) return rc;
     if (aev) {
       ESS_HIP(hipEventRecord(aev[1], ctx->side));
       ESS_HIP(hipEventRecord(aev[2], ctx->side));
     }
     // ev_fill[1] here: everything on the side stream done.  Each half is merged on the stream its Attn1 ran on: only half
-    // a merge, if any, is left behind the last fetch.
-    rc = attn1(hb0[0], hB[0], ctx->side, confine2 ? tk_xcd(ESS_TKT_ATTN1) : anywhere, plan.finish ? ctx->ev_fill[1] : nullptr, nullptr);
+    // a merge, if any, is left behind the last fetch.  Attn1 that finishes the second half's rows needs Attn0 alone, not the first half's
+    // Attn1 in front of it -- which then takes no tickets, so that the check at the end of the step has all ticket-fed launches
+    // behind it.  Waiting for both / for Attn0, us: 128 x 32K 240 misses 846 / 820, 480 misses 1470 / 1445, quantised 644 / 615 and
+    // 1060 / 1031; 48 x 64K 480 misses 610 / 597; 128 x 128K, two tokens, quantised, 600 misses 1384 / 1386; 64 x 128K 114, 195 and 494
+    // misses 404 / 396, 472 / 476 and 831 / 833.
+    rc = attn1(hb0[0], hB[0], ctx->side, confine2 && !plan.finish ? tk_xcd(ESS_TKT_ATTN1) : anywhere, plan.finish ? ctx->ev_fill[1] : nullptr, nullptr);
     if (rc != ESS_OK) return rc;
     if (!plan.finish) {
       rc = ess_launch_attn_merge(ctx, hB[0], T, pitch, wide, a->out_bf16, a->lse, ctx->side, nullptr, 0, hb0[0], nullptr, ctx->ev_fill[1]);
@@ -979,13 +984,13 @@ int ess_decode_step(ess_ctx* ctx, const ess_cache* cache, const ess_step_args* a
       ctx->prof_pair_stage[(size_t)pslot * ESS_PROF_FILL + 2] = 4;
     }
     ESS_BEGIN(4);
-    // Attn0 of the second half ran on the side stream: waited for where its results are read
+    // Attn0 of the second half ran on the side stream: waited for where its results are read; the rest of that stream at the end
     chk.need[ESS_TKT_INDEX] += check_extra;
-    if (plan.finish) ESS_HIP(hipStreamWaitEvent(st, ctx->ev_fill[1], 0));
+    if (plan.finish) ESS_HIP(hipStreamWaitEvent(st, ctx->ev_fill[0], 0));
     rc = attn1(hb0[1], hB[1], st, anywhere, nullptr, confine ? &chk : nullptr);
     if (rc != ESS_OK) return rc;
+    ESS_HIP(hipStreamWaitEvent(st, ctx->ev_fill[1], 0));
     if (!plan.finish) {
-      ESS_HIP(hipStreamWaitEvent(st, ctx->ev_fill[1], 0));
       rc = ess_launch_attn_merge(ctx, hB[1], T, pitch, wide, a->out_bf16, a->lse, st, nullptr, 0, hb0[1], confine ? &chk : nullptr);
       if (rc != ESS_OK) return rc;
     }
