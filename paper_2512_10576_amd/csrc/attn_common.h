@@ -42,17 +42,28 @@ __device__ __forceinline__ uint32_t lds_addr_of(const void* p) {
 __device__ __forceinline__ void dma16(const void* gptr, uint32_t lds_dst) {
   asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(gptr), "s"(lds_dst) : "memory", "m0");
 }
-// the same from a wave-uniform base and a byte offset per lane.  The base may come straight from v_readlane: a memory
-// instruction may read a scalar register five wait states after a vector ALU instruction wrote it, not earlier, and the
-// compiler's hazard logic does not look into asm statements, so the five are in the statement itself.
+// the same from a wave-uniform base and a byte offset per lane.  A memory instruction may read a scalar register five wait
+// states after a vector ALU instruction wrote it, not earlier, and the compiler's hazard logic does not look into asm
+// statements.  LANES: the base comes straight from v_readlane, and the five are in the statement.  Without, it has been through
+// scalar arithmetic (or a kernel argument), which needs none; in k_attn_partial_tr, bound by what its one wave per SIMD issues, they
+// cost 2 % (48 x 2 quantised ragged rows 87.9 us against 86.0).  tests/test_abi.py counts the states in all instances of both kernels.
+template <bool LANES = false>
 __device__ __forceinline__ void dma16_base(const void* base, uint32_t off, uint32_t lds_dst) {
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(off), "s"(base), "s"(lds_dst) : "memory", "m0");
+  if constexpr (LANES)
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(off), "s"(base), "s"(lds_dst) : "memory", "m0");
+  else
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(off), "s"(base), "s"(lds_dst) : "memory", "m0");
 }
 // the same for the first F8_PIECES lanes only (a quantised entry); all lanes are active before and after.  The execution
 // mask is set inside the statement: a branch around it would cut the pinned order of the loop into pieces.
+template <bool LANES = false>
 __device__ __forceinline__ void dma16_entry(const void* base, uint32_t off, uint32_t lds_dst) {
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 2\n\ts_mov_b64 exec, %3\n\tglobal_load_lds_dwordx4 %0, %1\n\ts_mov_b64 exec, -1"
-               : : "v"(off), "s"(base), "s"(lds_dst), "s"((1ull << 41) - 1) : "memory", "m0");
+  if constexpr (LANES)
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 2\n\ts_mov_b64 exec, %3\n\tglobal_load_lds_dwordx4 %0, %1\n\ts_mov_b64 exec, -1"
+                 : : "v"(off), "s"(base), "s"(lds_dst), "s"((1ull << 41) - 1) : "memory", "m0");
+  else
+    asm volatile("s_mov_b32 m0, %2\n\ts_mov_b64 exec, %3\n\tglobal_load_lds_dwordx4 %0, %1\n\ts_mov_b64 exec, -1"
+                 : : "v"(off), "s"(base), "s"(lds_dst), "s"((1ull << 41) - 1) : "memory", "m0");
 }
 #pragma clang diagnostic pop
 

@@ -416,7 +416,6 @@ __global__ __launch_bounds__(BT) void k_bookkeeping(
       // slots of smaller digits (all of them victims) plus the number of victims with its digit in front of it -- inside its
       // wave by matching the eight digit bits, and the counts of the waves before.  (Was: every key compared with
       // every other, 4.5 us for 280 victims; this takes 1.5.)
-      // Its former token is asked for as soon as the victim is known, and the pairing follows from the registers.
       // The former token is asked for as soon as the slot is known, and the pairing follows from the registers.
       uint8_t* const cnt8 = reinterpret_cast<uint8_t*>(s_cnt);         // [256 digits][16 waves]: at most 64 each
       __syncthreads();

@@ -129,6 +129,9 @@ int check_cache(const ess_ctx* ctx, const ess_cache* c) {
 // written and read once more by the merge, 256 KiB per 128 heads at about 4.5 TB/s, and a small batch's merge takes
 // 0.12 us longer per split.  The split count with the least sum is taken.  (Before, one count was aimed at that puts a
 // workgroup on every CU, rounded up: 96 rows got three splits each, 288 workgroups, i.e. a second round for 32 of them.)
+// (Five and a half tiles of start and end are from the time when the first tile rescaled its empty accumulators; it is four and a
+// half now, 9.5 us, as pick_form has it.  With that number the choice is the same for 1 to 256 rows of 128, 64 and 16 heads
+// and lists of 513, 1024 and 2048 but for 159 to 170 rows of 64 heads with lists of 1024.)
 // One time per tile serves both formats: 256 rows of 2048 N(0,1) entries take 179 us, quantised ones 195 (2.4 and 2.6 us a
 // tile with every CU at work, 1.6 and 2.0 where the power limit leaves the clock alone), 64 rows 53 and 58: the ratio of a
 // tile to start and end, which decides, is nearly the same.
@@ -170,10 +173,12 @@ int pick_splits_target(const ess_config& c, int B, int T, int cap, int target_wg
 // k_attn_h32 has 32 heads: it costs little to start and end (7 us against 9.5), but brings an entry through LDS once per 32
 // heads (1.5 us per 64 entries, against 2.1 per 32 entries of 128 heads, 1.1 where half the workgroup's waves have no
 // heads), and with one range a row it needs no merge.  Times of both from the same terms: rounds of 256 workgroups, start
-// and end, tiles, and the merge.  Attention and merge of lists of 2048, 128 heads, us, k_attn_partial_tr / k_attn_h32: 1 row
-// 16.0 / 12.4, 4 rows 20.8 / 16.0, 8 rows 25.2 / 20.1, 16 rows 28.0 / 23.9, 32 rows 37.0 / 37.5, 46 quantised rows 50.4 /
-// 60.8; 64 heads: 13 rows 22.5 / 19.1, 40 rows 32.0 / 28.7, 128 quantised rows 79.0 / 66.0; 16 heads, 32 rows 25.8 / 20.8.  Lists
-// of 64: 1 row 13.5 / 8.9, 16 rows 15.3 / 8.8, 64 rows 20.0 / 8.5, 128 rows of 16 heads 14.2 / 9.4.
+// and end, tiles, and the merge, of which only the reads count here (at 4.5 TB/s; the writes are in the workgroups' end).  1.5
+// us lies between the 1.2 of bf16 and the 1.6 of quantised entries, and k_attn_h32 has to win by 5 %.  Attention and merge of
+// lists of 2048, 128 heads, us, k_attn_partial_tr / k_attn_h32: 1 row 16.0 / 12.4, 4 rows 20.8 / 16.0, 8 rows 25.2 / 20.1, 16
+// rows 28.0 / 23.9, 32 rows 37.0 / 37.5, 46 quantised rows 50.4 / 60.8; 64 heads: 13 rows 22.5 / 19.1, 40 rows 32.0 / 28.7, 128
+// quantised rows 79.0 / 66.0; 16 heads, 32 rows 25.8 / 20.8.  Lists of 64: 1 row 13.5 / 8.9, 16 rows 15.3 / 8.8, 64 rows 20.0 /
+// 8.5, 128 rows of 16 heads 14.2 / 9.4.
 struct attn_form { bool h32; int ns; };
 attn_form pick_form(const ess_ctx* ctx, int B, int T) {
   const ess_config& c = ctx->cfg;
@@ -272,7 +277,11 @@ int run_merge(ess_ctx* ctx, attn_form f, int B, int T, void* out, float* lse, in
 //    Attn1 were one launch, with the merge behind): bf16, one miss, before / now, us: 97 x 16K 165 / 172, 100 x 32K 210 / 214, 200 x
 //    16K 269 / 281; but 120 x 32K quantised 251 / 244, 256 quantised rows 291 / 286, and 100 x 32K with 30 misses 286 / 272.
 //  * Fewer rows: ranges of both lists fill the chip in one round of k_attn_h32, then the merge (Attn0 in few enough ranges
-//    for an epilogue would be twice as long).
+//    for an epilogue would be twice as long).  Rows finished / this, us a step at 64K, 10, 120 and 900 misses: 6 rows 80 / 66, 83 /
+//    75, 202 / 190; 10 rows 86 / 78, 98 / 93, 281 / 284; 12 rows 87 / 80, 104 / 99, 319 / 323; 16 rows 93 / 89, 120 / 115, 401 / 403;
+//    20 rows 102 / 102, 135 / 130, 479 / 482; 23 rows 110 / 111, 147 / 143, 540 / 544: with few misses the line could lie at 20 rows.
+//  * Attn0 of rows that Attn1 finishes is k_attn_partial_tr with any number of heads: k_attn_h32 for 16 to 64 heads, which
+//    is the faster one without a fetch (see pick_form), was not measured here.
 //  * Lists longer than k_attn_h32 takes: k_attn_partial_tr and the merge throughout.
 struct attn_plan { bool h32, finish; int ns0, ns1; };
 attn_plan plan_offloaded(const ess_ctx* ctx, int B, int T) {
@@ -709,9 +718,11 @@ int ess_decode_step(ess_ctx* ctx, const ess_cache* cache, const ess_step_args* a
   // Attn0 and the fetch in one launch (see ess_fetch), nothing on the side stream: no event behind the bookkeeping (4 us until
   // what follows it starts), no wait for the other stream in front of Attn1 (6 us, 11 where Attn0 ends last), and a short
   // fetch runs beside Attn0 instead of in front of it.  A short one only where the CUs that the fetch leaves free do Attn0 in
-  // as many rounds as the whole chip, or what a round more takes is less than the fetch: with 193 to 256 workgroups of Attn0 the fetch goes
-  // in front.  In front / carried, us: 100 x 32K, 1 and 14 misses, 214 / 261 and 240 / 263; 200 x 16K, 1 miss, 281 / 378; 128 x 16K, two
-  // tokens, quantised, 8 misses 299 / 413; with 128 workgroups (64 x 32K, two tokens, 10 misses) 241 / 226.
+  // as many rounds as the whole chip, or what a round more takes is less than the fetch: with 193 to 256 workgroups of Attn0 the
+  // fetch goes in front.  In front / carried, us: 100 x 32K, 1 and 14 misses, 214 / 261 and 240 / 263; 200 x 16K, 1 miss, 281 /
+  // 378; 128 x 16K, two tokens, quantised, 8 misses 299 / 413; with 128 workgroups (64 x 32K, two tokens, 10 misses) 241 / 226.
+  // (35 us here and the 1.6 above were measured with two streams and their waits; between the two a fetch still goes its own
+  // way.)
   // Nothing of a carried step takes tickets.  With launches of a given size or a check that is to fail (test hooks) a confined DA
   // step is ticket-fed on two streams instead.
   const bool carried = mean_miss >= 0 && da_swap && ctx->xcds_even && (confine_da || (da_short && free_cus_do)) && ctx->ticket_grid == 0 && ctx->check_extra == 0;

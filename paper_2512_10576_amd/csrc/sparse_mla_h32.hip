@@ -1,7 +1,7 @@
 // Stage 4 for few rows, short lists and few heads: SparseMLA decode with 32 heads per workgroup.  The kernel in
 // sparse_mla.hip gives a workgroup all 128 heads, one wave per 32 of them: an entry is brought from memory once, but a
 // workgroup starts with 144 KiB of queries, ends with 128 KiB of results, and 16 heads use one wave of four.  Here a
-// workgroup owns 32 heads and its four waves share every tile: over the entries in the first product, over the value
+// workgroup owns 32 heads and its eight waves share every tile: over entries and heads in the first product, over the value
 // columns in the second.  It can also finish a row: merge its result with partial results written before it.
 #include "attn_common.h"
 #include "fetch.h"
@@ -205,8 +205,8 @@ __global__ __launch_bounds__(NT, 2) void k_attn_h32(
     if constexpr (r < 8) {
       const void* base = reinterpret_cast<const void*>((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)a.lo, r) |
                                                        (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)a.hi, r) << 32);
-      if constexpr (kBf) dma16_base(base, go ^ (uint32_t)(((r & 3) << 2 | (r >> 2)) << 4), dst + (uint32_t)((8 * wave + r) * TRP));
-      else dma16_entry(base, go, dst + (uint32_t)((8 * wave + r) * F8_PITCH));
+      if constexpr (kBf) dma16_base<true>(base, go ^ (uint32_t)(((r & 3) << 2 | (r >> 2)) << 4), dst + (uint32_t)((8 * wave + r) * TRP));
+      else dma16_entry<true>(base, go, dst + (uint32_t)((8 * wave + r) * F8_PITCH));
     } else if constexpr (kBf) {
       dma16(reinterpret_cast<const uint8_t*>((uint64_t)a.rlo | (uint64_t)a.rhi << 32) + rope_off, dst + (uint32_t)(ET * TRP + wave * 1024));
     }

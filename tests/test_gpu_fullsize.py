@@ -100,7 +100,8 @@ def test_cfg4_full_size_sampled_sequences(ess_lib):
 
 def test_cfg3_full_size_sampled_sequences(ess_lib):
     """B64, context 32768, 25 % slots, 80 % step-to-step overlap, in the schedule bench.py runs there: the switch
-    stays with DA (half a batch's index score at 32K is too short to be worth splitting) and confines the fetch."""
+    stays with DA (half a batch's index score at 32K is too short to be worth splitting) and the fetch, long enough to
+    be confined, travels with Attn0."""
     import bench
     print("full-size cfg3 (B64, ctx 32768, offloaded, 25% slots, trace-driven)", flush=True)
     steps = 3
@@ -143,10 +144,11 @@ def test_cfg3_full_size_sampled_sequences(ess_lib):
         back = torch.gather(cache.slot_of, 1, cache.token_of.clamp(min=0).long())
         assert bool((back[res] == torch.arange(S, device="cuda").expand(B, S)[res]).all())
         schedules.append((ctx.last_overlap(), ctx.last_confined()))
+    carried = ctx.last_carried()
     assert ctx.get_stats()["steps"] == steps
     ctx.close()
-    # the launch configuration bench.py times here: DA, the fetch confined, Attn0 beside it by ticket
-    assert schedules[0] == (0, 0) and schedules[-1] == (0, 1), schedules
+    # the launch configuration bench.py times here: DA, the fetch confined to two XCDs, in one launch with Attn0
+    assert schedules[0] == (0, 0) and schedules[-1] == (0, 1) and carried, schedules
 
 
 def test_cfg5_full_size_sampled_sequences(ess_lib):
