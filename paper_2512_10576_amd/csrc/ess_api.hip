@@ -955,7 +955,7 @@ int ess_decode_step(ess_ctx* ctx, const ess_cache* cache, const ess_step_args* a
     // microseconds when the event fires late, so the second fetch follows its bookkeeping on the caller's
     // stream (it may start while the first fetch is still finishing: the link just stays busy), and what
     // has time to spare goes to the side stream behind the first fetch: Attn0 of the whole batch and Attn1
-    // of the first half.  The caller's stream ends with Attn1 of the second half and the merge.
+    // of the first half.  The caller's stream ends with Attn1 of the second half and joins the side stream.
     const ess_cache c0 = shift_cache(c, *cache, hb0[0]), c1 = shift_cache(c, *cache, hb0[1]);
     const size_t bt1 = (size_t)hb0[1] * T;
     ESS_BEGIN(5);

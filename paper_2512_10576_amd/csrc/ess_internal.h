@@ -24,7 +24,7 @@ enum {                          // which launch uses which counter block
   ESS_TKT_BOOK = 5,             // bookkeeping
   ESS_TKT_FETCH2 = 6,           // the second fetch of the split-batch schedule
   ESS_TKT_ATTN0 = 7,
-  ESS_TKT_ATTN1 = 8
+  ESS_TKT_ATTN1 = 8             // (Attn1 that finishes no rows)
 };
 // Counters of one such launch.  They are device-scope atomics from all XCDs, which the memory side executes one
 // after the other per address range, so each counter has 256 bytes to itself: [ESS_TK_WORK] work items handed out,
@@ -122,7 +122,7 @@ struct ess_xcd {
   uint32_t* host_need;          // host memory, may be null: the launcher leaves the number of work items here
   int grid_override;            // > 0: launch exactly this many workgroups (test hook)
 };
-// The last kernel of a step that used such launches compares each launch's counters with its number of
+// A step that used such launches has a kernel behind all of them that compares each launch's counters with its number of
 // work items, as an assertion: a counter below it means a bug in the hand-out, reported through `flag`
 // (pinned host memory) at the host's next call.
 struct ess_ticket_check {
