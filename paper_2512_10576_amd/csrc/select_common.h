@@ -1,6 +1,7 @@
 // Pieces shared by the kernels of the selection (top-k, and the sampled lower bound of the fused selection).
 #pragma once
 #include "ess_internal.h"
+#include <type_traits>
 
 namespace ess_sel {
 
@@ -32,7 +33,26 @@ __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v, int /*lane*/) {
   return (uint32_t)r;
 }
 
-// The same inside each row of 16 lanes.
+// Largest value of the wave's 64 lanes (STEPS 6), or of its last eight (STEPS 3), in all lanes, by the same moves.  A NaN is skipped.
+template <int STEPS>
+__device__ __forceinline__ float wave_max(float x) {
+  constexpr int kLow = (int)0xff800000;
+  auto with = [&](auto ctrl, auto rows) {
+    x = fmaxf(x, __int_as_float(__builtin_amdgcn_update_dpp(kLow, __float_as_int(x), decltype(ctrl)::value, decltype(rows)::value, 0xf, false)));
+  };
+  using std::integral_constant;
+  with(integral_constant<int, 0x111>{}, integral_constant<int, 0xf>{});
+  with(integral_constant<int, 0x112>{}, integral_constant<int, 0xf>{});
+  with(integral_constant<int, 0x114>{}, integral_constant<int, 0xf>{});
+  if constexpr (STEPS > 3) {
+    with(integral_constant<int, 0x118>{}, integral_constant<int, 0xf>{});
+    with(integral_constant<int, 0x142>{}, integral_constant<int, 0xa>{});
+    with(integral_constant<int, 0x143>{}, integral_constant<int, 0xc>{});
+  }
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 63));
+}
+
+// The sum inside each row of 16 lanes.
 __device__ __forceinline__ uint32_t row_incl_scan(uint32_t v) {
   const int x = (int)v;
   int r = x + __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, true);
@@ -105,31 +125,6 @@ __device__ __forceinline__ void sample_bins(const uint32_t* shist, uint32_t* wav
   __syncthreads();
   *lo_bin = sel[0];
   *hi_bin = sel[1];
-  __syncthreads();
-}
-
-// The bin of a complete histogram (laid out by sample_slot<NTH>) that holds the need-th largest of its entries
-// (1 <= need <= their number) -> *sel (LDS).  Ends with a barrier.
-template <int NTH>
-__device__ __forceinline__ void crossing_bin(const uint32_t* shist, uint32_t* wave_tot, uint32_t* sel, uint32_t need) {
-  constexpr int BPT = SBINS / NTH;
-  const int top_bin = SBINS - 1 - (int)threadIdx.x * BPT;
-  const int top_slot = sample_slot<NTH>(top_bin);
-  uint32_t mine = 0, bin[BPT];
-#pragma unroll
-  for (int r = 0; r < BPT; ++r) { bin[r] = shist[top_slot - r]; mine += bin[r]; }
-  uint32_t total;
-  const uint32_t inc = block_incl_scan<NTH>(mine, wave_tot, &total);
-  uint32_t above = inc - mine;
-  if (above < need && inc >= need) {
-    int at = -1;
-#pragma unroll
-    for (int r = 0; r < BPT; ++r) {
-      above += bin[r];
-      if (at < 0 && above >= need) at = r;
-    }
-    *sel = (uint32_t)(top_bin - at);
-  }
   __syncthreads();
 }
 

@@ -8,21 +8,22 @@
 //
 // One workgroup per (b,t) row finds the threshold key T* = the k-th largest
 // composite key, then emits every position whose key is >= T*:
-//   A. long rows: a 14-bit histogram of a sample of the scores gives a key that is
-//      below the k-th largest score with high probability yet keeps only a few
+//   A. long rows: a histogram of a sample of the scores gives a score that is
+//      below the k-th largest with high probability yet keeps only a few
 //      thousand positions at or above it; one pass over the row collects those
-//      candidates (their composite keys) in LDS.  If their number is not in
+//      candidates in LDS.  If their number is not in
 //      [k, buffer size] (an unlucky sample, massive ties) path B runs instead.
 //   S. rows that fit the candidate buffer whole: all keys in registers, no list.
 //   B. general: MSD radix narrowing on the composite key straight from memory,
 //      11 bits a pass (histogram in 8 interleaved copies, copy = lane & 7, so
 //      that lanes hitting one hot bin do not serialise), until the positions
 //      matching the decided prefix fit the buffer; one pass collects them.
-//   C. both: radix select inside LDS over the candidates yields T* exactly.
-//   D. the selected positions are marked in an LDS bitmap of the row and read
-//      back in ascending order (a counting sort), so the output is ordered
-//      and deterministic.
-// Row passes keep four 16-byte loads per thread in flight; a workgroup that
+//   C. A and S: one histogram spread evenly over the candidates' scores, and
+//      counting inside the digit that holds the k-th; B, or where that digit
+//      is too full: radix select inside LDS over the candidates.
+//   D. positions leave in ascending order, each for its rank among the selected
+//      (a counting sort), so the output is ordered and deterministic.
+// Row passes keep several 16-byte loads per thread in flight; a workgroup that
 // issued one load per thread and round would crawl at memory latency.
 #include "index_tile.h"
 #include "select_common.h"
@@ -30,17 +31,27 @@
 
 namespace {
 
-constexpr int NT = 1024;
+// Eight waves, two per SIMD: an instruction of sixteen takes 16 cycles, and the phases that do not depend on the row's length --
+// scans, reductions, barriers -- are most of the kernel.  us a call, before (sixteen waves, a digit pass over 64-bit keys, positions read back
+// from a bitmap word by word) / now: 1 row of 8000 10.4 / 8.3, 32 rows of 4096 13.0 / 8.2, 13 of 12000 to 16384 14.8 / 10.5, 32 of
+// 32768 15.1 / 11.5, 46 of 24000 to 40000 17.8 / 12.6, 20 of 65000 18.5 / 13.7, 4 of 131072 17.5 / 13.7, 64 of 115000 21.4 / 18.5.
+constexpr int NT = 512;
 constexpr int HBITS = 11;
 constexpr int NBINS = 1 << HBITS;
 constexpr int COPIES = 8;
 using ess_sel::CAND_CAP;
 using ess_sel::SBITS;
 using ess_sel::SBINS;
-constexpr int SAMPLE_TARGET = 4096;         // at most this many samples per row (four per thread), about every 16th score or fewer
-static_assert(SAMPLE_TARGET <= 4 * NT, "the sample is loaded in one round of four per thread");
+constexpr int SAMPLE_TARGET = 4096;         // at most this many samples per row, about every 16th score or fewer
+constexpr int SAMPLE_PER = SAMPLE_TARGET / NT;
 constexpr int FAST_MIN_VIS = CAND_CAP + 1;   // rows above the candidate list's size are sampled (path A)
-constexpr int WHOLE_MIN_VIS = 4097;          // rows from here on that fit that list are done whole (path S)
+constexpr int PER = CAND_CAP / NT;           // keys per thread of a row or a list that is held in registers
+constexpr int LIST_AHEAD = 3072 / NT;        // rounds of NT list entries that are asked for before their number is known
+constexpr int ROUND = 8;                     // float4s per thread and round of a pass over a row
+constexpr int DPT = NBINS / NT;              // digits per thread of a scan over a digit histogram
+constexpr uint32_t SMALL = 1024;             // keys of one digit that are resolved by counting
+constexpr int RANK_WORDS = NBINS * 4;        // words of a row's bitmap up to which the words' ranks fit beside it (262144 positions)
+static_assert(PER * (NT / 64) == 128 && DPT == 4, "two counts a lane; digits are read 16 bytes at a time");
 constexpr uint32_t ROW_DONE = 0xffffffffu;   // in place of a candidate count: the candidate pass did the row itself
 
 struct __align__(16) TopkShared {
@@ -49,13 +60,24 @@ struct __align__(16) TopkShared {
     uint32_t shist[ess_sel::sample_words<NT>()];   // 68 KiB, bins placed by sample_slot
     unsigned long long cand[CAND_CAP];    // 64 KiB
   };
-  int32_t out_list[ESS_MAX_TOPK];         // 16 KiB
-  uint32_t lhist[NBINS];                  // 8 KiB: digit histogram of the candidates held in LDS
+  union {
+    int32_t out_list[ESS_MAX_TOPK];       // 16 KiB
+    struct {
+      unsigned long long few[SMALL + 8];  // the keys of one digit (read eight at a time)
+      uint32_t few_rank[SMALL];           // how many of them are larger
+    };
+  };
+  uint32_t lhist[NBINS];                  // 8 KiB: digit histogram of the candidates
   uint32_t wave_tot[NT / 64];
   unsigned long long red_and[NT / 64], red_or[NT / 64];
   uint32_t out_n, cand_n;
   uint32_t sel_digit, sel_above, sel_count;
   uint32_t sbin[2];                       // sample_bins' result words
+  uint32_t sel_to;                        // bounds_of: samples down to and with the digit sbin[0]
+  __align__(16) float stage[4 * ROUND * NT];               // 64 KiB: a round of a pass over a row
+  float red_lo[NT / 64], red_hi[NT / 64]; // value_range: extremes of the waves' scores
+  uint32_t few_bits[CAND_CAP / 32];       // whole_row: positions taken of the crossing digit
+  uint32_t taken[PER * (NT / 64)];        // whole_row: positions taken of every 64, in ascending order
 };
 
 __device__ __forceinline__ uint32_t orderable(float v) { return ess_orderable(v); }
@@ -83,7 +105,7 @@ __device__ __forceinline__ void wave_append(bool pred, V val, V* list, uint32_t*
 // times (f may hold wave-wide operations).  Each thread has four 16-byte loads in flight per round,
 // which is what makes one workgroup able to pull a 512 KiB row at cache bandwidth, not at latency.
 template <typename F>
-__device__ __forceinline__ void scan_row(int tid, const float* __restrict__ srow, int vis, bool vec_ok, F&& f) {
+__device__ __forceinline__ void scan_row(int tid, const float* srow, int vis, bool vec_ok, F&& f) {
   constexpr int U = 4;
   int done = 0;
   if (vec_ok) {
@@ -115,54 +137,77 @@ __device__ __forceinline__ void scan_row(int tid, const float* __restrict__ srow
   }
 }
 
-// Same walk, handing f one round (16 positions of this thread) at a time.  The loads of the next
-// round are issued before the current round is processed (two register sets); indices past the end
-// are clamped, not predicated, so that every load is unconditional.
-template <typename F>
-__device__ __forceinline__ void scan_row_rounds(int tid, const float* __restrict__ srow, int vis, bool vec_ok, F&& f) {
-  constexpr int U = 4;
-  int done = 0;
-  int pos[16];
-  float val[16];
-  bool ok[16];
-  if (vec_ok && vis >= 4) {
-    const int nvec = vis >> 2;
-    const float4* v4 = reinterpret_cast<const float4*>(srow);
-    auto load = [&](int base, float4 (&x)[U]) {
+// The positions of a row (or a slice of it) whose score reaches tau, as (position, score) pairs in LDS: `raw`, *n_raw of them,
+// of which CAND_CAP have room.  Rounds of 32 positions a thread: the scores go to LDS as they are, and a bit per position says
+// which reach tau (three instructions each); a lane then writes its few positions one after the other, and the wave fetches
+// their scores densely.  (A predicated write per position, 32 of them with a tenth of the lanes each, took 5 k cycles per 16K
+// positions; 3.3 k now.)  The loads of the first SETS rounds are issued by row_begin, before tau is known: one CU
+// pulls a row at 33 GB/s, a 32K row in about the time the threshold takes.  Indices past the end are
+// clamped, not predicated, so that every load is unconditional.  A row may start at any multiple of four bytes: its first
+// positions up to a 16-byte boundary and its last ones, at most six, come by themselves.
+__device__ __forceinline__ int to_boundary(const float* p) { return (int)((0u - (uint32_t)(reinterpret_cast<uintptr_t>(p) >> 2)) & 3u); }
+typedef float float4v __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ void row_load(int tid, const float* srow, int n, int base, float4v (&x)[ROUND]) {
+  const float4v* v4 = reinterpret_cast<const float4v*>(srow);
 #pragma unroll
-      for (int u = 0; u < U; ++u) x[u] = v4[min(base + u * NT + tid, nvec - 1)];
-    };
-    auto process = [&](int base, const float4 (&x)[U]) {
+  for (int g = 0; g < ROUND; ++g) x[g] = v4[max(min(base + g * NT + tid, (n >> 2) - 1), 0)];
+}
+template <int SETS>
+__device__ __forceinline__ void row_begin(int tid, const float* srow, int n, float4v (&x)[SETS][ROUND]) {
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int j = base + u * NT + tid;
-        const bool in = j < nvec;
-        pos[4 * u + 0] = 4 * j + 0; val[4 * u + 0] = x[u].x; ok[4 * u + 0] = in;
-        pos[4 * u + 1] = 4 * j + 1; val[4 * u + 1] = x[u].y; ok[4 * u + 1] = in;
-        pos[4 * u + 2] = 4 * j + 2; val[4 * u + 2] = x[u].z; ok[4 * u + 2] = in;
-        pos[4 * u + 3] = 4 * j + 3; val[4 * u + 3] = x[u].w; ok[4 * u + 3] = in;
+  for (int s = 0; s < SETS; ++s) row_load(tid, srow, n, s * ROUND * NT, x[s]);
+}
+template <int SETS>
+__device__ __forceinline__ void collect(int tid, const float* srow, int first, int n, float4v (&x)[SETS][ROUND], float tau,
+                                        uint2* raw, uint32_t* n_raw, float* stage) {
+  const int lane = tid & 63, head = to_boundary(srow), nvec = (n - head) >> 2;      // (n is at least 1024)
+  auto round = [&](int base, float4v (&y)[ROUND]) {
+    float4v* const st4 = reinterpret_cast<float4v*>(stage);
+    uint32_t hits = 0;                       // position 4 g + e of the thread's 32: bit 31 - (4 g + e)
+#pragma unroll
+    for (int g = 0; g < ROUND; ++g) {
+      st4[g * NT + tid] = y[g];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        hits = (hits << 1) | (y[g][e] >= tau ? 1u : 0u);
+        asm volatile("" : "+v"(hits));       // (one at a time: left alone, the bits are packed in a tree)
       }
-      f(pos, val, ok);
-    };
-    constexpr int R = NT * U;                    // float4s per round
-    float4 xa[U], xb[U];
-    load(0, xa);
-    for (int base = 0; base < nvec; base += 2 * R) {
-      load(base + R, xb);
-      process(base, xa);
-      if (base + R >= nvec) break;
-      load(base + 2 * R, xa);
-      process(base + R, xb);
     }
-    done = nvec << 2;
+    // groups past the end hold the last one's scores again
+    const int groups = min(max((nvec - base - tid + NT - 1) / NT, 0), ROUND);
+    hits &= groups == ROUND ? 0xffffffffu : ~(0xffffffffu >> (4 * groups));
+    if (base + SETS * ROUND * NT < nvec) row_load(tid, srow + head, n - head, base + SETS * ROUND * NT, y);
+    const uint32_t cnt = __popc(hits), inc = wave_incl_scan(cnt, lane), sum = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
+    if (sum == 0) return;
+    uint32_t at = 0;
+    if (lane == 0) at = atomicAdd(n_raw, sum);
+    const uint32_t from = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+    if (from + sum > (uint32_t)CAND_CAP) return;              // too many: the list is not used
+    at = from + inc - cnt;
+    while (hits) {
+      const uint32_t i = (uint32_t)__builtin_clz(hits);
+      hits &= ~(0x80000000u >> i);
+      raw[at++].x = 4u * ((i >> 2) * NT + (uint32_t)tid) + (i & 3u);
+    }
+    // (a wave reads what its own lanes wrote: nothing may be moved across)
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    for (uint32_t j = from + lane; j < from + sum; j += 64) {
+      const uint32_t i = raw[j].x;
+      raw[j] = make_uint2((uint32_t)(first + head + 4 * base) + i, __float_as_uint(stage[i]));
+    }
+    __builtin_amdgcn_wave_barrier();
+  };
+  for (int base = 0; base < nvec; base += SETS * ROUND * NT) {
+    round(base, x[0]);
+    if constexpr (SETS == 2)
+      if (base + ROUND * NT < nvec) round(base + ROUND * NT, x[SETS - 1]);
   }
-  for (int i0 = done; i0 < vis; i0 += 16 * NT) {
-#pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      const int i = i0 + e * NT + tid;
-      pos[e] = i; ok[e] = i < vis; val[e] = ok[e] ? srow[i] : 0.f;
-    }
-    f(pos, val, ok);
+  if (tid < 64) {
+    const int i = tid < head ? tid : 4 * nvec + tid;         // (behind the head come the vectors)
+    const float s = i < n ? srow[i] : 0.f;
+    wave_append<uint2>(i < n && s >= tau, make_uint2((uint32_t)(first + i), __float_as_uint(s)), raw, n_raw, CAND_CAP);
   }
 }
 
@@ -185,160 +230,344 @@ __device__ __forceinline__ void emit_bitmap(TopkShared& sm, int tid, const uint3
   }
 }
 
-// Which of the 2048 digits the radix select's histogram sm.lhist holds contains the need-th largest key, counted
+// Which of the 2048 digits of the histogram sm.lhist contains the need-th largest key, counted
 // from the top: sm.sel_digit, with sm.sel_above keys above it and sm.sel_count in it.  Ends with a barrier.
 __device__ __forceinline__ void crossing_digit(TopkShared& sm, int tid, uint32_t need) {
-  const int d_hi = NBINS - 1 - 2 * tid, d_lo = d_hi - 1;      // thread tid owns two digits, descending
-  const uint32_t c_hi = sm.lhist[d_hi], c_lo = sm.lhist[d_lo];
+  const int d0 = NBINS - DPT - DPT * tid;      // thread tid owns four digits, descending
+  const uint4 h = *reinterpret_cast<const uint4*>(&sm.lhist[d0]);
+  const uint32_t cnt[DPT] = {h.w, h.z, h.y, h.x};
+  const uint32_t mine = h.x + h.y + h.z + h.w;
   uint32_t total;
-  const uint32_t inc = block_incl_scan(c_hi + c_lo, sm.wave_tot, &total);
-  const uint32_t above_hi = inc - c_hi - c_lo;
-  const uint32_t above_lo = above_hi + c_hi;
-  if (above_hi < need && above_hi + c_hi >= need) {
-    sm.sel_digit = d_hi; sm.sel_above = above_hi; sm.sel_count = c_hi;
-  } else if (above_lo < need && above_lo + c_lo >= need) {
-    sm.sel_digit = d_lo; sm.sel_above = above_lo; sm.sel_count = c_lo;
+  uint32_t above = block_incl_scan(mine, sm.wave_tot, &total) - mine;
+  if (above < need && above + mine >= need) {
+#pragma unroll
+    for (int i = 0; i < DPT; ++i) {
+      if (above < need && above + cnt[i] >= need) {
+        sm.sel_digit = (uint32_t)(d0 + DPT - 1 - i); sm.sel_above = above; sm.sel_count = cnt[i];
+      }
+      above += cnt[i];
+    }
   }
   __syncthreads();
 }
 
-// A row finished from its candidate list (`listed` keys at grow, k <= listed <= CAND_CAP; SRC_LDS: the list is
-// sm.cand itself) when the k-th largest score very probably lies in [lo, hi) (ess_orderable images; see
-// sample_bins).  The keys stay in registers.  One
-// histogram pass spreads [lo, hi) over 2046 digits (what lies at or above hi goes into the top one, what lies below lo into
-// the bottom one), the digit
-// that holds the k-th largest key is found, and inside it -- a handful of keys -- the key is found by counting.
-// Returns false, with the keys copied to sm.cand, when that digit holds more keys than the counting step takes
-// (massive ties, or a k-th largest score outside the range): the caller goes on with the general selection.
-constexpr int PER = CAND_CAP / NT;           // keys per thread
-// WHOLE: the keys are a whole row, not a list of candidates.
-template <bool WHOLE>
-__device__ __forceinline__ bool finish_keys(TopkShared& sm, int tid, const unsigned long long (&c)[PER], uint32_t listed,
-                                            uint32_t lo, uint32_t hi, int vis, int k, int IB, int32_t* __restrict__ orow) {
-  constexpr uint32_t SMALL = 1024;           // keys the counting step takes: one per thread
-  const unsigned long long imask = (1ull << IB) - 1ull;
-  // (keys of a list may still be on their way:) clear the histogram and the row's bitmap
-  uint32_t* bmp = sm.hist;
-  const int W = (vis + 31) >> 5;
-  for (int j = tid; j < W; j += NT) bmp[j] = 0;
-  for (int j = tid; j < NBINS; j += NT) sm.lhist[j] = 0;
-  if (tid == 0) sm.cand_n = 0;
-  int sh = 0;
-  while (((hi - lo) >> sh) > (uint32_t)(NBINS - 3)) ++sh;
-  // (what lies below lo has digit 0 to itself: lo is a bin's lower end, a power of two times a small number, and often
-  // the k-th largest score itself where scores are whole numbers or sixteenths.  With the first digit of the range shared,
-  // such rows went to the general selection: 32 rows of 8192 whole numbers 18.8 us, 11.6 now.)
-  auto digit = [&](unsigned long long key) -> uint32_t {
-    const uint32_t sc = (uint32_t)(key >> IB);
-    return sc >= hi ? (uint32_t)(NBINS - 1) : (sc < lo ? 0u : min(1u + ((sc - lo) >> sh), (uint32_t)(NBINS - 2)));
-  };
+// Extremes of the workgroup's values (+inf and -inf where a thread has none), the same in all threads.  One barrier.
+__device__ __forceinline__ void value_range(TopkShared& sm, int tid, float& lo, float& hi) {
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  lo = -ess_sel::wave_max<6>(-lo);
+  hi = ess_sel::wave_max<6>(hi);
+  if (lane == 0) { sm.red_lo[wave] = lo; sm.red_hi[wave] = hi; }
   __syncthreads();
-  if constexpr (WHOLE) {
-    // The two end digits hold most keys of a whole row (all above and all below the crossing bin), and adds to one address
-    // pass one after the other: a wave counts those by ballot and adds each sum once.  (One row of 8192: the step of one
-    // sequence 40.0 us, now 36.4.  A list of candidates has few such keys: there the ballots cost more, 0.3 to 0.9 us.)
-    uint32_t n_top = 0, n_low = 0;
+  lo = -ess_sel::wave_max<3>(-sm.red_lo[lane & (NT / 64 - 1)]);
+  hi = ess_sel::wave_max<3>(sm.red_hi[lane & (NT / 64 - 1)]);
+}
+
+// Scores between lo and hi spread evenly over the digits 1 .. 2046; below lo, -inf and what is no number: 0 or 1; above hi: up
+// to 2047.  Monotone in the score, four instructions.  scale 0: the range gives no such digits.
+struct Spread {
+  float lo, scale;
+  __device__ __forceinline__ Spread(float lo_, float hi_) : lo(lo_) {
+    const float span = hi_ - lo_;
+    scale = span > 1e-30f && span < __builtin_inff() ? (float)(NBINS - 3) / span : 0.f;
+  }
+  __device__ __forceinline__ uint32_t digit(float v) const {
+    return (uint32_t)__builtin_amdgcn_fmed3f(fmaf(v - lo, scale, 1.0f), 0.f, (float)(NBINS - 1));
+  }
+  // a score that no score of digit d or above lies below (a hundredth of a digit covers the rounding of `digit`)
+  __device__ __forceinline__ float edge(uint32_t d) const { return fmaf((float)d - 1.01f, 1.0f / scale, lo); }
+};
+
+__device__ __forceinline__ float score_of(uint32_t o) {      // the score of an ess_orderable image
+  return __uint_as_float((o & 0x80000000u) ? (o & 0x7fffffffu) : ~o);
+}
+
+// Two bounds of a row's selection from a sample of its scores (ns in all, N a thread, the u-th of a thread valid where
+// u * NT + tid < ns): *tau, a score at or above which very probably lie the k largest and not many more (see sample_bins), and
+// *tau_hi, one at or above which lie about an eighth of those: a list spread between the two has few keys a digit near tau, and
+// its last digit is not crowded either (adds to one address pass one after the other: with the fewest that are surely taken, half of all, in the last
+// digit that pass took 3.3 k cycles instead of 1.6).  The sample is spread evenly between its extremes; where
+// that is too coarse (an outlier far away, a handful of values) by its top 14 bits, which takes twice as long.  False: no bounds.
+// sm.lhist must be clear and sm.sbin 0xffffffff once a barrier has passed; sm.shist is used in the second case.
+template <int N>
+__device__ __forceinline__ bool bounds_of(TopkShared& sm, int tid, const float (&sv)[N], int ns, int k, int vis, float* tau, float* tau_hi) {
+  constexpr float kInf = __builtin_inff();
+  float lo = kInf, hi = -kInf;
 #pragma unroll
-    for (int u = 0; u < PER; ++u) {
-      const bool in = (uint32_t)(u * NT + tid) < listed;
-      const uint32_t d = digit(c[u]);
-      n_top += (uint32_t)__popcll(__ballot(in && d == (uint32_t)(NBINS - 1)));
-      n_low += (uint32_t)__popcll(__ballot(in && d == 0u));
-      if (in && d != 0u && d != (uint32_t)(NBINS - 1)) atomicAdd(&sm.lhist[d], 1u);
-    }
-    if ((tid & 63) == 0) {
-      if (n_top) atomicAdd(&sm.lhist[NBINS - 1], n_top);
-      if (n_low) atomicAdd(&sm.lhist[0], n_low);
-    }
-  } else {
+  for (int u = 0; u < N; ++u) {
+    const bool fin = u * NT + tid < ns && fabsf(sv[u]) < kInf;
+    lo = fminf(lo, fin ? sv[u] : kInf);
+    hi = fmaxf(hi, fin ? sv[u] : -kInf);
+  }
+  value_range(sm, tid, lo, hi);
+  const Spread sp(lo, hi);
+  if (sp.scale != 0.f) {
 #pragma unroll
-    for (int u = 0; u < PER; ++u)
-      if ((uint32_t)(u * NT + tid) < listed) atomicAdd(&sm.lhist[digit(c[u])], 1u);
+    for (int u = 0; u < N; ++u)
+      if (u * NT + tid < ns) atomicAdd(&sm.lhist[sp.digit(sv[u])], 1u);
+    __syncthreads();
+    const float expct = (float)k * (float)ns / (float)vis, margin = 4.0f * sqrtf(expct) + 8.0f;
+    // (a quarter more than the margin asks for: a sample of blocks is no random one, and a list that turns out too short costs the
+    // row three times its time; 4 % more for the usual one)
+    const uint32_t target[2] = {(uint32_t)(1.25f * expct + margin), max((uint32_t)(0.125f * expct), 1u)};
+    const int d0 = NBINS - DPT - DPT * tid;
+    const uint4 h = *reinterpret_cast<const uint4*>(&sm.lhist[d0]);
+    const uint32_t cnt[DPT] = {h.w, h.z, h.y, h.x};
+    const uint32_t mine = h.x + h.y + h.z + h.w;
+    uint32_t total;
+    const uint32_t inc = block_incl_scan(mine, sm.wave_tot, &total);
+#pragma unroll
+    for (int w = 0; w < 2; ++w) {
+      uint32_t above = inc - mine;
+      if (target[w] > 0 && above < target[w] && inc >= target[w]) {
+#pragma unroll
+        for (int i = 0; i < DPT; ++i) {
+          if (above < target[w] && above + cnt[i] >= target[w]) {
+            sm.sbin[w] = (uint32_t)(d0 + DPT - 1 - i);
+            if (w == 0) sm.sel_to = above + cnt[i];
+          }
+          above += cnt[i];
+        }
+      }
+    }
+    __syncthreads();
+    const uint32_t b0 = sm.sbin[0], b1 = sm.sbin[1];
+    if (b0 != 0xffffffffu && b0 >= 1u && (float)sm.sel_to * (float)vis < 0.9f * CAND_CAP * (float)ns) {
+      *tau = sp.edge(b0);
+      *tau_hi = b1 == 0xffffffffu ? hi : sp.edge(b1 + 1);
+      return *tau_hi > *tau;
+    }
+    __syncthreads();
+    if (tid == 0) sm.sbin[0] = sm.sbin[1] = 0xffffffffu;
+  }
+  for (int j = tid; j < ess_sel::sample_words<NT>(); j += NT) sm.shist[j] = 0;
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < N; ++u)
+    if (u * NT + tid < ns) atomicAdd(&sm.shist[ess_sel::sample_slot<NT>(orderable(sv[u]) >> (32 - SBITS))], 1u);
+  __syncthreads();
+  uint32_t lo_bin, hi_bin;
+  ess_sel::sample_bins<NT>(sm.shist, sm.wave_tot, sm.sbin, k, ns, vis, &lo_bin, &hi_bin);
+  if (lo_bin == 0xffffffffu || lo_bin == 0u) return false;
+  // (the lower end of the bin of -inf, or of what lies above +inf, is no score)
+  *tau = fmaxf(score_of(lo_bin << (32 - SBITS)), -3.4028235e38f);
+  *tau_hi = hi_bin == 0xffffffffu || hi_bin == SBINS - 1 ? 3.4028235e38f : fminf(score_of((hi_bin + 1) << (32 - SBITS)), 3.4028235e38f);
+  return *tau_hi > *tau;
+}
+
+// Inside the digit that holds the k-th largest key -- a handful of keys, sm.few[0..cnt): f(key) for the `take` largest, found by
+// counting.  Keys are distinct.  Up to sixteen are counted by one thread each; of more (equal scores) each key's rivals are shared
+// by the threads that there are (145 keys: 15 k cycles by one thread each and one at a time, 2.5 k now).  Begins with a
+// barrier; sm.few_rank must be clear once it has passed.
+template <typename F>
+__device__ __forceinline__ void take_few(TopkShared& sm, int tid, uint32_t cnt, uint32_t take, F&& f) {
+  if (tid < 8) sm.few[cnt + tid] = 0ull;                     // (keys are read eight at a time; none is smaller than this one)
+  __syncthreads();
+  auto count = [&](unsigned long long my, uint32_t from, uint32_t step) {
+    uint32_t above = 0;
+    for (uint32_t i = from; i < cnt; i += step) {
+      unsigned long long x[8];
+#pragma unroll
+      for (uint32_t e = 0; e < 8; ++e) x[e] = sm.few[i + e];
+#pragma unroll
+      for (uint32_t e = 0; e < 8; ++e) {
+        above += x[e] > my ? 1u : 0u;
+        asm volatile("" : "+v"(above));      // (a compare and an add with carry; left alone, bits are packed and counted)
+      }
+    }
+    return above;
+  };
+  if (cnt <= 16) {
+    if ((uint32_t)tid < cnt && count(sm.few[tid], 0, 8) < take) f(sm.few[tid]);
+    return;
+  }
+  const uint32_t shares = max(NT / cnt, 1u), share = shares > 1 ? (uint32_t)tid / cnt : 0u;
+  if (share < shares)
+    for (uint32_t j = (uint32_t)tid - share * cnt; j < cnt; j += NT) {
+      const uint32_t above = count(sm.few[j], 8 * share, 8 * shares);
+      if (above) atomicAdd(&sm.few_rank[j], above);
+    }
+  __syncthreads();
+  for (uint32_t j = tid; j < cnt; j += NT)
+    if (sm.few_rank[j] < take) f(sm.few[j]);
+}
+
+// What bounds the two finishing forms below: the keys are few and everything waits for everything in front of it, so time is the
+// instructions of all waves and the barriers.  A key is worth as few instructions as can be: its digit is computed once
+// and kept, 64-bit keys are built for the one digit that has to be resolved, and positions leave by rank.
+
+// A row finished from its candidate list (`listed` scores v and positions p, k <= listed <= CAND_CAP) when the k-th largest score very probably lies in [tau, tau_hi) (see bounds_of).  One
+// histogram spreads that range over 2046 digits (what lies above goes into the last), the digit that holds the k-th largest
+// key is found, and inside it the key by counting.  The positions taken are marked in a bitmap of the row, and each leaves
+// for its rank: the positions taken in the words before, and in its word before it.
+// Returns false, with the keys in sm.cand, when that digit holds more keys than the counting step takes
+// (massive ties, or a k-th largest score outside the range): the caller goes on with the general selection.
+template <int N>
+__device__ __forceinline__ bool finish_rounds(TopkShared& sm, int tid, const float (&v)[PER], const uint32_t (&p)[PER], uint32_t listed,
+                                            float tau, float tau_hi, int vis, int k, int IB, int32_t* __restrict__ orow) {
+  const unsigned long long imask = (1ull << IB) - 1ull;
+  auto key = [&](int u) { return ((unsigned long long)orderable(v[u]) << IB) | (imask - (unsigned long long)p[u]); };
+  // (keys of a list may still be on their way:) clear the histogram and the row's bitmap
+  uint32_t* const bmp = sm.hist;
+  const int W = (vis + 31) >> 5;             // at most 16384 words
+  for (int j = 4 * tid; j < W; j += 4 * NT) *reinterpret_cast<uint4*>(&bmp[j]) = make_uint4(0, 0, 0, 0);
+  *reinterpret_cast<uint4*>(&sm.lhist[DPT * tid]) = make_uint4(0, 0, 0, 0);
+  if (tid == 0) sm.cand_n = 0;
+  const Spread sp(tau, tau_hi);
+  constexpr uint32_t NONE = 0xffffffffu;
+  uint32_t d[N];
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < N; ++u) {
+    d[u] = (uint32_t)(u * NT + tid) < listed ? sp.digit(v[u]) : NONE;
+    if (d[u] != NONE) atomicAdd(&sm.lhist[d[u]], 1u);
   }
   __syncthreads();
   crossing_digit(sm, tid, (uint32_t)k);
   const uint32_t dsel = sm.sel_digit, take = (uint32_t)k - sm.sel_above, cnt = sm.sel_count;
-  unsigned long long t_in = 0ull;            // inside the digit, keys at or above this one are taken
-  if (cnt != take) {
-    if (cnt > SMALL) {
+  if (cnt != take || sp.scale == 0.f) {
+    if (cnt > SMALL || sp.scale == 0.f) {
 #pragma unroll
       for (int u = 0; u < PER; ++u)
-        if ((uint32_t)(u * NT + tid) < listed) sm.cand[u * NT + tid] = c[u];
+        if ((uint32_t)(u * NT + tid) < listed) sm.cand[u * NT + tid] = key(u);
       if (tid == 0) sm.cand_n = listed;
       __syncthreads();
       return false;
     }
-    unsigned long long* few = reinterpret_cast<unsigned long long*>(sm.out_list);     // room for 2048 keys
+    for (int j = tid; j < (int)SMALL; j += NT) sm.few_rank[j] = 0;
 #pragma unroll
-    for (int u = 0; u < PER; ++u)
-      wave_append<unsigned long long>((uint32_t)(u * NT + tid) < listed && digit(c[u]) == dsel, c[u], few, &sm.cand_n);
-    __syncthreads();
-    if ((uint32_t)tid < cnt) {
-      const unsigned long long my = few[tid];
-      uint32_t above = 0;
-      for (uint32_t i = 0; i < cnt; ++i) above += few[i] > my ? 1u : 0u;
-      if (above == take - 1u) sm.red_and[0] = my;            // keys are distinct: exactly one thread
-    }
-    __syncthreads();
-    t_in = sm.red_and[0];
+    for (int u = 0; u < N; ++u)
+      if (d[u] == dsel) sm.few[atomicAdd(&sm.cand_n, 1u)] = key(u);
   }
+  const uint32_t above = cnt == take ? dsel : dsel + 1;      // digits from here on are taken whole
 #pragma unroll
-  for (int u = 0; u < PER; ++u) {
-    if ((uint32_t)(u * NT + tid) < listed) {
-      const uint32_t d = digit(c[u]);
-      if (d > dsel || (d == dsel && c[u] >= t_in)) {
-        const uint32_t pos = (uint32_t)(imask - (c[u] & imask));
-        atomicOr(&bmp[pos >> 5], 1u << (pos & 31));
-      }
-    }
-  }
+  for (int u = 0; u < N; ++u)
+    if (d[u] >= above && d[u] != NONE) atomicOr(&bmp[p[u] >> 5], 1u << (p[u] & 31));
+  if (cnt != take)
+    take_few(sm, tid, cnt, take, [&](unsigned long long c) {
+      const uint32_t pos = (uint32_t)(imask - (c & imask));
+      atomicOr(&bmp[pos >> 5], 1u << (pos & 31));
+    });
   __syncthreads();
-  emit_bitmap(sm, tid, bmp, W, k, orow);
+  if (W > RANK_WORDS) {
+    emit_bitmap(sm, tid, bmp, W, k, orow);
+    return true;
+  }
+  uint32_t* const rank0 = sm.hist + RANK_WORDS;            // behind the bitmap: the positions taken in front of each word
+  auto ranks = [&](auto quads) {                           // a thread's words: 4 * Q in a row
+    constexpr int Q = decltype(quads)::value;
+    uint4 w[Q];
+    uint32_t n = 0;
+#pragma unroll
+    for (int i = 0; i < Q; ++i) {
+      const int j = 4 * (Q * tid + i);
+      w[i] = j < W ? *reinterpret_cast<const uint4*>(&bmp[j]) : make_uint4(0, 0, 0, 0);
+      w[i] = make_uint4(__popc(w[i].x), __popc(w[i].y), __popc(w[i].z), __popc(w[i].w));
+      n += w[i].x + w[i].y + w[i].z + w[i].w;
+    }
+    uint32_t total;
+    uint32_t at = block_incl_scan(n, sm.wave_tot, &total) - n;
+#pragma unroll
+    for (int i = 0; i < Q; ++i) {
+      const int j = 4 * (Q * tid + i);
+      if (j < W) *reinterpret_cast<uint4*>(&rank0[j]) = make_uint4(at, at + w[i].x, at + w[i].x + w[i].y, at + w[i].x + w[i].y + w[i].z);
+      at += w[i].x + w[i].y + w[i].z + w[i].w;
+    }
+  };
+  if (W <= 4 * NT) ranks(std::integral_constant<int, 1>{});
+  else ranks(std::integral_constant<int, 4>{});
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < N; ++u) {
+    const uint32_t wd = (uint32_t)(u * NT + tid) < listed ? p[u] >> 5 : 0u, bits = bmp[wd], bit = 1u << (p[u] & 31u);
+    const uint32_t at = rank0[wd] + __popc(bits & (bit - 1u));
+    if ((uint32_t)(u * NT + tid) < listed && (bits & bit)) orow[at] = (int32_t)p[u];
+  }
   return true;
 }
-
-template <bool SRC_LDS>
-__device__ __forceinline__ bool finish_fast(TopkShared& sm, int tid, const unsigned long long* grow, uint32_t listed,
-                                            uint32_t lo, uint32_t hi, int vis, int k, int IB, int32_t* __restrict__ orow) {
-  unsigned long long c[PER];
-#pragma unroll
-  for (int u = 0; u < PER; ++u)
-    c[u] = (uint32_t)(u * NT + tid) < listed ? (SRC_LDS ? sm.cand[u * NT + tid] : grow[u * NT + tid]) : 0ull;
-  if (SRC_LDS) __syncthreads();              // the bitmap shares its memory with the list: every thread holds its keys first
-  return finish_keys<false>(sm, tid, c, listed, lo, hi, vis, k, IB, orow);
+__device__ __forceinline__ bool finish_list(TopkShared& sm, int tid, const float (&v)[PER], const uint32_t (&p)[PER], uint32_t listed,
+                                            float tau, float tau_hi, int vis, int k, int IB, int32_t* __restrict__ orow) {
+  if (listed <= 8u * NT) return finish_rounds<8>(sm, tid, v, p, listed, tau, tau_hi, vis, k, IB, orow);
+  return finish_rounds<PER>(sm, tid, v, p, listed, tau, tau_hi, vis, k, IB, orow);
 }
 
-// Path S: a row that fits the candidate list whole needs no sample and no list: eight keys per thread in registers, a
-// histogram of their top 14 bits tells exactly in which bin the k-th largest lies, and that bin's range is resolved like
-// the range between two sampled bounds.  Against path B (one 11-bit pass collects the row, up to five more follow in
-// LDS), one row / 32 rows, us: 8192 scores 10.8 / 10.9 against 13.1 / 13.5, 5000 10.0 / 10.5 against 10.5 / 12.0, but
-// 4096 10.0 / 10.7 against 8.8 / 10.6 and 2500 10.6 / 10.9 against 9.9 / 10.8: from 4097 on (WHOLE_MIN_VIS).
+// Path S: a row that fits the candidate list whole needs no sample and no list: its scores in registers.  They are spread evenly
+// over 2046 digits between the smallest and the largest finite one; the digit that holds the k-th
+// largest is found, and inside it the key by counting.  A wave holds 64 consecutive positions at a time, so a position's rank
+// is the number taken in the 64s before, plus a bit count: no bitmap.  (Even digits hold a dozen keys near the threshold where
+// scores are as they come; with an outlier a hundred times the spread away still a few hundred.)
 // Where rows are shared it is part 0 of the candidate pass (MODE 1) that takes such a row, not the finishing kernel:
-// inlined there beside its other paths it cost every longer row 0.4 to 0.6 us (and 256 bytes of scratch a lane where
-// work is drawn by ticket).
-// Returns false, with the keys in sm.cand, when more than 1024 keys share a digit of the bin.
-__device__ __forceinline__ bool whole_row(TopkShared& sm, int tid, const float* __restrict__ srow, int vis, int k, int IB,
+// inlined there beside its other paths it cost every longer row 0.4 to 0.6 us.
+// Returns false, with the keys in sm.cand, when more than SMALL keys share that digit (massive ties).
+__device__ __forceinline__ bool whole_row(TopkShared& sm, int tid, const float (&v)[PER], int vis, int k, int IB,
                                           int32_t* __restrict__ orow) {
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const unsigned long long imask = (1ull << IB) - 1ull;
-  float sv[PER];
-#pragma unroll
-  for (int u = 0; u < PER; ++u) sv[u] = u * NT + tid < vis ? srow[u * NT + tid] : 0.f;
-  for (int j = tid; j < ess_sel::sample_words<NT>(); j += NT) sm.shist[j] = 0;
-  if (tid == 0) sm.sbin[0] = 0u;
-  __syncthreads();
-  unsigned long long c[PER];
+  auto key = [&](int u) { return ((unsigned long long)orderable(v[u]) << IB) | (imask - (unsigned long long)(u * NT + tid)); };
+  *reinterpret_cast<uint4*>(&sm.lhist[DPT * tid]) = make_uint4(0, 0, 0, 0);
+  if (tid == 0) sm.cand_n = 0;
+  constexpr float kInf = __builtin_inff();
+  float lo = kInf, hi = -kInf;               // of the finite scores
 #pragma unroll
   for (int u = 0; u < PER; ++u) {
-    const int i = u * NT + tid;
-    c[u] = i < vis ? ((unsigned long long)orderable(sv[u]) << IB) | (imask - (unsigned long long)i) : 0ull;
-    if (i < vis) atomicAdd(&sm.shist[ess_sel::sample_slot<NT>((uint32_t)(c[u] >> IB) >> (32 - SBITS))], 1u);
+    const bool fin = u * NT + tid < vis && fabsf(v[u]) < kInf;
+    lo = fminf(lo, fin ? v[u] : kInf);
+    hi = fmaxf(hi, fin ? v[u] : -kInf);
+  }
+  value_range(sm, tid, lo, hi);
+  const Spread sp(lo, hi);
+  uint32_t d[PER];
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    d[u] = sp.digit(v[u]);
+    if (sp.scale == 0.f) d[u] = v[u] == kInf ? NBINS - 1 : (v[u] > -kInf ? 1u : 0u);      // (one value, or a span past a float's)
+    if (u * NT + tid < vis) atomicAdd(&sm.lhist[d[u]], 1u);
+    else d[u] = 0xffffffffu;
   }
   __syncthreads();
-  ess_sel::crossing_bin<NT>(sm.shist, sm.wave_tot, sm.sbin, (uint32_t)k);     // (ends with a barrier: shist is dead from here)
-  const uint32_t bin = sm.sbin[0];
-  const uint32_t lo = bin << (32 - SBITS), hi = bin == SBINS - 1 ? 0xffffffffu : (bin + 1) << (32 - SBITS);
+  crossing_digit(sm, tid, (uint32_t)k);
+  const uint32_t dsel = sm.sel_digit, take = (uint32_t)k - sm.sel_above, cnt = sm.sel_count;
+  if (cnt > SMALL && cnt != take) {
+#pragma unroll
+    for (int u = 0; u < PER; ++u)
+      if (u * NT + tid < vis) sm.cand[u * NT + tid] = key(u);
+    __syncthreads();
+    return false;
+  }
+  // the few that are taken of the crossing digit: a bit per position
+  const uint32_t above = cnt == take ? dsel : dsel + 1;      // digits from here on are taken whole
+  if (cnt != take) {
+    if (tid < (int)(sizeof(sm.few_bits) / 4)) sm.few_bits[tid] = 0;
+    for (int j = tid; j < (int)SMALL; j += NT) sm.few_rank[j] = 0;
+#pragma unroll
+    for (int u = 0; u < PER; ++u)
+      if (d[u] == dsel) sm.few[atomicAdd(&sm.cand_n, 1u)] = key(u);
+    take_few(sm, tid, cnt, take, [&](unsigned long long c) {
+      const uint32_t pos = (uint32_t)(imask - (c & imask));
+      atomicOr(&sm.few_bits[pos >> 5], 1u << (pos & 31));
+    });
+    __syncthreads();
+  }
+  uint2 bits = make_uint2(0u, 0u);           // lane u: those of the wave's u-th 64
+  if (cnt != take && lane < PER) bits = *reinterpret_cast<const uint2*>(&sm.few_bits[2 * (lane * (NT / 64) + wave)]);
+  unsigned long long m[PER];                 // taken positions of the wave's u-th 64
+  uint32_t n = 0;                            // lane u: how many
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    m[u] = __ballot(d[u] >= above && d[u] != 0xffffffffu) |
+           ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)bits.y, u) << 32 | (uint32_t)__builtin_amdgcn_readlane((int)bits.x, u));
+    n = lane == u ? (uint32_t)__popcll(m[u]) : n;
+  }
+  if (lane < PER) sm.taken[lane * (NT / 64) + wave] = n;
   __syncthreads();
-  return finish_keys<true>(sm, tid, c, (uint32_t)vis, lo, hi, vis, k, IB, orow);
+  const uint2 two = *reinterpret_cast<const uint2*>(&sm.taken[2 * lane]);
+  const uint32_t before = wave_incl_scan(two.x + two.y, lane) - (two.x + two.y) + ((wave & 1) ? two.x : 0u);
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    const uint32_t at = (uint32_t)__builtin_amdgcn_readlane((int)before, (u * (NT / 64) + wave) >> 1);
+    if ((m[u] >> lane) & 1ull)
+      orow[at + __builtin_amdgcn_mbcnt_hi((uint32_t)(m[u] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m[u], 0u))] = u * NT + tid;
+  }
+  return true;
 }
 
 // MODE 0: one workgroup does the whole row (grid: rows).
@@ -350,8 +579,8 @@ __device__ __forceinline__ bool whole_row(TopkShared& sm, int tid, const float* 
 // the row by itself like MODE 0.  The hand-over is the kernel boundary: workgroups of one kernel
 // never exchange data (an agent-scope fence inside a kernel costs tens of microseconds on this
 // multi-die part, where it writes the L2 back).  g_cnt is zero between steps: MODE 2 clears it.
-// MODE 4: as MODE 0 where max_ctx allows only rows that fit the candidate list (path S, and B for the shortest): without
-// path A's code one row of 8000 takes 9.9 us instead of 10.2.
+// MODE 4: as MODE 0 where max_ctx allows only rows that fit the candidate list (path S): the scores are asked for before the
+// row's length is known.
 // MODE 3: the finishing kernel of the fused selection (grid rows).  The row's list was written by the emitting
 // index-score pass (index_kernel.h), for rows of any length; `score` is scratch memory, not scores: a row whose list
 // cannot be used (fewer than k or more than the buffer holds: a misleading sample, massive ties) has its scores
@@ -362,7 +591,7 @@ struct TopkRecompute {                     // MODE 3: what it takes to compute a
   int n_pages, Hi, Di;
 };
 template <int MODE, bool DYN>
-__device__ __forceinline__ void topk_item(TopkShared& sm, int item, int parts, float* __restrict__ score,
+__device__ __forceinline__ void topk_item(TopkShared& sm, int item, int parts, float* score,
                                           const int32_t* __restrict__ ctx_len, int T, int Lmax, int k, int IB,
                                           int32_t* __restrict__ idx_out, unsigned long long* __restrict__ g_cand,
                                           uint32_t* __restrict__ g_cnt, uint32_t* __restrict__ g_tau, const TopkRecompute& rc) {
@@ -374,17 +603,37 @@ __device__ __forceinline__ void topk_item(TopkShared& sm, int item, int parts, f
   int tid_ = threadIdx.x;
   if constexpr (DYN) asm volatile("" : "+v"(tid_));
   const int tid = tid_, lane = tid & 63;
-  int vis = ctx_len[b] - (T - 1 - t);
-  vis = max(0, min(vis, Lmax));
   float* srow = score + (size_t)row * Lmax;
   int32_t* orow = idx_out + (size_t)row * k;
-
-  if (MODE == 1 && (vis <= k || vis < FAST_MIN_VIS)) {            // nothing to prepare: a short row is done here, or later
-    if (part == 0 && vis > k && vis >= WHOLE_MIN_VIS && whole_row(sm, tid, srow, vis, k, IB, orow) && tid == 0) g_cnt[row] = ROW_DONE;
+  float v[MODE == 2 || MODE == 3 ? 1 : PER];
+  if constexpr (MODE == 4) {               // no row is longer than the list: asked for beside the row's length
+#pragma unroll
+    for (int u = 0; u < PER; ++u) v[u] = u * NT + tid < Lmax ? srow[u * NT + tid] : 0.f;
+  }
+  int vis = ctx_len[b] - (T - 1 - t);
+  vis = max(0, min(vis, Lmax));
+  auto load_whole = [&](float (&v)[PER], int n) {
+#pragma unroll
+    for (int u = 0; u < PER; ++u) v[u] = u * NT + tid < n ? srow[u * NT + tid] : 0.f;
+  };
+  if constexpr (MODE == 1) if (vis <= k || vis < FAST_MIN_VIS) {  // nothing to prepare: a short row is done here, or later
+    if (part == 0 && vis > k) {
+      load_whole(v, vis);
+      if (whole_row(sm, tid, v, vis, k, IB, orow) && tid == 0) g_cnt[row] = ROW_DONE;
+    }
     return;
   }
   uint32_t listed = 0;
-  if (MODE == 2 || MODE == 3) {            // candidates prepared by the kernel in front (0 if none)
+  unsigned long long c[MODE == 2 || MODE == 3 ? PER : 1];
+  float list_lo = 0.f, list_hi = 0.f;
+  if constexpr (MODE == 2 || MODE == 3) {  // candidates prepared by the kernel in front (0 if none)
+    // (the first entries, usually all, are asked for beside their number: a place behind the list's end holds anything)
+    const unsigned long long* grow = g_cand + (size_t)row * CAND_CAP;
+#pragma unroll
+    for (int u = 0; u < LIST_AHEAD; ++u) c[u] = grow[u * NT + tid];
+    const uint2 bounds = *reinterpret_cast<const uint2*>(g_tau + 2 * row);      // left by the kernel that made the list
+    list_lo = score_of(bounds.x);
+    list_hi = bounds.x != 0u && bounds.y > bounds.x ? score_of(bounds.y) : list_lo;
     listed = g_cnt[row];
     __syncthreads();
     if (tid == 0) g_cnt[row] = 0;
@@ -411,8 +660,9 @@ __device__ __forceinline__ void topk_item(TopkShared& sm, int item, int parts, f
   int nc = 0;
 
   // ---- S: rows that fit the candidate list whole
-  if ((MODE == 0 || MODE == 4) && vis >= WHOLE_MIN_VIS && vis <= CAND_CAP) {
-    if (whole_row(sm, tid, srow, vis, k, IB, orow)) return;
+  if constexpr (MODE == 0 || MODE == 4) if (vis <= CAND_CAP) {
+    if constexpr (MODE == 0) load_whole(v, vis);
+    if (whole_row(sm, tid, v, vis, k, IB, orow)) return;
     nc = vis;                              // the keys are in sm.cand now, the general selection takes them
     have_cand = true;
     all_in_cand = true;
@@ -430,87 +680,70 @@ __device__ __forceinline__ void topk_item(TopkShared& sm, int item, int parts, f
     else ess_idx::row_scores_slow<32>(q_row, w_row, rc.Hi, keys, Lmax, table_row, rc.n_pages, vis, srow);
     __syncthreads();                       // the scores are read back by other threads of this workgroup
   }
-  if (use_list) {
+  if constexpr (MODE == 2 || MODE == 3) if (use_list) {
     const unsigned long long* grow = g_cand + (size_t)row * CAND_CAP;
-    bool copied = false;
-    {
-      const uint32_t lo = g_tau[2 * row], hi = g_tau[2 * row + 1];       // left by the kernel that made the list
-      if (lo != 0u && hi > lo) {
-        if (finish_fast<false>(sm, tid, grow, listed, lo, hi, vis, k, IB, orow)) return;
-        copied = true;
+    float lv[PER];
+    uint32_t lp[PER];
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      if (u >= LIST_AHEAD) c[u] = (uint32_t)(u * NT) < listed && (uint32_t)(u * NT + tid) < listed ? grow[u * NT + tid] : 0ull;
+      lv[u] = score_of((uint32_t)(c[u] >> IB));
+      lp[u] = (uint32_t)(imask - (c[u] & imask));
+    }
+    if (!(list_hi > list_lo)) {              // a list without bounds: its own extremes
+      constexpr float kInf = __builtin_inff();
+      list_lo = kInf;
+      list_hi = -kInf;
+#pragma unroll
+      for (int u = 0; u < PER; ++u) {
+        const bool fin = (uint32_t)(u * NT + tid) < listed && fabsf(lv[u]) < kInf;
+        list_lo = fminf(list_lo, fin ? lv[u] : kInf);
+        list_hi = fmaxf(list_hi, fin ? lv[u] : -kInf);
       }
+      value_range(sm, tid, list_lo, list_hi);
     }
-    if (!copied) {
-      for (int j = tid; j < (int)listed; j += NT) sm.cand[j] = grow[j];
-      if (tid == 0) sm.cand_n = listed;
-      __syncthreads();
-    }
+    if (finish_list(sm, tid, lv, lp, listed, list_lo, list_hi, vis, k, IB, orow)) return;
   }
   if (MODE != 4 && (vis >= FAST_MIN_VIS || use_list)) {
-   uint32_t lo_bin = 0, hi_bin = 0xffffffffu;
-   if (!use_list) {
-    // samples: blocks of 16 consecutive scores (one 64-byte piece of a cache line), every bstride-th block,
-    // about SAMPLE_TARGET scores in all.  (One score out of every 16th..32nd touches every cache line of the
-    // row: in cache-line traffic the sample then costs as much as the pass that follows.)
-    const int nblk_all = vis >> 4;
-    int bstride = 1;
-    while (nblk_all / bstride > SAMPLE_TARGET / 16) bstride <<= 1;
-    const int ns = (nblk_all / bstride) << 4;
-    // (at most SAMPLE_TARGET samples: four per thread, requested before the histogram is cleared)
-    float sv[4];
+    float tau = 0.f, tau_hi = 0.f;
+    bool found = use_list;
+    if (!use_list) {
+      // samples: blocks of 16 consecutive scores (one 64-byte piece of a cache line), one of every bstride blocks at a
+      // place that changes from one to the next (scores that repeat with the stride would else be counted all or not at all),
+      // about SAMPLE_TARGET scores in all.  (One score out of every 16th..32nd touches every cache line of the
+      // row: in cache-line traffic the sample then costs as much as the pass that follows.)
+      const int nblk_all = vis >> 4;
+      int bstride = 1;
+      while (nblk_all / bstride > SAMPLE_TARGET / 16) bstride <<= 1;
+      const int ns = (nblk_all / bstride) << 4;
+      float sv[SAMPLE_PER];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int j = u * NT + tid;
-      sv[u] = j < ns ? srow[(size_t)(j >> 4) * bstride * 16 + (j & 15)] : 0.f;
-    }
-    for (int j = tid; j < ess_sel::sample_words<NT>(); j += NT) sm.shist[j] = 0;
-    if (tid == 0) { sm.cand_n = 0; sm.sbin[0] = sm.sbin[1] = 0xffffffffu; }
-    __syncthreads();
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-      if (u * NT + tid < ns) atomicAdd(&sm.shist[ess_sel::sample_slot<NT>(orderable(sv[u]) >> (32 - SBITS))], 1u);
-    __syncthreads();
-    ess_sel::sample_bins<NT>(sm.shist, sm.wave_tot, sm.sbin, k, ns, vis, &lo_bin, &hi_bin);      // (ends with a barrier: shist is dead from here, cand may overwrite it)
-   }
-    if (MODE == 1 && lo_bin == 0xffffffffu) return;   // no usable threshold: the finishing kernel takes path B
-    if (use_list || lo_bin != 0xffffffffu) {
-     // the k-th largest score very probably lies in [tau, tau_hi) (see sample_bins)
-     const uint32_t tau = lo_bin << (32 - SBITS);
-     const uint32_t tau_hi = (hi_bin == 0xffffffffu || hi_bin == SBINS - 1) ? 0xffffffffu : (hi_bin + 1) << (32 - SBITS);
-     if (!use_list) {
-      // The pass only compares floats and stores (position, score) of the few positions at or above
-      // the key: v >= tau_f is the same predicate as orderable(v) >= tau (NaN fails both, -0 == +0),
-      // and the composite keys are computed afterwards, densely, for the candidates alone.
-      const float tau_f = __uint_as_float((tau & 0x80000000u) ? (tau & 0x7fffffffu) : ~tau);
-      uint2* raw = reinterpret_cast<uint2*>(sm.cand);
-      // this workgroup's slice of the row (boundaries on 16-byte pieces)
+      for (int u = 0; u < SAMPLE_PER; ++u) {
+        const int j = min(u * NT + tid, ns - 1);
+        const int blk = (j >> 4) * bstride + (int)(((uint32_t)(j >> 4) * 0x9e3779b1u >> 16) & (uint32_t)(bstride - 1));
+        sv[u] = srow[(size_t)blk * 16 + (j & 15)];
+      }
+      *reinterpret_cast<uint4*>(&sm.lhist[DPT * tid]) = make_uint4(0, 0, 0, 0);
+      if (tid == 0) { sm.cand_n = 0; sm.sbin[0] = sm.sbin[1] = 0xffffffffu; }
+      // this workgroup's slice of the row (boundaries on 16-byte pieces); its first round is asked for behind the samples
       const int s_lo = parts > 1 ? (int)(((long)vis * part / parts) & ~3L) : 0;
       const int s_hi = (parts > 1 && part + 1 < parts) ? (int)(((long)vis * (part + 1) / parts) & ~3L) : vis;
-      scan_row_rounds(tid, srow + s_lo, s_hi - s_lo, vec_ok, [&](const int (&pos)[16], const float (&val)[16], const bool (&ok)[16]) {
-        uint32_t cnt = 0, flags = 0;
-#pragma unroll
-        for (int e = 0; e < 16; ++e)
-          if (ok[e] && val[e] >= tau_f) { flags |= 1u << e; ++cnt; }
-        // one LDS atomic per wave and round
-        const uint32_t winc = wave_incl_scan(cnt, lane);
-        uint32_t base = 0;
-        if (lane == 63 && winc) base = atomicAdd(&sm.cand_n, winc);
-        base = __shfl(base, 63, 64) + winc - cnt;
-#pragma unroll
-        for (int e = 0; e < 16; ++e)
-          if (flags & (1u << e)) {
-            if (base < (uint32_t)CAND_CAP) raw[base] = make_uint2((uint32_t)(pos[e] + s_lo), __float_as_uint(val[e]));
-            ++base;
-          }
-      });
+      constexpr int SETS = MODE == 1 ? 1 : 2;
+      float4v x[SETS][ROUND];
+      const float* const slice = srow + s_lo;
+      const int head = to_boundary(slice);
+      row_begin<SETS>(tid, slice + head, s_hi - s_lo - head, x);
+      __builtin_amdgcn_sched_barrier(0);
+      found = bounds_of(sm, tid, sv, ns, k, vis, &tau, &tau_hi);
+      __syncthreads();                       // (the list shares its memory with the sample's histogram)
+      if (MODE == 1 && !found) return;       // no usable threshold: the finishing kernel takes path B
+      // The pass only compares floats and stores (position, score) of the few positions at or above
+      // the threshold (NaN is below, -0 == +0: the order of the keys),
+      // and the composite keys are computed afterwards, densely, for the candidates alone.
+      if (found) collect(tid, slice, s_lo, s_hi - s_lo, x, tau, reinterpret_cast<uint2*>(sm.cand), &sm.cand_n, sm.stage);
       __syncthreads();
-      if ((int)sm.cand_n <= CAND_CAP)
-        for (int j = tid; j < (int)sm.cand_n; j += NT) {
-          const uint2 pv = raw[j];
-          sm.cand[j] = comp_of((int)pv.x, __uint_as_float(pv.y));
-        }
-      __syncthreads();
-     }
+    }
+    if (found) {
       nc = (int)sm.cand_n;
       if (MODE == 1) {
         // append this slice's candidates to the row's list; the true count is added even when it overflows,
@@ -518,18 +751,31 @@ __device__ __forceinline__ void topk_item(TopkShared& sm, int item, int parts, f
         unsigned long long* grow = g_cand + (size_t)row * CAND_CAP;
         if (tid == 0) {
           sm.sel_above = atomicAdd(&g_cnt[row], (uint32_t)nc);
-          if (part == 0) { g_tau[2 * row] = tau; g_tau[2 * row + 1] = tau_hi; }    // (every part finds the same two)
+          if (part == 0) { g_tau[2 * row] = orderable(tau); g_tau[2 * row + 1] = orderable(tau_hi); }      // (every part finds the same two)
         }
         __syncthreads();
         const uint32_t gbase = sm.sel_above;
         if (nc <= CAND_CAP)
           for (int j = tid; j < nc; j += NT)
-            if (gbase + (uint32_t)j < (uint32_t)CAND_CAP) grow[gbase + j] = sm.cand[j];
+            if (gbase + (uint32_t)j < (uint32_t)CAND_CAP) {
+              const uint2 pv = reinterpret_cast<const uint2*>(sm.cand)[j];
+              grow[gbase + j] = comp_of((int)pv.x, __uint_as_float(pv.y));
+            }
         return;
       }
-      if (!use_list && nc >= k && nc <= CAND_CAP && tau != 0u && tau_hi > tau &&
-          finish_fast<true>(sm, tid, sm.cand, (uint32_t)nc, tau, tau_hi, vis, k, IB, orow))
-        return;
+      if (!use_list && nc >= k && nc <= CAND_CAP) {
+        float lv[PER];
+        uint32_t lp[PER];
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+          uint2 pv = make_uint2(0u, 0u);
+          if (u * NT < nc && u * NT + tid < nc) pv = reinterpret_cast<const uint2*>(sm.cand)[u * NT + tid];
+          lp[u] = pv.x;
+          lv[u] = __uint_as_float(pv.y);
+        }
+        __syncthreads();                   // the bitmap shares its memory with the list: every thread holds its keys first
+        if (finish_list(sm, tid, lv, lp, (uint32_t)nc, tau, tau_hi, vis, k, IB, orow)) return;
+      }
       if (nc >= k && nc <= CAND_CAP) {
         // bits on which the candidates differ: everything above is common and decided
         unsigned long long a = ~0ull, o = 0ull;
@@ -566,24 +812,14 @@ __device__ __forceinline__ void topk_item(TopkShared& sm, int item, int parts, f
           atomicAdd(&sm.hist[(((uint32_t)(c >> shift)) & dmask) * COPIES + (lane & 7)], 1u);
       });
       __syncthreads();
-      // thread tid owns digits NBINS-1-2*tid and NBINS-2-2*tid (descending), scan = suffix counts
-      const int d_hi = NBINS - 1 - 2 * tid, d_lo = d_hi - 1;
-      uint32_t c_hi = 0, c_lo = 0;
+      for (int j = tid; j < NBINS; j += NT) {              // the copies of a digit are added up
+        uint32_t sum = 0;
 #pragma unroll
-      for (int r = 0; r < COPIES; ++r) {
-        c_hi += sm.hist[d_hi * COPIES + r];
-        c_lo += sm.hist[d_lo * COPIES + r];
-      }
-      uint32_t total;
-      const uint32_t inc = block_incl_scan(c_hi + c_lo, sm.wave_tot, &total);
-      const uint32_t above_hi = inc - c_hi - c_lo;      // keys with a digit > d_hi
-      const uint32_t above_lo = above_hi + c_hi;        // keys with a digit > d_lo
-      if (above_hi < need && above_hi + c_hi >= need) {
-        sm.sel_digit = d_hi; sm.sel_above = above_hi; sm.sel_count = c_hi;
-      } else if (above_lo < need && above_lo + c_lo >= need) {
-        sm.sel_digit = d_lo; sm.sel_above = above_lo; sm.sel_count = c_lo;
+        for (int r = 0; r < COPIES; ++r) sum += sm.hist[j * COPIES + r];
+        sm.lhist[j] = sum;
       }
       __syncthreads();
+      crossing_digit(sm, tid, need);
       need -= sm.sel_above;
       prefix = (prefix << bits) | sm.sel_digit;
       cnt_match = sm.sel_count;
@@ -653,7 +889,7 @@ __device__ __forceinline__ void topk_item(TopkShared& sm, int item, int parts, f
 }
 
 template <int MODE, bool DYN>
-__global__ __launch_bounds__(NT) void k_topk(float* __restrict__ score, const int32_t* __restrict__ ctx_len,
+__global__ __launch_bounds__(NT) void k_topk(float* score, const int32_t* __restrict__ ctx_len,
                                              int T, int Lmax, int k, int IB, int32_t* __restrict__ idx_out,
                                              unsigned long long* __restrict__ g_cand, uint32_t* __restrict__ g_cnt,
                                              uint32_t* __restrict__ g_tau, ess_xcd xcd, int rows, int parts_arg,
@@ -681,8 +917,7 @@ __global__ __launch_bounds__(NT) void k_index_tau(const float* __restrict__ samp
                                                   int T, int Lmax, int k, int period, int nsamp,
                                                   uint32_t* __restrict__ tau, uint32_t* __restrict__ g_cnt, ess_xcd xcd,
                                                   int rows) {
-  __shared__ uint32_t shist[ess_sel::sample_words<NT>()];
-  __shared__ uint32_t wave_tot[NT / 64], sel[2];
+  __shared__ TopkShared sm;
   __shared__ int s_item;
   ESS_WORK_LOOP(DYN, xcd, blockIdx.x, rows, &s_item, row) {
     const int tid = threadIdx.x;
@@ -705,23 +940,17 @@ __global__ __launch_bounds__(NT) void k_index_tau(const float* __restrict__ samp
     const int ns = nv * 64;
     // the samples are requested before the histogram is cleared: one round trip to memory, not two
     const float* srow = sample + (size_t)row * nsamp * 64;
-    constexpr int PER = ESS_SAMPLE_BLOCKS * 64 / NT;
-    float sv[PER];
+    constexpr int N = ESS_SAMPLE_BLOCKS * 64 / NT;
+    float sv[N];
 #pragma unroll
-    for (int u = 0; u < PER; ++u) sv[u] = u * NT + tid < ns ? srow[u * NT + tid] : 0.f;
-    for (int j = tid; j < ess_sel::sample_words<NT>(); j += NT) shist[j] = 0;
-    if (tid == 0) sel[0] = sel[1] = 0xffffffffu;
-    __syncthreads();
-#pragma unroll
-    for (int u = 0; u < PER; ++u)
-      if (u * NT + tid < ns) atomicAdd(&shist[ess_sel::sample_slot<NT>(orderable(sv[u]) >> (32 - SBITS))], 1u);
-    __syncthreads();
-    uint32_t lo = 0xffffffffu, hi = 0xffffffffu;
-    if (ns > 0) ess_sel::sample_bins<NT>(shist, wave_tot, sel, k, ns, vis, &lo, &hi);
+    for (int u = 0; u < N; ++u) sv[u] = u * NT + tid < ns ? srow[u * NT + tid] : 0.f;
+    *reinterpret_cast<uint4*>(&sm.lhist[DPT * tid]) = make_uint4(0, 0, 0, 0);
+    if (tid == 0) sm.sbin[0] = sm.sbin[1] = 0xffffffffu;
+    float lo = 0.f, hi = 0.f;
+    const bool found = ns > 0 && bounds_of(sm, tid, sv, ns, k, vis, &lo, &hi);
     if (tid == 0) {
-      tau[2 * row] = lo == 0xffffffffu ? 0u : lo << (32 - SBITS);
-      // scores in the bins above `hi` are very probably fewer than k; no such bin: no upper bound
-      tau[2 * row + 1] = lo == 0xffffffffu ? 0u : ((hi == 0xffffffffu || hi == SBINS - 1) ? 0xffffffffu : (hi + 1) << (32 - SBITS));
+      tau[2 * row] = found ? orderable(lo) : 0u;
+      tau[2 * row + 1] = found ? orderable(hi) : 0u;
     }
   }
 }

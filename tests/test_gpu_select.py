@@ -193,3 +193,47 @@ def test_selection_nan_inf_and_wide_range_through_key_scales(ess_lib):
     ref = O.topk(sc, np.array(lens), k)
     _topk_sets_equal(_run_index_topk(ess_lib, q, w, pages, lens, k, block_table=table.numpy()), ref)
     _topk_sets_equal(_run_decode_step(ess_lib, q, w, pages, lens, k, block_table=table.numpy()), ref)
+
+
+def _hard_rows(kind, L):
+    """Scores that send a row through one branch of the selection each."""
+    rng = np.random.RandomState(len(kind) * 1000 + L)
+    x = (rng.randn(L) * 40 + 300).astype(np.float32)
+    if kind == "outlier":                 # the sample's extremes say nothing about the threshold
+        x[rng.randint(0, L, 3)] = np.float32(1e30)
+    elif kind.startswith("tied"):         # a group of equal scores round the k-th: counted by shares, or too many to count
+        n = int(kind[4:])
+        x[rng.permutation(L)[:n]] = np.sort(x)[-2048]
+    elif kind == "signed":
+        x -= 300
+    elif kind == "infinite":              # scores that no even spread has a place for
+        x[::7] = -np.inf
+        x[5::91] = np.inf
+        x[3::11] = np.nan
+    elif kind == "one":
+        x[:] = 2.5
+    elif kind == "two":
+        x[:] = np.where(rng.rand(L) < 0.1, 7.0, 7.0 + 1e-6)
+    return x
+
+
+@pytest.mark.parametrize("L,vis", [(8192, 8192), (8192, 4097), (8193, 8193), (20483, 20483), (49157, 40001), (65536, 65536), (131074, 131074),
+                                   (300001, 300001)])
+def test_topk_of_hard_rows_at_the_edges_of_its_paths(ess_lib, L, vis):
+    """Whole rows, rows in rounds and shared rows (64K and more), aligned and not, against the oracle: the set of the k largest
+    is one set, so it must be equal."""
+    from paper_2512_10576_amd import binding as bnd
+    kinds = ["plain", "outlier", "tied20", "tied100", "tied200", "tied400", "tied900", "tied3000", "signed", "infinite", "one", "two"]
+    sc = np.stack([_hard_rows(kind, L) for kind in kinds])[:, None, :]
+    lens = np.full(len(kinds), vis)
+    for k in (2048, 513):
+        print("hard rows", L, vis, k, flush=True)
+        ctx = bnd.Context(bnd.make_config(len(kinds), 1, L, 64, 128, k, 16))
+        idx = torch.empty((len(kinds), 1, k), dtype=torch.int32, device="cuda")
+        ctx.topk(torch.from_numpy(sc).cuda(), torch.from_numpy(lens).to(torch.int32).cuda(), idx)
+        torch.cuda.synchronize()
+        ref = np.sort(O.topk(sc, lens, k), axis=2)
+        got = idx.cpu().numpy()
+        for i, kind in enumerate(kinds):
+            assert np.array_equal(got[i], ref[i]), (kind, L, vis, k)
+        ctx.close()
