@@ -731,7 +731,27 @@ __global__ __launch_bounds__(256) void k_fill_gather(const ess_fetch f, const in
 // none (the entry then lives in the host pool only).  Without a host pool slot = position.
 // OFFLOADED false: without a host pool, a form of its own: a resident append has no use for the stamps, and with their 16
 // registers and the search beside it it took 0.6 us longer (6 sequences, two tokens: 4.8 us, now 4.2).
+// What bounds it: a launch (3.5 us) and the chain context length -> page -> stores.  So all that does not wait for it -- stamps, new keys and
+// rows of all tokens, each by threads of its own -- is asked for at the start; the tokens' victims are found one after the
+// other from registers, a wave's smallest by lane moves in 32 bits (stamp, then slot); the tables are written at the end.  (Before, each token in turn loaded its rows, compared 64-bit keys through the LDS and waited
+// for its victim's former token.)  us, before / now: 23 sequences, 9001 slots, two tokens, paged 8.6 / 7.1; 8 sequences, 20000 slots,
+// four tokens, a call 21.8 / 14.3; a whole step of 10 sequences, two tokens, with its append 89.4 / 87.4.
 constexpr int APPEND_NT = 1024;
+constexpr int APPEND_T = 4;                      // query tokens at most
+// smallest of the 64 lanes' values, in all lanes (see wave_max)
+__device__ __forceinline__ uint32_t wave_min_u32(uint32_t x) {
+  auto with = [&](auto ctrl, auto rows) {
+    x = min(x, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)x, decltype(ctrl)::value, decltype(rows)::value, 0xf, false));
+  };
+  using std::integral_constant;
+  with(integral_constant<int, 0x111>{}, integral_constant<int, 0xf>{});
+  with(integral_constant<int, 0x112>{}, integral_constant<int, 0xf>{});
+  with(integral_constant<int, 0x114>{}, integral_constant<int, 0xf>{});
+  with(integral_constant<int, 0x118>{}, integral_constant<int, 0xf>{});
+  with(integral_constant<int, 0x142>{}, integral_constant<int, 0xa>{});
+  with(integral_constant<int, 0x143>{}, integral_constant<int, 0xc>{});
+  return (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
+}
 template <bool OFFLOADED>
 __global__ __launch_bounds__(APPEND_NT) void k_append(
     const uint8_t* __restrict__ new_key, const uint8_t* __restrict__ new_rows, uint8_t* __restrict__ key,
@@ -739,10 +759,20 @@ __global__ __launch_bounds__(APPEND_NT) void k_append(
     int32_t* __restrict__ token_of, uint32_t* __restrict__ stamp, int32_t* __restrict__ ctx_len,
     int32_t* __restrict__ placed, int T, int Di, int Lmax, int S, int row_stride, uint32_t step,
     const float* __restrict__ new_scale, const int32_t* __restrict__ block_table, int n_pages) {
-  __shared__ unsigned long long red[APPEND_NT / 64];
+  __shared__ uint2 red[APPEND_T][APPEND_NT / 64];
   const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   uint32_t* stp = stamp + (size_t)b * S;
-  // the stamps of a thread's slots (tid, tid + 1024, ..), asked for before anything that waits; held for all T tokens
+  const int kchunks = Di >> 4, rchunks = row_stride >> 4;        // at most 8 and 128
+  // threads 128 t .. bring the row of token t, threads 512 + 16 t .. its key, thread 512 + 16 t + 15 its scale
+  const int rt = tid >> 7, rc = tid & 127, kt = (tid - 512) >> 4, kc = (tid - 512) & 15;
+  const bool my_row = rt < T && rc < rchunks, my_key = tid >= 512 && kt < T && kc < kchunks, my_scale = tid >= 512 && kt < T && kc == 15 && new_scale;
+  uint4 piece = make_uint4(0, 0, 0, 0);
+  float scale = 0.f;
+  if (my_row) piece = reinterpret_cast<const uint4*>(new_rows + ((size_t)b * T + rt) * row_stride)[rc];
+  if (my_key) piece = reinterpret_cast<const uint4*>(new_key + ((size_t)b * T + kt) * Di)[kc];
+  if (my_scale) scale = new_scale[(size_t)b * T + kt];
+  // the stamps of a thread's slots (tid, tid + 1024, ..)
   constexpr int AS = 16;
   const bool held = OFFLOADED && S <= APPEND_NT * AS;
   uint32_t sr[AS];
@@ -759,76 +789,78 @@ __global__ __launch_bounds__(APPEND_NT) void k_append(
       const int pid = bt[(L0 + t) / ESS_PAGE_TOKENS];
       if (pid < 0 || pid >= n_pages) { n = t; break; }
     }
-  const int kchunks = Di >> 4, rchunks = row_stride >> 4;
-  int32_t* so = slot_of + (size_t)b * Lmax;
-  int32_t* to = token_of + (size_t)b * S;
-  for (int t = 0; t < T; ++t) {
-    if (t >= n) {                                  // no room left in the buffers: dropped
-      if (tid == 0 && placed) placed[(size_t)b * T + t] = -1;
-      continue;
-    }
-    const int p = L0 + t;
-    const uint4* krow = reinterpret_cast<const uint4*>(new_key + ((size_t)b * T + t) * Di);
-    const uint4* erow = reinterpret_cast<const uint4*>(new_rows + ((size_t)b * T + t) * row_stride);
+  // keys, and rows to the host pool
+  if (tid >= 512 && kt < n) {
+    const int p = L0 + kt;
     if (bt) {
       uint8_t* page = key + (size_t)bt[p / ESS_PAGE_TOKENS] * ((size_t)ESS_PAGE_TOKENS * (Di + 4));
       const int r = p % ESS_PAGE_TOKENS;
-      if (tid < kchunks) reinterpret_cast<uint4*>(page + (size_t)r * Di)[tid] = krow[tid];
-      if (tid == 32) reinterpret_cast<float*>(page + (size_t)ESS_PAGE_TOKENS * Di)[r] = new_scale[(size_t)b * T + t];
-    } else if (tid < kchunks) {
-      reinterpret_cast<uint4*>(key + ((size_t)b * Lmax + p) * Di)[tid] = krow[tid];
+      if (my_key) reinterpret_cast<uint4*>(page + (size_t)r * Di)[kc] = piece;
+      if (my_scale) reinterpret_cast<float*>(page + (size_t)ESS_PAGE_TOKENS * Di)[r] = scale;
+    } else if (my_key) {
+      reinterpret_cast<uint4*>(key + ((size_t)b * Lmax + p) * Di)[kc] = piece;
     }
-    if (OFFLOADED && tid >= 64 && tid - 64 < rchunks)
-      reinterpret_cast<uint4*>(host_pool + ((size_t)b * Lmax + p) * row_stride)[tid - 64] = erow[tid - 64];
-    int v = p;
-    if constexpr (OFFLOADED) {
-      unsigned long long best = ~0ull;
+  }
+  if (OFFLOADED && my_row && rt < n) reinterpret_cast<uint4*>(host_pool + ((size_t)b * Lmax + L0 + rt) * row_stride)[rc] = piece;
+  // slot of each token: its position, or the smallest in (stamp, slot) of those below `step`, each taken once
+  int v[APPEND_T];
+#pragma unroll
+  for (int t = 0; t < APPEND_T; ++t) v[t] = t < n ? L0 + t : -1;
+  if constexpr (OFFLOADED) {
+    uint2 best = make_uint2(0xffffffffu, 0xffffffffu);         // the thread's smallest: stamp, slot
+    auto mine = [&](int taken) {                   // ... of its slots but those taken
+      best = make_uint2(0xffffffffu, 0xffffffffu);
+      auto look = [&](uint32_t x, int s) {
+        bool free_slot = s < S && x < step && x < best.x;      // (slots in ascending order: of equal stamps the first)
+#pragma unroll
+        for (int t = 0; t < APPEND_T; ++t) free_slot = free_slot && !(t < taken && v[t] == s);
+        if (free_slot) best = make_uint2(x, (uint32_t)s);
+      };
       if (held) {
 #pragma unroll
-        for (int j = 0; j < AS; ++j) {             // (a slot past the pool holds the largest stamp: never below step)
-          const unsigned long long cand = ((unsigned long long)sr[j] << 32) | (uint32_t)(tid + j * APPEND_NT);
-          if (sr[j] < step && tid + j * APPEND_NT < S) best = cand < best ? cand : best;
-        }
+        for (int j = 0; j < AS; ++j) look(sr[j], tid + j * APPEND_NT);
       } else {
-        for (int s = tid; s < S; s += APPEND_NT) {
-          const uint32_t x = stp[s];
-          if (x < step) {
-            const unsigned long long cand = ((unsigned long long)x << 32) | (uint32_t)s;
-            best = cand < best ? cand : best;
-          }
-        }
+        for (int s = tid; s < S; s += APPEND_NT) look(stp[s], s);
       }
+    };
+    mine(0);
 #pragma unroll
-      for (int d = 1; d < 64; d <<= 1) {
-        const unsigned long long o = __shfl_xor(best, d, 64);
-        best = o < best ? o : best;
-      }
-      if (lane == 0) red[tid >> 6] = best;
+    for (int t = 0; t < APPEND_T; ++t) {
+      if (t >= n) break;                           // (the same in all threads)
+      const uint32_t lo = wave_min_u32(best.x), at = wave_min_u32(best.x == lo ? best.y : 0xffffffffu);
+      if (lane == 0) red[t][wave] = make_uint2(lo, at);
       __syncthreads();
-      best = red[0];
-#pragma unroll
-      for (int i = 1; i < APPEND_NT / 64; ++i) best = red[i] < best ? red[i] : best;
-      v = best == ~0ull ? -1 : (int)(uint32_t)best;
-      if (held && v >= 0 && v % APPEND_NT == tid) {
-#pragma unroll
-        for (int j = 0; j < AS; ++j) sr[j] = v / APPEND_NT == j ? step : sr[j];
-      }
+      const uint2 r = lane < APPEND_NT / 64 ? red[t][lane] : make_uint2(0xffffffffu, 0xffffffffu);
+      const uint32_t all = wave_min_u32(r.x), slot = wave_min_u32(r.x == all ? r.y : 0xffffffffu);
+      v[t] = all == 0xffffffffu ? -1 : (int)slot;
+      if (v[t] >= 0 && v[t] % APPEND_NT == tid) mine(t + 1);
     }
-    if (v >= 0) {
-      if (tid >= 256 && tid - 256 < rchunks)
-        reinterpret_cast<uint4*>(slot_pool + ((size_t)b * S + v) * row_stride)[tid - 256] = erow[tid - 256];
-      if (tid == 0) {
-        const int old = to[v];
-        if (old >= 0) so[old] = -1;
-        to[v] = p;
-        so[p] = v;
-        stp[v] = step;
-      }
-    }
-    if (tid == 0 && placed) placed[(size_t)b * T + t] = v;
-    __syncthreads();                               // the next token's search sees this stamp; red is free again
+  } else {
+    __syncthreads();                               // (everyone has read ctx_len)
   }
-  if (tid == 0) ctx_len[b] = L0 + n;               // every thread read ctx_len before the first barrier or exit
+#pragma unroll
+  for (int t = 0; t < APPEND_T; ++t)
+    if (v[t] >= 0 && rt == t && rc < rchunks) reinterpret_cast<uint4*>(slot_pool + ((size_t)b * S + v[t]) * row_stride)[rc] = piece;
+  // The tables: one thread, token by token (a former token may be a position that this very call fills: a context that was
+  // cut back), the former tokens asked for together.
+  if (tid == APPEND_NT - 64) {
+    int32_t* so = slot_of + (size_t)b * Lmax;
+    int32_t* to = token_of + (size_t)b * S;
+    int old[APPEND_T];
+#pragma unroll
+    for (int t = 0; t < APPEND_T; ++t) old[t] = v[t] >= 0 ? to[v[t]] : -1;
+#pragma unroll
+    for (int t = 0; t < APPEND_T; ++t) {
+      if (v[t] >= 0) {
+        if (old[t] >= 0) so[old[t]] = -1;
+        to[v[t]] = L0 + t;
+        so[L0 + t] = v[t];
+        stp[v[t]] = step;
+      }
+      if (t < T && placed) placed[(size_t)b * T + t] = v[t];   // no room, no page or no slot: -1
+    }
+  }
+  if (tid == 0) ctx_len[b] = L0 + n;               // (every thread has read it: a barrier lies between, or nothing is appended)
 }
 
 __global__ __launch_bounds__(256) void k_calib_copy(uint4* __restrict__ dst, const uint4* __restrict__ src, size_t n) {

@@ -474,6 +474,7 @@ __device__ __forceinline__ bool finish_rounds(TopkShared& sm, int tid, const flo
     }
   };
   if (W <= 4 * NT) ranks(std::integral_constant<int, 1>{});
+  else if (W <= 8 * NT) ranks(std::integral_constant<int, 2>{});
   else ranks(std::integral_constant<int, 4>{});
   __syncthreads();
 #pragma unroll

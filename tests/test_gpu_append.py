@@ -158,3 +158,40 @@ def test_append_argument_errors(ess_lib):
     with pytest.raises(bnd.EssError):
         ctx.append(cache, torch.zeros((3, 1, 32), dtype=torch.uint8, device="cuda"), nr, key, cl, 1)   # B > max_batch
     ctx.close()
+
+
+@pytest.mark.parametrize("fmt,T,S,L", [(0, 4, 37, 6000), (1, 4, 16385, 17000), (1, 3, 1024, 6000), (0, 4, 3, 6000)])
+def test_append_of_several_tokens_and_after_a_cut(ess_lib, fmt, T, S, L):
+    """Three and four tokens a call, pools of one slot a thread and less, of more than the registers hold, and of fewer slots than
+    tokens; then contexts cut back, so that a victim's former token may be a position that the same call fills."""
+    from paper_2512_10576_amd import binding as bnd
+    print("append several", fmt, T, S, L, flush=True)
+    B, Hi, Di, k = 3, 4, 64, 2
+    stride = (1152, 656)[fmt]
+    _, _, key = synth.indexer_inputs(61, B, T, Hi, Di, L, 8, 8, 16)
+    hp = torch.empty((B, L, stride), dtype=torch.uint8, pin_memory=True).zero_()
+    ctx = _ctx(ess_lib, max_batch=B, max_q_tokens=T, max_ctx=L, idx_heads=Hi, idx_dim=Di, topk=k if T * k <= S else 1,
+               attn_heads=8, slots_per_seq=max(S, T), latent_fmt=fmt)
+    S = ctx.cfg.slots_per_seq
+    cache = bnd.Cache.allocate(ctx.cfg, B, host_pool=hp)
+    ctx.cache_reset(cache, B)
+    oc, opool, ohost = O.SlotCache(B, L, S), np.zeros((B, S, stride), np.uint8), np.zeros((B, L, stride), np.uint8)
+    okey, octx = key.numpy().copy(), np.array([100, 2000, L - 11], np.int32)
+    dkey, dctx = key.cuda(), torch.from_numpy(octx.copy()).cuda()
+    cache.slot_pool.zero_()
+    placed = torch.empty((B, T), dtype=torch.int32, device="cuda")
+    for step in range(1, 14):
+        if step % 3 == 0:                              # the last tokens are taken back
+            octx -= np.array([1, T, T - 1], np.int32)
+            dctx.copy_(torch.from_numpy(octx))
+        nk, nr = _new_entries(80 + step, B, T, Hi, Di, fmt)
+        ref = O.append_tokens(oc, okey, ohost, opool, octx, nk.numpy(), nr.numpy(), step)
+        ctx.append(cache, nk.cuda(), nr.cuda(), dkey, dctx, step, placed)
+        torch.cuda.synchronize()
+        assert np.array_equal(placed.cpu().numpy(), ref), step
+        assert np.array_equal(dctx.cpu().numpy(), octx) and np.array_equal(dkey.cpu().numpy(), okey) and np.array_equal(hp.numpy(), ohost)
+        assert np.array_equal(cache.slot_of.cpu().numpy(), oc.slot_of), step
+        assert np.array_equal(cache.token_of.cpu().numpy(), oc.token_of), step
+        assert np.array_equal(cache.stamp.cpu().numpy().view(np.uint32), oc.stamp)
+        assert np.array_equal(cache.slot_pool.cpu().numpy(), opool)
+    ctx.close()
