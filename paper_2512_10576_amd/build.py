@@ -16,7 +16,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libess.so")
-SOURCES = ["ess_api.hip", "index_score.hip", "index_select.hip", "index_sample.hip", "topk.hip", "cache.hip", "sparse_mla.hip", "sparse_mla_h32.hip"]
+SOURCES = ["ess_api.hip", "index_score.hip", "index_select.hip", "index_kept.hip", "index_sample.hip", "topk.hip", "cache.hip", "sparse_mla.hip", "sparse_mla_h32.hip"]
 FLAGS = ["-O3", "--offload-arch=gfx950", "-fPIC", "-std=c++17", "-I" + os.path.join(ROOT, "include"),
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wno-unused-command-line-argument"]
 

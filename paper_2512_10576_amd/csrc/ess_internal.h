@@ -267,7 +267,9 @@ int ess_launch_index_score(const ess_config& c, const uint8_t* q, const float* w
                            const int32_t* ctx_len, int B, int T, float* score, hipStream_t st,
                            const int32_t* block_table = nullptr, int n_pages = 0,
                            // optional: events that take the kernel's own start and end times
-                           hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr, ess_xcd xcd = ess_xcd{nullptr, 0, nullptr, 0});
+                           hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr, ess_xcd xcd = ess_xcd{nullptr, 0, nullptr, 0},
+                           // the scores are read next and are few: ordinary stores (see ess_decode_step)
+                           bool keep_scores = false);
 // The fused selection (index score + top-k without a score array) is four launches: scores of each sequence's
 // sample blocks -> sel_sample; lower bounds -> sel_tau (and sel_cnt cleared); the emitting index-score pass ->
 // sel_cand / sel_cnt; the top-k finish -> idx.  b0: first sequence of the (sub-)batch, for the context's arrays;

@@ -9,14 +9,15 @@
 // ReLU / head-weighted reduction stays in registers (see index_tile.h).
 //
 // Two forms of the one kernel body:
-//   * dense (EMIT false): every score is written to score[b,t,s];
-//   * emit (EMIT true): no score is written; positions whose score reaches the row's lower bound tau[b,t]
+//   * dense: every score is written to score[b,t,s];
+//   * emit: no score is written; positions whose score reaches the row's lower bound tau[b,t]
 //     (derived from a sample of the sequence's keys by the pass in front, index_sample.hip) are collected in LDS
 //     as composite selection keys and appended, once per workgroup, to the row's candidate list, from which the
 //     top-k is finished.  The score stream (4 bytes per key and query token, and the pass of the top-k that would
 //     read it back) does not exist in this form.
 //
-// This header is compiled into two translation units (EMIT false / true), which halves the build time.
+// This header is compiled into three translation units (FORM: dense, emitting, dense with ordinary stores), for the build time.
+// (The kind of store is not a branch: with one in its loop the dense launch of 13 x 128K took 44.6 us instead of 43.4.)
 #pragma once
 #include "index_tile.h"
 #include <hip/hip_ext.h>
@@ -24,6 +25,8 @@
 namespace ess_idx {
 
 constexpr int kWaves = 4;                 // waves per workgroup
+// what a launch leaves behind: every score, stored past the caches or (few of them, read next) the ordinary way, or candidates
+enum { DENSE = 0, EMITTING = 1, DENSE_KEPT = 2 };
 constexpr int kMaxChunk = 2048;           // keys per work item at most
 
 struct IdxArgs {
@@ -51,8 +54,9 @@ struct IdxArgs {
 // vector-register results: with one wave allowed it puts them in accumulation registers and copies every one back
 // before the ReLU (64 v_accvgpr_read per batch of 64 keys).  The looping single-token form is left as it was: beside
 // a fetch, on six XCDs, it measured 2 % slower in the other form.
-template <int HB, int DI, int T, bool PAGED, bool DYN, bool EMIT>
+template <int HB, int DI, int T, bool PAGED, bool DYN, int FORM>
 __global__ __launch_bounds__(kWaves * 64, (T == 2 || !DYN) ? 2 : 1) void k_index_score(const IdxArgs a) {
+  constexpr bool EMIT = FORM == EMITTING;
   constexpr int KS = DI / 32;
   constexpr size_t kPageBytes = (size_t)kBatchTokens * (DI + 4);
   __shared__ int s_item;
@@ -164,7 +168,10 @@ __global__ __launch_bounds__(kWaves * 64, (T == 2 || !DYN) ? 2 : 1) void k_index
       if (tok < blk_end) {
 #pragma unroll
         for (int t = 0; t < T; ++t) {
-          __builtin_nontemporal_store(PAGED ? res[t] * kr.sc : res[t], &score[(size_t)(b * Ttot + t0 + t) * Lmax + tok]);
+          const float v = PAGED ? res[t] * kr.sc : res[t];
+          float* const at = &score[(size_t)(b * Ttot + t0 + t) * Lmax + tok];
+          if constexpr (FORM == DENSE_KEPT) *at = v;
+          else __builtin_nontemporal_store(v, at);
         }
       }
     }
@@ -217,7 +224,7 @@ __global__ __launch_bounds__(kWaves * 64, (T == 2 || !DYN) ? 2 : 1) void k_index
   }
 }
 
-template <int HB, int DI, int T, bool PAGED, bool DYN, bool EMIT>
+template <int HB, int DI, int T, bool PAGED, bool DYN, int FORM>
 void launch_d(dim3 grid, hipStream_t st, const IdxArgs& a0, hipEvent_t ev_start, hipEvent_t ev_stop) {
   const dim3 block(kWaves * 64);
   IdxArgs a = a0;
@@ -226,48 +233,50 @@ void launch_d(dim3 grid, hipStream_t st, const IdxArgs& a0, hipEvent_t ev_start,
     static int per_cu = 0;
     if (per_cu == 0) {
       int n = 0;
-      if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_index_score<HB, DI, T, PAGED, true, EMIT>, kWaves * 64, 0) != hipSuccess || n < 1) n = 1;
+      if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_index_score<HB, DI, T, PAGED, true, FORM>, kWaves * 64, 0) != hipSuccess || n < 1) n = 1;
       per_cu = n;
     }
     grid = dim3(ess_xcd_grid(a.nx * a.nb_seq, a.xcd, per_cu));
   }
   if (ev_start || ev_stop)          // timed launch: the events take the kernel's own start and end
-    hipExtLaunchKernelGGL((k_index_score<HB, DI, T, PAGED, DYN, EMIT>), grid, block, 0, st, ev_start, ev_stop, 0, a);
+    hipExtLaunchKernelGGL((k_index_score<HB, DI, T, PAGED, DYN, FORM>), grid, block, 0, st, ev_start, ev_stop, 0, a);
   else
-    hipLaunchKernelGGL((k_index_score<HB, DI, T, PAGED, DYN, EMIT>), grid, block, 0, st, a);
+    hipLaunchKernelGGL((k_index_score<HB, DI, T, PAGED, DYN, FORM>), grid, block, 0, st, a);
 }
 
-template <int HB, int DI, int T, bool PAGED, bool EMIT>
+template <int HB, int DI, int T, bool PAGED, int FORM>
 void launch_k(dim3 grid, hipStream_t st, const IdxArgs& a, hipEvent_t e0, hipEvent_t e1) {
-  if (a.xcd.ticket) launch_d<HB, DI, T, PAGED, true, EMIT>(grid, st, a, e0, e1);
-  else launch_d<HB, DI, T, PAGED, false, EMIT>(grid, st, a, e0, e1);
+  if constexpr (FORM != DENSE_KEPT) {
+    if (a.xcd.ticket) { launch_d<HB, DI, T, PAGED, true, FORM>(grid, st, a, e0, e1); return; }
+  }
+  launch_d<HB, DI, T, PAGED, false, FORM>(grid, st, a, e0, e1);
 }
 
-template <int HB, int DI, int T, bool EMIT>
+template <int HB, int DI, int T, int FORM>
 void launch_p(dim3 grid, hipStream_t st, const IdxArgs& a, hipEvent_t e0, hipEvent_t e1) {
-  if (a.block_table) launch_k<HB, DI, T, true, EMIT>(grid, st, a, e0, e1);
-  else launch_k<HB, DI, T, false, EMIT>(grid, st, a, e0, e1);
+  if (a.block_table) launch_k<HB, DI, T, true, FORM>(grid, st, a, e0, e1);
+  else launch_k<HB, DI, T, false, FORM>(grid, st, a, e0, e1);
 }
 
-template <int HB, int DI, bool EMIT>
+template <int HB, int DI, int FORM>
 void launch_t(int T, dim3 grid, hipStream_t st, const IdxArgs& a, hipEvent_t e0, hipEvent_t e1) {
-  if (T == 1) launch_p<HB, DI, 1, EMIT>(grid, st, a, e0, e1);
-  else launch_p<HB, DI, 2, EMIT>(grid, st, a, e0, e1);
+  if (T == 1) launch_p<HB, DI, 1, FORM>(grid, st, a, e0, e1);
+  else launch_p<HB, DI, 2, FORM>(grid, st, a, e0, e1);
 }
 
-template <int DI, bool EMIT>
+template <int DI, int FORM>
 void launch_hb(int HB, int T, dim3 grid, hipStream_t st, const IdxArgs& a, hipEvent_t e0, hipEvent_t e1) {
   switch (HB) {
-    case 1: launch_t<1, DI, EMIT>(T, grid, st, a, e0, e1); break;
-    case 2: launch_t<2, DI, EMIT>(T, grid, st, a, e0, e1); break;
-    case 3: launch_t<3, DI, EMIT>(T, grid, st, a, e0, e1); break;
-    default: launch_t<4, DI, EMIT>(T, grid, st, a, e0, e1); break;
+    case 1: launch_t<1, DI, FORM>(T, grid, st, a, e0, e1); break;
+    case 2: launch_t<2, DI, FORM>(T, grid, st, a, e0, e1); break;
+    case 3: launch_t<3, DI, FORM>(T, grid, st, a, e0, e1); break;
+    default: launch_t<4, DI, FORM>(T, grid, st, a, e0, e1); break;
   }
 }
 
 // One launch per pair of query tokens; the events of a timed call bracket the whole series.  `a` describes the
 // work of one launch except Ttot / t0, which are set here.
-template <bool EMIT>
+template <int FORM>
 int launch_series(const ess_config& c, int T, dim3 grid, hipStream_t st, IdxArgs a, hipEvent_t ev_start, hipEvent_t ev_stop) {
   const int HB = (c.idx_heads + 15) / 16;
   if (a.xcd.ticket && T > 2) return ess_fail(ESS_ERR_UNSUPPORTED, "internal: one ticket serves one index-score launch");
@@ -277,9 +286,9 @@ int launch_series(const ess_config& c, int T, dim3 grid, hipStream_t st, IdxArgs
     a.t0 = t0;
     hipEvent_t e0 = t0 == 0 ? ev_start : nullptr, e1 = t0 + 2 >= T ? ev_stop : nullptr;
     switch (c.idx_dim) {
-      case 32: launch_hb<32, EMIT>(HB, Tl, grid, st, a, e0, e1); break;
-      case 64: launch_hb<64, EMIT>(HB, Tl, grid, st, a, e0, e1); break;
-      case 128: launch_hb<128, EMIT>(HB, Tl, grid, st, a, e0, e1); break;
+      case 32: launch_hb<32, FORM>(HB, Tl, grid, st, a, e0, e1); break;
+      case 64: launch_hb<64, FORM>(HB, Tl, grid, st, a, e0, e1); break;
+      case 128: launch_hb<128, FORM>(HB, Tl, grid, st, a, e0, e1); break;
       default: return ess_fail(ESS_ERR_UNSUPPORTED, "idx_dim %d (supported: 32, 64, 128)", c.idx_dim);
     }
   }
@@ -295,5 +304,8 @@ inline int pick_chunk(int B, int Lmax) {
   if ((long)B * ((Lmax + 511) / 512) <= 256) return 512;
   return (long)B * Lmax >= 2048L * 1024 ? 2048 : 1024;
 }
+
+// (index_kept.hip)
+int launch_index_kept(const ess_config& c, int T, dim3 grid, hipStream_t st, const IdxArgs& a, hipEvent_t ev_start, hipEvent_t ev_stop);
 
 }  // namespace ess_idx

@@ -17,5 +17,5 @@ int ess_launch_index_emit(const ess_config& c, const uint8_t* q, const float* w,
   int IB = 1;
   while ((1 << IB) < c.max_ctx) ++IB;
   a.IB = IB;
-  return launch_series<true>(c, T, dim3(a.nx, B), st, a, ev_start, ev_stop);
+  return launch_series<EMITTING>(c, T, dim3(a.nx, B), st, a, ev_start, ev_stop);
 }
