@@ -729,6 +729,7 @@ __device__ __forceinline__ void topk_item(TopkShared& sm, int item, int parts, f
       // this workgroup's slice of the row (boundaries on 16-byte pieces); its first round is asked for behind the samples
       const int s_lo = parts > 1 ? (int)(((long)vis * part / parts) & ~3L) : 0;
       const int s_hi = (parts > 1 && part + 1 < parts) ? (int)(((long)vis * (part + 1) / parts) & ~3L) : vis;
+      // (a shared row's slice is one round up to 128K: with two sets a step of 4 x 128K takes 42.3 us instead of 41.9)
       constexpr int SETS = MODE == 1 ? 1 : 2;
       float4v x[SETS][ROUND];
       const float* const slice = srow + s_lo;
