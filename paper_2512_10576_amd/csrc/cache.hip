@@ -916,7 +916,7 @@ int ess_launch_append(const ess_config& c, const ess_cache& cache, const uint8_t
   hipLaunchKernelGGL(kern, dim3(B), dim3(APPEND_NT), 0, st, new_key, new_rows, key,
                      const_cast<uint8_t*>(cache.host_pool_dev), cache.slot_pool, cache.slot_of, cache.token_of,
                      cache.stamp, ctx_len, placed, T, c.idx_dim, c.max_ctx, c.slots_per_seq, c.row_stride, step,
-                     new_scale, block_table, n_pages);
+                     block_table ? new_scale : nullptr, block_table, n_pages);   // (flat keys have no scales: what the caller gave is not read)
   ESS_HIP(hipGetLastError());
   return ESS_OK;
 }

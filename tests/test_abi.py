@@ -252,3 +252,41 @@ def test_short_index_chunks_only_where_they_fit_the_chip_at_once(tmp_path):
     for (B, L), chunk in zip(shapes, got):
         want = 512 if B * -(-L // 512) <= 256 else (2048 if B * L >= 2048 * 1024 else 1024)
         assert chunk == want, (B, L, chunk)
+
+
+def test_append_to_flat_keys_hands_no_scale_array_to_the_kernel(lib, tmp_path):
+    """Only a paged Indexer-Cache has key scales: with flat keys ess_append takes whatever new_key_scale holds, and the kernel
+    must not read it.  What the launch passes is taken from the runtime's launch functions, replaced in a process of its own (no GPU)."""
+    import subprocess
+    import sys
+    (tmp_path / "shim.c").write_text(
+        "#include <stddef.h>\n"
+        "typedef struct { unsigned x, y, z; } d3;\n"
+        "void* shim_seen; int shim_launches;\n"
+        "int __hipPushCallConfiguration(d3 g, d3 b, size_t lds, void* st) { return 0; }\n"
+        "int __hipPopCallConfiguration(d3* g, d3* b, size_t* lds, void** st) {\n"
+        "  d3 one = {1, 1, 1}; *g = one; *b = one; *lds = 0; *st = 0; return 0;\n}\n"
+        "int hipLaunchKernel(const void* f, d3 g, d3 b, void** args, size_t lds, void* st) {\n"
+        "  shim_seen = *(void**)args[16]; ++shim_launches; return 0;\n}\n")
+    subprocess.run(["gcc", "-shared", "-fPIC", "-o", str(tmp_path / "shim.so"), str(tmp_path / "shim.c")], check=True)
+    (tmp_path / "run.py").write_text("""
+import ctypes as C, sys
+shim = C.CDLL(sys.argv[1], mode=C.RTLD_GLOBAL)
+import torch
+from paper_2512_10576_amd import binding as b
+lib = b.load()
+cfg = b.make_config(1, 1, 256, 4, 32, 8, 8)
+cache = b.EssCache(4096, None, 4096, 4096, 4096)
+f = lib._Z17ess_launch_appendRK10ess_configRK9ess_cachePKhS6_PhPiiijS8_PKfPKiiP12ihipStream_t
+vp, i32 = C.c_void_p, C.c_int32
+f.argtypes = [vp, vp, vp, vp, vp, vp, i32, i32, C.c_uint32, vp, vp, vp, i32, vp]
+for table, want in ((None, None), (4096, 0x1234)):
+    f(C.addressof(cfg), C.addressof(cache), 4096, 4096, 4096, 4096, 1, 1, 1, None, 0x1234, table, 1, None)
+    got = C.c_void_p.in_dll(shim, "shim_seen").value
+    assert got == want, (table, got)
+assert C.c_int.in_dll(shim, "shim_launches").value == 2
+print("handed over as it should be")
+""")
+    p = subprocess.run([sys.executable, str(tmp_path / "run.py"), str(tmp_path / "shim.so")], cwd=ROOT, stdout=subprocess.PIPE,
+                       stderr=subprocess.STDOUT, text=True, env=dict(os.environ, PYTHONPATH=ROOT))
+    assert p.returncode == 0 and "handed over as it should be" in p.stdout, p.stdout
