@@ -1,6 +1,7 @@
 // Pieces shared by the kernels of the selection (top-k, and the sampled lower bound of the fused selection).
 #pragma once
 #include "ess_internal.h"
+#include <math.h>
 #include <type_traits>
 
 namespace ess_sel {
@@ -8,6 +9,31 @@ namespace ess_sel {
 constexpr int SBITS = 14;                  // sample histogram: top 14 bits of the orderable key
 constexpr int SBINS = 1 << SBITS;
 constexpr int CAND_CAP = 8192;             // candidate keys a row's list (and the LDS of the finishing kernel) holds
+constexpr int HBITS = 11;                  // digits of a radix or of an even spread
+constexpr int NBINS = 1 << HBITS;
+constexpr uint32_t FEW = 128;              // keys of one digit of a whole row that are counted at once; of more the digit is spread again
+constexpr uint32_t SMALL = 1024;           // keys of one digit that are counted at all
+constexpr int NARROW = 3;                  // times a whole row's spread is narrowed to the digit that holds the k-th largest
+
+// Scores between lo and hi spread evenly over the digits 1 .. 2046; below lo, -inf and what is no number: 0 or 1; above hi: up
+// to 2047.  Monotone in the score, four instructions.  scale 0: the range gives no such digits.  (Ends past 1.6e38 are taken in,
+// so that their distance is a number.)
+struct Spread {
+  float lo, scale;
+  __host__ __device__ __forceinline__ Spread(float lo_, float hi_) : lo(fmaxf(lo_, -1.6e38f)) {
+    const float span = fminf(hi_, 1.6e38f) - lo;
+    scale = span > 1e-30f ? (float)(NBINS - 3) / span : 0.f;
+  }
+  __host__ __device__ __forceinline__ uint32_t digit(float v) const {
+#ifdef __HIP_DEVICE_COMPILE__
+    return (uint32_t)__builtin_amdgcn_fmed3f(fmaf(v - lo, scale, 1.0f), 0.f, (float)(NBINS - 1));
+#else
+    return (uint32_t)fminf(fmaxf(fmaf(v - lo, scale, 1.0f), 0.f), (float)(NBINS - 1));
+#endif
+  }
+  // a score that no score of digit d or above lies below (a hundredth of a digit covers the rounding of `digit`)
+  __host__ __device__ __forceinline__ float edge(uint32_t d) const { return fmaf((float)d - 1.01f, 1.0f / scale, lo); }
+};
 
 // Where bin i of a sample histogram lives in LDS when NTH threads scan it: each thread sums SBINS / NTH consecutive
 // bins, so consecutive threads would read addresses a power of two apart -- the same bank in every lane.  One unused

@@ -36,10 +36,14 @@ namespace {
 // from a bitmap word by word) / now: 1 row of 8000 10.4 / 8.3, 32 rows of 4096 13.0 / 8.2, 13 of 12000 to 16384 14.8 / 10.5, 32 of
 // 32768 15.1 / 11.5, 46 of 24000 to 40000 17.8 / 12.6, 20 of 65000 18.5 / 13.7, 4 of 131072 17.5 / 13.7, 64 of 115000 21.4 / 18.5.
 constexpr int NT = 512;
-constexpr int HBITS = 11;
-constexpr int NBINS = 1 << HBITS;
 constexpr int COPIES = 8;
 using ess_sel::CAND_CAP;
+using ess_sel::FEW;
+using ess_sel::HBITS;
+using ess_sel::NARROW;
+using ess_sel::NBINS;
+using ess_sel::SMALL;
+using ess_sel::Spread;
 using ess_sel::SBITS;
 using ess_sel::SBINS;
 constexpr int SAMPLE_TARGET = 4096;         // at most this many samples per row, about every 16th score or fewer
@@ -49,7 +53,6 @@ constexpr int PER = CAND_CAP / NT;           // keys per thread of a row or a li
 constexpr int LIST_AHEAD = 3072 / NT;        // rounds of NT list entries that are asked for before their number is known
 constexpr int ROUND = 8;                     // float4s per thread and round of a pass over a row
 constexpr int DPT = NBINS / NT;              // digits per thread of a scan over a digit histogram
-constexpr uint32_t SMALL = 1024;             // keys of one digit that are resolved by counting
 constexpr int RANK_WORDS = NBINS * 4;        // words of a row's bitmap up to which the words' ranks fit beside it (262144 positions)
 static_assert(PER * (NT / 64) == 128 && DPT == 4, "two counts a lane; digits are read 16 bytes at a time");
 constexpr uint32_t ROW_DONE = 0xffffffffu;   // in place of a candidate count: the candidate pass did the row itself
@@ -75,7 +78,7 @@ struct __align__(16) TopkShared {
   uint32_t sbin[2];                       // sample_bins' result words
   uint32_t sel_to;                        // bounds_of: samples down to and with the digit sbin[0]
   __align__(16) float stage[4 * ROUND * NT];               // 64 KiB: a round of a pass over a row
-  float red_lo[NT / 64], red_hi[NT / 64]; // value_range: extremes of the waves' scores
+  float red_lo[NT / 64], red_hi[NT / 64], probe[64];       // value_range: extremes of the waves' scores, and 64 of them
   uint32_t few_bits[CAND_CAP / 32];       // whole_row: positions taken of the crossing digit
   uint32_t taken[PER * (NT / 64)];        // whole_row: positions taken of every 64, in ascending order
 };
@@ -232,7 +235,8 @@ __device__ __forceinline__ void emit_bitmap(TopkShared& sm, int tid, const uint3
 
 // Which of the 2048 digits of the histogram sm.lhist contains the need-th largest key, counted
 // from the top: sm.sel_digit, with sm.sel_above keys above it and sm.sel_count in it.  Ends with a barrier.
-__device__ __forceinline__ void crossing_digit(TopkShared& sm, int tid, uint32_t need) {
+// all: the number of keys, those of digit 0 need not be in the histogram then.
+__device__ __forceinline__ void crossing_digit(TopkShared& sm, int tid, uint32_t need, uint32_t all = 0u) {
   const int d0 = NBINS - DPT - DPT * tid;      // thread tid owns four digits, descending
   const uint4 h = *reinterpret_cast<const uint4*>(&sm.lhist[d0]);
   const uint32_t cnt[DPT] = {h.w, h.z, h.y, h.x};
@@ -248,34 +252,45 @@ __device__ __forceinline__ void crossing_digit(TopkShared& sm, int tid, uint32_t
       above += cnt[i];
     }
   }
+  if (all != 0u && total < need && tid == 0) { sm.sel_digit = 0u; sm.sel_above = total; sm.sel_count = all - total; }
   __syncthreads();
 }
 
 // Extremes of the workgroup's values (+inf and -inf where a thread has none), the same in all threads.  One barrier.
-__device__ __forceinline__ void value_range(TopkShared& sm, int tid, float& lo, float& hi) {
+// probe: eight lanes' worth of each wave's are handed round as well, one to a lane.
+__device__ __forceinline__ void value_range(TopkShared& sm, int tid, float& lo, float& hi, float& probe) {
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  if (lane < 64 / (NT / 64)) sm.probe[wave * (64 / (NT / 64)) + lane] = probe;
   lo = -ess_sel::wave_max<6>(-lo);
   hi = ess_sel::wave_max<6>(hi);
   if (lane == 0) { sm.red_lo[wave] = lo; sm.red_hi[wave] = hi; }
   __syncthreads();
   lo = -ess_sel::wave_max<3>(-sm.red_lo[lane & (NT / 64 - 1)]);
   hi = ess_sel::wave_max<3>(sm.red_hi[lane & (NT / 64 - 1)]);
+  probe = sm.probe[lane];
 }
 
-// Scores between lo and hi spread evenly over the digits 1 .. 2046; below lo, -inf and what is no number: 0 or 1; above hi: up
-// to 2047.  Monotone in the score, four instructions.  scale 0: the range gives no such digits.
-struct Spread {
-  float lo, scale;
-  __device__ __forceinline__ Spread(float lo_, float hi_) : lo(lo_) {
-    const float span = hi_ - lo_;
-    scale = span > 1e-30f && span < __builtin_inff() ? (float)(NBINS - 3) / span : 0.f;
-  }
-  __device__ __forceinline__ uint32_t digit(float v) const {
-    return (uint32_t)__builtin_amdgcn_fmed3f(fmaf(v - lo, scale, 1.0f), 0.f, (float)(NBINS - 1));
-  }
-  // a score that no score of digit d or above lies below (a hundredth of a digit covers the rounding of `digit`)
-  __device__ __forceinline__ float edge(uint32_t d) const { return fmaf((float)d - 1.01f, 1.0f / scale, lo); }
-};
+// The spread of a set of scores of which the one with `share` of the set at or above it is looked for; lo, hi: a thread's
+// extremes of the finite ones; probe: one of them, or NaN (64 are looked at).  Between their extremes, unless of 64 pairs of probes four
+// share a digit then -- an outlier far away, a mask of the lowest number, magnitudes apart --: between two probes in whose middle, by
+// rank, the one looked for is expected; what lies outside is in the end digits.  All threads find the same.  One barrier.
+__device__ __forceinline__ Spread spread_of(TopkShared& sm, int tid, float lo, float hi, float probe, float share) {
+  constexpr float kInf = __builtin_inff();
+  value_range(sm, tid, lo, hi, probe);
+  const Spread sp(lo, hi);
+  const uint32_t d = sp.digit(probe);
+  const uint32_t next = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)d, 0x121, 0xf, 0xf, true);      // (the lane beside, in a ring of 16)
+  if (__builtin_expect(__popcll(__ballot(d == next)) < 4, 1)) return sp;
+  uint32_t larger = 0;                       // of 32 probes, how many are larger than the lane's
+#pragma unroll
+  for (int j = 0; j < 32; ++j)
+    larger += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(probe), 4 * (j >> 1) + (j & 1))) > probe ? 1u : 0u;
+  const float rank = share * 0.5f * (float)__popcll(__ballot(probe == probe)), at = (float)larger;
+  const bool fin = fabsf(probe) < kInf;
+  const float below = ess_sel::wave_max<6>(fin && at >= rank + 6.0f ? probe : -kInf), over = -ess_sel::wave_max<6>(fin && at <= rank - 6.0f ? -probe : -kInf);
+  const Spread finer(below > -kInf ? below : lo, over < kInf ? over : hi);
+  return finer.scale == 0.f ? sp : finer;
+}
 
 __device__ __forceinline__ float score_of(uint32_t o) {      // the score of an ess_orderable image
   return __uint_as_float((o & 0x80000000u) ? (o & 0x7fffffffu) : ~o);
@@ -298,7 +313,8 @@ __device__ __forceinline__ bool bounds_of(TopkShared& sm, int tid, const float (
     lo = fminf(lo, fin ? sv[u] : kInf);
     hi = fmaxf(hi, fin ? sv[u] : -kInf);
   }
-  value_range(sm, tid, lo, hi);
+  float none = 0.f;
+  value_range(sm, tid, lo, hi, none);
   const Spread sp(lo, hi);
   if (sp.scale != 0.f) {
 #pragma unroll
@@ -491,14 +507,20 @@ __device__ __forceinline__ bool finish_list(TopkShared& sm, int tid, const float
   return finish_rounds<PER>(sm, tid, v, p, listed, tau, tau_hi, vis, k, IB, orow);
 }
 
+constexpr uint32_t NONE = 0xffffffffu, ABOVE = NONE - 1u;     // in place of a digit: no key, or one that is not taken; one that is
+
 // Path S: a row that fits the candidate list whole needs no sample and no list: its scores in registers.  They are spread evenly
-// over 2046 digits between the smallest and the largest finite one; the digit that holds the k-th
+// over 2046 digits (spread_of); the digit that holds the k-th
 // largest is found, and inside it the key by counting.  A wave holds 64 consecutive positions at a time, so a position's rank
-// is the number taken in the 64s before, plus a bit count: no bitmap.  (Even digits hold a dozen keys near the threshold where
-// scores are as they come; with an outlier a hundred times the spread away still a few hundred.)
+// is the number taken in the 64s before, plus a bit count: no bitmap.  Even digits hold a dozen keys near the threshold where
+// scores are as they come.  Where one holds more than counting takes, its keys alone are spread between their own extremes; equal scores are
+// taken by position, like the ranks.  us, 1 row / 32 rows of 8000, k 2048, of a form with 14 bits of the float as first digit and sixteen waves, of an even spread
+// between the extremes with the general selection behind it, and of this: as they come 10.3, 11.0 / 8.5, 8.3 / 8.4, 8.2; one score a thousand spreads away
+// 10.3, 11.0 / 19.5, 25.4 / 8.7, 10.5; 1e30 10.3, 11.0 / 24.5, 26.0 / 8.2, 9.9; a fifth masked with -3.4e38 10.5, 11.2 / 22.5, 23.8 / 8.0, 8.6; exponentials of
+// twice a normal value 9.8, 10.4 / 23.0, 39.1 / 8.0, 8.9; 900 equal at the threshold 29.7, 30.4 / 34.7, 35.5 / 11.3, 11.8; three values 28.7, 30.3 / 26.2, 28.1 / 11.1, 11.6.
 // Where rows are shared it is part 0 of the candidate pass (MODE 1) that takes such a row, not the finishing kernel:
 // inlined there beside its other paths it cost every longer row 0.4 to 0.6 us.
-// Returns false, with the keys in sm.cand, when more than SMALL keys share that digit (massive ties).
+// Returns false, with the keys in sm.cand, when more than SMALL keys share that digit all the same (magnitudes apart in several steps).
 __device__ __forceinline__ bool whole_row(TopkShared& sm, int tid, const float (&v)[PER], int vis, int k, int IB,
                                           int32_t* __restrict__ orow) {
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -514,29 +536,88 @@ __device__ __forceinline__ bool whole_row(TopkShared& sm, int tid, const float (
     lo = fminf(lo, fin ? v[u] : kInf);
     hi = fmaxf(hi, fin ? v[u] : -kInf);
   }
-  value_range(sm, tid, lo, hi);
-  const Spread sp(lo, hi);
+  // (probes from two places of the row)
+  const float probe = (lane & 1) ? (PER / 2 * NT + tid < vis ? v[PER / 2] : __builtin_nanf("")) : (tid < vis ? v[0] : __builtin_nanf(""));
+  const Spread sp = spread_of(sm, tid, lo, hi, probe, (float)k / (float)vis);
   uint32_t d[PER];
 #pragma unroll
   for (int u = 0; u < PER; ++u) {
     d[u] = sp.digit(v[u]);
-    if (sp.scale == 0.f) d[u] = v[u] == kInf ? NBINS - 1 : (v[u] > -kInf ? 1u : 0u);      // (one value, or a span past a float's)
-    if (u * NT + tid < vis) atomicAdd(&sm.lhist[d[u]], 1u);
-    else d[u] = 0xffffffffu;
+    if (sp.scale == 0.f) d[u] = v[u] == kInf ? NBINS - 1 : (v[u] > -kInf ? 1u : 0u);      // (one value)
+    if (u * NT + tid >= vis) d[u] = NONE;
+    if (d[u] - 1u < (uint32_t)(NBINS - 1)) atomicAdd(&sm.lhist[d[u]], 1u);
   }
   __syncthreads();
-  crossing_digit(sm, tid, (uint32_t)k);
-  const uint32_t dsel = sm.sel_digit, take = (uint32_t)k - sm.sel_above, cnt = sm.sel_count;
-  if (cnt > SMALL && cnt != take) {
+  crossing_digit(sm, tid, (uint32_t)k, (uint32_t)vis);
+  uint32_t dsel = sm.sel_digit, take = (uint32_t)k - sm.sel_above, cnt = sm.sel_count;
+  bool equal = false;                        // all keys of that digit have one score
+  // (rare: kept out of the way of the instructions that every row fetches)
+#pragma unroll 1
+  for (int round = 0; round < NARROW && __builtin_expect(cnt > FEW && cnt != take, 0); ++round) {      // the keys of that digit alone
+    lo = kInf;
+    hi = -kInf;
+#pragma unroll
+    for (int u = 0; u < PER; ++u)
+      if (d[u] == dsel) {
+        const float x = v[u] == v[u] ? v[u] : -kInf;         // (as a key has it)
+        lo = fminf(lo, x);
+        hi = fmaxf(hi, x);
+      }
+    *reinterpret_cast<uint4*>(&sm.lhist[DPT * tid]) = make_uint4(0, 0, 0, 0);
+    float none = 0.f;
+    value_range(sm, tid, lo, hi, none);
+    equal = lo == hi;
+    const Spread finer(lo, hi);
+    if (equal || finer.scale == 0.f) break;
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      if (d[u] == dsel) {
+        d[u] = finer.digit(v[u]);
+        atomicAdd(&sm.lhist[d[u]], 1u);
+      } else {
+        d[u] = d[u] == NONE || d[u] < dsel ? NONE : ABOVE;
+      }
+    }
+    __syncthreads();
+    crossing_digit(sm, tid, take);
+    dsel = sm.sel_digit; take -= sm.sel_above; cnt = sm.sel_count;
+  }
+  if (cnt > SMALL && cnt != take && !equal) {
 #pragma unroll
     for (int u = 0; u < PER; ++u)
       if (u * NT + tid < vis) sm.cand[u * NT + tid] = key(u);
     __syncthreads();
     return false;
   }
+  // n in lane u of a wave: a count of its u-th 64 positions; in lane (8 u + wave) / 2 afterwards: that of all positions before.  One barrier
+  auto counts_before = [&](uint32_t n) {
+    if (lane < PER) sm.taken[lane * (NT / 64) + wave] = n;
+    __syncthreads();
+    const uint2 two = *reinterpret_cast<const uint2*>(&sm.taken[2 * lane]);
+    return wave_incl_scan(two.x + two.y, lane) - (two.x + two.y) + ((wave & 1) ? two.x : 0u);
+  };
+  auto before_of = [&](uint32_t before, int u) { return (uint32_t)__builtin_amdgcn_readlane((int)before, (u * (NT / 64) + wave) >> 1); };
+  auto rank_in = [](unsigned long long m) { return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u)); };
   // the few that are taken of the crossing digit: a bit per position
   const uint32_t above = cnt == take ? dsel : dsel + 1;      // digits from here on are taken whole
-  if (cnt != take) {
+  uint2 bits = make_uint2(0u, 0u);           // lane u: those of the wave's u-th 64
+  if (__builtin_expect(equal, 0)) {          // of equal scores the first positions
+    uint32_t n = 0;
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      const unsigned long long t = __ballot(d[u] == dsel);
+      n = lane == u ? (uint32_t)__popcll(t) : n;
+    }
+    const uint32_t before = counts_before(n);
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      const unsigned long long t = __ballot(d[u] == dsel);
+      const uint32_t rank = before_of(before, u) + rank_in(t);
+      const unsigned long long first = t & __ballot(rank < take);
+      if (lane == u) bits = make_uint2((uint32_t)first, (uint32_t)(first >> 32));
+    }
+    __syncthreads();                         // (sm.taken has been read)
+  } else if (cnt != take) {
     if (tid < (int)(sizeof(sm.few_bits) / 4)) sm.few_bits[tid] = 0;
     for (int j = tid; j < (int)SMALL; j += NT) sm.few_rank[j] = 0;
 #pragma unroll
@@ -547,26 +628,21 @@ __device__ __forceinline__ bool whole_row(TopkShared& sm, int tid, const float (
       atomicOr(&sm.few_bits[pos >> 5], 1u << (pos & 31));
     });
     __syncthreads();
+    if (lane < PER) bits = *reinterpret_cast<const uint2*>(&sm.few_bits[2 * (lane * (NT / 64) + wave)]);
   }
-  uint2 bits = make_uint2(0u, 0u);           // lane u: those of the wave's u-th 64
-  if (cnt != take && lane < PER) bits = *reinterpret_cast<const uint2*>(&sm.few_bits[2 * (lane * (NT / 64) + wave)]);
   unsigned long long m[PER];                 // taken positions of the wave's u-th 64
   uint32_t n = 0;                            // lane u: how many
 #pragma unroll
   for (int u = 0; u < PER; ++u) {
-    m[u] = __ballot(d[u] >= above && d[u] != 0xffffffffu) |
+    m[u] = __ballot(d[u] >= above && d[u] != NONE) |
            ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)bits.y, u) << 32 | (uint32_t)__builtin_amdgcn_readlane((int)bits.x, u));
     n = lane == u ? (uint32_t)__popcll(m[u]) : n;
   }
-  if (lane < PER) sm.taken[lane * (NT / 64) + wave] = n;
-  __syncthreads();
-  const uint2 two = *reinterpret_cast<const uint2*>(&sm.taken[2 * lane]);
-  const uint32_t before = wave_incl_scan(two.x + two.y, lane) - (two.x + two.y) + ((wave & 1) ? two.x : 0u);
+  const uint32_t before = counts_before(n);
 #pragma unroll
   for (int u = 0; u < PER; ++u) {
-    const uint32_t at = (uint32_t)__builtin_amdgcn_readlane((int)before, (u * (NT / 64) + wave) >> 1);
-    if ((m[u] >> lane) & 1ull)
-      orow[at + __builtin_amdgcn_mbcnt_hi((uint32_t)(m[u] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m[u], 0u))] = u * NT + tid;
+    const uint32_t at = before_of(before, u);                // (by all lanes: a lane that is off need not hold its value)
+    if ((m[u] >> lane) & 1ull) orow[at + rank_in(m[u])] = u * NT + tid;
   }
   return true;
 }
@@ -701,7 +777,8 @@ __device__ __forceinline__ void topk_item(TopkShared& sm, int item, int parts, f
         list_lo = fminf(list_lo, fin ? lv[u] : kInf);
         list_hi = fmaxf(list_hi, fin ? lv[u] : -kInf);
       }
-      value_range(sm, tid, list_lo, list_hi);
+      float none = 0.f;
+      value_range(sm, tid, list_lo, list_hi, none);
     }
     if (finish_list(sm, tid, lv, lp, listed, list_lo, list_hi, vis, k, IB, orow)) return;
   }

@@ -290,3 +290,75 @@ print("handed over as it should be")
     p = subprocess.run([sys.executable, str(tmp_path / "run.py"), str(tmp_path / "shim.so")], cwd=ROOT, stdout=subprocess.PIPE,
                        stderr=subprocess.STDOUT, text=True, env=dict(os.environ, PYTHONPATH=ROOT))
     assert p.returncode == 0 and "handed over as it should be" in p.stdout, p.stdout
+
+
+def test_whole_rows_narrow_to_the_digit_of_the_kth_score(tmp_path):
+    """A row held whole is spread evenly over digits, and the keys of the digit that holds the k-th largest score again among
+    themselves, until counting can take what is left or it is equal.  The spread itself, compiled for the host and replayed from the row's
+    extremes: rows as they come need no second round, one outlier or a mask of the lowest number one, both two, magnitudes apart
+    three at most, and none ends in the general selection (-1)."""
+    import subprocess
+    import numpy as np
+    from paper_2512_10576_amd import build
+    src = tmp_path / "narrow.hip"
+    src.write_text('''#include "select_common.h"
+#include <stdio.h>
+#include <cmath>
+#include <vector>
+using namespace ess_sel;
+int main(int argc, char** argv) {
+  const int n = atoi(argv[2]), k = atoi(argv[3]);
+  std::vector<float> row(n);
+  FILE* f = fopen(argv[1], "rb");
+  while (fread(row.data(), 4, n, f) == (size_t)n) {
+    float lo = INFINITY, hi = -INFINITY;
+    for (float x : row) if (std::isfinite(x)) { lo = fminf(lo, x); hi = fmaxf(hi, x); }
+    std::vector<float> v = row;                      // the keys still in question
+    int take = k, rounds = -1;
+    for (int round = 0; round <= NARROW; ++round) {
+      const Spread sp(lo, hi);
+      if (round > 0 && lo == hi) { rounds = round; break; }          // equal: by position
+      if (round > 0 && sp.scale == 0.f) break;
+      std::vector<std::vector<float>> h(NBINS);
+      for (float x : v)
+        h[sp.scale != 0.f ? sp.digit(x) : (x == INFINITY ? NBINS - 1 : (x > -INFINITY ? 1u : 0u))].push_back(x);
+      float top = -INFINITY;                                         // the digits keep the order of the scores
+      for (auto& part : h) {
+        for (float x : part) if (x < top) { printf("disorder\\n"); return 1; }
+        for (float x : part) top = fmaxf(top, x);
+      }
+      int at = NBINS - 1;
+      while (take > (int)h[at].size()) take -= (int)h[at--].size();
+      v = h[at];
+      if (v.size() <= FEW || (int)v.size() == take) { rounds = round; break; }
+      lo = INFINITY; hi = -INFINITY;
+      for (float x : v) { const float y = x == x ? x : -INFINITY; lo = fminf(lo, y); hi = fmaxf(hi, y); }
+    }
+    printf("%d\\n", rounds);
+  }
+}
+''')
+    n, k = 8000, 2048
+    rng = np.random.RandomState(3)
+    base = (rng.randn(n) * 40 + 300).astype(np.float32)
+
+    def with_(at, value, x=base):
+        x = x.copy()
+        x[at] = value
+        return x
+
+    mask = with_(slice(0, n, 5), -3.4028235e38)
+    rows = [(base, 0, 0), (with_([5], 300 + 40 * 50), 0, 0), (with_([5], 300 + 40 * 1000), 1, 1), (with_([5], 1e30), 1, 1),
+            (with_([5], -1e30), 1, 1), (mask, 1, 1), (with_([7], 1e30, mask), 1, 2), (with_([7], 3.4028235e38, with_([8], -3.4028235e38)), 1, 1),
+            (with_(slice(0, n, 7), -np.inf), 0, 0), (with_([7, 9, 11], [1e30, np.inf, np.nan], with_(slice(0, n, 5), -np.inf)), 1, 1),
+            (np.exp((base - 300) / 20).astype(np.float32), 1, 3), (np.exp((base - 300) / 10).astype(np.float32), 1, 3),
+            (with_(slice(0, n, 20), np.sort(base)[-k]), 1, 2), (with_(slice(0, n), 2.5), 1, 1), (with_(slice(0, n, 2), np.sort(base)[-k]), 1, 2),
+            (np.where(rng.rand(n) < 0.1, np.float32(7.0), np.float32(7.000001)), 0, 1), (with_(slice(0, n), np.nan), 1, 1),
+            (with_(slice(100, n), -np.inf, with_(slice(0, n, 3), np.nan)), 1, 1)]
+    np.stack([r[0] for r in rows]).astype(np.float32).tofile(tmp_path / "rows")
+    exe = tmp_path / "narrow"
+    subprocess.run([build._hipcc(), *build.FLAGS, "-I" + build.CSRC, str(src), "-o", str(exe)], check=True, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)
+    got = [int(x) for x in subprocess.run([str(exe), str(tmp_path / "rows"), str(n), str(k)], check=True, stdout=subprocess.PIPE, text=True).stdout.split()]
+    assert len(got) == len(rows)
+    for i, (rounds, (_, least, most)) in enumerate(zip(got, rows)):
+        assert least <= rounds <= most, (i, rounds)

@@ -237,3 +237,56 @@ def test_topk_of_hard_rows_at_the_edges_of_its_paths(ess_lib, L, vis):
         for i, kind in enumerate(kinds):
             assert np.array_equal(got[i], ref[i]), (kind, L, vis, k)
         ctx.close()
+
+
+def _far_rows(L, k):
+    """Scores that one even spread between the extremes says little about, and ties of any number at the k-th."""
+    rng = np.random.RandomState(L + k)
+    base = (rng.randn(L) * 40 + 300).astype(np.float32)
+    kth = np.sort(base)[max(L - k, 0)]
+
+    def with_(at, value, x=base):
+        x = x.copy()
+        x[at] = value
+        return x
+
+    def some(n):
+        return rng.permutation(L)[:min(n, L)]
+
+    masked = with_(rng.rand(L) < 0.2, -3.4028235e38)
+    far = np.array([3.4e38, -3.4e38, 1e30, np.inf, np.nan], np.float32)[:min(5, L)]
+    rows = [with_(some(1), 300 + 40 * m) for m in (100, 300, 1000, 1e6)] + [with_(some(1), 1e30), with_(some(3), -1e30), masked]
+    rows += [with_(some(1), 1e30, masked), with_(rng.rand(L) < 0.7, -3.4028235e38), with_(rng.rand(L) < 0.9, -np.inf),
+             with_(rng.rand(L) < 0.5, -np.inf, with_(rng.rand(L) < 0.8, np.nan))]
+    rows += [np.exp((base - 300) / d).astype(np.float32) for d in (40, 20, 10)]
+    rows += [with_(some(n), kth) for n in (60, 127, 128, 129, 300, 1023, 1025, L // 2)]
+    rows += [with_(some(n), kth, with_(some(1), 1e30)) for n in (200, 2000)]
+    rows += [np.where(rng.rand(L) < 0.5, np.float32(0.0), np.float32(-0.0)), rng.randint(0, 3, L).astype(np.float32),
+             with_(some(far.size), far), (base - 300) * np.float32(1e-37), with_(slice(0, L), np.nan)]
+    # groups of scores many magnitudes apart
+    rows.append((rng.rand(L) * 10.0 ** rng.randint(-30, 31, L)).astype(np.float32))
+    return np.stack(rows).astype(np.float32)
+
+
+@pytest.mark.parametrize("L,vis,k", [(8192, 8192, 2048), (8192, 8191, 4096), (8192, 2049, 2048), (8192, 600, 511), (8192, 513, 1), (8192, 17, 5),
+                                     (8200, 8192, 2048), (8200, 8193, 4096), (65536, 8192, 2048), (65536, 5000, 513), (65536, 40003, 2048),
+                                     (49157, 40001, 2048), (262144, 262143, 4096)])
+def test_topk_of_rows_with_scores_far_apart_or_equal(ess_lib, L, vis, k):
+    """Rows held whole (alone, beside the sampled form, and as the short rows of shared ones) and sampled rows: outliers, masks, magnitudes apart, ties
+    of up to all scores, NaN as low as -inf; the set of the k largest is one set, so it must be equal."""
+    from paper_2512_10576_amd import binding as bnd
+    print("far rows", L, vis, k, flush=True)
+    rows = _far_rows(vis, k)
+    sc = np.zeros((rows.shape[0], 1, L), np.float32)
+    sc[:, 0, :vis] = rows
+    sc[:, 0, vis:] = 1e35                                      # what lies behind a row must not matter
+    lens = np.full(rows.shape[0], vis)
+    ref = np.sort(O.topk(sc, lens, k), axis=2)
+    ctx = bnd.Context(bnd.make_config(rows.shape[0], 1, L, 64, 128, k, 16))
+    idx = torch.empty((rows.shape[0], 1, k), dtype=torch.int32, device="cuda")
+    ctx.topk(torch.from_numpy(sc).cuda(), torch.from_numpy(lens).to(torch.int32).cuda(), idx)
+    torch.cuda.synchronize()
+    got = idx.cpu().numpy()
+    for i in range(rows.shape[0]):
+        assert np.array_equal(got[i], ref[i]), (i, L, vis, k)
+    ctx.close()
