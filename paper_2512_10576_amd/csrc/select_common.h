@@ -35,6 +35,21 @@ struct Spread {
   __host__ __device__ __forceinline__ float edge(uint32_t d) const { return fmaf((float)d - 1.01f, 1.0f / scale, lo); }
 };
 
+// Samples of a row above CAND_CAP positions: blocks of 16 scores, at most this many blocks; twice as many where more than 2048 are to be
+// found beyond 262144 positions: with the fewer a list of 4096 at 300000 positions missed its size in one row of fifty.
+constexpr int SAMPLE_TARGET = 4096;
+__host__ __device__ inline int sample_blocks(int k, int vis) { return (k > 2048 && vis > 262144 ? 2 : 1) * SAMPLE_TARGET / 16; }
+// A row's list takes the positions whose score reaches that of the t-th largest of its samples, `per` of them to a score; it must hold at least
+// the k largest and at most CAND_CAP.  t: a quarter and about four standard deviations above the number of samples that are expected
+// among the k largest (a sample of blocks is no random one, and a list that turns out too short costs the row a multiple of its time; the
+// quarter makes the usual list 4 % more expensive), but not past the middle between that number and the one that a full list stands for:
+// there both ends are more than three deviations away with k 4096 and 64 scores a sample.  (Without the middle every row of 4096 past 131072 positions
+// asked for more than fits.)
+__host__ __device__ inline uint32_t sample_target(int k, float per) {
+  const float expct = (float)k * per;
+  return (uint32_t)fmaxf(fminf(1.25f * expct + 4.0f * sqrtf(expct) + 8.0f, 0.47f * (expct + (float)CAND_CAP * per)), 1.0f);
+}
+
 // Where bin i of a sample histogram lives in LDS when NTH threads scan it: each thread sums SBINS / NTH consecutive
 // bins, so consecutive threads would read addresses a power of two apart -- the same bank in every lane.  One unused
 // word after each thread's bins makes the stride odd.  The histogram takes SBINS + NTH words.

@@ -46,8 +46,7 @@ using ess_sel::SMALL;
 using ess_sel::Spread;
 using ess_sel::SBITS;
 using ess_sel::SBINS;
-constexpr int SAMPLE_TARGET = 4096;         // at most this many samples per row, about every 16th score or fewer
-constexpr int SAMPLE_PER = SAMPLE_TARGET / NT;
+constexpr int SAMPLE_PER = 2 * ess_sel::SAMPLE_TARGET / NT;   // samples per thread at most
 constexpr int FAST_MIN_VIS = CAND_CAP + 1;   // rows above the candidate list's size are sampled (path A)
 constexpr int PER = CAND_CAP / NT;           // keys per thread of a row or a list that is held in registers
 constexpr int LIST_AHEAD = 3072 / NT;        // rounds of NT list entries that are asked for before their number is known
@@ -297,7 +296,7 @@ __device__ __forceinline__ float score_of(uint32_t o) {      // the score of an 
 }
 
 // Two bounds of a row's selection from a sample of its scores (ns in all, N a thread, the u-th of a thread valid where
-// u * NT + tid < ns): *tau, a score at or above which very probably lie the k largest and not many more (see sample_bins), and
+// u * NT + tid < ns): *tau, a score at or above which very probably lie the k largest and not many more (see sample_target), and
 // *tau_hi, one at or above which lie about an eighth of those: a list spread between the two has few keys a digit near tau, and
 // its last digit is not crowded either (adds to one address pass one after the other: with the fewest that are surely taken, half of all, in the last
 // digit that pass took 3.3 k cycles instead of 1.6).  The sample is spread evenly between its extremes; where
@@ -309,6 +308,7 @@ __device__ __forceinline__ bool bounds_of(TopkShared& sm, int tid, const float (
   float lo = kInf, hi = -kInf;
 #pragma unroll
   for (int u = 0; u < N; ++u) {
+    if (u == N / 2 && ns <= N / 2 * NT) break;
     const bool fin = u * NT + tid < ns && fabsf(sv[u]) < kInf;
     lo = fminf(lo, fin ? sv[u] : kInf);
     hi = fmaxf(hi, fin ? sv[u] : -kInf);
@@ -318,13 +318,13 @@ __device__ __forceinline__ bool bounds_of(TopkShared& sm, int tid, const float (
   const Spread sp(lo, hi);
   if (sp.scale != 0.f) {
 #pragma unroll
-    for (int u = 0; u < N; ++u)
+    for (int u = 0; u < N; ++u) {
+      if (u == N / 2 && ns <= N / 2 * NT) break;
       if (u * NT + tid < ns) atomicAdd(&sm.lhist[sp.digit(sv[u])], 1u);
+    }
     __syncthreads();
-    const float expct = (float)k * (float)ns / (float)vis, margin = 4.0f * sqrtf(expct) + 8.0f;
-    // (a quarter more than the margin asks for: a sample of blocks is no random one, and a list that turns out too short costs the
-    // row three times its time; 4 % more for the usual one)
-    const uint32_t target[2] = {(uint32_t)(1.25f * expct + margin), max((uint32_t)(0.125f * expct), 1u)};
+    const float per = (float)ns / (float)vis;
+    const uint32_t target[2] = {ess_sel::sample_target(k, per), max((uint32_t)(0.125f * (float)k * per), 1u)};
     const int d0 = NBINS - DPT - DPT * tid;
     const uint4 h = *reinterpret_cast<const uint4*>(&sm.lhist[d0]);
     const uint32_t cnt[DPT] = {h.w, h.z, h.y, h.x};
@@ -347,7 +347,7 @@ __device__ __forceinline__ bool bounds_of(TopkShared& sm, int tid, const float (
     }
     __syncthreads();
     const uint32_t b0 = sm.sbin[0], b1 = sm.sbin[1];
-    if (b0 != 0xffffffffu && b0 >= 1u && (float)sm.sel_to * (float)vis < 0.9f * CAND_CAP * (float)ns) {
+    if (b0 != 0xffffffffu && b0 >= 1u && (float)sm.sel_to < 0.9f * CAND_CAP * per) {
       *tau = sp.edge(b0);
       *tau_hi = b1 == 0xffffffffu ? hi : sp.edge(b1 + 1);
       return *tau_hi > *tau;
@@ -788,15 +788,16 @@ __device__ __forceinline__ void topk_item(TopkShared& sm, int item, int parts, f
     if (!use_list) {
       // samples: blocks of 16 consecutive scores (one 64-byte piece of a cache line), one of every bstride blocks at a
       // place that changes from one to the next (scores that repeat with the stride would else be counted all or not at all),
-      // about SAMPLE_TARGET scores in all.  (One score out of every 16th..32nd touches every cache line of the
+      // SAMPLE_TARGET scores in all at most, or twice that (sample_blocks).  (One score out of every 16th..32nd touches every cache line of the
       // row: in cache-line traffic the sample then costs as much as the pass that follows.)
-      const int nblk_all = vis >> 4;
+      const int nblk_all = vis >> 4, blocks = ess_sel::sample_blocks(k, vis);
       int bstride = 1;
-      while (nblk_all / bstride > SAMPLE_TARGET / 16) bstride <<= 1;
+      while (nblk_all / bstride > blocks) bstride <<= 1;
       const int ns = (nblk_all / bstride) << 4;
       float sv[SAMPLE_PER];
 #pragma unroll
       for (int u = 0; u < SAMPLE_PER; ++u) {
+        if (u == SAMPLE_PER / 2 && ns <= SAMPLE_PER / 2 * NT) break;
         const int j = min(u * NT + tid, ns - 1);
         const int blk = (j >> 4) * bstride + (int)(((uint32_t)(j >> 4) * 0x9e3779b1u >> 16) & (uint32_t)(bstride - 1));
         sv[u] = srow[(size_t)blk * 16 + (j & 15)];

@@ -362,3 +362,34 @@ int main(int argc, char** argv) {
     assert len(got) == len(rows)
     for i, (rounds, (_, least, most)) in enumerate(zip(got, rows)):
         assert least <= rounds <= most, (i, rounds)
+
+
+def test_sample_target_leaves_room_on_both_sides(tmp_path):
+    """The list of a sampled row takes what reaches the t-th largest of its samples: it must hold the k largest and fit its buffer.  For every k and row
+    length the bound has to be one the list can be made with (it once asked for more than fits for k above 3500 past 131072 positions), and both
+    ways of missing must be rare where samples are drawn at random."""
+    import subprocess
+    from scipy.stats import hypergeom
+    from paper_2512_10576_amd import build
+    cap, shapes = 8192, []
+    for vis in (8193, 8224, 12000, 20000, 40000, 65536, 115000, 131072, 131088, 140000, 200000, 262144, 262160, 300000, 400001, 524288):
+        blocks = vis >> 4                                # the sample, as the kernel takes it
+        for k in (1, 2, 16, 100, 513, 1024, 2048, 3000, 3584, 4000, 4096):
+            most, stride = 512 if k > 2048 and vis > 262144 else 256, 1
+            while blocks // stride > most:
+                stride <<= 1
+            shapes.append((k, blocks // stride << 4, vis))
+        shapes += [(k, -(-vis // 32) // 64 * 64, vis) for k in (1, 513, 2048, 4096) if vis <= 262144]      # and of the fused selection
+    src = tmp_path / "target.hip"
+    src.write_text('#include "select_common.h"\n#include <stdio.h>\nint main(int c, char** v) {\n'
+                   "  for (int i = 1; i + 2 < c; i += 3)\n"
+                   '    printf("%u\\n", ess_sel::sample_target(atoi(v[i]), (float)atoi(v[i + 1]) / atoi(v[i + 2])));\n}\n')
+    exe = tmp_path / "target"
+    subprocess.run([build._hipcc(), *build.FLAGS, "-I" + build.CSRC, str(src), "-o", str(exe)], check=True, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)
+    got = subprocess.run([str(exe), *(str(x) for s in shapes for x in s)], check=True, stdout=subprocess.PIPE, text=True).stdout.split()
+    assert len(got) == len(shapes)
+    for (k, ns, vis), t in zip(shapes, map(int, got)):
+        assert 1 <= t and t * vis < 0.85 * cap * ns, (k, ns, vis, t)
+        short = hypergeom.sf(t - 1, vis, k, ns)          # t or more of the samples among the k largest
+        full = hypergeom.cdf(t - 1, vis, cap, ns)        # fewer than t among those that fit
+        assert short + full < 2e-3, (k, ns, vis, t, short, full)

@@ -270,7 +270,7 @@ def _far_rows(L, k):
 
 @pytest.mark.parametrize("L,vis,k", [(8192, 8192, 2048), (8192, 8191, 4096), (8192, 2049, 2048), (8192, 600, 511), (8192, 513, 1), (8192, 17, 5),
                                      (8200, 8192, 2048), (8200, 8193, 4096), (65536, 8192, 2048), (65536, 5000, 513), (65536, 40003, 2048),
-                                     (49157, 40001, 2048), (262144, 262143, 4096)])
+                                     (49157, 40001, 2048), (262144, 262143, 4096), (300001, 300000, 3584), (524288, 524288, 4096)])
 def test_topk_of_rows_with_scores_far_apart_or_equal(ess_lib, L, vis, k):
     """Rows held whole (alone, beside the sampled form, and as the short rows of shared ones) and sampled rows: outliers, masks, magnitudes apart, ties
     of up to all scores, NaN as low as -inf; the set of the k largest is one set, so it must be equal."""
