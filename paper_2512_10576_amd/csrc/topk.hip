@@ -525,7 +525,11 @@ __device__ __forceinline__ bool whole_row(TopkShared& sm, int tid, const float (
                                           int32_t* __restrict__ orow) {
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const unsigned long long imask = (1ull << IB) - 1ull;
-  auto key = [&](int u) { return ((unsigned long long)orderable(v[u]) << IB) | (imask - (unsigned long long)(u * NT + tid)); };
+  auto key = [&](int u) {
+    uint32_t low = (uint32_t)imask - (uint32_t)(u * NT + tid);
+    asm volatile("" : "+v"(low));            // (where it is asked for: left alone, all sixteen are computed by every row, 0.3 us)
+    return ((unsigned long long)orderable(v[u]) << IB) | low;
+  };
   *reinterpret_cast<uint4*>(&sm.lhist[DPT * tid]) = make_uint4(0, 0, 0, 0);
   if (tid == 0) sm.cand_n = 0;
   constexpr float kInf = __builtin_inff();
@@ -551,36 +555,38 @@ __device__ __forceinline__ bool whole_row(TopkShared& sm, int tid, const float (
   crossing_digit(sm, tid, (uint32_t)k, (uint32_t)vis);
   uint32_t dsel = sm.sel_digit, take = (uint32_t)k - sm.sel_above, cnt = sm.sel_count;
   bool equal = false;                        // all keys of that digit have one score
-  // (rare: kept out of the way of the instructions that every row fetches)
+  // (rare)
+  if (__builtin_expect(cnt > FEW && cnt != take, 0)) {
 #pragma unroll 1
-  for (int round = 0; round < NARROW && __builtin_expect(cnt > FEW && cnt != take, 0); ++round) {      // the keys of that digit alone
-    lo = kInf;
-    hi = -kInf;
+    for (int round = 0; round < NARROW && cnt > FEW && cnt != take; ++round) {      // the keys of that digit alone
+      lo = kInf;
+      hi = -kInf;
 #pragma unroll
-    for (int u = 0; u < PER; ++u)
-      if (d[u] == dsel) {
-        const float x = v[u] == v[u] ? v[u] : -kInf;         // (as a key has it)
-        lo = fminf(lo, x);
-        hi = fmaxf(hi, x);
-      }
-    *reinterpret_cast<uint4*>(&sm.lhist[DPT * tid]) = make_uint4(0, 0, 0, 0);
-    float none = 0.f;
-    value_range(sm, tid, lo, hi, none);
-    equal = lo == hi;
-    const Spread finer(lo, hi);
-    if (equal || finer.scale == 0.f) break;
+      for (int u = 0; u < PER; ++u)
+        if (d[u] == dsel) {
+          const float x = v[u] == v[u] ? v[u] : -kInf;         // (as a key has it)
+          lo = fminf(lo, x);
+          hi = fmaxf(hi, x);
+        }
+      *reinterpret_cast<uint4*>(&sm.lhist[DPT * tid]) = make_uint4(0, 0, 0, 0);
+      float none = 0.f;
+      value_range(sm, tid, lo, hi, none);
+      equal = lo == hi;
+      const Spread finer(lo, hi);
+      if (equal || finer.scale == 0.f) break;
 #pragma unroll
-    for (int u = 0; u < PER; ++u) {
-      if (d[u] == dsel) {
-        d[u] = finer.digit(v[u]);
-        atomicAdd(&sm.lhist[d[u]], 1u);
-      } else {
-        d[u] = d[u] == NONE || d[u] < dsel ? NONE : ABOVE;
+      for (int u = 0; u < PER; ++u) {
+        if (d[u] == dsel) {
+          d[u] = finer.digit(v[u]);
+          atomicAdd(&sm.lhist[d[u]], 1u);
+        } else {
+          d[u] = d[u] == NONE || d[u] < dsel ? NONE : ABOVE;
+        }
       }
+      __syncthreads();
+      crossing_digit(sm, tid, take);
+      dsel = sm.sel_digit; take -= sm.sel_above; cnt = sm.sel_count;
     }
-    __syncthreads();
-    crossing_digit(sm, tid, take);
-    dsel = sm.sel_digit; take -= sm.sel_above; cnt = sm.sel_count;
   }
   if (cnt > SMALL && cnt != take && !equal) {
 #pragma unroll
