@@ -44,9 +44,6 @@ using ess_sel::NARROW;
 using ess_sel::NBINS;
 using ess_sel::SMALL;
 using ess_sel::Spread;
-using ess_sel::SBITS;
-using ess_sel::SBINS;
-constexpr int SAMPLE_PER = 2 * ess_sel::SAMPLE_TARGET / NT;   // samples per thread at most
 constexpr int FAST_MIN_VIS = CAND_CAP + 1;   // rows above the candidate list's size are sampled (path A)
 constexpr int PER = CAND_CAP / NT;           // keys per thread of a row or a list that is held in registers
 constexpr int LIST_AHEAD = 3072 / NT;        // rounds of NT list entries that are asked for before their number is known
@@ -54,12 +51,21 @@ constexpr int ROUND = 8;                     // float4s per thread and round of 
 constexpr int DPT = NBINS / NT;              // digits per thread of a scan over a digit histogram
 constexpr int RANK_WORDS = NBINS * 4;        // words of a row's bitmap up to which the words' ranks fit beside it (262144 positions)
 static_assert(PER * (NT / 64) == 128 && DPT == 4, "two counts a lane; digits are read 16 bytes at a time");
+constexpr uint32_t NONE = 0xffffffffu, ABOVE = NONE - 1u;     // in place of a digit: no key, or one that is not taken; one that is
 constexpr uint32_t ROW_DONE = 0xffffffffu;   // in place of a candidate count: the candidate pass did the row itself
 
-struct __align__(16) TopkShared {
-  union {
+// what bounds_of needs (all that k_index_tau holds)
+struct __align__(16) BoundsShared {
+  uint32_t lhist[NBINS];                  // 8 KiB: digit histogram of the candidates, or of a sample
+  uint32_t wave_tot[NT / 64];
+  uint32_t sel_digit, sel_above, sel_count;
+  uint32_t sbin[2];                       // bounds_of: the digits of its two bounds
+  float red_lo[NT / 64], red_hi[NT / 64], probe[64];       // value_range: extremes of the waves' scores, and 64 of them
+};
+
+struct TopkShared : BoundsShared {
+  union __align__(16) {
     uint32_t hist[NBINS * COPIES];        // 64 KiB
-    uint32_t shist[ess_sel::sample_words<NT>()];   // 68 KiB, bins placed by sample_slot
     unsigned long long cand[CAND_CAP];    // 64 KiB
   };
   union {
@@ -69,15 +75,9 @@ struct __align__(16) TopkShared {
       uint32_t few_rank[SMALL];           // how many of them are larger
     };
   };
-  uint32_t lhist[NBINS];                  // 8 KiB: digit histogram of the candidates
-  uint32_t wave_tot[NT / 64];
   unsigned long long red_and[NT / 64], red_or[NT / 64];
   uint32_t out_n, cand_n;
-  uint32_t sel_digit, sel_above, sel_count;
-  uint32_t sbin[2];                       // sample_bins' result words
-  uint32_t sel_to;                        // bounds_of: samples down to and with the digit sbin[0]
   __align__(16) float stage[4 * ROUND * NT];               // 64 KiB: a round of a pass over a row
-  float red_lo[NT / 64], red_hi[NT / 64], probe[64];       // value_range: extremes of the waves' scores, and 64 of them
   uint32_t few_bits[CAND_CAP / 32];       // whole_row: positions taken of the crossing digit
   uint32_t taken[PER * (NT / 64)];        // whole_row: positions taken of every 64, in ascending order
 };
@@ -256,26 +256,26 @@ __device__ __forceinline__ void crossing_digit(TopkShared& sm, int tid, uint32_t
 }
 
 // Extremes of the workgroup's values (+inf and -inf where a thread has none), the same in all threads.  One barrier.
-// probe: eight lanes' worth of each wave's are handed round as well, one to a lane.
-__device__ __forceinline__ void value_range(TopkShared& sm, int tid, float& lo, float& hi, float& probe) {
+__device__ __forceinline__ void value_range(BoundsShared& sm, int tid, float& lo, float& hi) {
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  if (lane < 64 / (NT / 64)) sm.probe[wave * (64 / (NT / 64)) + lane] = probe;
   lo = -ess_sel::wave_max<6>(-lo);
   hi = ess_sel::wave_max<6>(hi);
   if (lane == 0) { sm.red_lo[wave] = lo; sm.red_hi[wave] = hi; }
   __syncthreads();
   lo = -ess_sel::wave_max<3>(-sm.red_lo[lane & (NT / 64 - 1)]);
   hi = ess_sel::wave_max<3>(sm.red_hi[lane & (NT / 64 - 1)]);
-  probe = sm.probe[lane];
 }
 
 // The spread of a set of scores of which the one with `share` of the set at or above it is looked for; lo, hi: a thread's
 // extremes of the finite ones; probe: one of them, or NaN (64 are looked at).  Between their extremes, unless of 64 pairs of probes four
 // share a digit then -- an outlier far away, a mask of the lowest number, magnitudes apart --: between two probes in whose middle, by
 // rank, the one looked for is expected; what lies outside is in the end digits.  All threads find the same.  One barrier.
-__device__ __forceinline__ Spread spread_of(TopkShared& sm, int tid, float lo, float hi, float probe, float share) {
+__device__ __forceinline__ Spread spread_of(BoundsShared& sm, int tid, float lo, float hi, float probe, float share) {
   constexpr float kInf = __builtin_inff();
-  value_range(sm, tid, lo, hi, probe);
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  if (lane < 64 / (NT / 64)) sm.probe[wave * (64 / (NT / 64)) + lane] = probe;         // eight lanes' worth of each wave's, one to a lane
+  value_range(sm, tid, lo, hi);
+  probe = sm.probe[lane];
   const Spread sp(lo, hi);
   const uint32_t d = sp.digit(probe);
   const uint32_t next = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)d, 0x121, 0xf, 0xf, true);      // (the lane beside, in a ring of 16)
@@ -299,32 +299,41 @@ __device__ __forceinline__ float score_of(uint32_t o) {      // the score of an 
 // u * NT + tid < ns): *tau, a score at or above which very probably lie the k largest and not many more (see sample_target), and
 // *tau_hi, one at or above which lie about an eighth of those: a list spread between the two has few keys a digit near tau, and
 // its last digit is not crowded either (adds to one address pass one after the other: with the fewest that are surely taken, half of all, in the last
-// digit that pass took 3.3 k cycles instead of 1.6).  The sample is spread evenly between its extremes; where
-// that is too coarse (an outlier far away, a handful of values) by its top 14 bits, which takes twice as long.  False: no bounds.
-// sm.lhist must be clear and sm.sbin 0xffffffff once a barrier has passed; sm.shist is used in the second case.
+// digit that pass took 3.3 k cycles instead of 1.6).
+// The sample is spread evenly over the digits from the smallest of the threads' largest finite samples (with k below a third of the row the bound lies above it; what
+// lies below, half of the sample or a mask of the lowest number, need not be counted) to the second largest of the waves' (one outlier is not among them).  Where the
+// digit of the bound is still too full for the list, its samples alone are spread again, like the keys of a whole row.
+// us, k 2048, of a form with the top 14 bits of the float as digits and sixteen waves, of an even spread between the extremes with those bits behind it, and of this.
+// 1 x 12000: as they come 12.8 / 10.3 / 10.5, one score 1e30 12.8 / 16.4 / 10.3, a fifth masked 12.1 / 15.7 / 10.6, 70 % masked 13.4 / 19.6 / 15.8;
+// 64 x 115000: 21.2 / 17.8 / 17.9, 21.4 / 24.6 / 17.9, 21.4 / 24.0 / 18.2, 22.9 / 25.2 / 20.4.
+// False: no bounds: nothing finite to go by, or more equal scores than a list holds.
+// sm.lhist must be clear and sm.sbin 0xffffffff once a barrier has passed.
 template <int N>
-__device__ __forceinline__ bool bounds_of(TopkShared& sm, int tid, const float (&sv)[N], int ns, int k, int vis, float* tau, float* tau_hi) {
-  constexpr float kInf = __builtin_inff();
-  float lo = kInf, hi = -kInf;
+__device__ __forceinline__ bool bounds_of(BoundsShared& sm, int tid, const float (&sv)[N], int ns, int k, int vis, float* tau, float* tau_hi) {
+  constexpr float kInf = __builtin_inff(), kMost = 3.4028235e38f;
+  float lo = kInf, hi = -kInf;               // of a thread's finite samples
 #pragma unroll
   for (int u = 0; u < N; ++u) {
-    if (u == N / 2 && ns <= N / 2 * NT) break;
     const bool fin = u * NT + tid < ns && fabsf(sv[u]) < kInf;
     lo = fminf(lo, fin ? sv[u] : kInf);
     hi = fmaxf(hi, fin ? sv[u] : -kInf);
   }
-  float none = 0.f;
-  value_range(sm, tid, lo, hi, none);
-  const Spread sp(lo, hi);
-  if (sp.scale != 0.f) {
+  if (3 * k < vis && hi > -kInf) lo = hi;
+  value_range(sm, tid, lo, hi);
+  const float x = sm.red_hi[tid & (NT / 64 - 1)], second = ess_sel::wave_max<3>(x == hi ? -kInf : x);
+  auto beyond = [](float v) { return v + fmaxf(fabsf(v) * 1e-6f, 1e-29f); };
+  Spread sp(lo, fmaxf(second > -kInf ? second : hi, beyond(lo)));
+  if (sp.scale == 0.f) return false;         // nothing finite, or scores past 1.6e38 alone
 #pragma unroll
-    for (int u = 0; u < N; ++u) {
-      if (u == N / 2 && ns <= N / 2 * NT) break;
-      if (u * NT + tid < ns) atomicAdd(&sm.lhist[sp.digit(sv[u])], 1u);
-    }
-    __syncthreads();
-    const float per = (float)ns / (float)vis;
-    const uint32_t target[2] = {ess_sel::sample_target(k, per), max((uint32_t)(0.125f * (float)k * per), 1u)};
+  for (int u = 0; u < N; ++u) {
+    const uint32_t du = sp.digit(sv[u]);
+    if (u * NT + tid < ns && du != 0u) atomicAdd(&sm.lhist[du], 1u);
+  }
+  const float per = (float)ns / (float)vis, room = (float)CAND_CAP * per;         // room: the samples that a full list stands for
+  uint32_t need[2] = {ess_sel::sample_target(k, per), max((uint32_t)(0.125f * (float)k * per), 1u)};
+  __syncthreads();
+  // the digits of the need[0]-th and the need[1]-th largest of `all`: sm.sbin; of the first also how many lie above and in it
+  auto search = [&](uint32_t all) {
     const int d0 = NBINS - DPT - DPT * tid;
     const uint4 h = *reinterpret_cast<const uint4*>(&sm.lhist[d0]);
     const uint32_t cnt[DPT] = {h.w, h.z, h.y, h.x};
@@ -334,40 +343,76 @@ __device__ __forceinline__ bool bounds_of(TopkShared& sm, int tid, const float (
 #pragma unroll
     for (int w = 0; w < 2; ++w) {
       uint32_t above = inc - mine;
-      if (target[w] > 0 && above < target[w] && inc >= target[w]) {
+      if (above < need[w] && inc >= need[w]) {
 #pragma unroll
         for (int i = 0; i < DPT; ++i) {
-          if (above < target[w] && above + cnt[i] >= target[w]) {
+          if (above < need[w] && above + cnt[i] >= need[w]) {
             sm.sbin[w] = (uint32_t)(d0 + DPT - 1 - i);
-            if (w == 0) sm.sel_to = above + cnt[i];
+            if (w == 0) { sm.sel_above = above; sm.sel_count = cnt[i]; }
           }
           above += cnt[i];
         }
       }
+      if (tid == 0 && total < need[w] && all >= need[w]) {   // (those of digit 0 need not be in the histogram)
+        sm.sbin[w] = 0u;
+        if (w == 0) { sm.sel_above = total; sm.sel_count = all - total; }
+      }
     }
     __syncthreads();
-    const uint32_t b0 = sm.sbin[0], b1 = sm.sbin[1];
-    if (b0 != 0xffffffffu && b0 >= 1u && (float)sm.sel_to < 0.9f * CAND_CAP * per) {
-      *tau = sp.edge(b0);
-      *tau_hi = b1 == 0xffffffffu ? hi : sp.edge(b1 + 1);
+  };
+  search((uint32_t)ns);
+  uint32_t b0 = sm.sbin[0], b1 = sm.sbin[1], above = sm.sel_above;
+  uint32_t reach = above + sm.sel_count;     // samples that reach digit b0
+  if (__builtin_expect(b0 - 1u < NONE - 1u && (float)reach < 0.9f * room, 1)) {
+    *tau = sp.edge(b0);
+    *tau_hi = sp.edge(b1 + 1);
+    return *tau_hi > *tau;
+  }
+  if (b0 == NONE) return false;              // fewer samples than the bound asks for
+  // (rare) the digit's own samples, spread again
+  uint32_t d[N];
+#pragma unroll
+  for (int u = 0; u < N; ++u) d[u] = u * NT + tid < ns ? sp.digit(sv[u]) : NONE;
+#pragma unroll 1
+  for (int round = 0; round < NARROW; ++round) {
+    lo = kInf;
+    hi = -kInf;
+#pragma unroll
+    for (int u = 0; u < N; ++u)
+      if (d[u] == b0) {
+        const float x = sv[u] == sv[u] ? sv[u] : -kInf;      // (as a key has it)
+        lo = fminf(lo, x);
+        hi = fmaxf(hi, x);
+      }
+    *reinterpret_cast<uint4*>(&sm.lhist[DPT * tid]) = make_uint4(0, 0, 0, 0);
+    value_range(sm, tid, lo, hi);
+    sp = Spread(lo, hi);
+    if (sp.scale == 0.f) {                   // equal, or as good as equal
+      *tau = fminf(lo, kMost);
+      *tau_hi = beyond(*tau);
+      return *tau >= -kMost && (float)reach < room && *tau_hi > *tau;
+    }
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+      d[u] = d[u] == b0 ? sp.digit(sv[u]) : NONE;
+      if (d[u] != NONE) atomicAdd(&sm.lhist[d[u]], 1u);
+    }
+    __syncthreads();
+    need[0] -= above;
+    need[1] = b1 == b0 ? need[1] - above : 1u;               // (or the upper bound is that of this digit)
+    const uint32_t in = sm.sel_count, before = reach - in;
+    search(in);
+    b0 = sm.sbin[0];
+    b1 = sm.sbin[1];
+    above = sm.sel_above;
+    reach = before + above + sm.sel_count;
+    if (b0 >= 1u && ((float)reach < 0.9f * room || (round == NARROW - 1 && (float)reach < room))) {
+      *tau = fmaxf(sp.edge(b0), -kMost);
+      *tau_hi = fminf(sp.edge(b1 + 1), kMost);
       return *tau_hi > *tau;
     }
-    __syncthreads();
-    if (tid == 0) sm.sbin[0] = sm.sbin[1] = 0xffffffffu;
   }
-  for (int j = tid; j < ess_sel::sample_words<NT>(); j += NT) sm.shist[j] = 0;
-  __syncthreads();
-#pragma unroll
-  for (int u = 0; u < N; ++u)
-    if (u * NT + tid < ns) atomicAdd(&sm.shist[ess_sel::sample_slot<NT>(orderable(sv[u]) >> (32 - SBITS))], 1u);
-  __syncthreads();
-  uint32_t lo_bin, hi_bin;
-  ess_sel::sample_bins<NT>(sm.shist, sm.wave_tot, sm.sbin, k, ns, vis, &lo_bin, &hi_bin);
-  if (lo_bin == 0xffffffffu || lo_bin == 0u) return false;
-  // (the lower end of the bin of -inf, or of what lies above +inf, is no score)
-  *tau = fmaxf(score_of(lo_bin << (32 - SBITS)), -3.4028235e38f);
-  *tau_hi = hi_bin == 0xffffffffu || hi_bin == SBINS - 1 ? 3.4028235e38f : fminf(score_of((hi_bin + 1) << (32 - SBITS)), 3.4028235e38f);
-  return *tau_hi > *tau;
+  return false;
 }
 
 // Inside the digit that holds the k-th largest key -- a handful of keys, sm.few[0..cnt): f(key) for the `take` largest, found by
@@ -429,7 +474,6 @@ __device__ __forceinline__ bool finish_rounds(TopkShared& sm, int tid, const flo
   *reinterpret_cast<uint4*>(&sm.lhist[DPT * tid]) = make_uint4(0, 0, 0, 0);
   if (tid == 0) sm.cand_n = 0;
   const Spread sp(tau, tau_hi);
-  constexpr uint32_t NONE = 0xffffffffu;
   uint32_t d[N];
   __syncthreads();
 #pragma unroll
@@ -507,8 +551,6 @@ __device__ __forceinline__ bool finish_list(TopkShared& sm, int tid, const float
   return finish_rounds<PER>(sm, tid, v, p, listed, tau, tau_hi, vis, k, IB, orow);
 }
 
-constexpr uint32_t NONE = 0xffffffffu, ABOVE = NONE - 1u;     // in place of a digit: no key, or one that is not taken; one that is
-
 // Path S: a row that fits the candidate list whole needs no sample and no list: its scores in registers.  They are spread evenly
 // over 2046 digits (spread_of); the digit that holds the k-th
 // largest is found, and inside it the key by counting.  A wave holds 64 consecutive positions at a time, so a position's rank
@@ -569,8 +611,7 @@ __device__ __forceinline__ bool whole_row(TopkShared& sm, int tid, const float (
           hi = fmaxf(hi, x);
         }
       *reinterpret_cast<uint4*>(&sm.lhist[DPT * tid]) = make_uint4(0, 0, 0, 0);
-      float none = 0.f;
-      value_range(sm, tid, lo, hi, none);
+      value_range(sm, tid, lo, hi);
       equal = lo == hi;
       const Spread finer(lo, hi);
       if (equal || finer.scale == 0.f) break;
@@ -783,8 +824,7 @@ __device__ __forceinline__ void topk_item(TopkShared& sm, int item, int parts, f
         list_lo = fminf(list_lo, fin ? lv[u] : kInf);
         list_hi = fmaxf(list_hi, fin ? lv[u] : -kInf);
       }
-      float none = 0.f;
-      value_range(sm, tid, list_lo, list_hi, none);
+      value_range(sm, tid, list_lo, list_hi);
     }
     if (finish_list(sm, tid, lv, lp, listed, list_lo, list_hi, vis, k, IB, orow)) return;
   }
@@ -792,24 +832,14 @@ __device__ __forceinline__ void topk_item(TopkShared& sm, int item, int parts, f
     float tau = 0.f, tau_hi = 0.f;
     bool found = use_list;
     if (!use_list) {
-      // samples: blocks of 16 consecutive scores (one 64-byte piece of a cache line), one of every bstride blocks at a
+      // samples: blocks of 16 consecutive scores (one 64-byte piece of a cache line), one of every 1, 2, 4 .. blocks at a
       // place that changes from one to the next (scores that repeat with the stride would else be counted all or not at all),
       // SAMPLE_TARGET scores in all at most, or twice that (sample_blocks).  (One score out of every 16th..32nd touches every cache line of the
       // row: in cache-line traffic the sample then costs as much as the pass that follows.)
       const int nblk_all = vis >> 4, blocks = ess_sel::sample_blocks(k, vis);
-      int bstride = 1;
-      while (nblk_all / bstride > blocks) bstride <<= 1;
-      const int ns = (nblk_all / bstride) << 4;
-      float sv[SAMPLE_PER];
-#pragma unroll
-      for (int u = 0; u < SAMPLE_PER; ++u) {
-        if (u == SAMPLE_PER / 2 && ns <= SAMPLE_PER / 2 * NT) break;
-        const int j = min(u * NT + tid, ns - 1);
-        const int blk = (j >> 4) * bstride + (int)(((uint32_t)(j >> 4) * 0x9e3779b1u >> 16) & (uint32_t)(bstride - 1));
-        sv[u] = srow[(size_t)blk * 16 + (j & 15)];
-      }
-      *reinterpret_cast<uint4*>(&sm.lhist[DPT * tid]) = make_uint4(0, 0, 0, 0);
-      if (tid == 0) { sm.cand_n = 0; sm.sbin[0] = sm.sbin[1] = 0xffffffffu; }
+      int every = 0;                         // (a power of two as its exponent)
+      while ((nblk_all >> every) > blocks) ++every;
+      const int ns = (nblk_all >> every) << 4;
       // this workgroup's slice of the row (boundaries on 16-byte pieces); its first round is asked for behind the samples
       const int s_lo = parts > 1 ? (int)(((long)vis * part / parts) & ~3L) : 0;
       const int s_hi = (parts > 1 && part + 1 < parts) ? (int)(((long)vis * (part + 1) / parts) & ~3L) : vis;
@@ -818,10 +848,23 @@ __device__ __forceinline__ void topk_item(TopkShared& sm, int item, int parts, f
       float4v x[SETS][ROUND];
       const float* const slice = srow + s_lo;
       const int head = to_boundary(slice);
-      row_begin<SETS>(tid, slice + head, s_hi - s_lo - head, x);
-      __builtin_amdgcn_sched_barrier(0);
-      found = bounds_of(sm, tid, sv, ns, k, vis, &tau, &tau_hi);
-      __syncthreads();                       // (the list shares its memory with the sample's histogram)
+      auto sampled = [&](auto per_thread) {
+        constexpr int N = decltype(per_thread)::value;
+        float sv[N];
+#pragma unroll
+        for (int u = 0; u < N; ++u) {
+          const int j = min(u * NT + tid, ns - 1);
+          const int blk = ((j >> 4) << every) + (int)(((uint32_t)(j >> 4) * 0x9e3779b1u >> 16) & ((1u << every) - 1u));
+          sv[u] = srow[(size_t)blk * 16 + (j & 15)];
+        }
+        *reinterpret_cast<uint4*>(&sm.lhist[DPT * tid]) = make_uint4(0, 0, 0, 0);
+        if (tid == 0) { sm.cand_n = 0; sm.sbin[0] = sm.sbin[1] = NONE; }
+        row_begin<SETS>(tid, slice + head, s_hi - s_lo - head, x);
+        __builtin_amdgcn_sched_barrier(0);
+        return bounds_of(sm, tid, sv, ns, k, vis, &tau, &tau_hi);
+      };
+      found = __builtin_expect(blocks * 16 == ess_sel::SAMPLE_TARGET, 1) ? sampled(std::integral_constant<int, ess_sel::SAMPLE_TARGET / NT>{})
+                                                                         : sampled(std::integral_constant<int, 2 * ess_sel::SAMPLE_TARGET / NT>{});
       if (MODE == 1 && !found) return;       // no usable threshold: the finishing kernel takes path B
       // The pass only compares floats and stores (position, score) of the few positions at or above
       // the threshold (NaN is below, -0 == +0: the order of the keys),
@@ -994,16 +1037,15 @@ __global__ __launch_bounds__(NT) void k_topk(float* score, const int32_t* __rest
 // tau[row][0] = a score that very probably has at least k and at most a few thousand of the row's scores at or above
 // it; 0 (everything is a candidate) for rows that fit the candidate buffer whole or whose sample gives no bound;
 // 0xffffffff (nothing) for rows with at most k visible positions, which need no list;
-// tau[row][1] = a score that very probably has fewer than k of the row's scores at or above it (0xffffffff if the
-// sample gives none; 0 with no lower bound): the k-th largest score very probably lies between the two, which lets
-// the finishing kernel resolve that range in one pass.
+// tau[row][1] = a score with about an eighth of k of the row's scores at or above it (see bounds_of; 0 without a bound): the k-th
+// largest score very probably lies between the two, which lets the finishing kernel resolve that range in one pass.
 // Also clears the row's candidate counter for the pass that follows.
 template <bool DYN>
 __global__ __launch_bounds__(NT) void k_index_tau(const float* __restrict__ sample, const int32_t* __restrict__ ctx_len,
                                                   int T, int Lmax, int k, int period, int nsamp,
                                                   uint32_t* __restrict__ tau, uint32_t* __restrict__ g_cnt, ess_xcd xcd,
                                                   int rows) {
-  __shared__ TopkShared sm;
+  __shared__ BoundsShared sm;
   __shared__ int s_item;
   ESS_WORK_LOOP(DYN, xcd, blockIdx.x, rows, &s_item, row) {
     const int tid = threadIdx.x;

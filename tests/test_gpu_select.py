@@ -265,12 +265,16 @@ def _far_rows(L, k):
              with_(some(far.size), far), (base - 300) * np.float32(1e-37), with_(slice(0, L), np.nan)]
     # groups of scores many magnitudes apart
     rows.append((rng.rand(L) * 10.0 ** rng.randint(-30, 31, L)).astype(np.float32))
+    # a floor that many scores lie on, with more or fewer than k above it; two groups of outliers
+    rows += [np.maximum(base, np.float32(x)) for x in (np.sort(base)[max(L - k - 300, 0)], np.sort(base)[L - 1 - k // 2])]
+    rows += [with_(rng.rand(L) < 0.005, 1e30), with_(rng.rand(L) < 0.005, 1e30, with_(rng.rand(L) < 0.4, -1e25))]
     return np.stack(rows).astype(np.float32)
 
 
 @pytest.mark.parametrize("L,vis,k", [(8192, 8192, 2048), (8192, 8191, 4096), (8192, 2049, 2048), (8192, 600, 511), (8192, 513, 1), (8192, 17, 5),
                                      (8200, 8192, 2048), (8200, 8193, 4096), (65536, 8192, 2048), (65536, 5000, 513), (65536, 40003, 2048),
-                                     (49157, 40001, 2048), (262144, 262143, 4096), (300001, 300000, 3584), (524288, 524288, 4096)])
+                                     (49157, 40001, 2048), (262144, 262143, 4096), (300001, 300000, 3584), (524288, 524288, 4096),
+                                     (12003, 12000, 2048), (12000, 12000, 4096), (40000, 40000, 1), (131072, 131072, 2048)])
 def test_topk_of_rows_with_scores_far_apart_or_equal(ess_lib, L, vis, k):
     """Rows held whole (alone, beside the sampled form, and as the short rows of shared ones) and sampled rows: outliers, masks, magnitudes apart, ties
     of up to all scores, NaN as low as -inf; the set of the k largest is one set, so it must be equal."""
