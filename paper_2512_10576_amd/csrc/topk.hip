@@ -18,9 +18,9 @@
 //      11 bits a pass (histogram in 8 interleaved copies, copy = lane & 7, so
 //      that lanes hitting one hot bin do not serialise), until the positions
 //      matching the decided prefix fit the buffer; one pass collects them.
-//   C. A and S: one histogram spread evenly over the candidates' scores, and
-//      counting inside the digit that holds the k-th; B, or where that digit
-//      is too full: radix select inside LDS over the candidates.
+//   C. A and S: one histogram spread evenly over the candidates' scores, the
+//      digit that holds the k-th spread again while it is too full, and
+//      counting inside it; B: radix select inside LDS over the candidates.
 //   D. positions leave in ascending order, each for its rank among the selected
 //      (a counting sort), so the output is ordered and deterministic.
 // Row passes keep several 16-byte loads per thread in flight; a workgroup that
@@ -49,6 +49,8 @@ constexpr int PER = CAND_CAP / NT;           // keys per thread of a row or a li
 constexpr int LIST_AHEAD = 3072 / NT;        // rounds of NT list entries that are asked for before their number is known
 constexpr int ROUND = 8;                     // float4s per thread and round of a pass over a row
 constexpr int DPT = NBINS / NT;              // digits per thread of a scan over a digit histogram
+constexpr uint32_t LIST_FEW = 320;           // keys of one digit of a list that are counted at once; of more the digit is spread again: 200 equal
+                                             // scores counted / spread 12.7 / 14.7 us (a row of 12000), 900 38.6 / 15.5
 constexpr int RANK_WORDS = NBINS * 4;        // words of a row's bitmap up to which the words' ranks fit beside it (262144 positions)
 static_assert(PER * (NT / 64) == 128 && DPT == 4, "two counts a lane; digits are read 16 bytes at a time");
 constexpr uint32_t NONE = 0xffffffffu, ABOVE = NONE - 1u;     // in place of a digit: no key, or one that is not taken; one that is
@@ -460,13 +462,19 @@ __device__ __forceinline__ void take_few(TopkShared& sm, int tid, uint32_t cnt, 
 // histogram spreads that range over 2046 digits (what lies above goes into the last), the digit that holds the k-th largest
 // key is found, and inside it the key by counting.  The positions taken are marked in a bitmap of the row, and each leaves
 // for its rank: the positions taken in the words before, and in its word before it.
-// Returns false, with the keys in sm.cand, when that digit holds more keys than the counting step takes
-// (massive ties, or a k-th largest score outside the range): the caller goes on with the general selection.
+// Where that digit holds more keys than counting takes (ties, a k-th largest score outside the range), its keys alone are spread between
+// their own extremes, and equal scores by their positions.  us, a row of 12000, counted or by the general selection / now: 900 equal
+// scores at the k-th 38.6 / 15.5, 3000 28.7 / 22.2; 64 rows of 115000: 45.7 / 24.5, 36.1 / 28.3.
+// Returns false, with the keys in sm.cand, when that did not help (or the range gives no digits): the caller goes on with the general selection.
 template <int N>
 __device__ __forceinline__ bool finish_rounds(TopkShared& sm, int tid, const float (&v)[PER], const uint32_t (&p)[PER], uint32_t listed,
                                             float tau, float tau_hi, int vis, int k, int IB, int32_t* __restrict__ orow) {
   const unsigned long long imask = (1ull << IB) - 1ull;
-  auto key = [&](int u) { return ((unsigned long long)orderable(v[u]) << IB) | (imask - (unsigned long long)p[u]); };
+  auto key = [&](int u) {
+    uint32_t low = (uint32_t)imask - p[u];
+    asm volatile("" : "+v"(low));            // (where it is asked for, not by every list)
+    return ((unsigned long long)orderable(v[u]) << IB) | low;
+  };
   // (keys of a list may still be on their way:) clear the histogram and the row's bitmap
   uint32_t* const bmp = sm.hist;
   const int W = (vis + 31) >> 5;             // at most 16384 words
@@ -483,7 +491,44 @@ __device__ __forceinline__ bool finish_rounds(TopkShared& sm, int tid, const flo
   }
   __syncthreads();
   crossing_digit(sm, tid, (uint32_t)k);
-  const uint32_t dsel = sm.sel_digit, take = (uint32_t)k - sm.sel_above, cnt = sm.sel_count;
+  uint32_t dsel = sm.sel_digit, take = (uint32_t)k - sm.sel_above, cnt = sm.sel_count;
+  // (rare) that digit's keys alone, spread again; equal ones by their positions
+  if (__builtin_expect(cnt > LIST_FEW && cnt != take && sp.scale != 0.f, 0)) {
+    bool by_position = false;
+#pragma unroll 1
+    for (int round = 0; round < NARROW + 2 && cnt > FEW && cnt != take; ++round) {
+      constexpr float kInf = __builtin_inff();
+      float lo = kInf, hi = -kInf;
+      auto value = [&](int u) { return by_position ? -(float)p[u] : v[u]; };        // (below 2^19: exact)
+#pragma unroll
+      for (int u = 0; u < N; ++u)
+        if (d[u] == dsel) {
+          lo = fminf(lo, value(u));
+          hi = fmaxf(hi, value(u));
+        }
+      *reinterpret_cast<uint4*>(&sm.lhist[DPT * tid]) = make_uint4(0, 0, 0, 0);
+      value_range(sm, tid, lo, hi);
+      const Spread finer(lo, hi);
+      if (lo == hi && !by_position) {
+        by_position = true;
+        __syncthreads();                       // (every wave has its extremes)
+        continue;
+      }
+      if (finer.scale == 0.f) break;
+#pragma unroll
+      for (int u = 0; u < N; ++u) {
+        if (d[u] == dsel) {
+          d[u] = finer.digit(value(u));
+          atomicAdd(&sm.lhist[d[u]], 1u);
+        } else {
+          d[u] = d[u] == NONE || d[u] < dsel ? NONE : ABOVE;
+        }
+      }
+      __syncthreads();
+      crossing_digit(sm, tid, take);
+      dsel = sm.sel_digit; take -= sm.sel_above; cnt = sm.sel_count;
+    }
+  }
   if (cnt != take || sp.scale == 0.f) {
     if (cnt > SMALL || sp.scale == 0.f) {
 #pragma unroll
