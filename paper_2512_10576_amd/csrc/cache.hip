@@ -833,7 +833,7 @@ __global__ __launch_bounds__(APPEND_NT) void k_append(
       const uint2 r = lane < APPEND_NT / 64 ? red[t][lane] : make_uint2(0xffffffffu, 0xffffffffu);
       const uint32_t all = wave_min_u32(r.x), slot = wave_min_u32(r.x == all ? r.y : 0xffffffffu);
       v[t] = all == 0xffffffffu ? -1 : (int)slot;
-      if (v[t] >= 0 && v[t] % APPEND_NT == tid) mine(t + 1);
+      if (t + 1 < n && v[t] >= 0 && v[t] % APPEND_NT == tid) mine(t + 1);      // (after the last token nobody asks)
     }
   } else {
     __syncthreads();                               // (everyone has read ctx_len)
