@@ -16,11 +16,28 @@ constexpr int NARROW = 3;                  // times a whole row's spread is narr
 // Scores between lo and hi spread evenly over the digits 1 .. 2046; below lo, -inf and what is no number: 0 or 1; above hi: up
 // to 2047.  Monotone in the score, four instructions.  scale 0: the range gives no such digits.  (Ends past 1.6e38 are taken in,
 // so that their distance is a number.)
+// (Reciprocals and roots to the last bit but one, in an instruction where the exact ones take a dozen: a kernel that others have pushed out
+// of the instruction cache waits for every line of its code.)
+__host__ __device__ __forceinline__ float quick_rcp(float x) {
+#ifdef __HIP_DEVICE_COMPILE__
+  return __builtin_amdgcn_rcpf(x);
+#else
+  return 1.0f / x;
+#endif
+}
+__host__ __device__ __forceinline__ float quick_sqrt(float x) {
+#ifdef __HIP_DEVICE_COMPILE__
+  return __builtin_amdgcn_sqrtf(x);
+#else
+  return sqrtf(x);
+#endif
+}
 struct Spread {
-  float lo, scale;
+  float lo, scale, step;                     // step: of a digit
   __host__ __device__ __forceinline__ Spread(float lo_, float hi_) : lo(fmaxf(lo_, -1.6e38f)) {
     const float span = fminf(hi_, 1.6e38f) - lo;
-    scale = span > 1e-30f ? (float)(NBINS - 3) / span : 0.f;
+    step = span * (1.0f / (float)(NBINS - 3));
+    scale = span > 1e-30f ? quick_rcp(step) : 0.f;
   }
   __host__ __device__ __forceinline__ uint32_t digit(float v) const {
 #ifdef __HIP_DEVICE_COMPILE__
@@ -30,7 +47,7 @@ struct Spread {
 #endif
   }
   // a score that no score of digit d or above lies below (a hundredth of a digit covers the rounding of `digit`)
-  __host__ __device__ __forceinline__ float edge(uint32_t d) const { return fmaf((float)d - 1.01f, 1.0f / scale, lo); }
+  __host__ __device__ __forceinline__ float edge(uint32_t d) const { return fmaf((float)d - 1.01f, step, lo); }
 };
 
 // Samples of a row above CAND_CAP positions: blocks of 16 scores, at most this many blocks; twice as many where more than 2048 are to be
@@ -45,7 +62,7 @@ __host__ __device__ inline int sample_blocks(int k, int vis) { return (k > 2048 
 // asked for more than fits.)
 __host__ __device__ inline uint32_t sample_target(int k, float per) {
   const float expct = (float)k * per;
-  return (uint32_t)fmaxf(fminf(1.25f * expct + 4.0f * sqrtf(expct) + 8.0f, 0.47f * (expct + (float)CAND_CAP * per)), 1.0f);
+  return (uint32_t)fmaxf(fminf(1.25f * expct + 4.0f * quick_sqrt(expct) + 8.0f, 0.47f * (expct + (float)CAND_CAP * per)), 1.0f);
 }
 
 // Inclusive prefix sum over the 64 lanes of a wave, by data-parallel-primitive moves inside the vector ALU (seven

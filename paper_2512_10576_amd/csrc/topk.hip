@@ -234,6 +234,17 @@ __device__ __forceinline__ void emit_bitmap(TopkShared& sm, int tid, const uint3
   }
 }
 
+// A running sum over four counts starts at `above`, below need: the index of the count that takes it to need or beyond, with the sum in front of it
+// in `above` and with it in `upto`.  (Selects: with a branch a count this was three times the code.)
+__device__ __forceinline__ uint32_t crossing_of(const uint32_t (&cnt)[DPT], uint32_t need, uint32_t& above, uint32_t& upto) {
+  static_assert(DPT == 4, "written for four");
+  const uint32_t s0 = above + cnt[0], s1 = s0 + cnt[1], s2 = s1 + cnt[2], s3 = s2 + cnt[3];
+  const bool p0 = s0 < need, p1 = s1 < need, p2 = s2 < need;
+  above = p2 ? s2 : (p1 ? s1 : (p0 ? s0 : above));
+  upto = p2 ? s3 : (p1 ? s2 : (p0 ? s1 : s0));
+  return (p0 ? 1u : 0u) + (p1 ? 1u : 0u) + (p2 ? 1u : 0u);
+}
+
 // Which of the 2048 digits of the histogram sm.lhist contains the need-th largest key, counted
 // from the top: sm.sel_digit, with sm.sel_above keys above it and sm.sel_count in it.  Ends with a barrier.
 // all: the number of keys, those of digit 0 need not be in the histogram then.
@@ -245,13 +256,9 @@ __device__ __forceinline__ void crossing_digit(TopkShared& sm, int tid, uint32_t
   uint32_t total;
   uint32_t above = block_incl_scan(mine, sm.wave_tot, &total) - mine;
   if (above < need && above + mine >= need) {
-#pragma unroll
-    for (int i = 0; i < DPT; ++i) {
-      if (above < need && above + cnt[i] >= need) {
-        sm.sel_digit = (uint32_t)(d0 + DPT - 1 - i); sm.sel_above = above; sm.sel_count = cnt[i];
-      }
-      above += cnt[i];
-    }
+    uint32_t upto;
+    const uint32_t i = crossing_of(cnt, need, above, upto);
+    sm.sel_digit = (uint32_t)(d0 + DPT - 1) - i; sm.sel_above = above; sm.sel_count = upto - above;
   }
   if (all != 0u && total < need && tid == 0) { sm.sel_digit = 0u; sm.sel_above = total; sm.sel_count = all - total; }
   __syncthreads();
@@ -331,7 +338,7 @@ __device__ __forceinline__ bool bounds_of(BoundsShared& sm, int tid, const float
     const uint32_t du = sp.digit(sv[u]);
     if (u * NT + tid < ns && du != 0u) atomicAdd(&sm.lhist[du], 1u);
   }
-  const float per = (float)ns / (float)vis, room = (float)CAND_CAP * per;         // room: the samples that a full list stands for
+  const float per = (float)ns * ess_sel::quick_rcp((float)vis), room = (float)CAND_CAP * per;         // room: the samples that a full list stands for
   uint32_t need[2] = {ess_sel::sample_target(k, per), max((uint32_t)(0.125f * (float)k * per), 1u)};
   __syncthreads();
   // the digits of the need[0]-th and the need[1]-th largest of `all`: sm.sbin; of the first also how many lie above and in it
@@ -346,14 +353,9 @@ __device__ __forceinline__ bool bounds_of(BoundsShared& sm, int tid, const float
     for (int w = 0; w < 2; ++w) {
       uint32_t above = inc - mine;
       if (above < need[w] && inc >= need[w]) {
-#pragma unroll
-        for (int i = 0; i < DPT; ++i) {
-          if (above < need[w] && above + cnt[i] >= need[w]) {
-            sm.sbin[w] = (uint32_t)(d0 + DPT - 1 - i);
-            if (w == 0) { sm.sel_above = above; sm.sel_count = cnt[i]; }
-          }
-          above += cnt[i];
-        }
+        uint32_t upto;
+        sm.sbin[w] = (uint32_t)(d0 + DPT - 1) - crossing_of(cnt, need[w], above, upto);
+        if (w == 0) { sm.sel_above = above; sm.sel_count = upto - above; }
       }
       if (tid == 0 && total < need[w] && all >= need[w]) {   // (those of digit 0 need not be in the histogram)
         sm.sbin[w] = 0u;
