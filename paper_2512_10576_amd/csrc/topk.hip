@@ -779,13 +779,13 @@ __device__ __forceinline__ void topk_item(TopkShared& sm, int item, int parts, f
   float v[MODE == 2 || MODE == 3 ? 1 : PER];
   if constexpr (MODE == 4) {               // no row is longer than the list: asked for beside the row's length
 #pragma unroll
-    for (int u = 0; u < PER; ++u) v[u] = u * NT + tid < Lmax ? srow[u * NT + tid] : 0.f;
+    for (int u = 0; u < PER; ++u) v[u] = srow[min(u * NT + tid, Lmax - 1)];
   }
   int vis = ctx_len[b] - (T - 1 - t);
   vis = max(0, min(vis, Lmax));
   auto load_whole = [&](float (&v)[PER], int n) {
 #pragma unroll
-    for (int u = 0; u < PER; ++u) v[u] = u * NT + tid < n ? srow[u * NT + tid] : 0.f;
+    for (int u = 0; u < PER; ++u) v[u] = srow[min(u * NT + tid, n - 1)];      // (clamped, not predicated; what lies past the end is not looked at)
   };
   if constexpr (MODE == 1) if (vis <= k || vis < FAST_MIN_VIS) {  // nothing to prepare: a short row is done here, or later
     if (part == 0 && vis > k) {
