@@ -162,7 +162,7 @@ def test_append_argument_errors(ess_lib):
 
 @pytest.mark.parametrize("fmt,T,S,L", [(0, 4, 37, 6000), (1, 4, 16385, 17000), (1, 3, 1024, 6000), (0, 4, 3, 6000)])
 def test_append_of_several_tokens_and_after_a_cut(ess_lib, fmt, T, S, L):
-    """Three and four tokens a call, pools of one slot a thread and less, of more than the registers hold, and of fewer slots than
+    """Three and four tokens a call, pools of one slot a thread and less, of more than the registers hold, and of as many slots as a call has
     tokens; then contexts cut back, so that a victim's former token may be a position that the same call fills."""
     from paper_2512_10576_amd import binding as bnd
     print("append several", fmt, T, S, L, flush=True)
@@ -194,4 +194,84 @@ def test_append_of_several_tokens_and_after_a_cut(ess_lib, fmt, T, S, L):
         assert np.array_equal(cache.token_of.cpu().numpy(), oc.token_of), step
         assert np.array_equal(cache.stamp.cpu().numpy().view(np.uint32), oc.stamp)
         assert np.array_equal(cache.slot_pool.cpu().numpy(), opool)
+    ctx.close()
+
+
+@pytest.mark.parametrize("T", [1, 2, 3, 4])
+@pytest.mark.parametrize("free", [1, 2, 3])
+@pytest.mark.parametrize("S", [0, 17000])
+def test_append_to_fewer_free_slots_than_tokens(ess_lib, T, free, S):
+    """Calls under one step number: the last slots below it go to a call's first tokens and the others find none.  Pools held in
+    registers (S 0: just enough slots) and a pool that is not, whose other slots carry the step's stamp already."""
+    from paper_2512_10576_amd import binding as bnd
+    print("append to free slots", T, free, S, flush=True)
+    B, Hi, Di, L = 2, 4, 32, 17408
+    S = S or T + free
+    hp = torch.empty((B, L, 1152), dtype=torch.uint8, pin_memory=True).zero_()
+    ctx = _ctx(ess_lib, max_batch=B, max_q_tokens=T, max_ctx=L, idx_heads=Hi, idx_dim=Di, topk=1, attn_heads=8, slots_per_seq=S)
+    cache = bnd.Cache.allocate(ctx.cfg, B, host_pool=hp)
+    ctx.cache_reset(cache, B)
+    cache.slot_pool.zero_()
+    oc, opool, ohost = O.SlotCache(B, L, S), np.zeros((B, S, 1152), np.uint8), np.zeros((B, L, 1152), np.uint8)
+    left = np.random.RandomState(T * 8 + free).permutation(S)[:T + free]             # slots below the step's number
+    oc.stamp[:, :] = 7
+    oc.stamp[:, left] = np.arange(T + free) // 2
+    cache.stamp.copy_(torch.from_numpy(oc.stamp.astype(np.int32)))
+    okey, octx = np.zeros((B, L, Di), np.uint8), np.array([5, L - 9], np.int32)
+    dkey, dctx = torch.zeros((B, L, Di), dtype=torch.uint8, device="cuda"), torch.from_numpy(octx.copy()).cuda()
+    placed = torch.empty((B, T), dtype=torch.int32, device="cuda")
+    for call in range(3):
+        nk, nr = _new_entries(30 + call, B, T, Hi, Di, 0, qk=4)
+        ref = O.append_tokens(oc, okey, ohost, opool, octx, nk.numpy(), nr.numpy(), 7)
+        ctx.append(cache, nk.cuda(), nr.cuda(), dkey, dctx, 7, placed)
+        torch.cuda.synchronize()
+        assert (ref[0] >= 0).sum() == max(0, min(T, T + free - call * T))
+        assert np.array_equal(placed.cpu().numpy(), ref), call
+        assert np.array_equal(dctx.cpu().numpy(), octx) and np.array_equal(dkey.cpu().numpy(), okey) and np.array_equal(hp.numpy(), ohost)
+        assert np.array_equal(cache.slot_of.cpu().numpy(), oc.slot_of) and np.array_equal(cache.token_of.cpu().numpy(), oc.token_of)
+        assert np.array_equal(cache.stamp.cpu().numpy().view(np.uint32), oc.stamp)
+        assert np.array_equal(cache.slot_pool.cpu().numpy(), opool)
+    ctx.close()
+
+
+@pytest.mark.parametrize("T,paged,resident", [(2, False, True), (4, False, True), (4, True, True), (4, True, False)])
+def test_append_of_several_tokens_resident_and_paged(ess_lib, T, paged, resident):
+    """Two and four tokens a call without a host pool (slot = position), four across a page's end with a scale each, and contexts that
+    reach the buffer's end or an unmapped page inside a call."""
+    from paper_2512_10576_amd import binding as bnd
+    print("append several, resident", resident, "paged", paged, T, flush=True)
+    B, Hi, Di, L = 4, 4, 64, 1024
+    S = L if resident else 700
+    octx = np.array([62, 511, L - 3, 0], np.int32)
+    _, _, key = synth.indexer_inputs(67, B, 1, Hi, Di, L, 8, 8, 16)
+    hp = None if resident else torch.empty((B, L, 1152), dtype=torch.uint8, pin_memory=True).zero_()
+    ctx = _ctx(ess_lib, max_batch=B, max_q_tokens=T, max_ctx=L, idx_heads=Hi, idx_dim=Di, topk=2, attn_heads=8, slots_per_seq=S)
+    cache = bnd.Cache.allocate(ctx.cfg, B, host_pool=hp, slot_pool=torch.zeros((B, S, 1152), dtype=torch.uint8, device="cuda"))
+    ctx.cache_reset(cache, B)
+    oc, opool = O.SlotCache(B, L, S), np.zeros((B, S, 1152), np.uint8)
+    if resident:
+        oc.make_resident_identity()
+    ohost = None if resident else np.zeros((B, L, 1152), np.uint8)
+    if paged:                                              # the second sequence has no page past 513 .. 575
+        pages, table, _ = synth.paged_indexer_cache(33, key, torch.tensor([200, 513, L, 130], dtype=torch.int32), n_spare_pages=2)
+        okeys, otable = pages.numpy().copy(), table.numpy()
+        dkeys, dtable = pages.cuda(), table.cuda()
+    else:
+        okeys, dkeys, dtable = key.numpy().copy(), key.cuda(), None
+    dctx = torch.from_numpy(octx.copy()).cuda()
+    placed = torch.empty((B, T), dtype=torch.int32, device="cuda")
+    g = torch.Generator().manual_seed(6)
+    for step in range(1, 20):
+        nk, nr = _new_entries(80 + step, B, T, Hi, Di, 0)
+        ns = (0.25 + torch.rand((B, T), generator=g)).to(torch.float32)
+        ref = O.append_tokens(oc, None if paged else okeys, ohost, opool, octx, nk.numpy(), nr.numpy(), step,
+                              paged=(okeys, otable, ns.numpy()) if paged else None)
+        ctx.append(cache, nk.cuda(), nr.cuda(), dkeys, dctx, step, placed, ns.cuda() if paged else None, dtable)
+        torch.cuda.synchronize()
+        assert np.array_equal(placed.cpu().numpy(), ref), step
+        assert np.array_equal(dctx.cpu().numpy(), octx) and np.array_equal(dkeys.cpu().numpy(), okeys), step
+        assert resident or np.array_equal(hp.numpy(), ohost)
+        assert np.array_equal(cache.slot_of.cpu().numpy(), oc.slot_of), step
+        assert np.array_equal(cache.slot_pool.cpu().numpy(), opool), step
+    assert octx[2] == L and octx[0] == 62 + 19 * T and octx[1] == (576 if paged else 511 + 19 * T)
     ctx.close()

@@ -233,6 +233,49 @@ def test_ticket_fed_launches_complete_at_any_launch_size(ess_lib, grid):
     assert confined[0] == 0 and confined[3] == 0 and min(confined[1:3] + confined[4:]) >= 1, confined
 
 
+@pytest.mark.parametrize("grid", [1, 7])
+@pytest.mark.parametrize("L,lens", [(12000, [12000, 9001, 0, 8192, 700]), (65536, [65536, 40000, 8000, 300, 65001])])
+def test_ticket_fed_topk_of_long_rows_at_any_launch_size(ess_lib, grid, L, lens):
+    """One workgroup that draws sampled rows, rows held whole, short ones and (from 64K on) the parts of shared rows one after the
+    other: its working memory passes from one to the next.  Selections and outputs equal the plain schedule bit for bit."""
+    from paper_2512_10576_amd import binding as bnd
+    print("edges: ticket-fed top-k of long rows,", grid, "workgroups,", L, flush=True)
+    B, T, Hi, Di, k, H, S = 5, 2, 4, 64, 512, 16, 1300
+    ctx_len = torch.tensor(lens, dtype=torch.int32)
+    qws = [tuple(x.cuda() for x in synth.indexer_inputs(187 + s, B, T, Hi, Di, 64, 8, 8, 16)[:2]) for s in range(3)]
+    key = synth.indexer_inputs(187, B, T, Hi, Di, L, 8, 8, 16)[2].cuda()
+    hp = torch.empty((B, L, 1152), dtype=torch.uint8, pin_memory=True)
+    hp.copy_(synth.latent_rows_bf16(187, L).reshape(1, L, 1152).expand(B, L, 1152))
+    results, confined = {}, []
+    for flags in (0, 4, 20):                                     # 20: stages 1-2 in the fused form
+        ctx = _ctx(max_batch=B, max_q_tokens=T, max_ctx=L, idx_heads=Hi, idx_dim=Di, topk=k, attn_heads=H,
+                   slots_per_seq=S, flags=flags)
+        if flags != 0:
+            ctx.set_overlap_threshold(0)
+            ctx.debug_ticket_grid(grid)
+        cache = bnd.Cache.allocate(ctx.cfg, B, host_pool=hp,
+                                   slot_pool=torch.full((B, S, 1152), 0x7F, dtype=torch.uint8, device="cuda"))
+        ctx.cache_reset(cache, B)
+        idx_out = torch.empty((B, T, k), dtype=torch.int32, device="cuda")
+        out = torch.empty((B, T, H, 512), dtype=torch.bfloat16, device="cuda")
+        steps = []
+        for step in range(1, 4):
+            q = synth.attn_query(95 + step, B, T, H)
+            ctx.decode_step(cache, *qws[step - 1], key, ctx_len.cuda(), q.cuda(), step, idx_out, out)
+            torch.cuda.synchronize()
+            if flags != 0:
+                confined.append(ctx.last_confined())
+            steps.append((idx_out.clone(), out.clone(), cache.slot_of.clone()))
+        assert ctx.get_stats()["steps"] == 3
+        ctx.close()
+        results[flags] = steps
+    for other in (4, 20):
+        for s0, s4 in zip(results[0], results[other]):
+            for x, y in zip(s0, s4):
+                assert torch.equal(x, y)
+    assert min(confined[1:3] + confined[4:]) >= 1, confined
+
+
 @pytest.mark.parametrize("stride,fmt", [(1152, 0), (656, 1)])
 def test_calib_memcpy_rows_delivers_host_pool_rows(ess_lib, stride, fmt):
     """The per-entry copy the paper starts from (Sec. 3.1: one memcpy per block): the rows it delivers are the
