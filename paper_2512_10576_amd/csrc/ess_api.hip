@@ -793,7 +793,8 @@ int ess_decode_step(ess_ctx* ctx, const ess_cache* cache, const ess_step_args* a
       // Scores of less than 16 MiB are stored the ordinary way: the top-k that follows finds them in the memory-side cache, and
       // so few modified lines cost the next launch nothing.  Non-temporal / ordinary, us a step: 1 x 8K 24.5 / 24.2, 4 x 128K 42.7 / 42.3,
       // 23 x 48K paged, two tokens (9 MiB), 140.2 / 138.5, 64 x 32K (8 MiB) 351.8 / 350.2; but 64 x 128K in halves of 16 MiB 531.2 / 532.1, and
-      // ess_index_score alone, which nothing follows, 13 x 128K 43.4 / 44.6.
+      // ess_index_score alone, which nothing follows, 13 x 128K 43.4 / 44.6.  Round the line, resident, one token: 64 x 32K (8 MiB) 128.8 / 126.3,
+      // 16 x 128K (8) 91.3 / 92.8, 24 x 128K (12) 130.4 / 129.1, 30 x 128K (15) 157.2 / 156.5, 32 x 128K (16) 162.7 / 162.8, 48 x 128K (24) 218.7 / 219.5.
       const bool keep_scores = (size_t)Bh * T * c.max_ctx * 4 < ((size_t)16 << 20);
       rc = ess_launch_index_score(c, q_h, w_h, key_h, a->ctx_len + b0, Bh, T, sc, st, table_h, np_h, ev_s, ev_e, xcd_of(ESS_TKT_INDEX), keep_scores);
       if (rc != ESS_OK) return rc;

@@ -9,7 +9,9 @@ namespace ess_sel {
 constexpr int CAND_CAP = 8192;             // candidate keys a row's list (and the LDS of the finishing kernel) holds
 constexpr int HBITS = 11;                  // digits of a radix or of an even spread
 constexpr int NBINS = 1 << HBITS;
-constexpr uint32_t FEW = 128;              // keys of one digit of a whole row that are counted at once; of more the digit is spread again
+// Keys of one digit that are counted at once; of more the digit is spread again: 200 equal scores counted / spread 10.2 / 11.0 us in a row of 8000, 12.7 /
+// 14.7 in one of 12000; 900 34.8 / 11.1 and 38.6 / 17.4.
+constexpr uint32_t FEW = 320;
 constexpr uint32_t SMALL = 1024;           // keys of one digit that are counted at all
 constexpr int NARROW = 3;                  // times a whole row's spread is narrowed to the digit that holds the k-th largest
 
@@ -100,7 +102,7 @@ __device__ __forceinline__ float wave_max(float x) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 63));
 }
 
-// The sum inside each row of 16 lanes.
+// The inclusive prefix sum inside each row of 16 lanes.
 __device__ __forceinline__ uint32_t row_incl_scan(uint32_t v) {
   const int x = (int)v;
   int r = x + __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, true);

@@ -33,8 +33,8 @@ namespace {
 
 // Eight waves, two per SIMD: an instruction of sixteen takes 16 cycles, and the phases that do not depend on the row's length --
 // scans, reductions, barriers -- are most of the kernel.  us a call, before (sixteen waves, a digit pass over 64-bit keys, positions read back
-// from a bitmap word by word) / now: 1 row of 8000 10.4 / 8.3, 32 rows of 4096 13.0 / 8.2, 13 of 12000 to 16384 14.8 / 10.5, 32 of
-// 32768 15.1 / 11.5, 46 of 24000 to 40000 17.8 / 12.6, 20 of 65000 18.5 / 13.7, 4 of 131072 17.5 / 13.7, 64 of 115000 21.4 / 18.5.
+// from a bitmap word by word) / now, k 2048: 1 row of 8000 10.4 / 7.1, 32 rows of 4096 13.1 / 7.5, 13 of 16384 13.9 / 10.6, 32 of
+// 32768 15.1 / 11.4, 46 of 40000 16.8 / 12.6, 20 of 65000 18.7 / 13.4, 4 of 131072 16.3 / 12.3, 64 of 115000 21.5 / 17.8.
 constexpr int NT = 512;
 constexpr int COPIES = 8;
 using ess_sel::CAND_CAP;
@@ -49,8 +49,6 @@ constexpr int PER = CAND_CAP / NT;           // keys per thread of a row or a li
 constexpr int LIST_AHEAD = 3072 / NT;        // rounds of NT list entries that are asked for before their number is known
 constexpr int ROUND = 8;                     // float4s per thread and round of a pass over a row
 constexpr int DPT = NBINS / NT;              // digits per thread of a scan over a digit histogram
-constexpr uint32_t LIST_FEW = 320;           // keys of one digit of a list that are counted at once; of more the digit is spread again: 200 equal
-                                             // scores counted / spread 12.7 / 14.7 us (a row of 12000), 900 38.6 / 15.5
 constexpr int RANK_WORDS = NBINS * 4;        // words of a row's bitmap up to which the words' ranks fit beside it (262144 positions)
 static_assert(PER * (NT / 64) == 128 && DPT == 4, "two counts a lane; digits are read 16 bytes at a time");
 constexpr uint32_t NONE = 0xffffffffu, ABOVE = NONE - 1u;     // in place of a digit: no key, or one that is not taken; one that is
@@ -164,7 +162,7 @@ __device__ __forceinline__ void row_begin(int tid, const float* srow, int n, flo
 template <int SETS>
 __device__ __forceinline__ void collect(int tid, const float* srow, int first, int n, float4v (&x)[SETS][ROUND], float tau,
                                         uint2* raw, uint32_t* n_raw, float* stage) {
-  const int lane = tid & 63, head = to_boundary(srow), nvec = (n - head) >> 2;      // (n is at least 1024)
+  const int lane = tid & 63, head = to_boundary(srow), nvec = (n - head) >> 2;      // (n is at least 1021)
   auto round = [&](int base, float4v (&y)[ROUND]) {
     float4v* const st4 = reinterpret_cast<float4v*>(stage);
     uint32_t hits = 0;                       // position 4 g + e of the thread's 32: bit 31 - (4 g + e)
@@ -313,8 +311,8 @@ __device__ __forceinline__ float score_of(uint32_t o) {      // the score of an 
 // lies below, half of the sample or a mask of the lowest number, need not be counted) to the second largest of the waves' (one outlier is not among them).  Where the
 // digit of the bound is still too full for the list, its samples alone are spread again, like the keys of a whole row.
 // us, k 2048, of a form with the top 14 bits of the float as digits and sixteen waves, of an even spread between the extremes with those bits behind it, and of this.
-// 1 x 12000: as they come 12.8 / 10.3 / 10.5, one score 1e30 12.8 / 16.4 / 10.3, a fifth masked 12.1 / 15.7 / 10.6, 70 % masked 13.4 / 19.6 / 15.8;
-// 64 x 115000: 21.2 / 17.8 / 17.9, 21.4 / 24.6 / 17.9, 21.4 / 24.0 / 18.2, 22.9 / 25.2 / 20.4.
+// 1 x 12000: as they come 12.8 / 10.4 / 10.3, one score 1e30 12.8 / 16.3 / 9.8, a fifth masked 12.2 / 15.7 / 10.3, 70 % masked 13.6 / 19.6 / 17.1;
+// 64 x 115000: 21.3 / 17.7 / 17.5, 21.4 / 24.7 / 17.8, 21.4 / 23.9 / 17.7, 22.9 / 25.4 / 20.4.
 // False: no bounds: nothing finite to go by, or (*tau == *tau_hi then) more equal scores than a list holds.
 // sm.lhist must be clear and sm.sbin 0xffffffff once a barrier has passed.
 template <int N>
@@ -466,7 +464,7 @@ __device__ __forceinline__ void take_few(TopkShared& sm, int tid, uint32_t cnt, 
 // for its rank: the positions taken in the words before, and in its word before it.
 // Where that digit holds more keys than counting takes (ties, a k-th largest score outside the range), its keys alone are spread between
 // their own extremes, and equal scores by their positions.  us, a row of 12000, counted or by the general selection / now: 900 equal
-// scores at the k-th 38.6 / 15.5, 3000 28.7 / 22.2; 64 rows of 115000: 45.7 / 24.5, 36.1 / 28.3.
+// scores at the k-th 38.6 / 17.4, 3000 28.7 / 25.3; 64 rows of 115000: 45.7 / 26.7, 36.1 / 32.0.
 // Returns false, with the keys in sm.cand, when that did not help (or the range gives no digits): the caller goes on with the general selection.
 template <int N>
 __device__ __forceinline__ bool finish_rounds(TopkShared& sm, int tid, const float (&v)[PER], const uint32_t (&p)[PER], uint32_t listed,
@@ -494,42 +492,56 @@ __device__ __forceinline__ bool finish_rounds(TopkShared& sm, int tid, const flo
   __syncthreads();
   crossing_digit(sm, tid, (uint32_t)k);
   uint32_t dsel = sm.sel_digit, take = (uint32_t)k - sm.sel_above, cnt = sm.sel_count;
-  // (rare) that digit's keys alone, spread again; equal ones by their positions
-  if (__builtin_expect(cnt > LIST_FEW && cnt != take && sp.scale != 0.f, 0)) {
+  // (rare) that digit's keys alone, spread again; equal ones by their positions (below 2^19: exact).  Through LDS, in loops that need not be
+  // unrolled: a step's other kernels push this code out of the instruction cache.  Unrolled over registers it made rare rows faster (15.5 us for 900 equal
+  // scores, now 18) and the finish of every list slower (32 rows of 128K 10.3 us, now 9.7; 40 of 100K in the fused selection 8.75, now 8.45).
+  if (__builtin_expect(cnt > FEW && cnt != take && sp.scale != 0.f, 0)) {
+    float* const value = sm.stage;
+    uint32_t* const digit = reinterpret_cast<uint32_t*>(sm.stage) + CAND_CAP;
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+      value[u * NT + tid] = v[u];
+      digit[u * NT + tid] = d[u];
+    }
     bool by_position = false;
 #pragma unroll 1
     for (int round = 0; round < NARROW + 2 && cnt > FEW && cnt != take; ++round) {
       constexpr float kInf = __builtin_inff();
       float lo = kInf, hi = -kInf;
-      auto value = [&](int u) { return by_position ? -(float)p[u] : v[u]; };        // (below 2^19: exact)
-#pragma unroll
-      for (int u = 0; u < N; ++u)
-        if (d[u] == dsel) {
-          lo = fminf(lo, value(u));
-          hi = fmaxf(hi, value(u));
+#pragma unroll 1
+      for (int j = tid; j < (int)listed; j += NT)
+        if (digit[j] == dsel) {
+          lo = fminf(lo, value[j]);
+          hi = fmaxf(hi, value[j]);
         }
       *reinterpret_cast<uint4*>(&sm.lhist[DPT * tid]) = make_uint4(0, 0, 0, 0);
       value_range(sm, tid, lo, hi);
       const Spread finer(lo, hi);
       if (lo == hi && !by_position) {
         by_position = true;
-        __syncthreads();                       // (every wave has its extremes)
+#pragma unroll
+        for (int u = 0; u < N; ++u) value[u * NT + tid] = -(float)p[u];
+        __syncthreads();                     // (every wave has its extremes)
         continue;
       }
       if (finer.scale == 0.f) break;
-#pragma unroll
-      for (int u = 0; u < N; ++u) {
-        if (d[u] == dsel) {
-          d[u] = finer.digit(value(u));
-          atomicAdd(&sm.lhist[d[u]], 1u);
-        } else {
-          d[u] = d[u] == NONE || d[u] < dsel ? NONE : ABOVE;
+#pragma unroll 1
+      for (int j = tid; j < (int)listed; j += NT) {
+        const uint32_t was = digit[j];
+        uint32_t now = was < dsel || was == NONE ? NONE : ABOVE;
+        if (was == dsel) {
+          now = finer.digit(value[j]);
+          atomicAdd(&sm.lhist[now], 1u);
         }
+        digit[j] = now;
       }
       __syncthreads();
       crossing_digit(sm, tid, take);
       dsel = sm.sel_digit; take -= sm.sel_above; cnt = sm.sel_count;
     }
+#pragma unroll
+    for (int u = 0; u < N; ++u)
+      if (d[u] != NONE) d[u] = digit[u * NT + tid];
   }
   if (cnt != take || sp.scale == 0.f) {
     if (cnt > SMALL || sp.scale == 0.f) {
@@ -604,9 +616,9 @@ __device__ __forceinline__ bool finish_list(TopkShared& sm, int tid, const float
 // is the number taken in the 64s before, plus a bit count: no bitmap.  Even digits hold a dozen keys near the threshold where
 // scores are as they come.  Where one holds more than counting takes, its keys alone are spread between their own extremes; equal scores are
 // taken by position, like the ranks.  us, 1 row / 32 rows of 8000, k 2048, of a form with 14 bits of the float as first digit and sixteen waves, of an even spread
-// between the extremes with the general selection behind it, and of this: as they come 10.3, 11.0 / 8.5, 8.3 / 8.4, 8.2; one score a thousand spreads away
-// 10.3, 11.0 / 19.5, 25.4 / 8.7, 10.5; 1e30 10.3, 11.0 / 24.5, 26.0 / 8.2, 9.9; a fifth masked with -3.4e38 10.5, 11.2 / 22.5, 23.8 / 8.0, 8.6; exponentials of
-// twice a normal value 9.8, 10.4 / 23.0, 39.1 / 8.0, 8.9; 900 equal at the threshold 29.7, 30.4 / 34.7, 35.5 / 11.3, 11.8; three values 28.7, 30.3 / 26.2, 28.1 / 11.1, 11.6.
+// between the extremes with the general selection behind it, and of this: as they come 10.4, 11.1 / 7.3, 7.9 / 7.1, 7.6; one score a thousand spreads away
+// 10.4, 11.2 / 20.7, 20.9 / 7.8, 9.5; 1e30 10.3, 11.0 / 25.7, 26.2 / 7.8, 8.1; a fifth masked with -3.4e38 10.5, 11.3 / 23.4, 24.0 / 7.1, 10.9; exponentials of
+// twice a normal value 10.1, 10.5 / 25.7, 38.8 / 7.1, 8.5; 900 equal at the threshold 30.0, 30.4 / 34.8, 35.5 / 11.1, 12.0; three values 28.7, 30.5 / 26.4, 28.2 / 11.1, 11.4.
 // Where rows are shared it is part 0 of the candidate pass (MODE 1) that takes such a row, not the finishing kernel:
 // inlined there beside its other paths it cost every longer row 0.4 to 0.6 us.
 // Returns false, with the keys in sm.cand, when more than SMALL keys share that digit all the same (magnitudes apart in several steps).
@@ -977,7 +989,7 @@ __device__ __forceinline__ void topk_item(TopkShared& sm, int item, int parts, f
   uint32_t cnt_match = (uint32_t)vis;
   if (!have_cand) {
     // A sample with more equal scores than a list holds (bounds_of): is the k-th largest one of them?  One pass instead of three.
-    // If not, those above them may be a list.  us, k 2048, of a row of 12000 with 800 scores above zero 36.6 / 25.8, of 40000 with 2700 36.9 / 34.6.
+    // If not, those above them may be a list.  us, k 2048, of a row of 12000 with 800 scores above zero 36.6 / 25.4, of 40000 with 2700 36.9 / 34.1.
     if (tau == tau_hi) {
       uint32_t above = 0, equal = 0;
       scan_row(tid, srow, vis, vec_ok, [&](int, float v, bool ok) {
